@@ -196,23 +196,45 @@ int check_phi(const rehyat_phi_params* p, int d) {
   return REHYAT_OK;
 }
 
-// pieces per segment: more workgroups when (b, h, segment) alone cannot fill the chip
-int choose_nsplit(int BH, int n_seg_total, Slots sl) {
-  if (n_seg_total < 1) return 1;
-  int best = 1;
+// How the chunk-state work of a call is cut: every segment into `nsplit` pieces, the chunks into
+// equal windows of `win` whose pieces fit the partial slots together.
+struct Cut {
+  int nsplit, win;
+};
+
+// The cheapest cut by a model of what was measured on the 480p and 320x480 shapes (12 heads of
+// 128): a state workgroup takes about 10 us to load its weights and store its sums and 4 us per
+// 64-token tile (3.2 us at d = 64, where two workgroups share a CU); each partial sum is read
+// once more by the prefix pass; each further window costs its own launches, and the attention
+// launch of a window ends on a partly empty round (about half of a workgroup's time).
+// `n` chunks (or frames) are windowed, at most `limit` to a window; `n_seg` of them (n or n - 1)
+// have a segment; `most_pieces` bounds the pieces of a segment.  What the
+// windows cost is why fewer pieces can win: 34 chunks of 1,800 tokens took 1,600 us cut into
+// seven pieces each (least state time, four windows) and take 1,300 us in two windows of 17.
+Cut choose_cut(int BH, int n, int n_seg, int64_t seg_tokens, int64_t keys, int d, int partial_slots, int limit,
+               int most_pieces) {
+  Cut best{1, 1};
+  if (n < 1) return best;
+  const int slots = d == 128 ? kCUs : 2 * kCUs;      // state workgroups resident at once
+  const double tile_us = d == 128 ? 4.0 : 3.2, setup_us = 10.0;
+  const double window_us = 25.0 + 0.9 * (double)((keys + 63) / 64);
+  const double partial_us = (double)BH * (d * 2 * d + 2 * d) * sizeof(float) / 4e6;   // at 4 TB/s
+  const int64_t tiles = (seg_tokens + 63) / 64;
   double best_cost = 1e30;
-  for (int ns = 1; ns <= kMaxSplit && ns <= sl.partial; ++ns) {
-    int win = sl.partial / ns;
-    if (win > sl.state) win = sl.state;
-    const int segs = n_seg_total < win ? n_seg_total : win;
-    const int windows = (n_seg_total + win - 1) / win;
-    const long wgs = (long)BH * segs * ns;
-    const double rounds = std::ceil((double)wgs / kCUs);
-    // time in units of "one whole segment on one CU"
-    const double cost = windows * rounds / ns;
-    if (cost < best_cost * 0.9) {
+  for (int ns = 1; ns <= most_pieces && ns <= partial_slots; ++ns) {
+    if (ns > 1 && ns > tiles) break;                 // a piece is at least one tile
+    int win = partial_slots / ns;
+    if (win > limit) win = limit;
+    const int windows = (n + win - 1) / win;
+    win = (n + windows - 1) / windows;               // equal windows
+    const int segs = win < n_seg ? win : n_seg;
+    const double rounds = std::ceil((double)BH * segs * ns / slots);
+    const double piece_tiles = (double)(((seg_tokens + ns - 1) / ns + 63) / 64);
+    const double cost = windows * (rounds * (setup_us + piece_tiles * tile_us) + segs * ns * partial_us) +
+                        (windows - 1) * window_us;
+    if (cost < best_cost * 0.98) {
       best_cost = cost;
-      best = ns;
+      best = Cut{ns, win};
     }
   }
   return best;
@@ -338,8 +360,9 @@ int forward_bidirectional(const Ctx& c, const void* q, const void* k, const void
   int win_frames = chunk + overlap;  // frames one window can span (both are <= T here)
   if (win_frames > T) win_frames = T;
   if (win_frames > c.sl.partial) return REHYAT_E_UNSUPPORTED;
-  int nsplit = choose_nsplit(B * H, T, c.sl);
-  while (nsplit > 1 && c.sl.partial / nsplit < win_frames) --nsplit;
+  // the frames of one window must fit the partial slots together
+  const int nsplit = choose_cut(B * H, T, T, HW, (int64_t)win_frames * HW, d, c.sl.partial, c.sl.partial,
+                                c.sl.partial / win_frames < kMaxSplit ? c.sl.partial / win_frames : kMaxSplit).nsplit;
   const int fwin = c.sl.partial / nsplit;  // frames whose sums fit the partial slots
 
   // pass 1: total over all frames, left in the carry
@@ -436,9 +459,9 @@ int forward_core(const Ctx& c, const void* q, const void* k, const void* v,
     return forward_bidirectional(c, q, k, v, phi, out, debug, B, H, T, HW, d, dp, chunk, overlap,
                                  stab_mode);
   const int nc = num_chunks(T, chunk);
-  const int nsplit = choose_nsplit(B * H, nc - 1, c.sl);
-  int win = c.sl.partial / nsplit;
-  if (win > c.sl.state) win = c.sl.state;
+  const Cut cut = choose_cut(B * H, nc, nc - 1, (int64_t)chunk * HW, (int64_t)(chunk + overlap) * HW, d, c.sl.partial,
+                             c.sl.state, kMaxSplit);
+  const int nsplit = cut.nsplit, win = cut.win;
   const int qtile = attn_query_tile(d);
   const int qtiles = (int)(((int64_t)chunk * HW + qtile - 1) / qtile);
 
@@ -478,7 +501,8 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   const size_t BH = (size_t)B * H, N = (size_t)T * HW;
   P.nc = num_chunks(T, chunk);
   P.n_seg = P.nc > 1 ? P.nc - 1 : 1;
-  P.nsplit = choose_nsplit((int)BH, P.n_seg, Slots{kMaxSplit * P.nc, P.nc});
+  P.nsplit = choose_cut((int)BH, P.n_seg, P.n_seg, (int64_t)chunk * HW, 0, d, kMaxSplit * P.nc, P.n_seg,
+                        kMaxSplit).nsplit;
   P.sl = Slots{P.n_seg * P.nsplit, P.nc};
   P.F = ws_layout(B, H, d, dp, P.sl);
   // weight-gradient kernels: one (b, h) token range cut so that the pieces about fill the chip
@@ -1196,9 +1220,8 @@ int rehyat_state(const void* k, const void* v, const rehyat_phi_params* phi, flo
   rc = ensure_workspace(c.L.total, st, &c.ws);
   if (rc != REHYAT_OK) return rc;
   // one frame per chunk, no overlap: segment f is frame f
-  const int nsplit = choose_nsplit(B * H, upto_frames, c.sl);
-  int win = c.sl.partial / nsplit;
-  if (win > c.sl.state) win = c.sl.state;
+  const Cut cut = choose_cut(B * H, upto_frames, upto_frames, HW, 0, d, c.sl.partial, c.sl.state, kMaxSplit);
+  const int nsplit = cut.nsplit, win = cut.win;
   for (int c0 = 0; c0 < upto_frames; c0 += win) {
     const int n_seg = (upto_frames - c0 < win) ? upto_frames - c0 : win;
     rc = launch_state_window(c, k, v, phi, B, H, T, HW, d, 1, 0, c0, n_seg, nsplit);
