@@ -101,6 +101,15 @@ def test_small_shapes_match_gradient_oracle(case):
     run_case(*case, seed=sum(case[:7]))
 
 
+@pytest.mark.parametrize("case", [
+    (2, 2, 6, 300, 128, 1, 0, 4.0),     # 58 partials per head: three batches of a reduction wave
+    (3, 1, 5, 150, 64, 2, 0, 4.0),      # 36 partials of three batch elements, 12 each
+    (5, 1, 2, 60, 64, 1, 0, 4.0),       # a batch element has fewer partials than a block has waves
+])
+def test_partial_sums_over_batch_and_pieces(case):
+    run_case(*case, seed=sum(case[:7]))
+
+
 def test_l1_distillation_gradient():
     run_case(1, 2, 5, 200, 128, 1, 0, 4.0, seed=5, l1=True)
 
