@@ -8,7 +8,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librehyat.so")
 SOURCES = ["rehyat_api.hip", "rehyat_state.hip", "rehyat_prefix.hip", "rehyat_attn.hip",
            "rehyat_grad.hip"]
-HEADERS = ["rehyat_device.h", "rehyat_kernels.h"]
+HEADERS = ["rehyat_device.h", "rehyat_kernels.h", "rehyat_state_body.h"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          # no NaN is ever produced on purpose (masked scores are -inf, never inf - inf):

@@ -338,7 +338,8 @@ int launch_attn_window(const Ctx& c, const void* q, const void* k, const void* v
   hipError_t e;
   {
     ProfScope prof(c.prof, 2, c.st);
-    e = launch_attn(a, d, a.items_per_xcd * 8, c.st);
+    const int64_t frames = (int64_t)chunk + overlap < T ? (int64_t)chunk + overlap : T;
+    e = launch_attn(a, nullptr, d, attn_splits(a.n_items, frames * HW, d), c.st);
   }
   if (e != hipSuccess) return hip_fail(e, "attention kernel launch");
   return REHYAT_OK;
@@ -1070,26 +1071,28 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   // tokens that leave the window are absorbed afterwards (Eq. 17-18: state kernel in pieces,
   // then S, z += the pieces, in place and in the caller's layout); the attention kernel does
   // not depend on that and runs beside it when a second stream is at hand.
-  SideStream* side = n_absorb > 0 ? side_stream(st) : nullptr;
+  const int qtile = attn_query_tile(d);
+  const int attn_wgs = B * H * ((n_q + qtile - 1) / qtile);   // 64-row tiles of the queries fit an int
+  // An attention launch that leaves CUs free absorbs beside its own work, in the same launch;
+  // otherwise on a second stream when one is at hand.
+  const bool joint = n_absorb > 0 && attn_wgs <= kCUs;
+  SideStream* side = n_absorb > 0 && !joint ? side_stream(st) : nullptr;
   hipStream_t upd = side ? side->s : st;   // stream of the state update
-  int nsplit = 1;
+  StateArgs s{};
   if (n_absorb > 0) {
     // One segment only, cut into pieces: one workgroup of the state kernel fills a CU, and a
     // piece pays the workgroup's set-up (its weight slices into registers) once.  Beside the
     // attention kernel, which spreads its workgroups over as many CUs, the pieces should fit
     // the CUs it leaves free; alone, three quarters of the chip measured best (480p shape,
-    // 12 heads: 8 pieces forked, 16 serial; 25 pieces of one tile each were 30 % slower).
-    const int attn_wgs = B * H * ((n_q + attn_query_tile(d) - 1) / attn_query_tile(d));
-    int free_cus = side ? kCUs - attn_wgs : 3 * kCUs / 4;
+    // 12 heads: 8 pieces beside the attention kernel, 16 serial; 25 pieces of one tile each
+    // were 30 % slower).
+    int free_cus = joint || side ? kCUs - attn_wgs : 3 * kCUs / 4;
     if (free_cus < kCUs / 4) free_cus = kCUs / 4;
-    nsplit = free_cus / (B * H);
+    int nsplit = free_cus / (B * H);
     if (nsplit < 1) nsplit = 1;
     if (nsplit > c.sl.partial) nsplit = c.sl.partial;
     const int max_pieces = (n_absorb + 63) / 64;
     if (nsplit > max_pieces) nsplit = max_pieces;
-  }
-  auto launch_absorb_pieces = [&]() -> int {
-    StateArgs s;
     s.k = (const bf16_t*)k_win;
     s.v = (const bf16_t*)v_win;
     s.w1_k = (const bf16_t*)phi->w1_k;
@@ -1099,8 +1102,6 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
     s.partial = (float*)(ws + L.partial);
     s.H = H;
     s.T = s.HW = s.chunk = 1;
-    s.overlap = 0;
-    s.chunk0 = 0;
     s.n_seg = 1;
     s.nsplit = nsplit;
     s.partial_slots = c.sl.partial;
@@ -1108,46 +1109,43 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
     s.items_per_xcd = (s.n_items + 7) / 8;
     s.kv_bh_stride = (int64_t)n_win * d;
     s.step_n = n_absorb;
-    s.query_segments = 0;
+  }
+  auto launch_pieces = [&]() -> int {
     ProfScope prof(true, 0, upd);
     hipError_t es = launch_state(s, d, s.items_per_xcd * 8, upd);
     if (es != hipSuccess) return hip_fail(es, "state kernel launch");
     return REHYAT_OK;
   };
+  auto launch_slot = [&](int nsplit, int write_slot, hipStream_t on) -> int {
+    ss.nsplit = nsplit;
+    ss.write_slot = write_slot;
+    ProfScope prof(true, 1, on);
+    hipError_t es = launch_step_state(ss, on);
+    if (es != hipSuccess) return hip_fail(es, "step state kernel launch");
+    return REHYAT_OK;
+  };
   if (side) {
     // caller's stream: slot 0 <- state; fork; second stream: pieces, then state += pieces
-    ss.nsplit = 0;
-    ss.write_slot = 1;
-    {
-      ProfScope prof(true, 1, st);
-      e = launch_step_state(ss, st);
-    }
-    if (e != hipSuccess) return hip_fail(e, "step state kernel launch");
+    rc = launch_slot(0, 1, st);
+    if (rc != REHYAT_OK) return rc;
     e = hipEventRecord(side->fork, st);
     if (e == hipSuccess) e = hipStreamWaitEvent(side->s, side->fork, 0);
     if (e != hipSuccess) return hip_fail(e, "fork to the second stream");
-    rc = launch_absorb_pieces();
+    rc = launch_pieces();
     if (rc != REHYAT_OK) return rc;
-    ss.nsplit = nsplit;
-    ss.write_slot = 0;
-    {
-      ProfScope prof(true, 1, upd);
-      e = launch_step_state(ss, upd);
-    }
-    if (e != hipSuccess) return hip_fail(e, "step state kernel launch");
+    rc = launch_slot(s.nsplit, 0, upd);
+    if (rc != REHYAT_OK) return rc;
     e = hipEventRecord(side->join, side->s);
     if (e != hipSuccess) return hip_fail(e, "hipEventRecord(join)");
+  } else if (joint || n_absorb == 0) {
+    rc = launch_slot(0, 1, st);   // slot 0 <- state
+    if (rc != REHYAT_OK) return rc;
   } else {
     // one stream: pieces, then slot 0 <- state and state += pieces in one kernel
-    if (n_absorb > 0) {
-      rc = launch_absorb_pieces();
-      if (rc != REHYAT_OK) return rc;
-    }
-    ss.nsplit = n_absorb > 0 ? nsplit : 0;
-    ss.write_slot = 1;
-    ProfScope prof(true, 1, st);
-    e = launch_step_state(ss, st);
-    if (e != hipSuccess) return hip_fail(e, "step state kernel launch");
+    rc = launch_pieces();
+    if (rc != REHYAT_OK) return rc;
+    rc = launch_slot(s.nsplit, 1, st);
+    if (rc != REHYAT_OK) return rc;
   }
 
   AttnArgs a;
@@ -1168,7 +1166,6 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   a.overlap = 0;
   a.chunk0 = 0;
   a.n_win_chunks = 1;
-  const int qtile = attn_query_tile(d);
   a.qtiles = (n_q + qtile - 1) / qtile;
   a.state_slots = c.sl.state;
   a.stab_mode = stab_mode;
@@ -1183,9 +1180,13 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   a.n_short = 0;
   {
     ProfScope prof(true, 2, st);
-    e = launch_attn(a, d, a.items_per_xcd * 8, st);
+    e = launch_attn(a, joint ? &s : nullptr, d, joint || attn_splits(attn_wgs, n_win, d), st);
   }
   if (e != hipSuccess) return hip_fail(e, "attention kernel launch");
+  if (joint) {   // state += pieces
+    rc = launch_slot(s.nsplit, 0, st);
+    if (rc != REHYAT_OK) return rc;
+  }
   if (side) {   // the call's work is complete, for the caller's stream, when both branches are
     e = hipStreamWaitEvent(st, side->join, 0);
     if (e != hipSuccess) return hip_fail(e, "join of the second stream");

@@ -26,6 +26,7 @@
 
 #include "rehyat_device.h"
 #include "rehyat_kernels.h"
+#include "rehyat_state_body.h"
 
 namespace rehyat {
 
@@ -79,25 +80,30 @@ __device__ __forceinline__ FragOffsets<D> make_frag_offsets(int lane) {
   return f;
 }
 
-// One 64-key tile of the softmax part for the wave's 32*QB queries (Eq. 6, 8):
-// exponents K Q^T, online row maximum and sum, numerator += V^T P.
-// E[kb][qb] register 4i+j = (key 32kb + 8i + 4g + j, query 32qb + r).
+// One 64-key tile of the softmax part for the wave's 32*QB queries (Eq. 6, 8) in two steps:
+// softmax_scores forms the exponents K Q^T, softmax_weights the online row maximum and sum and
+// numerator += V^T P.  E[kb][qb] register 4i+j = (key 32kb + 8i + 4g + j, query 32qb + r).
 // LDS reads are issued one batch ahead of the MFMAs that consume them; the
 // scheduling barriers keep the compiler from collapsing that order.
-template <int D, int QB, bool TAIL>
-__device__ __forceinline__ void softmax_tile(const char* Ks, const char* Vs, const FragOffsets<D>& fo,
-                                             const bf16x8 (&Qr)[QB][D / 16], f32x16 (&O)[D / 32][QB],
-                                             float (&mrun)[QB], float (&mtru)[QB], float (&lrun)[QB],
-                                             float sc, int valid_keys, int lane) {
-  using C = AttnShape<D, QB>;
-  constexpr int KS = C::KS, DB = C::DB;
-  constexpr int KB_BYTES = 32 * D * 2;   // 32 rows further down the tile
-  constexpr int STEP_BYTES = 16 * D * 2; // 16 rows
-  const int g = lane >> 5;
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  f32x16 E[2][QB];
+template <int D>
+__device__ __forceinline__ void read_v_step(const char* Vs, const FragOffsets<D>& fo, int step, bf16x8 (&vf)[D / 32]) {
+  constexpr int STEP_BYTES = 16 * D * 2;   // 16 rows further down the tile
+#pragma unroll
+  for (int db = 0; db < D / 32; ++db) {
+    i16x4 lo = lds_read_tr(reinterpret_cast<const bf16_t*>(Vs + fo.v_lo[db] + step * STEP_BYTES));
+    i16x4 hi = lds_read_tr(reinterpret_cast<const bf16_t*>(Vs + fo.v_hi[db] + step * STEP_BYTES));
+    vf[db] = join_tr(lo, hi);
+  }
+}
 
-  // ---- exponents: batches of two k-steps (4 fragments) ------------------------
+// `last` runs with the last batch of products (a place for the LDS reads of what follows).
+template <int D, int QB, typename Last>
+__device__ __forceinline__ void softmax_scores(const char* Ks, const FragOffsets<D>& fo, const bf16x8 (&Qr)[QB][D / 16],
+                                               f32x16 (&E)[2][QB], Last last) {
+  constexpr int KS = D / 16;
+  constexpr int KB_BYTES = 32 * D * 2;   // 32 rows further down the tile
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  // batches of two k-steps (4 fragments)
   bf16x8 kf[2][2][2];  // [batch parity][k-step in batch][key block]
   auto read_k = [&](int b, int par) {
 #pragma unroll
@@ -106,20 +112,11 @@ __device__ __forceinline__ void softmax_tile(const char* Ks, const char* Vs, con
       for (int kb = 0; kb < 2; ++kb)
         kf[par][t][kb] = *reinterpret_cast<const bf16x8*>(Ks + fo.k[2 * b + t] + kb * KB_BYTES);
   };
-  bf16x8 vf[2][DB];    // [batch parity][feature block]
-  auto read_v = [&](int step, int par) {
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      i16x4 lo = lds_read_tr(reinterpret_cast<const bf16_t*>(Vs + fo.v_lo[db] + step * STEP_BYTES));
-      i16x4 hi = lds_read_tr(reinterpret_cast<const bf16_t*>(Vs + fo.v_hi[db] + step * STEP_BYTES));
-      vf[par][db] = join_tr(lo, hi);
-    }
-  };
   read_k(0, 0);
 #pragma unroll
   for (int b = 0; b < KS / 2; ++b) {
     if (b + 1 < KS / 2) read_k(b + 1, (b + 1) & 1);
-    else read_v(0, 0);
+    else last();
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int t = 0; t < 2; ++t)
@@ -130,6 +127,16 @@ __device__ __forceinline__ void softmax_tile(const char* Ks, const char* Vs, con
           E[kb][qb] = mfma(kf[b & 1][t][kb], Qr[qb][2 * b + t], (b == 0 && t == 0) ? zero : E[kb][qb]);
     __builtin_amdgcn_sched_barrier(0);
   }
+}
+
+// vf[0] holds the V fragments of step 0.
+template <int D, int QB, bool TAIL>
+__device__ __forceinline__ void softmax_weights(const char* Vs, const FragOffsets<D>& fo, f32x16 (&E)[2][QB],
+                                                bf16x8 (&vf)[2][D / 32], f32x16 (&O)[D / 32][QB], float (&mrun)[QB],
+                                                float (&mtru)[QB], float (&lrun)[QB], float sc, int valid_keys,
+                                                int lane) {
+  constexpr int DB = D / 32;
+  const int g = lane >> 5;
 
   // ---- online softmax: new maximum, rescale of the running sums --------------------
   float mnew[QB], alpha[QB];
@@ -173,7 +180,7 @@ __device__ __forceinline__ void softmax_tile(const char* Ks, const char* Vs, con
   for (int qb = 0; qb < QB; ++qb) sum[qb] = 0.f;
 #pragma unroll
   for (int step = 0; step < 4; ++step) {
-    if (step + 1 < 4) read_v(step + 1, (step + 1) & 1);
+    if (step + 1 < 4) read_v_step<D>(Vs, fo, step + 1, vf[(step + 1) & 1]);
     bf16x8 pf[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
@@ -211,6 +218,17 @@ __device__ __forceinline__ void softmax_tile(const char* Ks, const char* Vs, con
     __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
   }
   __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int D, int QB, bool TAIL>
+__device__ __forceinline__ void softmax_tile(const char* Ks, const char* Vs, const FragOffsets<D>& fo,
+                                             const bf16x8 (&Qr)[QB][D / 16], f32x16 (&O)[D / 32][QB],
+                                             float (&mrun)[QB], float (&mtru)[QB], float (&lrun)[QB],
+                                             float sc, int valid_keys, int lane) {
+  f32x16 E[2][QB];
+  bf16x8 vf[2][D / 32];   // [step parity][feature block]
+  softmax_scores<D, QB>(Ks, fo, Qr, E, [&] { read_v_step<D>(Vs, fo, 0, vf[0]); });
+  softmax_weights<D, QB, TAIL>(Vs, fo, E, vf, O, mrun, mtru, lrun, sc, valid_keys, lane);
 }
 
 // ---------------------------------------------------------------------------
@@ -293,6 +311,57 @@ __device__ __forceinline__ void static_for(F&& f) {
   static_for_impl(f, std::make_integer_sequence<int, N>{});
 }
 
+// Which (batch*head, chunk of the window, query tile) this workgroup computes; false: none.
+__device__ __forceinline__ bool attn_item(const AttnArgs& a, int& bh, int& tc, int& qt) {
+  if (a.n_short == 0) {
+    const int item = xcd_swizzle(blockIdx.x, a.items_per_xcd);
+    if (item >= a.n_items) return false;
+    // item = (bh * n_win_chunks + tc) * qtiles + qt, qt fastest
+    qt = item % a.qtiles;
+    const int rest = item / a.qtiles;
+    tc = rest % a.n_win_chunks;
+    bh = rest / a.n_win_chunks;
+  } else {
+    // The window starts at chunk 0, whose items have no read-out phase and are the shortest:
+    // every XCD runs its share of them last, so that the launch does not end on long items.
+    const int xcd = blockIdx.x & 7, i = blockIdx.x >> 3;
+    const int n_long = a.n_items - a.n_short;
+    const int per_long = (n_long + 7) / 8, per_short = (a.n_short + 7) / 8;
+    if (i < per_long) {
+      const int li = xcd * per_long + i;
+      if (li >= n_long) return false;
+      const int per_bh = (a.n_win_chunks - 1) * a.qtiles;
+      bh = li / per_bh;
+      const int rest = li % per_bh;
+      tc = 1 + rest / a.qtiles;
+      qt = rest % a.qtiles;
+    } else {
+      const int si = xcd * per_short + (i - per_long);
+      if (si >= a.n_short) return false;
+      bh = si / a.qtiles;
+      tc = 0;
+      qt = si % a.qtiles;
+    }
+  }
+  return true;
+}
+
+// Token ranges of chunk t.
+__device__ __forceinline__ ChunkRange attn_range(const AttnArgs& a, int t) {
+  ChunkRange cr;
+  if (a.step_nq > 0) {  // streaming step: explicit ranges, state always read
+    cr.q_lo = 0;
+    cr.q_hi = a.step_nq;
+    cr.s_lo = 0;
+    cr.s_hi = a.step_nwin;
+    cr.l_hi = 1;
+  } else {
+    cr = chunk_range(a.T, a.HW, a.chunk, a.overlap, t);
+    if (a.all_linear) cr.l_hi = 1;
+  }
+  return cr;
+}
+
 // second bound: waves per SIMD the register budget is sized for
 template <int D, int QB, int NWV>
 __global__ void __launch_bounds__(64 * NWV, (QB == 1 ? 2 : 1))
@@ -320,49 +389,10 @@ attn_kernel(AttnArgs a) {
   // ---- which work item -------------------------------------------------
   if (!((a.xcd_mask >> (blockIdx.x & 7)) & 1u)) return;   // measurement hook; all bits set normally
   int qt, tc, bh;
-  if (a.n_short == 0) {
-    const int item = xcd_swizzle(blockIdx.x, a.items_per_xcd);
-    if (item >= a.n_items) return;
-    // item = (bh * n_win_chunks + tc) * qtiles + qt, qt fastest
-    qt = item % a.qtiles;
-    const int rest = item / a.qtiles;
-    tc = rest % a.n_win_chunks;
-    bh = rest / a.n_win_chunks;
-  } else {
-    // The window starts at chunk 0, whose items have no read-out phase and are the shortest:
-    // every XCD runs its share of them last, so that the launch does not end on long items.
-    const int xcd = blockIdx.x & 7, i = blockIdx.x >> 3;
-    const int n_long = a.n_items - a.n_short;
-    const int per_long = (n_long + 7) / 8, per_short = (a.n_short + 7) / 8;
-    if (i < per_long) {
-      const int li = xcd * per_long + i;
-      if (li >= n_long) return;
-      const int per_bh = (a.n_win_chunks - 1) * a.qtiles;
-      bh = li / per_bh;
-      const int rest = li % per_bh;
-      tc = 1 + rest / a.qtiles;
-      qt = rest % a.qtiles;
-    } else {
-      const int si = xcd * per_short + (i - per_long);
-      if (si >= a.n_short) return;
-      bh = si / a.qtiles;
-      tc = 0;
-      qt = si % a.qtiles;
-    }
-  }
+  if (!attn_item(a, bh, tc, qt)) return;
   const int t = a.chunk0 + tc;
   const int h = bh % a.H;
-  ChunkRange cr;
-  if (a.step_nq > 0) {  // streaming step: explicit ranges, state always read
-    cr.q_lo = 0;
-    cr.q_hi = a.step_nq;
-    cr.s_lo = 0;
-    cr.s_hi = a.step_nwin;
-    cr.l_hi = 1;
-  } else {
-    cr = chunk_range(a.T, a.HW, a.chunk, a.overlap, t);
-    if (a.all_linear) cr.l_hi = 1;
-  }
+  const ChunkRange cr = attn_range(a, t);
   const int64_t q0 = cr.q_lo + (int64_t)qt * C::QT;
   if (q0 >= cr.q_hi) return;  // short last chunk: fewer query tiles
   const int64_t N = (int64_t)a.T * a.HW;  // rows per (b, h) of the debug outputs
@@ -703,6 +733,407 @@ attn_kernel(AttnArgs a) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// The same result for launches too small to fill the chip: a workgroup of eight waves owns 128
+// queries, and two groups of four waves share the work of each query block.  Group kg takes the
+// key tiles with index = kg mod 2 in phase S and the feature blocks with index = kg mod 2 in
+// phase L; the two numerators and normalisers are brought to one reference after phase S and
+// added through LDS at the end.
+//
+// What bounds it: as attn_kernel (per-wave chains of score products, exponentials and numerator
+// products), but a launch of at most 256 attn_kernel workgroups leaves one wave on a SIMD, which
+// runs a tile in 2,650 cycles where two waves run two in 2,930.  Here every SIMD that has work
+// has two waves, each with half of the tiles: 0.82 us per key tile and workgroup instead of 1.02
+// (streaming step at the 480p shape with T_o = 1, 156 items: 59.6 instead of 67.4 us without the
+// state update).  0.14 of the 0.82 us goes away with the tile loads: tiles are requested three
+// half-steps ahead because one trip ahead, in lockstep, took 0.89 us.
+// 128 KB of tile buffers (K and V of two tiles per group): one workgroup per CU, which is why
+// attn_kernel stays the better one as soon as its own launch fills the chip (split_pays).
+// ---------------------------------------------------------------------------
+template <int D>
+__global__ void __launch_bounds__(512, 2)
+attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
+  using C = AttnShape<D, 1, 4>;
+  constexpr int HID = C::HID, DP = C::DP, KS = C::KS, DB = C::DB;
+  constexpr int TB = C::TILE_BYTES;
+  constexpr int NT = 512;
+  constexpr int GB = 4 * TB;             // tile buffers of one group: K 0/1, V 0/1
+  constexpr int L4 = TB / (1024 * 4);    // direct loads per wave per tile moved by one group
+  constexpr int L8 = TB / (1024 * 8);    // direct loads per wave per tile moved by all eight waves
+  constexpr float kLowest = -3.402823466e38f;
+  using SL = StateLds<D>;
+  __shared__ __attribute__((aligned(1024))) char tiles[2 * GB > SL::XV + SL::US ? 2 * GB : SL::XV + SL::US];
+  __shared__ __attribute__((aligned(256))) float sb1[HID];
+  __shared__ __attribute__((aligned(16))) float sb2[DP];
+  __shared__ __attribute__((aligned(16))) float sz[DP];
+  __shared__ float xref[2][C::QT], xmax[2][C::QT], xsum[2][C::QT], xlin[2][C::QT];
+
+  // streaming step: the workgroups beyond the attention items absorb the tokens that leave the
+  // window (pieces of the chunk-state increment) on CUs that the attention items leave free
+  if ((int)blockIdx.x >= attn_blocks) {
+    constexpr int NW = D / 16;   // waves of the chunk-state body; the others are done
+    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < NW)
+      state_body<D, NW>(sa, blockIdx.x - attn_blocks, tiles, tiles + SL::XV, sb1);
+    return;
+  }
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kg = wave >> 2, qg = wave & 3;   // key group, query block
+  const int g = lane >> 5;
+  const int r = lane & 31;
+
+  if (!((a.xcd_mask >> (blockIdx.x & 7)) & 1u)) return;   // measurement hook; all bits set normally
+  int qt, tc, bh;
+  if (!attn_item(a, bh, tc, qt)) return;
+  const int h = bh % a.H;
+  const ChunkRange cr = attn_range(a, a.chunk0 + tc);
+  const int64_t q0 = cr.q_lo + (int64_t)qt * C::QT;
+  if (q0 >= cr.q_hi) return;   // short last chunk: fewer query tiles
+  const int64_t N = (int64_t)a.T * a.HW;
+  const bf16_t* Qg = a.q + (int64_t)bh * a.q_bh_stride;
+  const bf16_t* Kg = a.k + (int64_t)bh * a.kv_bh_stride;
+  const bf16_t* Vg = a.v + (int64_t)bh * a.kv_bh_stride;
+  bf16_t* Og = a.out + (int64_t)bh * a.q_bh_stride;
+  const bool has_linear = cr.l_hi > 0;
+
+  const int64_t row = q0 + 32 * qg + r;            // this lane's query
+  const bool wave_live = q0 + 32 * qg < cr.q_hi;   // else: moves tiles and meets barriers only
+  bf16x8 Qr[1][KS];
+  {
+    const bf16_t* p = Qg + (row < cr.q_hi ? row : cr.q_hi - 1) * D + 8 * g;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) Qr[0][ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
+  }
+  f32x16 O[DB][1];
+#pragma unroll
+  for (int db = 0; db < DB; ++db)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) O[db][0][e] = 0.f;
+  // The reference starts at the lowest finite value: a group may see no key at all, or only
+  // scores of -inf, for a row whose other keys are the other group's.
+  float mrun[1] = {kLowest}, mtru[1] = {-INFINITY}, lrun[1] = {0.f};
+
+  // =========================== phase S =====================================
+  {
+    FragOffsets<D> fo = make_frag_offsets<D>(lane);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) fo.k[ks] += kg * GB;
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      fo.v_lo[db] += kg * GB;
+      fo.v_hi[db] += kg * GB;
+    }
+    const int n_full = (int)((cr.s_hi - cr.s_lo) / 64);
+    const int rem = (int)((cr.s_hi - cr.s_lo) - 64 * (int64_t)n_full);
+    const int n_tiles = n_full + (rem > 0 ? 1 : 0);
+    const int trips = (n_tiles + 1) / 2;
+    const u32x4 Kr = make_rsrc_words(Kg + cr.s_lo * D), Vr = make_rsrc_words(Vg + cr.s_lo * D);
+    const uint32_t group_lds = __builtin_amdgcn_readfirstlane(lds_address(tiles) + kg * GB);
+    const int voff_full = tile_voff_full<2 * D, 4>(qg, lane);
+    // This group's K or V tile of trip j into the buffer of the trip's parity.  Past the end the
+    // last tile is moved again (never read), so that every wave always has the same number of
+    // loads behind the one it waits for.
+    auto load = [&](u32x4 rsrc, int j, int which) {
+      const int want = 2 * j + kg, it = want < n_tiles ? want : n_tiles - 1;
+      tile_load_fast<2 * D, TB, 4>(rsrc, __builtin_amdgcn_readfirstlane(it * TB), group_lds + (which + (j & 1)) * TB, qg,
+                                   lane, it < n_full ? 64 : rem, voff_full);
+    };
+    auto load_k = [&](int j) { load(Kr, j, 0); };
+    auto load_v = [&](int j) { load(Vr, j, 2); };
+    load_k(0);
+    load_v(0);
+    load_k(1);
+    if (has_linear) {
+      const float* zt = a.state_z + ((int64_t)bh * a.state_slots + tc) * DP;
+      for (int i = tid; i < HID; i += NT) sb1[i] = a.b1_q[(int64_t)h * HID + i];
+      for (int i = tid; i < DP; i += NT) {
+        sb2[i] = a.b2_q[(int64_t)h * DP + i];
+        sz[i] = zt[i];
+      }
+    }
+    wait_loads_and_barrier<0>();   // also publishes the bias vectors
+    auto k_tile = [&](int j) -> const char* { return tiles + (j & 1) * TB; };
+    auto v_tile = [&](int j) -> const char* { return tiles + (2 + (j & 1)) * TB; };
+    // A trip has two half-steps, scores and weights, each ended by a barrier; group 1 runs one
+    // half-step behind, so that the two waves of a SIMD are in different ones.  A buffer is
+    // refilled as soon as the half-step that read it is over: every tile is requested three
+    // half-steps ahead, and two younger tiles may be in flight when it has to be there.
+    f32x16 E[2][1];
+    bf16x8 vf[2][DB];
+    if (kg == 1) lds_barrier();
+    for (int j = 0; j + 1 < trips; ++j) {   // every tile of the trips before the last one is full
+      load_v(j + 1);
+      if (wave_live) softmax_scores<D, 1>(k_tile(j), fo, Qr, E, [] {});
+      wait_loads_and_barrier<2 * L4>();
+      load_k(j + 2);
+      if (wave_live) {
+        read_v_step<D>(v_tile(j), fo, 0, vf[0]);
+        softmax_weights<D, 1, false>(v_tile(j), fo, E, vf, O, mrun, mtru, lrun, a.scale_log2e, 64, lane);
+      }
+      wait_loads_and_barrier<2 * L4>();
+    }
+    {
+      const int j = trips - 1, it = 2 * j + kg;   // a full tile, the ragged one, or none
+      const bool work = wave_live && it < n_tiles;
+      if (work) softmax_scores<D, 1>(k_tile(j), fo, Qr, E, [] {});
+      wait_loads_and_barrier<0>();
+      if (work) {
+        read_v_step<D>(v_tile(j), fo, 0, vf[0]);
+        softmax_weights<D, 1, true>(v_tile(j), fo, E, vf, O, mrun, mtru, lrun, a.scale_log2e,
+                                    it < n_full ? 64 : rem, lane);
+      }
+    }
+    lds_barrier();
+    if (kg == 0) lds_barrier();
+  }
+
+  // Phase L streams through the eight tile buffers: W1 tiles into 0 .. NW1-1, then sets of two
+  // W2 tiles (one per group) and the S tile of their 64 features, alternating between buffers
+  // 4, 5, 6 and 0, 1, 2.  Tile kinds as in LinStep.
+  constexpr int NW1 = HID / 64, NP = DP / 64;
+  static_assert(NW1 <= 4, "the W1 tiles and the first set share the eight buffers");
+  const uint32_t tiles_lds = lds_address(tiles);
+  const u32x4 W1r = make_rsrc_words(a.w1_q + (int64_t)h * HID * D), W2r = make_rsrc_words(a.w2_q + (int64_t)h * DP * HID),
+              Str = make_rsrc_words(a.state_s + ((int64_t)bh * a.state_slots + tc) * (int64_t)D * DP);
+  constexpr int RPB = 1024 / (2 * D);   // rows of W1 / W2 tiles per 1 KB block
+  auto issue_w1 = [&](int idx, int buf) {
+    const int voff = tile_voff_full<2 * D, 8>(wave, lane);
+#pragma unroll
+    for (int n = 0; n < L8; ++n) {
+      const int blk = wave + 8 * n;
+      direct_load_16(W1r, voff, idx * TB + blk * 1024, tiles_lds + buf * TB + blk * 1024);
+    }
+  };
+  auto issue_w2 = [&](int pb, int buf) {   // rows 32pb ..: first k-half in tile rows 0..31, second in 32..63
+    constexpr int CPR = 2 * D / 16;
+    const int jr = lane / CPR;
+    const int voff = jr * (4 * D) + (((lane % CPR) ^ swz<2 * D>(wave * RPB + jr)) << 4);
+#pragma unroll
+    for (int n = 0; n < L8; ++n) {
+      const int blk = wave + 8 * n, R = blk * RPB;
+      direct_load_16(W2r, voff, pb * 32 * (4 * D) + (R & 31) * (4 * D) + (R >> 5) * (2 * D),
+                     tiles_lds + buf * TB + blk * 1024);
+    }
+  };
+  auto issue_s = [&](int pp, int buf) {    // S_t^T columns 64pp .. of all D rows
+    const int jr = lane >> 3;
+    const int voff = jr * (4 * D) + (((lane & 7) ^ swz<128>(wave * 8 + jr)) << 4);
+#pragma unroll
+    for (int n = 0; n < L8; ++n) {
+      const int blk = wave + 8 * n;
+      direct_load_16(Str, voff, pp * 128 + blk * 8 * (4 * D), tiles_lds + buf * TB + blk * 1024);
+    }
+  };
+  auto issue_set = [&](int p) {
+    const int b = (p & 1) ? 0 : 4;
+    issue_w2(2 * p, b);
+    issue_w2(2 * p + 1, b + 1);
+    issue_s(p, b + 2);
+  };
+  const bool dbg_soft = a.dbg_m || a.dbg_nS || a.dbg_aS;
+  auto prologue = [&]() {
+#pragma unroll
+    for (int i = 0; i < NW1; ++i) issue_w1(i, i);
+    issue_set(0);
+  };
+  if (has_linear && !dbg_soft) prologue();
+
+  // ---- one reference for both groups -------------------------------------------------
+  {
+    const float part = half_swap_sum(lrun[0]);
+    if (g == 0) {
+      xref[kg][32 * qg + r] = mrun[0];
+      xmax[kg][32 * qg + r] = mtru[0];
+      xsum[kg][32 * qg + r] = part;
+    }
+  }
+  lds_barrier();
+  float nS, dscale;
+  {
+    const float r0 = xref[0][32 * qg + r], r1 = xref[1][32 * qg + r];
+    const float mref = fmaxf(r0, r1);
+    mtru[0] = fmaxf(xmax[0][32 * qg + r], xmax[1][32 * qg + r]);
+    nS = xsum[0][32 * qg + r] * __builtin_amdgcn_exp2f(r0 - mref) +
+         xsum[1][32 * qg + r] * __builtin_amdgcn_exp2f(r1 - mref);
+    const float f = __builtin_amdgcn_exp2f(mrun[0] - mref);
+    mrun[0] = mref;
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) O[db][0][e] *= f;
+    dscale = __builtin_amdgcn_exp2f(mrun[0] - mtru[0]);
+  }
+  // numerator registers 4i .. 4i+3 of feature block db, exchanged at 16 bytes per lane
+  auto slot = [&](int q, int n) { return reinterpret_cast<f32x4*>(tiles + (q * (4 * DB) + n) * 1024 + lane * 16); };
+  auto quad = [&](int db, int i) {
+    f32x4 x = {O[db][0][4 * i], O[db][0][4 * i + 1], O[db][0][4 * i + 2], O[db][0][4 * i + 3]};
+    return x;
+  };
+  if (dbg_soft) {   // component outputs: the two softmax parts are added for them alone
+    if (kg == 1) {
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *slot(qg, 4 * db + i) = quad(db, i);
+    }
+    lds_barrier();
+    if (kg == 0 && row < cr.q_hi) {
+      const int64_t o = (int64_t)bh * N + row;
+      if (g == 0) {
+        if (a.dbg_m) a.dbg_m[o] = mtru[0] * 0.6931471805599453f;   // back from base 2
+        if (a.dbg_nS) a.dbg_nS[o] = nS * dscale;
+      }
+      if (a.dbg_aS) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            *reinterpret_cast<f32x4*>(a.dbg_aS + o * D + 32 * db + 8 * i + 4 * g) =
+                (quad(db, i) + *slot(qg, 4 * db + i)) * dscale;
+      }
+    }
+    // the parts have been read, a^S is in memory, and the counted waits of phase L see tile
+    // loads only
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (has_linear) prologue();
+  }
+
+  // =========================== phase L =====================================
+  float nL = 0.f;
+  if (has_linear) {
+    const float lin_scale = __builtin_amdgcn_exp2f((a.stab_mode == 1 ? 0.f : mtru[0]) - mrun[0]);
+    const int sr = (r & 0x13) | ((r & 4) << 1) | ((r & 8) >> 1);
+    int woff[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) woff[ks] = tile_off<2 * D>(sr, 16 * ks + 8 * g);
+    auto unit_of = [&](int i) { return 16 * (i >> 1) + 8 * g + 4 * (i & 1); };
+    bf16x8 Ub[HID / 16];
+    wait_loads_and_barrier<3 * L8>();   // W1 has landed, the first set may be in flight
+    if (wave_live) {
+#pragma unroll
+      for (int hb = 0; hb < HID / 32; ++hb) {
+        f32x16 acc;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const f32x4 bias = *reinterpret_cast<const f32x4*>(sb1 + 32 * hb + unit_of(i));
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) acc[4 * i + jj] = bias[jj];
+        }
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          acc = mfma(*reinterpret_cast<const bf16x8*>(tiles + hb * (32 * 2 * D) + woff[ks]), Qr[0][ks], acc);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[e] = fmaxf(acc[e], 0.f);
+        Ub[2 * hb] = acc_to_operand(acc, 0);
+        Ub[2 * hb + 1] = acc_to_operand(acc, 1);
+      }
+    }
+    static_for<NP>([&](auto PC) {
+      constexpr int p = decltype(PC)::value;
+      wait_loads_and_barrier<0>();      // set p has landed; everyone is done with the other buffers
+      if constexpr (p + 1 < NP) issue_set(p + 1);
+      if (!wave_live) return;
+      constexpr int base = (p & 1) ? 0 : 4;
+      const char* const Ws = tiles + base * TB + kg * TB;
+      const char* const Ss = tiles + (base + 2) * TB;
+      const int pb = 2 * p + kg;
+      f32x16 acc;
+      float zv[16];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4 bias = *reinterpret_cast<const f32x4*>(sb2 + 32 * pb + unit_of(i));
+        const f32x4 zz = *reinterpret_cast<const f32x4*>(sz + 32 * pb + unit_of(i));
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          acc[4 * i + jj] = bias[jj];
+          zv[4 * i + jj] = zz[jj];
+        }
+      }
+#pragma unroll
+      for (int half = 0; half < 2; ++half)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+          acc = mfma(*reinterpret_cast<const bf16x8*>(Ws + half * (32 * 2 * D) + woff[ks]), Ub[half * KS + ks], acc);
+      constexpr bool squared = (64 * p >= DP / 2);
+      float part = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        float x = fmaxf(acc[e], 0.f);
+        if (squared) x = x * x;
+        x = x * lin_scale;   // unrounded in the normaliser, as in attn_kernel
+        acc[e] = x;
+        part += x * zv[e];
+      }
+      nL += part;
+#pragma unroll
+      for (int sidx = 0; sidx < 2; ++sidx) {
+        const bf16x8 fb = acc_to_operand(acc, sidx);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          const int rw = 32 * db + r;
+          const int c = (4 * kg + 2 * sidx) | g;
+          O[db][0] = mfma(*reinterpret_cast<const bf16x8*>(Ss + rw * 128 + ((c ^ swz<128>(rw)) << 4)), fb, O[db][0]);
+        }
+      }
+    });
+    nL = half_swap_sum(nL);
+    lds_barrier();   // the last set has been read
+  }
+
+  // =========================== merge (Eq. 5) ================================
+  // each group hands the other half of its numerator over and finishes DB / 2 feature blocks
+  if (g == 0) xlin[kg][32 * qg + r] = nL;
+  auto finish = [&](auto GC) {
+    constexpr int own = decltype(GC)::value, other = 1 - own;
+#pragma unroll
+    for (int n = 0; n < 2 * DB; ++n)
+      *slot(qg, (2 * DB) * other + n) = quad((DB / 2) * other + (n >> 2), n & 3);
+    lds_barrier();
+    if (row >= cr.q_hi) return;
+    const float nLt = xlin[0][32 * qg + r] + xlin[1][32 * qg + r];
+    const int64_t o = (int64_t)bh * N + row;
+    if (own == 0 && g == 0 && a.dbg_nL) a.dbg_nL[o] = nLt * dscale;
+    const float inv = 1.0f / (nS + nLt);
+#pragma unroll
+    for (int n = 0; n < 2 * DB; ++n) {
+      const int db = (DB / 2) * own + (n >> 2), i = n & 3;
+      const int col = 32 * db + 8 * i + 4 * g;
+      const f32x4 y = quad(db, i) + *slot(qg, (2 * DB) * own + n);
+      if (a.dbg_aL) {
+        f32x4 as = {0.f, 0.f, 0.f, 0.f};
+        if (a.dbg_aS) as = *reinterpret_cast<const f32x4*>(a.dbg_aS + o * D + col);
+        f32x4 x;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) {
+          // rounded as when a^S was stored, so that an empty linear set reports exactly zero
+          float t = y[jj] * dscale;
+          asm volatile("" : "+v"(t));
+          x[jj] = t - as[jj];
+        }
+        *reinterpret_cast<f32x4*>(a.dbg_aL + o * D + col) = x;
+      }
+      u32x2 pk;
+      pk[0] = pack_bf16(y[0] * inv, y[1] * inv);
+      pk[1] = pack_bf16(y[2] * inv, y[3] * inv);
+      *reinterpret_cast<u32x2*>(Og + row * D + col) = pk;
+    }
+  };
+  if (kg == 0) finish(std::integral_constant<int, 0>{});
+  else finish(std::integral_constant<int, 1>{});
+}
+
+// The split kernel holds one workgroup per CU (tile buffers of 128 KB), so it can only win while
+// its launch is a single round: at 256 items and fewer.  Measured whole calls, split against not, at
+// d = 128: 72 items of 39 key tiles 65.8 against 71.2 us, 144 of 15 tiles 55.7 against 57.7, 144 of
+// 8 tiles 49.9 against 50.7, 144 of 7 tiles 48.5 against 48.7; 312 items of 25 tiles 94 against 81,
+// 624 items 134 against 121.  At d = 64 (half the products per key, three attn_kernel
+// workgroups per CU): 72 items of 32 tiles 44.5 against 45.8, 20 tiles even, 8 tiles 28.1 against 27.6.
+bool attn_splits(int64_t n_items, int64_t n_keys, int d) {
+  return n_items <= 256 && n_keys >= (d == 128 ? 448 : 1536);
+}
+
 int attn_query_tile(int d) { return AttnShape<128, kAttnQB, kAttnNW>::QT; }
 
 const char* attn_kernel_name(int d) {
@@ -712,8 +1143,15 @@ const char* attn_kernel_name(int d) {
   return n;
 }
 
-hipError_t launch_attn(const AttnArgs& a, int d, int grid, hipStream_t stream) {
-  if (d == 128) {
+hipError_t launch_attn(const AttnArgs& a, const StateArgs* absorb, int d, bool split, hipStream_t stream) {
+  const int grid = a.items_per_xcd * 8;
+  if (split) {
+    StateArgs s{};
+    if (absorb) s = *absorb;
+    const int blocks = grid + (absorb ? s.items_per_xcd * 8 : 0);
+    if (d == 128) hipLaunchKernelGGL(attn_split_kernel<128>, dim3(blocks), dim3(512), 0, stream, a, s, grid);
+    else hipLaunchKernelGGL(attn_split_kernel<64>, dim3(blocks), dim3(512), 0, stream, a, s, grid);
+  } else if (d == 128) {
     hipLaunchKernelGGL((attn_kernel<128, kAttnQB, kAttnNW>), dim3(grid), dim3(64 * kAttnNW), 0, stream, a);
   } else {
     hipLaunchKernelGGL((attn_kernel<64, kAttnQB, kAttnNW>), dim3(grid), dim3(64 * kAttnNW), 0, stream, a);

@@ -236,7 +236,12 @@ hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t stream);
 
 hipError_t launch_state(const StateArgs& a, int d, int grid, hipStream_t stream);
 hipError_t launch_prefix(const PrefixArgs& a, hipStream_t stream);
-hipError_t launch_attn(const AttnArgs& a, int d, int grid, hipStream_t stream);
+// `split`: attn_split_kernel, otherwise attn_kernel.  `absorb` (with split only): chunk-state
+// pieces run by further workgroups of the launch.
+hipError_t launch_attn(const AttnArgs& a, const StateArgs* absorb, int d, bool split, hipStream_t stream);
+// whether attn_split_kernel is the better one for a launch of n_items 128-query workgroups whose
+// softmax windows hold n_keys keys
+bool attn_splits(int64_t n_items, int64_t n_keys, int d);
 int attn_query_tile(int d);  // query tokens per workgroup of the attention kernel
 const char* attn_kernel_name(int d);  // the instance launched for head width d, as profilers show it
 hipError_t launch_state_out(const StateOutArgs& a, hipStream_t stream);

@@ -1,0 +1,99 @@
+"""The attention kernel for launches that leave the chip unfilled (two groups of waves share the key
+tiles and the features of a query block) at the sizes where it can go wrong: one key tile, an odd
+and an even number of them, a ragged last one on either group, query blocks without a query, chunks
+without a linear part, both head widths; and the streaming step that absorbs beside it."""
+import pytest
+import torch
+
+from oracle import cref
+from paper_2601_04342_amd import binding, synth
+from tests import parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _announce(request):
+    print(f"[gpu-test] {request.node.nodeid}", flush=True)
+    yield
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("case", [
+    # B, H, T, HW, d, chunk, overlap, stab, gain: whole-sequence calls, windows of 448 keys (1,536
+    # at d = 64) and more
+    (1, 1, 2, 448, 128, 1, 0, 0, 4.0),     # the smallest window: 7 full tiles
+    (1, 1, 2, 1024, 128, 1, 0, 0, 4.0),    # 16 full tiles
+    (1, 1, 2, 1025, 128, 1, 0, 0, 4.0),    # 17 tiles: one key in the last, the second group has none
+    (1, 2, 2, 1150, 128, 1, 0, 1, 4.0),    # 18 tiles, the second group's last one ragged; c = 0
+    (2, 1, 3, 520, 128, 2, 0, 0, 4.0),     # short last chunk: a window of 9 tiles beside one of 17
+    (1, 1, 3, 600, 128, 1, 1, 0, 4.0),     # chunk 0 sees half a window and has no linear part
+    (1, 1, 2, 1700, 64, 1, 0, 0, 6.0),     # the other head width
+    (1, 1, 1, 1300, 128, 1, 0, 0, 1.0),    # one chunk: softmax only
+])
+def test_whole_sequence(case):
+    B, H, T, HW, d, chunk, overlap, stab, gain = case
+    parity.run_case(B, H, T, HW, d, chunk, overlap, stab, gain, seed=sum(case[:6]))
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("n_q,n_win,n_absorb", [
+    (1, 1, 1),           # one query, one key
+    (33, 64, 64),        # one key tile: the second group has no key
+    (128, 65, 1),        # the second group's only tile holds one key
+    (129, 200, 72),      # two query tiles, the second with one query
+    (200, 320, 320),
+])
+def test_step_absorbs_beside_the_attention(d, n_q, n_win, n_absorb):
+    """One step from a state of earlier tokens: output and state against the oracle's recurrence
+    (a two-chunk sequence whose second chunk holds the window)."""
+    B, H, n0 = 2, 2, 96
+    q, k, v = synth.make_qkv(B, H, n0 + n_win, d, seed=n_q + n_win + d)
+    phi = synth.make_phi(H, d, seed=5, gain=4.0)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    S, z = (torch.zeros(B, H, 2 * d, d, device="cuda"), torch.zeros(B, H, 2 * d, device="cuda"))
+    first = [x[:, :, :n0].contiguous() for x in (dq, dk, dv)]
+    binding.step(*first, dphi, S, z, n0)
+    win_q, win_k, win_v = (x[:, :, n0:].contiguous() for x in (dq, dk, dv))
+    queries = win_q.repeat(1, 1, -(-n_q // n_win), 1)[:, :, :n_q].contiguous()   # may outnumber the keys
+    out = binding.step(queries, win_k, win_v, dphi, S, z, n_absorb)
+    torch.cuda.synchronize()
+    pn = {m: p.double().numpy() for m, p in phi.items()}
+    for b in range(B):
+        for h in range(H):
+            args = [pn[m][h] for m in ("w1_k", "b1_k", "w2_k", "b2_k")]
+            kk, vv = k[b, h].double().numpy(), v[b, h].double().numpy()
+            S0, z0 = cref.state(kk, vv, n0, *args)
+            S1, z1 = cref.state(kk, vv, n0 + n_absorb, *args)
+            tol = 6e-3 * abs(S1).max()   # bars of the state hook's test
+            assert abs(S[b, h].cpu().numpy() - S1).max() <= tol
+            assert abs(z[b, h].cpu().numpy() - z1).max() <= 3e-3 * abs(z1).max()
+            # read-out with the state before the increment (Eq. 16)
+            x = queries[b, h].double().cpu()
+            U = torch.relu(x @ torch.from_numpy(pn["w1_q"][h]).T + torch.from_numpy(pn["b1_q"][h]))
+            f = torch.relu(U @ torch.from_numpy(pn["w2_q"][h]).T + torch.from_numpy(pn["b2_q"][h]))
+            f[:, d:] = f[:, d:] ** 2
+            s = x @ torch.from_numpy(kk[n0:]).T / d ** 0.5
+            w = torch.exp(s - s.max(dim=1, keepdim=True).values)
+            want = (w @ torch.from_numpy(vv[n0:]) + f @ torch.from_numpy(S0)) / (
+                w.sum(1, keepdim=True) + (f @ torch.from_numpy(z0))[:, None])
+            err = (out[b, h].double().cpu() - want).abs()
+            assert err.max() <= parity.OUT_MAX_ABS and err.mean() <= parity.OUT_MEAN_ABS, (b, h, err.max())
+
+
+def test_keys_that_weigh_nothing_in_one_group():
+    """Every key of the second group scores -inf (fp32 overflow of the product): those keys have
+    weight zero and the others carry the row."""
+    H, HW, d = 1, 1088, 128
+    q, k, v = synth.make_qkv(1, H, HW, d, seed=3)
+    q[..., 0], k[..., 0] = 1e19, 0.0
+    tile = torch.arange(HW) // 64
+    k[:, :, tile % 2 == 1, 0] = -1e25
+    q, k = synth.round_bf16(q), synth.round_bf16(k)
+    phi = {n: torch.zeros_like(p) for n, p in synth.make_phi(H, d).items()}
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    out = binding.forward(dq, dk, dv, dphi, 1, HW, 1).float().cpu().double()
+    keep = tile % 2 == 0
+    s = q.double() @ k[:, :, keep].double().transpose(-1, -2) / d ** 0.5
+    want = torch.softmax(s, dim=-1) @ v[:, :, keep].double()
+    assert (out - want).abs().max() <= parity.OUT_MAX_ABS
