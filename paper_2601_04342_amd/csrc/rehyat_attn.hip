@@ -853,6 +853,7 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
         sz[i] = zt[i];
       }
     }
+    settle(Qr[0]);
     wait_loads_and_barrier<0>();   // also publishes the bias vectors
     auto k_tile = [&](int j) -> const char* { return tiles + (j & 1) * TB; };
     auto v_tile = [&](int j) -> const char* { return tiles + (2 + (j & 1)) * TB; };

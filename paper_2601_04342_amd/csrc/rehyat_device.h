@@ -260,6 +260,17 @@ __device__ __forceinline__ void tile_load_fast(u32x4 rsrc, int soff, uint32_t ld
   }
 }
 
+// Makes the compiler wait here for the loads that filled these operands.  Without it the wait
+// goes to their first use inside the tile loop and stays there for every tile, as a count of
+// outstanding loads in which the direct loads issued as inline asm are not known: it then
+// waits for the tiles just requested and undoes their prefetch.
+template <int N>
+__device__ __forceinline__ void settle(bf16x8 (&x)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
+}
+__device__ __forceinline__ void settle(float& x) { asm volatile("" : "+v"(x)); }
+
 // Wait until at most N of this wave's direct loads are outstanding (and all of
 // its LDS accesses are done), then workgroup barrier.  Written as one asm block:
 // the compiler's own barrier would wait for every outstanding direct load and

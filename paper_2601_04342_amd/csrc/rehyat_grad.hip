@@ -550,6 +550,7 @@ tn_gemm_kernel(TnGemmArgs a) {
   if (pc.n_tiles > 0) {
     issue_x(0);
     issue_p(0);
+    settle(w1f);
     wait_loads_and_barrier<0>();
     if (pc.n_tiles > 1) issue_x(1);
     build_u(0);
@@ -643,7 +644,7 @@ hid_grad_kernel(HidGradArgs a) {
   const u32x4 Pr = make_rsrc_words(a.dpsi + row0 * DP), Xr = make_rsrc_words(a.x + row0 * D);
 
   const int unit = wave * 32 + r;   // this lane's hidden unit
-  const float b1v = a.b1[(int64_t)h * HID + unit];
+  float b1v = a.b1[(int64_t)h * HID + unit];
   bf16x8 w1f[KS];                   // B operands: column = hidden unit, k = head dimension
   {
     const bf16_t* p = a.w1 + ((int64_t)h * HID + unit) * D + 8 * g;
@@ -677,6 +678,9 @@ hid_grad_kernel(HidGradArgs a) {
     tile_load_fast<2 * D, TB, NW>(Xr, __builtin_amdgcn_readfirstlane(it * TB), base + TBU, wave, lane, valid, xvoff);
   };
   if (pc.n_tiles > 0) issue(0);
+  settle(w1f);
+  settle(w2tf);
+  settle(b1v);
   for (int it = 0; it < pc.n_tiles; ++it) {
     const int valid = (it + 1 < pc.n_tiles) ? 64 : pc.last_rows;
     const char* const Ps = Ts + (it & 1) * SET;

@@ -77,7 +77,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   if (tid < HID) B1s[tid] = a.b1_k[(int64_t)h * HID + tid];
   const float* const b1rows = B1s + wave * 32 + 4 * g;
   const int unit = wave * 32 + r;  // this lane's hidden unit (first half) and feature (second half)
-  const float b2v = a.b2_k[(int64_t)h * DP + unit];
+  float b2v = a.b2_k[(int64_t)h * DP + unit];
   bf16x8 w1f[KS];   // A operands: row = hidden unit, k = head dimension
   {
     const bf16_t* p = a.w1_k + ((int64_t)h * HID + unit) * D + 8 * g;
@@ -156,6 +156,11 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   if (n_tiles > 0) {
     issue_k(0);
     issue_v(0);
+  }
+  settle(w1f);
+  settle(w2f);
+  settle(b2v);
+  if (n_tiles > 0) {
     wait_loads_and_barrier<0>();   // also: the bias is in LDS
     if (n_tiles > 1) issue_k(1);
     const int ln = opaque_lane();
