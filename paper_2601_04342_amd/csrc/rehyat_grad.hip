@@ -162,8 +162,10 @@ hipError_t launch_transpose(const TransposeArgs& a, hipStream_t stream) {
 // waits.  Vector memory operations of a wave complete in the order issued, stores included,
 // so "at most n outstanding" after n younger stores means every older load has landed.
 // ------------------------------------------------------------------------------------
+// Two waves per SIMD, also where a workgroup has four waves: with the whole register file to use the
+// compiler keeps accumulators in AGPRs and copies each one out before vector work.
 template <int D, int NW, bool TW>
-__global__ void __launch_bounds__(64 * NW)
+__global__ void __launch_bounds__(64 * NW, 2)
 act_grad_kernel(ActGradArgs a) {
   constexpr int HID = 2 * D, DP = 2 * D;
   constexpr int KS = D / 16;
@@ -443,7 +445,7 @@ __device__ __forceinline__ BiasRows load_bias_rows(const float* bp) {
 // requested at the start of tile t.
 // ------------------------------------------------------------------------------------
 template <int D, int NW>
-__global__ void __launch_bounds__(64 * NW)
+__global__ void __launch_bounds__(64 * NW, 2)
 tn_gemm_kernel(TnGemmArgs a) {
   constexpr int W = 2 * D;          // features = hidden units
   constexpr int KS = D / 16;
@@ -615,7 +617,7 @@ hipError_t launch_tn_gemm(const TnGemmArgs& a, int d, int grid, hipStream_t stre
 // of dW1^T, exactly as the chunk-state kernel accumulates V^T phi.
 // ------------------------------------------------------------------------------------
 template <int D, int NW>
-__global__ void __launch_bounds__(64 * NW)
+__global__ void __launch_bounds__(64 * NW, 2)
 hid_grad_kernel(HidGradArgs a) {
   constexpr int HID = 2 * D, DP = 2 * D;
   constexpr int KS = D / 16;

@@ -29,8 +29,10 @@
 
 namespace rehyat {
 
+// Two waves per SIMD, also where a workgroup has four waves: with the whole register file to use the
+// compiler keeps accumulators in AGPRs and copies each one out before vector work.
 template <int D, int NW>
-__global__ void __launch_bounds__(64 * NW)
+__global__ void __launch_bounds__(64 * NW, 2)
 state_kernel(StateArgs a) {
   __shared__ __attribute__((aligned(1024))) char XV[StateLds<D>::XV];   // K tiles 0/1, then V tiles 0/1
   __shared__ __attribute__((aligned(1024))) char Us[StateLds<D>::US];   // U of the current and of the next tile
