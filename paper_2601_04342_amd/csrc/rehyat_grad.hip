@@ -162,6 +162,11 @@ hipError_t launch_transpose(const TransposeArgs& a, hipStream_t stream) {
 // waits.  Vector memory operations of a wave complete in the order issued, stores included,
 // so "at most n outstanding" after n younger stores means every older load has landed.
 // ------------------------------------------------------------------------------------
+// The kernel was bound by vector work (18 instructions per feature and token: selects for the
+// squared half and for rows past the end, a conversion per stored element).  The two halves of
+// the features and the ragged tile now have code of their own, elements are converted in pairs, the
+// bias is the accumulators' start and the key side leaves out the sum it does not need: 168 -> 147
+// us (queries) and 167 -> 131 us (keys) at the 480p shape.
 // Two waves per SIMD, also where a workgroup has four waves: with the whole register file to use the
 // compiler keeps accumulators in AGPRs and copies each one out before vector work.
 template <int D, int NW, bool TW>
@@ -289,7 +294,7 @@ act_grad_kernel(ActGradArgs a) {
   char* const Sg = Stg + wave * (32 * SROW);   // this wave's patch: [32 tokens][32 features]
 
   float db2acc = 0.f, dzacc = 0.f;
-  const bool squared = (wave * 32 >= DP / 2);
+  const int valid_last = rem;   // rows of the ragged last tile
   const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
   if (n_tiles > 0) issue(0);
@@ -300,8 +305,9 @@ act_grad_kernel(ActGradArgs a) {
     wait_loads_and_barrier<0>();
   }
 
-  for (int it = 0; it < n_tiles; ++it) {
-    const int valid = it < n_full ? 64 : rem;
+  auto tile = [&](auto TAILC, auto SQC, int it) {
+    constexpr bool TAIL = decltype(TAILC)::value;      // fewer than 64 rows count
+    constexpr bool squared = decltype(SQC)::value;     // Phi = psi^2, psi = relu(.) otherwise
     const char* const Xs = XV + (it & 1) * TB;
     const char* const Vs = XV + (2 + (it & 1)) * TB;
     const float* const tws = Tws + (it & 1) * 64;
@@ -312,7 +318,13 @@ act_grad_kernel(ActGradArgs a) {
     // ---- first half ----------------------------------------------------------
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
-      f32x16 u = zero;
+      f32x16 u;   // starts from the bias: no addition per element
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const f32x4 bb = *reinterpret_cast<const f32x4*>(b1rows + 8 * i);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[4 * i + j] = bb[j];
+      }
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) {
         bf16x8 xf = *reinterpret_cast<const bf16x8*>(Xs + (xbase ^ (32 * ks)) + tb * (32 * 2 * D));
@@ -320,10 +332,9 @@ act_grad_kernel(ActGradArgs a) {
       }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const f32x4 bb = *reinterpret_cast<const f32x4*>(b1rows + 8 * i);
         u32x2 pk;
-        pk[0] = pack_bf16(fmaxf(u[4 * i] + bb[0], 0.f), fmaxf(u[4 * i + 1] + bb[1], 0.f));
-        pk[1] = pack_bf16(fmaxf(u[4 * i + 2] + bb[2], 0.f), fmaxf(u[4 * i + 3] + bb[3], 0.f));
+        pk[0] = pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f));
+        pk[1] = pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f));
         *reinterpret_cast<u32x2*>(Us + uwbase + 16 * i + tb * (32 * UPAD)) = pk;
       }
     }
@@ -343,35 +354,37 @@ act_grad_kernel(ActGradArgs a) {
         bf16x8 vf = *reinterpret_cast<const bf16x8*>(Vs + (xbase ^ (32 * ks)) + tb * (32 * 2 * D));
         dphi = mfma(vf, mf[ks], dphi);
       }
-      float pdb = 0.f, pdz = 0.f;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         f32x4 tw = {1.f, 1.f, 1.f, 1.f};   // weights of zv for tokens 32 tb + 8 i + 4 g + j
         if (TW) tw = *reinterpret_cast<const f32x4*>(tws + 32 * tb + 8 * i + 4 * g);
+        float dp[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const int e = 4 * i + j;
-          const bool live = 32 * tb + 8 * i + 4 * g + j < valid;
+          const bool live = !TAIL || 32 * tb + 8 * i + 4 * g + j < valid_last;
           const float psi = fmaxf(ps[e] + b2v, 0.f);
-          const float base = dphi[e] + tw[j] * zvv;   // dL/dPhi
-          // Phi = psi^2 in the squared half, psi = relu(.) in the other (wave-uniform choice)
-          const float dp = squared ? 2.f * psi * base : (psi > 0.f ? base : 0.f);
-          const float ph = squared ? psi * psi : psi;
-          pdb += live ? dp : 0.f;
-          pdz += live ? tw[j] * ph : 0.f;
-          *reinterpret_cast<bf16_t*>(Sg + (8 * i + 4 * g + j) * SROW + 2 * r) =
-              (bf16_t)(pack_bf16(dp, 0.f) & 0xffffu);
+          const float base = TW ? dphi[e] + tw[j] * zvv : dphi[e] + zvv;   // dL/dPhi
+          dp[j] = squared ? (psi + psi) * base : (psi > 0.f ? base : 0.f);
+          db2acc += live ? dp[j] : 0.f;
+          // dL/dz_t is a sum over queries only
+          if (TW) dzacc += live ? tw[j] * (squared ? psi * psi : psi) : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; j += 2) {
+          const uint32_t pk = pack_bf16(dp[j], dp[j + 1]);
+          char* const w = Sg + (8 * i + 4 * g + j) * SROW + 2 * r;
+          *reinterpret_cast<bf16_t*>(w) = (bf16_t)pk;
+          *reinterpret_cast<bf16_t*>(w + SROW) = (bf16_t)(pk >> 16);
         }
       }
-      db2acc += pdb;
-      dzacc += pdz;
       // the patch leaves token-major: 4 chunks of 16 bytes per token row, two per lane
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
         const int idx = ln + 64 * n;
         const int row = idx >> 2, c = idx & 3;
         const u32x4 val = *reinterpret_cast<const u32x4*>(Sg + row * SROW + 16 * c);
-        if (32 * tb + row < valid)
+        if (!TAIL || 32 * tb + row < valid_last)
           *reinterpret_cast<u32x4*>(Pg + ((int64_t)it * 64 + 32 * tb + row) * (DP * 2) + wave * 64 + 16 * c) = val;
       }
     }
@@ -381,7 +394,13 @@ act_grad_kernel(ActGradArgs a) {
       wait_loads_and_barrier<NST>();
       if (it + 2 < n_tiles) issue(it + 2);
     }
-  }
+  };
+  auto all_tiles = [&](auto SQC) {   // the waves of both instances meet at the same barriers
+    for (int it = 0; it < n_full; ++it) tile(std::false_type{}, SQC, it);
+    if (rem > 0) tile(std::true_type{}, SQC, n_full);
+  };
+  if (wave * 32 >= DP / 2) all_tiles(std::true_type{});
+  else all_tiles(std::false_type{});
 
   const float db2 = half_swap_sum(db2acc);
   const float dz = half_swap_sum(dzacc);
