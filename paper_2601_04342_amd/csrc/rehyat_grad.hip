@@ -87,19 +87,40 @@ suffix_kernel(SuffixArgs a) {
   if (idx >= a.elems) return;
   const bool is_s = idx < a.s_elems;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  for (int c = a.n_seg - 1; c >= 0; --c) {
-    if (is_s) {
-      const float* p = a.s_part + ((int64_t)bh * a.s_slots + (int64_t)c * a.s_nsplit) * a.elems + idx;
-      for (int sp = 0; sp < a.s_nsplit; ++sp) acc += *reinterpret_cast<const f32x4*>(p + (int64_t)sp * a.elems);
-      u32x2 pk;
-      pk[0] = pack_bf16(acc[0], acc[1]);
-      pk[1] = pack_bf16(acc[2], acc[3]);
-      *reinterpret_cast<u32x2*>(a.Rt + ((int64_t)bh * a.slots + c) * a.s_elems + idx) = pk;
-    } else {
-      const int zi = idx - a.s_elems;
-      const float* p = a.z_part + (((int64_t)bh * a.n_seg + c) * a.z_nsplit) * a.dp + zi;
-      for (int sp = 0; sp < a.z_nsplit; ++sp) acc += *reinterpret_cast<const f32x4*>(p + (int64_t)sp * a.dp);
-      *reinterpret_cast<f32x4*>(a.r + ((int64_t)bh * a.slots + c) * a.dp + zi) = acc;
+  // pieces of segment c, then its sum goes out; kScanDepth pieces are loaded ahead of their sums
+  const int ns = is_s ? a.s_nsplit : a.z_nsplit;
+  const float* const base = is_s ? a.s_part + (int64_t)bh * a.s_slots * a.elems + idx
+                                 : a.z_part + (int64_t)bh * a.n_seg * a.z_nsplit * a.dp + (idx - a.s_elems);
+  const int64_t stride = is_s ? a.elems : a.dp;
+  int lc = a.n_seg - 1, lsp = 0;   // next piece to load
+  int c = a.n_seg - 1, sp = 0;     // next piece to add
+  while (c >= 0) {
+    f32x4 x[kScanDepth];
+#pragma unroll
+    for (int u = 0; u < kScanDepth; ++u) {
+      if (lc >= 0) {
+        x[u] = *reinterpret_cast<const f32x4*>(base + ((int64_t)lc * ns + lsp) * stride);
+        if (++lsp == ns) {
+          lsp = 0;
+          --lc;
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kScanDepth; ++u) {
+      if (c < 0) break;
+      acc += x[u];
+      if (++sp < ns) continue;
+      if (is_s) {
+        u32x2 pk;
+        pk[0] = pack_bf16(acc[0], acc[1]);
+        pk[1] = pack_bf16(acc[2], acc[3]);
+        *reinterpret_cast<u32x2*>(a.Rt + ((int64_t)bh * a.slots + c) * a.s_elems + idx) = pk;
+      } else {
+        *reinterpret_cast<f32x4*>(a.r + ((int64_t)bh * a.slots + c) * a.dp + idx - a.s_elems) = acc;
+      }
+      sp = 0;
+      --c;
     }
   }
 }

@@ -34,6 +34,9 @@ struct StateArgs {
                         // (the sums of phi_q(q) u^T behind the gradient of the chunk state)
 };
 
+// pieces in flight per thread of the prefix and suffix passes
+constexpr int kScanDepth = 8;
+
 // ---- prefix kernel: states S_t, z_t of the window's chunks ---------------------
 struct PrefixArgs {
   const float* partial;  // as written by the state kernel

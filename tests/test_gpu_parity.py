@@ -177,6 +177,13 @@ def test_state_hook_matches_oracle_state():
             assert np.abs(z[0, h].cpu().numpy() - zr).max() <= 3e-3 * max(np.abs(zr).max(), 1e-30) + 1e-30
 
 
+@pytest.mark.parametrize("T,HW", [(2, 130), (9, 40), (10, 40), (18, 500), (33, 20)])
+def test_states_around_whole_batches_of_pieces(T, HW):
+    """The prefix pass loads eight pieces at a time: one piece, eight, nine, pieces of split segments
+    and a second window, each state read by a chunk."""
+    parity.run_case(1, 1, T, HW, 64, 1, 0, 0, 3.0, seed=T + HW)
+
+
 def test_causal_prefix_consistency_on_gpu():
     """Appending frames does not change earlier outputs (Eq. 13)."""
     B, H, T, HW, d = 1, 2, 6, 100, 128
