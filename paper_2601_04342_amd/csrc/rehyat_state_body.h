@@ -201,7 +201,6 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
         bf16x8 uf = *reinterpret_cast<const bf16x8*>(Uc + urbase + 32 * ks + tb * (32 * UPAD));
         ps = mfma(uf, w2f[ks], ps);
       }
-      float part = 0.f;
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         float x = fmaxf(ps[e] + b2v, 0.f);
@@ -209,16 +208,27 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
         if (TAIL) {
           if (32 * tb + 8 * (e >> 2) + 4 * g + (e & 3) >= rem) x = 0.f;   // token beyond the range
         }
-        // the product below rounds x to bf16; the normaliser takes it unrounded (random signs,
-        // relative size 2^-9 per term), which saves two instructions per feature
         ps[e] = x;
-        part += x;
+      }
+      // The normaliser sums the features as rounded for the product below: with unrounded ones S
+      // and z weigh a token differently, and for keys that resemble each other the differences
+      // add up (equal keys: error of y against fp64 up to 30 % larger, of gradients 40 %).
+      const bf16x8 fbs[2] = {acc_to_operand(ps, 0), acc_to_operand(ps, 1)};
+      float part = 0.f;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const u32x4 w = __builtin_bit_cast(u32x4, fbs[s]);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          part += __builtin_bit_cast(float, w[i] << 16);
+          part += __builtin_bit_cast(float, w[i] & 0xffff0000u);
+        }
       }
       zacc += part;
       // state slice += V^T phi, two 16-token steps
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        bf16x8 fb = acc_to_operand(ps, s);
+        const bf16x8 fb = fbs[s];
 #pragma unroll
         for (int db = 0; db < DB; ++db) {
           const int so = (2 * tb + s) * (16 * 2 * D);
@@ -232,9 +242,10 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
 
   // A loop for each half of the features: decided per element, squaring costs a select each (the
   // waves of both loops meet at the same number of barriers).  With the bias in the first
-  // product and no rounding before z this takes the vector work of a tile from 290 to 160
-  // instructions per wave: 105 -> 103 us at the 480p shape, where the LDS latency of eight waves in
-  // step bounds a tile, 81 -> 65 us at 24 heads of 64 (with the accumulators out of the AGPRs).
+  // product and z summed from the operands of the second this takes the vector work of a tile from
+  // 290 to 190 instructions per wave: 105 -> 103 us at the 480p shape, where the LDS latency of
+  // eight waves in step bounds a tile, 81 -> 65 us at 24 heads of 64 (with the accumulators out of
+  // the AGPRs).  160 instructions with z of unrounded features took the same time at both shapes.
   auto all_tiles = [&](auto SQC) {
     for (int it = 0; it < n_full; ++it) tile_step(std::false_type{}, SQC, it);
     if (rem > 0) tile_step(std::true_type{}, SQC, n_full);

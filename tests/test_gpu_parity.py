@@ -177,6 +177,27 @@ def test_state_hook_matches_oracle_state():
             assert np.abs(z[0, h].cpu().numpy() - zr).max() <= 3e-3 * max(np.abs(zr).max(), 1e-30) + 1e-30
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_state_and_normaliser_weigh_a_token_alike(d):
+    """Equal keys and v = 1: every column of S is the same sum as z, of up to N terms of one sign, so
+    the two differ by fp32 summation alone (N additions of 2^-24 each), through the state hook and
+    through a streaming step.  A feature rounded for one of them only shows as up to 2^-9."""
+    B, H, T, HW = 1, 2, 2, 300
+    N = T * HW
+    _, k, v = synth.make_qkv(B, H, N, d, seed=12)
+    k, v = k[:, :, :1].expand_as(k).contiguous(), torch.ones_like(v)
+    phi = synth.make_phi(H, d, seed=13, gain=4.0)
+    dk, _, dv, dphi = parity.to_device(k, k, v, phi)
+    states = [binding.state(dk, dv, dphi, T, HW, T)]
+    S, z = torch.zeros(B, H, 2 * d, d, device="cuda"), torch.zeros(B, H, 2 * d, device="cuda")
+    binding.step(dk[:, :, :64].contiguous(), dk, dv, dphi, S, z, N)
+    states.append((S, z))
+    torch.cuda.synchronize()
+    for S, z in states:
+        assert (z > 0).any()
+        assert ((S.double() - z.double()[..., None]).abs() <= N * 2.0 ** -24 * z.double()[..., None]).all()
+
+
 @pytest.mark.parametrize("T,HW", [(2, 130), (9, 40), (10, 40), (18, 500), (33, 20)])
 def test_states_around_whole_batches_of_pieces(T, HW):
     """The prefix pass loads eight pieces at a time: one piece, eight, nine, pieces of split segments
