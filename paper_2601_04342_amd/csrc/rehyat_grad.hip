@@ -375,6 +375,7 @@ act_grad_kernel(ActGradArgs a) {
         bf16x8 vf = *reinterpret_cast<const bf16x8*>(Vs + (xbase ^ (32 * ks)) + tb * (32 * 2 * D));
         dphi = mfma(vf, mf[ks], dphi);
       }
+      float pdb = 0.f, pdz = 0.f;   // the block's own sums: short chains of additions in fp32
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
         f32x4 tw = {1.f, 1.f, 1.f, 1.f};   // weights of zv for tokens 32 tb + 8 i + 4 g + j
@@ -387,9 +388,9 @@ act_grad_kernel(ActGradArgs a) {
           const float psi = fmaxf(ps[e] + b2v, 0.f);
           const float base = TW ? dphi[e] + tw[j] * zvv : dphi[e] + zvv;   // dL/dPhi
           dp[j] = squared ? (psi + psi) * base : (psi > 0.f ? base : 0.f);
-          db2acc += live ? dp[j] : 0.f;
+          pdb += live ? dp[j] : 0.f;
           // dL/dz_t is a sum over queries only
-          if (TW) dzacc += live ? tw[j] * (squared ? psi * psi : psi) : 0.f;
+          if (TW) pdz += live ? tw[j] * (squared ? psi * psi : psi) : 0.f;
         }
 #pragma unroll
         for (int j = 0; j < 4; j += 2) {
@@ -399,6 +400,8 @@ act_grad_kernel(ActGradArgs a) {
           *reinterpret_cast<bf16_t*>(w + SROW) = (bf16_t)(pk >> 16);
         }
       }
+      db2acc += pdb;
+      if (TW) dzacc += pdz;
       // the patch leaves token-major: 4 chunks of 16 bytes per token row, two per lane
 #pragma unroll
       for (int n = 0; n < 2; ++n) {

@@ -217,3 +217,30 @@ def test_saved_forward_pass_gives_the_same_gradients():
         a, b = g_full[n].double(), g_saved[n].double()
         assert torch.isfinite(b).all(), n
         assert (a - b).norm() <= 2e-3 * a.norm(), (n, float((a - b).norm() / a.norm()))
+
+
+@pytest.mark.parametrize("d,H,HW", [(128, 256, 2048), (64, 512, 1024)])
+def test_bias_gradient_sums_stay_short(d, H, HW):
+    """Every query of chunk 1 contributes the same gradient, so db2_q is HW times that of one query,
+    up to the roundings of the sum alone.  A lane sums 16 features of a 32-token block, then the
+    blocks of its piece (half the tokens each of two lanes), then pieces: no term passes more than
+    16 + HW / 32 + 8 additions, of a relative rounding of 2^-24 each (all terms have one sign)."""
+    T, N = 2, 2 * HW
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    row = lambda n: torch.randn(1, H, n, d, generator=gen, device="cuda").to(torch.bfloat16)
+    q = row(1).expand(1, H, N, d).contiguous()
+    k, v = row(N), row(N)
+    G = (row(1) / 64).expand(1, H, N, d).contiguous()
+    dphi = binding.phi_to_device(synth.make_phi(H, d, seed=8, gain=4.0))
+    one = torch.zeros_like(G)
+    one[:, :, HW] = G[:, :, HW]
+    full = binding.phi_backward(q, k, v, dphi, G, T, HW, 1)[0]["b2_q"]
+    single = binding.phi_backward(q, k, v, dphi, one, T, HW, 1)[0]["b2_q"]
+    torch.cuda.synchronize()
+    assert (single != 0).float().mean() > 0.1
+    want = single.double() * HW
+    err = (full.double() - want).abs()
+    bound = (16 + HW / 32 + 8) * 2.0 ** -24
+    worst = (err / want.abs().clamp_min(1e-300)).max().item()
+    print(f"   worst relative error {worst:.2e}, bound {bound:.2e}", flush=True)
+    assert (err <= bound * want.abs()).all(), worst
