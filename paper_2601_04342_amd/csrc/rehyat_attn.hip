@@ -36,6 +36,9 @@ namespace rehyat {
 // tile, and weights stay below 2^kLazyMax (harmless for bf16 weights and fp32 sums; the
 // final division cancels the reference).  The true maximum is tracked beside it.
 constexpr float kLazyMax = 8.0f;
+// Where the reference starts: finite, so that a row whose first key tiles score -inf (or a group
+// of waves that sees no key of a row) weighs them exp2(-inf - reference) = 0, not a NaN.
+constexpr float kLowest = -3.402823466e38f;
 // Query blocks of 32 per wave.  1 -> 128-query workgroups, two resident per CU, whose
 // waves share each SIMD and fill each other's stalls; 2 (one wave per SIMD with twice the
 // registers, half the LDS operand traffic per MFMA) measured 30 % slower at the 480p shape.
@@ -431,7 +434,7 @@ attn_kernel(AttnArgs a) {
   float lrun[QB];  // this lane half's share of the sum
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
-    mrun[qb] = -INFINITY;
+    mrun[qb] = kLowest;
     mtru[qb] = -INFINITY;
     lrun[qb] = 0.f;
   }
@@ -760,7 +763,6 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   constexpr int GB = 4 * TB;             // tile buffers of one group: K 0/1, V 0/1
   constexpr int L4 = TB / (1024 * 4);    // direct loads per wave per tile moved by one group
   constexpr int L8 = TB / (1024 * 8);    // direct loads per wave per tile moved by all eight waves
-  constexpr float kLowest = -3.402823466e38f;
   using SL = StateLds<D>;
   __shared__ __attribute__((aligned(1024))) char tiles[2 * GB > SL::XV + SL::US ? 2 * GB : SL::XV + SL::US];
   __shared__ __attribute__((aligned(256))) float sb1[HID];
@@ -811,8 +813,6 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   for (int db = 0; db < DB; ++db)
 #pragma unroll
     for (int e = 0; e < 16; ++e) O[db][0][e] = 0.f;
-  // The reference starts at the lowest finite value: a group may see no key at all, or only
-  // scores of -inf, for a row whose other keys are the other group's.
   float mrun[1] = {kLowest}, mtru[1] = {-INFINITY}, lrun[1] = {0.f};
 
   // =========================== phase S =====================================

@@ -97,3 +97,25 @@ def test_keys_that_weigh_nothing_in_one_group():
     s = q.double() @ k[:, :, keep].double().transpose(-1, -2) / d ** 0.5
     want = torch.softmax(s, dim=-1) @ v[:, :, keep].double()
     assert (out - want).abs().max() <= parity.OUT_MAX_ABS
+
+
+@pytest.mark.parametrize("H", [1, 60])
+def test_first_key_tiles_weigh_nothing(H):
+    """Every other key tile scores -inf (fp32 overflow of the product), the first one among them,
+    in a launch of 9 workgroups (the split kernel) and in one of 540 (attn_kernel): those keys
+    have weight zero and the others carry the row."""
+    HW, d = 1088, 128
+    q, k, v = synth.make_qkv(1, H, HW, d, seed=3)
+    q[..., 0], k[..., 0] = 1e19, 0.0
+    tile = torch.arange(HW) // 64
+    k[:, :, tile % 2 == 0, 0] = -1e25
+    q, k = synth.round_bf16(q), synth.round_bf16(k)
+    phi = {n: torch.zeros_like(p) for n, p in synth.make_phi(H, d).items()}
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    out = binding.forward(dq, dk, dv, dphi, 1, HW, 1)
+    torch.cuda.synchronize()
+    keep = tile % 2 == 1
+    for h in {0, H - 1}:
+        s = q[0, h].double() @ k[0, h, keep].double().T / d ** 0.5
+        want = torch.softmax(s, dim=-1) @ v[0, h, keep].double()
+        assert (out[0, h].double().cpu() - want).abs().max() <= parity.OUT_MAX_ABS, h
