@@ -339,7 +339,8 @@ int launch_attn_window(const Ctx& c, const void* q, const void* k, const void* v
   {
     ProfScope prof(c.prof, 2, c.st);
     const int64_t frames = (int64_t)chunk + overlap < T ? (int64_t)chunk + overlap : T;
-    e = launch_attn(a, nullptr, d, attn_splits(a.n_items, frames * HW, d), c.st);
+    const bool read_out = bidir || chunk_range(T, HW, chunk, overlap, c0 + n_chunks - 1).l_hi > 0;
+    e = launch_attn(a, nullptr, d, attn_splits(a.n_items, frames * HW, d, read_out), c.st);
   }
   if (e != hipSuccess) return hip_fail(e, "attention kernel launch");
   return REHYAT_OK;
@@ -1180,7 +1181,7 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   a.n_short = 0;
   {
     ProfScope prof(true, 2, st);
-    e = launch_attn(a, joint ? &s : nullptr, d, joint || attn_splits(attn_wgs, n_win, d), st);
+    e = launch_attn(a, joint ? &s : nullptr, d, joint || attn_splits(attn_wgs, n_win, d, true), st);
   }
   if (e != hipSuccess) return hip_fail(e, "attention kernel launch");
   if (joint) {   // state += pieces

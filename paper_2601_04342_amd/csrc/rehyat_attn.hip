@@ -751,7 +751,7 @@ attn_kernel(AttnArgs a) {
 // state update).  0.14 of the 0.82 us goes away with the tile loads: tiles are requested three
 // half-steps ahead because one trip ahead, in lockstep, took 0.89 us.
 // 128 KB of tile buffers (K and V of two tiles per group): one workgroup per CU, which is why
-// attn_kernel stays the better one as soon as its own launch fills the chip (split_pays).
+// attn_kernel stays the better one as soon as its own launch fills the chip (attn_splits).
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(512, 2)
@@ -1131,8 +1131,13 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
 // 8 tiles 49.9 against 50.7, 144 of 7 tiles 48.5 against 48.7; 312 items of 25 tiles 94 against 81,
 // 624 items 134 against 121.  At d = 64 (half the products per key, three attn_kernel
 // workgroups per CU): 72 items of 32 tiles 44.5 against 45.8, 20 tiles even, 8 tiles 28.1 against 27.6.
-bool attn_splits(int64_t n_items, int64_t n_keys, int d) {
-  return n_items <= 256 && n_keys >= (d == 128 ? 448 : 1536);
+// Without a read-out phase, half of which each group would take, the two groups' meeting has to be
+// paid by the keys alone: at d = 128 4 - 256 items of 8 tiles 15.4 - 18.3 against 13.4 - 16.2 us, of 16
+// tiles 21.8 - 26.2 against 21.4 - 25.4, of 25 tiles 28.6 - 33.9 against 29.9 - 34.8; at d = 64 of 24 tiles
+// 21.6 - 24.2 against 21.0 - 23.2, of 48 tiles 36.6 - 38.5 against 37.7 - 40.2.
+bool attn_splits(int64_t n_items, int64_t n_keys, int d, bool read_out) {
+  if (n_items > 256) return false;
+  return read_out ? n_keys >= (d == 128 ? 448 : 1536) : n_keys >= (d == 128 ? 1536 : 2560);
 }
 
 int attn_query_tile(int d) { return AttnShape<128, kAttnQB, kAttnNW>::QT; }

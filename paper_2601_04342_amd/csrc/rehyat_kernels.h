@@ -243,8 +243,8 @@ hipError_t launch_prefix(const PrefixArgs& a, hipStream_t stream);
 // pieces run by further workgroups of the launch.
 hipError_t launch_attn(const AttnArgs& a, const StateArgs* absorb, int d, bool split, hipStream_t stream);
 // whether attn_split_kernel is the better one for a launch of n_items 128-query workgroups whose
-// softmax windows hold n_keys keys
-bool attn_splits(int64_t n_items, int64_t n_keys, int d);
+// softmax windows hold n_keys keys; `read_out`: some of them read a chunk state
+bool attn_splits(int64_t n_items, int64_t n_keys, int d, bool read_out);
 int attn_query_tile(int d);  // query tokens per workgroup of the attention kernel
 const char* attn_kernel_name(int d);  // the instance launched for head width d, as profilers show it
 hipError_t launch_state_out(const StateOutArgs& a, hipStream_t stream);

@@ -119,3 +119,27 @@ def test_first_key_tiles_weigh_nothing(H):
         s = q[0, h].double() @ k[0, h, keep].double().T / d ** 0.5
         want = torch.softmax(s, dim=-1) @ v[0, h, keep].double()
         assert (out[0, h].double().cpu() - want).abs().max() <= parity.OUT_MAX_ABS, h
+
+
+@pytest.mark.parametrize("case", [
+    (1, 1, 1, 1601, 128, 1, 0, 0, 1.0),    # 26 key tiles, the last with one key
+    (1, 2, 1, 2750, 64, 1, 0, 0, 1.0),
+])
+def test_softmax_only(case):
+    B, H, T, HW, d, chunk, overlap, stab, gain = case
+    parity.run_case(B, H, T, HW, d, chunk, overlap, stab, gain, seed=sum(case[:6]))
+
+
+@pytest.mark.parametrize("d,HW", [(128, 500), (64, 1600)])
+def test_short_softmax_only_rows_do_not_depend_on_the_launch(d, HW):
+    """A window this short without a read-out is not worth splitting: the same kernel, so the same
+    bits, in a launch of a few workgroups and in one of more than 256."""
+    H = 256 // -(-HW // 128) + 2
+    q, k, v = synth.make_qkv(1, H, HW, d, seed=9)
+    phi = synth.make_phi(H, d, seed=10)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    many = binding.forward(dq, dk, dv, dphi, 1, HW, 1)
+    few = [x[:, :2].contiguous() for x in (dq, dk, dv)]
+    out = binding.forward(*few, {n: p[:2].contiguous() for n, p in dphi.items()}, 1, HW, 1)
+    torch.cuda.synchronize()
+    assert torch.equal(out, many[:, :2])
