@@ -216,14 +216,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
       const bf16x8 fbs[2] = {acc_to_operand(ps, 0), acc_to_operand(ps, 1)};
       float part = 0.f;
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const u32x4 w = __builtin_bit_cast(u32x4, fbs[s]);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          part += __builtin_bit_cast(float, w[i] << 16);
-          part += __builtin_bit_cast(float, w[i] & 0xffff0000u);
-        }
-      }
+      for (int s = 0; s < 2; ++s) part = sum_operand(fbs[s], part);
       zacc += part;
       // state slice += V^T phi, two 16-token steps
 #pragma unroll
@@ -243,9 +236,9 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   // A loop for each half of the features: decided per element, squaring costs a select each (the
   // waves of both loops meet at the same number of barriers).  With the bias in the first
   // product and z summed from the operands of the second this takes the vector work of a tile from
-  // 290 to 190 instructions per wave: 105 -> 103 us at the 480p shape, where the LDS latency of
+  // 290 to 150 instructions per wave: 105 -> 101 us at the 480p shape, where the LDS latency of
   // eight waves in step bounds a tile, 81 -> 65 us at 24 heads of 64 (with the accumulators out of
-  // the AGPRs).  160 instructions with z of unrounded features took the same time at both shapes.
+  // the AGPRs).
   auto all_tiles = [&](auto SQC) {
     for (int it = 0; it < n_full; ++it) tile_step(std::false_type{}, SQC, it);
     if (rem > 0) tile_step(std::true_type{}, SQC, n_full);
