@@ -94,7 +94,10 @@ __device__ __forceinline__ float sum_operand(bf16x8 x, float c) {
   const u32x4 w = __builtin_bit_cast(u32x4, x);
   const bf16x2 one = __builtin_bit_cast(bf16x2, 0x3f803f80u);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, w[i]), one, c, false);
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t pair = w[i];   // by value: a bit cast of w[i] itself reads element 0 each time
+    c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), one, c, false);
+  }
   return c;
 }
 
