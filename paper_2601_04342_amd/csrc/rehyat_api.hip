@@ -320,11 +320,13 @@ int launch_attn_window(const Ctx& c, const void* q, const void* k, const void* v
   a.chunk = chunk;
   a.overlap = overlap;
   a.chunk0 = c0;
-  a.n_win_chunks = n_chunks;
   a.qtiles = qtiles;
+  const ChunkRange last = chunk_range(T, HW, chunk, overlap, c0 + n_chunks - 1);
+  const int qtile = attn_query_tile(d);
+  a.bh_items = (n_chunks - 1) * qtiles + (int)((last.q_hi - last.q_lo + qtile - 1) / qtile);
   a.state_slots = c.sl.state;
   a.stab_mode = stab_mode;
-  a.n_items = B * H * n_chunks * qtiles;
+  a.n_items = B * H * a.bh_items;
   a.items_per_xcd = (a.n_items + 7) / 8;
   a.n_short = 0;
   if (c0 == 0 && !bidir && n_chunks > 1) {   // chunk 0 has no read-out phase: its items go last
@@ -339,8 +341,8 @@ int launch_attn_window(const Ctx& c, const void* q, const void* k, const void* v
   {
     ProfScope prof(c.prof, 2, c.st);
     const int64_t frames = (int64_t)chunk + overlap < T ? (int64_t)chunk + overlap : T;
-    const bool read_out = bidir || chunk_range(T, HW, chunk, overlap, c0 + n_chunks - 1).l_hi > 0;
-    e = launch_attn(a, nullptr, d, attn_splits(a.n_items, frames * HW, d, read_out), c.st);
+    const bool read_out = bidir || last.l_hi > 0;
+    e = launch_attn(a, nullptr, d, attn_splits((int64_t)B * H * n_chunks * qtiles, frames * HW, d, read_out), c.st);
   }
   if (e != hipSuccess) return hip_fail(e, "attention kernel launch");
   return REHYAT_OK;
@@ -1166,8 +1168,7 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   a.T = a.HW = a.chunk = 1;
   a.overlap = 0;
   a.chunk0 = 0;
-  a.n_win_chunks = 1;
-  a.qtiles = (n_q + qtile - 1) / qtile;
+  a.qtiles = a.bh_items = (n_q + qtile - 1) / qtile;
   a.state_slots = c.sl.state;
   a.stab_mode = stab_mode;
   a.n_items = B * H * a.qtiles;

@@ -319,11 +319,11 @@ __device__ __forceinline__ bool attn_item(const AttnArgs& a, int& bh, int& tc, i
   if (a.n_short == 0) {
     const int item = xcd_swizzle(blockIdx.x, a.items_per_xcd);
     if (item >= a.n_items) return false;
-    // item = (bh * n_win_chunks + tc) * qtiles + qt, qt fastest
-    qt = item % a.qtiles;
-    const int rest = item / a.qtiles;
-    tc = rest % a.n_win_chunks;
-    bh = rest / a.n_win_chunks;
+    // item = bh * bh_items + tc * qtiles + qt, qt fastest
+    bh = item / a.bh_items;
+    const int rest = item % a.bh_items;
+    tc = rest / a.qtiles;
+    qt = rest % a.qtiles;
   } else {
     // The window starts at chunk 0, whose items have no read-out phase and are the shortest:
     // every XCD runs its share of them last, so that the launch does not end on long items.
@@ -333,7 +333,7 @@ __device__ __forceinline__ bool attn_item(const AttnArgs& a, int& bh, int& tc, i
     if (i < per_long) {
       const int li = xcd * per_long + i;
       if (li >= n_long) return false;
-      const int per_bh = (a.n_win_chunks - 1) * a.qtiles;
+      const int per_bh = a.bh_items - a.qtiles;
       bh = li / per_bh;
       const int rest = li % per_bh;
       tc = 1 + rest / a.qtiles;
@@ -397,7 +397,6 @@ attn_kernel(AttnArgs a) {
   const int h = bh % a.H;
   const ChunkRange cr = attn_range(a, t);
   const int64_t q0 = cr.q_lo + (int64_t)qt * C::QT;
-  if (q0 >= cr.q_hi) return;  // short last chunk: fewer query tiles
   const int64_t N = (int64_t)a.T * a.HW;  // rows per (b, h) of the debug outputs
   const bf16_t* Qg = a.q + (int64_t)bh * a.q_bh_stride;
   const bf16_t* Kg = a.k + (int64_t)bh * a.kv_bh_stride;
@@ -792,7 +791,6 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   const int h = bh % a.H;
   const ChunkRange cr = attn_range(a, a.chunk0 + tc);
   const int64_t q0 = cr.q_lo + (int64_t)qt * C::QT;
-  if (q0 >= cr.q_hi) return;   // short last chunk: fewer query tiles
   const int64_t N = (int64_t)a.T * a.HW;
   const bf16_t* Qg = a.q + (int64_t)bh * a.q_bh_stride;
   const bf16_t* Kg = a.k + (int64_t)bh * a.kv_bh_stride;

@@ -66,8 +66,11 @@ struct AttnArgs {
   float *dbg_m, *dbg_nS, *dbg_aS, *dbg_nL, *dbg_aL;
   float scale_log2e;      // log2(e) / sqrt(d)
   int H, T, HW, chunk, overlap;
-  int chunk0, n_win_chunks;  // chunks [chunk0, chunk0 + n_win_chunks)
-  int qtiles;                // query tiles per (full) chunk
+  int chunk0;            // first chunk of the window
+  int qtiles;            // query tiles per (full) chunk
+  int bh_items;          // query tiles of the window's chunks; only the last one can have fewer than
+                         // qtiles (counted as a full one, its missing tiles left some XCDs with
+                         // less work: 3 heads of 61 frames in chunks of five 4,270 us, now 3,994)
   int state_slots;
   int stab_mode;
   int n_items, items_per_xcd;

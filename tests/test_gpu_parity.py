@@ -279,3 +279,26 @@ def test_xcd_mask_hook_skips_whole_workgroups_and_resets():
     again = binding.forward(dq, dk, dv, dphi, T, HW, 1)
     torch.cuda.synchronize()
     assert torch.equal(again, want)
+
+
+def test_short_last_chunk_leaves_the_xcds_evenly_loaded():
+    """Three heads of three chunks, the last of 3 query tiles instead of 8: by the measurement hook, no
+    XCD runs more than its share of the 24 tiles of chunk 0 (dealt last) and of the 33 others."""
+    B, H, T, HW, d, chunk = 1, 3, 7, 300, 128, 3
+    q, k, v = synth.make_qkv(B, H, T * HW, d, seed=73)
+    phi = synth.make_phi(H, d, seed=74)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    tiles = [(h, lo, min(lo + 128, q_hi)) for h in range(H)
+             for q_lo, q_hi, *_ in binding.chunk_plan(T, HW, chunk).tolist() for lo in range(q_lo, q_hi, 128)]
+    assert len(tiles) == 24 + 33
+    ran = []
+    try:
+        for xcd in range(8):
+            binding.debug_set_xcd_mask(1 << xcd)
+            out = binding.forward(dq, dk, dv, dphi, T, HW, chunk, out=parity.nan_like(dq))
+            torch.cuda.synchronize()
+            ran.append([t for t in tiles if torch.isfinite(out[0, t[0], t[1]:t[2]].float()).all()])
+    finally:
+        binding.debug_set_xcd_mask(0xFF)
+    assert sorted(t for r in ran for t in r) == sorted(tiles)    # every tile once
+    assert max(len(r) for r in ran) <= -(-24 // 8) + -(-33 // 8)
