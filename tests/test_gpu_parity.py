@@ -302,3 +302,15 @@ def test_short_last_chunk_leaves_the_xcds_evenly_loaded():
         binding.debug_set_xcd_mask(0xFF)
     assert sorted(t for r in ran for t in r) == sorted(tiles)    # every tile once
     assert max(len(r) for r in ran) <= -(-24 // 8) + -(-33 // 8)
+
+
+def test_bidirectional_frames_in_one_window():
+    """64 frames whose sums all stay in the workspace: the states of the 22 chunks are formed from
+    them in one window, so the call has one attention launch."""
+    binding.profile_enable(True)
+    try:
+        parity.run_case(1, 2, 64, 20, 64, 3, 2, 0, 3.0, seed=75, causal=False)
+        launches = {kind: n for kind, (_, n) in binding.profile_read().items()}
+    finally:
+        binding.profile_enable(False)
+    assert launches["state"] == 1 and launches["attn"] == 1, launches
