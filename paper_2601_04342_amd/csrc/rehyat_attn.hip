@@ -397,6 +397,9 @@ attn_kernel(AttnArgs a) {
   const int h = bh % a.H;
   const ChunkRange cr = attn_range(a, t);
   const int64_t q0 = cr.q_lo + (int64_t)qt * C::QT;
+  if (q0 >= cr.q_hi) return;   // never with the item counts of the host layer; without it the code before
+                               // the first loads is ordered worse (24 heads x 11 chunks of 63 tokens
+                               // 47.0 us a call, 45.1 with it)
   const int64_t N = (int64_t)a.T * a.HW;  // rows per (b, h) of the debug outputs
   const bf16_t* Qg = a.q + (int64_t)bh * a.q_bh_stride;
   const bf16_t* Kg = a.k + (int64_t)bh * a.kv_bh_stride;
@@ -791,6 +794,7 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   const int h = bh % a.H;
   const ChunkRange cr = attn_range(a, a.chunk0 + tc);
   const int64_t q0 = cr.q_lo + (int64_t)qt * C::QT;
+  if (q0 >= cr.q_hi) return;   // as in attn_kernel
   const int64_t N = (int64_t)a.T * a.HW;
   const bf16_t* Qg = a.q + (int64_t)bh * a.q_bh_stride;
   const bf16_t* Kg = a.k + (int64_t)bh * a.kv_bh_stride;
