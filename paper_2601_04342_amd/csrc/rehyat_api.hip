@@ -204,9 +204,9 @@ struct Cut {
 
 // The cheapest cut by a model of what was measured on the 480p and 320x480 shapes (12 heads of
 // 128): a state workgroup takes about 10 us to load its weights and store its sums and 4 us per
-// 64-token tile (3.2 us at d = 64, where two workgroups share a CU); each partial sum is read
-// once more by the prefix pass; each further window costs its own launches, and the attention
-// launch of a window ends on a partly empty round (about half of a workgroup's time).
+// 64-token tile (at d = 64 1.5 us alone on a CU and 2.1 us beside another one); each partial sum
+// is read once more by the prefix pass; each further window costs its own launches, and the
+// attention launch of a window ends on a partly empty round (about half of a workgroup's time).
 // `n` chunks (or frames) are windowed, at most `limit` to a window; `n_seg` of them (n or n - 1)
 // have a segment; `most_pieces` bounds the pieces of a segment.  What the
 // windows cost is why fewer pieces can win: 34 chunks of 1,800 tokens took 1,600 us cut into
@@ -216,7 +216,7 @@ Cut choose_cut(int BH, int n, int n_seg, int64_t seg_tokens, int64_t keys, int d
   Cut best{1, 1};
   if (n < 1) return best;
   const int slots = d == 128 ? kCUs : 2 * kCUs;      // state workgroups resident at once
-  const double tile_us = d == 128 ? 4.0 : 3.2, setup_us = 10.0;
+  const double setup_us = 10.0;
   const double window_us = 25.0 + 0.9 * (double)((keys + 63) / 64);
   const double partial_us = (double)BH * (d * 2 * d + 2 * d) * sizeof(float) / 4e6;   // at 4 TB/s
   const int64_t tiles = (seg_tokens + 63) / 64;
@@ -228,7 +228,11 @@ Cut choose_cut(int BH, int n, int n_seg, int64_t seg_tokens, int64_t keys, int d
     const int windows = (n + win - 1) / win;
     win = (n + windows - 1) / windows;               // equal windows
     const int segs = win < n_seg ? win : n_seg;
-    const double rounds = std::ceil((double)BH * segs * ns / slots);
+    const double wgs = (double)BH * segs * ns;
+    const double rounds = std::ceil(wgs / slots);
+    // 3.2 us for every tile at d = 64 cut short segments into one-tile pieces that doubled the
+    // workgroups of a CU: 24 (batch, head) x 10 frames of 95 tokens 21.3 us whole, 23.2 us in halves
+    const double tile_us = d == 128 ? 4.0 : wgs <= kCUs ? 1.5 : 2.1;
     const double piece_tiles = (double)(((seg_tokens + ns - 1) / ns + 63) / 64);
     const double cost = windows * (rounds * (setup_us + piece_tiles * tile_us) + segs * ns * partial_us) +
                         (windows - 1) * window_us;
