@@ -197,7 +197,7 @@ int check_phi(const rehyat_phi_params* p, int d) {
 }
 
 // How the chunk-state work of a call is cut: every segment into `nsplit` pieces, the chunks into
-// equal windows of `win` whose pieces fit the partial slots together.
+// windows of `win` whose pieces fit the partial slots together.
 struct Cut {
   int nsplit, win;
 };
@@ -226,7 +226,10 @@ Cut choose_cut(int BH, int n, int n_seg, int64_t seg_tokens, int64_t keys, int d
     int win = partial_slots / ns;
     if (win > limit) win = limit;
     const int windows = (n + win - 1) / win;
-    win = (n + windows - 1) / windows;               // equal windows
+    // Equal windows, unless the last chunk falls alone into the last one: it has no segment, so
+    // that window runs no state kernel (33 chunks of 96 tokens as 32 + 1 75 us, as 17 + 16 87 us).
+    const bool last_alone = n_seg == (windows - 1) * win;
+    if (!last_alone) win = (n + windows - 1) / windows;
     const int segs = win < n_seg ? win : n_seg;
     const double wgs = (double)BH * segs * ns;
     const double rounds = std::ceil(wgs / slots);
@@ -234,7 +237,8 @@ Cut choose_cut(int BH, int n, int n_seg, int64_t seg_tokens, int64_t keys, int d
     // workgroups of a CU: 24 (batch, head) x 10 frames of 95 tokens 21.3 us whole, 23.2 us in halves
     const double tile_us = d == 128 ? 4.0 : wgs <= kCUs ? 1.5 : 2.1;
     const double piece_tiles = (double)(((seg_tokens + ns - 1) / ns + 63) / 64);
-    const double cost = windows * (rounds * (setup_us + piece_tiles * tile_us) + segs * ns * partial_us) +
+    const double cost = (last_alone ? windows - 1 : windows) *
+                            (rounds * (setup_us + piece_tiles * tile_us) + segs * ns * partial_us) +
                         (windows - 1) * window_us;
     if (cost < best_cost * 0.98) {
       best_cost = cost;

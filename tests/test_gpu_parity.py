@@ -314,3 +314,15 @@ def test_bidirectional_frames_in_one_window():
     finally:
         binding.profile_enable(False)
     assert launches["state"] == 1 and launches["attn"] == 1, launches
+
+
+def test_last_chunk_in_a_window_of_its_own():
+    """33 chunks: the first 32 fill a window, the last one has no segment to sum, so its window runs
+    no state kernel."""
+    binding.profile_enable(True)
+    try:
+        parity.run_case(1, 2, 33, 40, 64, 1, 0, 0, 3.0, seed=76)
+        launches = {kind: n for kind, (_, n) in binding.profile_read().items()}
+    finally:
+        binding.profile_enable(False)
+    assert launches["state"] == 1 and launches["attn"] == 2, launches
