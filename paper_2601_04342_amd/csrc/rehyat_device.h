@@ -87,16 +87,22 @@ __device__ __forceinline__ bf16x8 acc_to_operand(const f32x16& c, int s) {
   return __builtin_bit_cast(bf16x8, p);
 }
 
-// c + the eight elements of an operand, as products with 1 in fp32: one instruction for two
-// elements.  It rounds each pair once (2^20 draws: at most 9.9e-8 of the sum off, two fp32 additions
-// 1.2e-7) and keeps denormals.
+// c + the eight elements of an operand, in fp32.  DOT: as products with 1, one instruction for two
+// elements; it rounds each pair once (2^20 draws: at most 9.9e-8 of the sum off, two fp32 additions
+// 1.2e-7) and keeps denormals.  Otherwise each element is unpacked and added.
+template <bool DOT>
 __device__ __forceinline__ float sum_operand(bf16x8 x, float c) {
   const u32x4 w = __builtin_bit_cast(u32x4, x);
-  const bf16x2 one = __builtin_bit_cast(bf16x2, 0x3f803f80u);
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const uint32_t pair = w[i];   // by value: a bit cast of w[i] itself reads element 0 each time
-    c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), one, c, false);
+    if (DOT) {
+      const bf16x2 one = __builtin_bit_cast(bf16x2, 0x3f803f80u);
+      c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), one, c, false);
+    } else {
+      c += __builtin_bit_cast(float, pair << 16);
+      c += __builtin_bit_cast(float, pair & 0xffff0000u);
+    }
   }
   return c;
 }

@@ -27,6 +27,10 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   constexpr int TB = 64 * 2 * D;  // bytes of a K, V or W1 tile (64 rows of 2D bytes)
   constexpr int UROW = HID * 2;   // bytes of a row of U
   static_assert(DP / NW == 32, "each wave owns 32 features");
+  // Dot products for z where vector work bounds a tile (d = 64; unpacked 2 - 4 % slower).  At
+  // d = 128 the state kernel takes the same time either way, and the pieces in an attention launch less
+  // unpacked (steps of 64 heads with 2,048 tokens absorbed: 167.6 us, 161.5 unpacked).
+  constexpr bool kDotSum = D == 64;
 
   // U[token][hidden] with 16 bytes of padding per row: consecutive rows start four banks
   // apart, so fragment reads and writes are conflict-free without a chunk permutation
@@ -216,7 +220,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
       const bf16x8 fbs[2] = {acc_to_operand(ps, 0), acc_to_operand(ps, 1)};
       float part = 0.f;
 #pragma unroll
-      for (int s = 0; s < 2; ++s) part = sum_operand(fbs[s], part);
+      for (int s = 0; s < 2; ++s) part = sum_operand<kDotSum>(fbs[s], part);
       zacc += part;
       // state slice += V^T phi, two 16-token steps
 #pragma unroll
@@ -236,8 +240,8 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   // A loop for each half of the features: decided per element, squaring costs a select each (the
   // waves of both loops meet at the same number of barriers).  With the bias in the first
   // product and z summed from the operands of the second this takes the vector work of a tile from
-  // 290 to 150 instructions per wave: 105 -> 101 us at the 480p shape, where the LDS latency of
-  // eight waves in step bounds a tile, 81 -> 65 us at 24 heads of 64 (with the accumulators out of
+  // 290 to 190 instructions per wave at d = 128: 105 -> 102 us at the 480p shape, where the LDS latency
+  // of eight waves in step bounds a tile, 81 -> 65 us at 24 heads of 64 (with the accumulators out of
   // the AGPRs).
   auto all_tiles = [&](auto SQC) {
     for (int it = 0; it < n_full; ++it) tile_step(std::false_type{}, SQC, it);
