@@ -2,6 +2,9 @@
 a call allocates nothing and enqueues only kernels, so it can be recorded once and
 replayed.  Every replay is checked against the eager result, with eager calls and
 synchronisations between replays."""
+import importlib.util
+import shutil
+
 import pytest
 import torch
 
@@ -86,10 +89,19 @@ def test_gradient_step_replays_from_a_graph():
 
 
 def test_streaming_steps_replay_from_a_graph():
-    """rehyat_step forks its state update onto the library's second stream and joins it before
-    returning: recorded into a graph, the fork and join become graph edges.  Three consecutive
-    steps are recorded and replayed from the same starting state."""
-    B, H, T, HW, d = 1, 2, 4, 200, 128
+    """rehyat_step with few query tiles: every kernel of a step is launched on the caller's stream,
+    the chunk-state pieces inside the attention launch.  Three consecutive steps are recorded and
+    replayed from the same starting state."""
+    replay_steps(1, 2, 4, 200, 128)
+
+
+def test_steps_on_two_streams_replay_from_a_graph():
+    """260 query tiles: a step forks its state update onto the library's second stream and joins
+    it before returning; recorded, the fork and the join become graph edges."""
+    replay_steps(1, 130, 4, 129, 64)
+
+
+def replay_steps(B, H, T, HW, d):
     q, k, v = synth.make_qkv(B, H, T * HW, d, seed=46)
     phi = synth.make_phi(H, d, seed=47, gain=3.0)
     dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
@@ -106,7 +118,7 @@ def test_streaming_steps_replay_from_a_graph():
         for q_t, k_w, v_w, o_t, n_absorb in pieces:
             binding.step(q_t, k_w, v_w, dphi, S, z, n_absorb, out=o_t)
 
-    steps()                                  # workspace and second stream exist before the capture
+    steps()                 # the workspace (and the second stream, where one is used) exists before the capture
     torch.cuda.synchronize()
     want = [p[3].clone() for p in pieces]
     want_S, want_z = S.clone(), z.clone()
@@ -143,3 +155,48 @@ def test_streaming_steps_replay_from_a_graph():
         steps()
         torch.cuda.synchronize()
         assert torch.equal(S, want_S)
+
+
+def test_first_step_of_a_device_under_capture(tmp_path):
+    """A library that has not run a step yet creates nothing inside a capture: with 260 query tiles
+    the state update is recorded on the caller's stream.  Every replay gives what eager steps give."""
+    B, H, HW, d = 1, 130, 129, 64
+    fresh = importlib.util.spec_from_file_location("fresh_binding", binding.__file__)
+    lib = importlib.util.module_from_spec(fresh)
+    fresh.loader.exec_module(lib)
+    lib.LIB_PATH = shutil.copy(binding.LIB_PATH, tmp_path / "librehyat_fresh.so")   # state of its own
+    q, k, v = synth.make_qkv(B, H, HW, d, seed=48)
+    phi = synth.make_phi(H, d, seed=49, gain=3.0)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    S0 = torch.rand(B, H, 2 * d, d, device="cuda")
+    z0 = torch.rand(B, H, 2 * d, device="cuda")
+    want_S, want_z = S0.clone(), z0.clone()
+    want = binding.step(dq, dk, dv, dphi, want_S, want_z, 100)
+    ws = torch.empty(lib.workspace_bytes(B, H, d), device="cuda", dtype=torch.uint8)
+    lib.set_workspace(ws)
+    # eager calls that make no second stream: the kernels are loaded outside the capture
+    S, z, out = S0.clone(), z0.clone(), torch.empty_like(dq)
+    few = [x[:, :2].contiguous() for x in (dq, dk, dv)]
+    lib.step(*few, {n: t[:2].contiguous() for n, t in dphi.items()}, S[:, :2].contiguous(),
+             z[:, :2].contiguous(), 100)
+    lib.state(dk, dv, dphi, 1, HW, 1)
+    lib.forward(dq, dk, dv, dphi, 1, HW, 1)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        lib.step(dq, dk, dv, dphi, S, z, 100, out=out)
+    for i in range(3):
+        S.copy_(S0)
+        z.copy_(z0)
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), f"replay {i}"
+        # eager work of the same library between replays (it shares the workspace)
+        assert torch.isfinite(lib.forward(dq, dk, dv, dphi, 1, HW, 1).float()).all()
+        # the pieces of the increment may be cut differently from the eager call's
+        for got, ref, start in ((S, want_S, S0), (z, want_z, z0)):
+            assert (got - ref).abs().max() <= 1e-5 * ref.abs().max(), f"replay {i}"
+            assert (got - start).abs().max() > 0
+    lib.set_workspace(None)

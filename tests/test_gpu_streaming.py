@@ -123,3 +123,30 @@ def test_state_that_is_only_four_byte_aligned():
     assert b[1].data_ptr() % 16 == 4
     for x, y in zip(a, b):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("B,H,T,HW,d,chunk,overlap", [
+    (1, 130, 3, 129, 64, 1, 0),      # 260 query tiles, the second of each head with one query
+    (2, 65, 4, 140, 128, 1, 1),      # 260 of the other head width, two-frame windows, batch of two
+])
+def test_step_with_more_query_tiles_than_compute_units(B, H, T, HW, d, chunk, overlap):
+    """Steps whose attention launch fills the chip run the state update on the library's second
+    stream: outputs of every step and the state after it against the oracle."""
+    assert B * H * -(-chunk * HW // 128) > 256
+    q, k, v = synth.make_qkv(B, H, T * HW, d, seed=23)
+    phi = synth.make_phi(H, d, seed=24, gain=4.0)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+
+    def on_step(t, upto, S, z):
+        for b, h in ((0, 0), (B - 1, H - 1)):
+            one = {n: p[h:h + 1] for n, p in phi.items()}
+            check_state(k[b:b + 1, h:h + 1], v[b:b + 1, h:h + 1], one, upto, S[b:b + 1, h:h + 1],
+                        z[b:b + 1, h:h + 1], f"state after step {t}")
+
+    out, S, z = stream(dq, dk, dv, dphi, T, HW, chunk, overlap, absorb_all_at_end=True, on_step=on_step)
+    ref = cref.forward(*parity.oracle_inputs(q, k, v, phi), T, HW, chunk, overlap=overlap)
+    parity.compare(out, None, ref, label="streaming vs oracle")
+    # without a wait between the steps: the order on the caller's stream is all there is
+    again = stream(dq, dk, dv, dphi, T, HW, chunk, overlap, absorb_all_at_end=True)
+    for x, y in zip((out, S, z), again):
+        assert torch.equal(x, y)
