@@ -30,8 +30,8 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, published
 # and valid for the library version they were measured on (profiles/*_hbm_traffic_pmc.md).
 # Anything else reports null.
 ATTN_TRAFFIC = {
-    # 2.0 x 178,013 KiB + 1.0 x 98,280 KiB (profiles/wan480p_hbm_traffic_pmc.md)
-    ("wan480p", "forward", 304): 465_200_000,   # 303 and 304 share the forward kernels
+    # 2.0 x 178,913 KiB + 1.0 x 98,280 KiB (profiles/wan480p_hbm_traffic_pmc.md)
+    ("wan480p", "forward", 305): 467_100_000,
 }
 
 
@@ -325,7 +325,15 @@ def main():
     kern_ms = {kk: (tot / n if n else None) for kk, (tot, n) in prof.items()}
     # all launches of the attention kernel in one step share the step's algorithmic work
     attn_ms = prof["attn"][0] / args.steps
-    achieved = fl["attn_kernel"] / (attn_ms * 1e-3) / 1e12
+    attn_name, attn_flops = binding.attn_kernel_name(w.d), fl["attn_kernel"]
+    if args.mode == "stream":
+        absorbing = sum(1 for p in pieces if p[4] > 0)
+        state_launches = prof["state"][1] / args.steps
+        if absorbing and state_launches == 0:   # the state pieces run in the attention launches
+            attn_name, attn_flops = f"attn_split_kernel<{w.d}> with the chunk-state pieces", fl["total"]
+        elif state_launches < absorbing:        # some do: no single kernel to speak of
+            attn_name, attn_flops = None, None
+    achieved = attn_flops / (attn_ms * 1e-3) / 1e12 if attn_flops else None
     traffic = ATTN_TRAFFIC.get((w.name, args.mode, binding.version()))
     res = {
         "metric": "hybrid-attn tokens/s per layer @Wan2.1-480p shape; TFLOP/s and % MFMA peak",
@@ -349,9 +357,9 @@ def main():
         "kernel_launches_per_step": {kk: n / args.steps for kk, (_, n) in prof.items()},
         "workspace_bytes": binding.workspace_bytes(w.B, w.H, w.d),
         "library_version": binding.version(),
-        "roofline": {"bound": "mfma", "kernel": binding.attn_kernel_name(w.d), "achieved": achieved,
+        "roofline": {"bound": "mfma", "kernel": attn_name, "achieved": achieved,
                      "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                     "frac": achieved / PEAK_BF16_TFLOPS, "traffic": traffic},
+                     "frac": achieved / PEAK_BF16_TFLOPS if achieved else None, "traffic": traffic},
         "copy_GBps": copy_gbps,
         "state_kernel_tflops": (fl["state_kernel"] / (prof["state"][0] / args.steps * 1e-3) / 1e12
                                 if prof["state"][1] else None),

@@ -324,7 +324,9 @@ int rehyat_state(const void *k, const void *v,
  * rehyat_profile_read waits for the recorded events, then returns for each
  * kernel kind (0 = chunk state, 1 = prefix, 2 = fused attention) the summed
  * duration in milliseconds and the number of launches since the last read or
- * enable, in HOST arrays of three elements each, and clears the record.
+ * enable, in HOST arrays of three elements each, and clears the record.  A
+ * streaming step that computes its state pieces in the attention launch (see
+ * rehyat_step) has no launch of kind 0: they are part of its kind-2 duration.
  */
 int rehyat_profile_enable(int on);
 int rehyat_profile_read(double *total_ms, int *launches);
@@ -350,8 +352,10 @@ const char *rehyat_status_string(int code);
 /* Library version: major * 10000 + minor * 100 + patch. */
 int rehyat_version(void);
 
-/* Name of the fused attention kernel instance launched for head width d, as a
- * profiler's kernel trace shows it ("" for an unsupported d). */
+/* Name of the fused attention kernel instance that launches of more than 256
+ * query tiles run for head width d, as a profiler's kernel trace shows it ("" for
+ * an unsupported d).  Smaller launches with long enough windows, and streaming
+ * steps that absorb in the attention launch, run attn_split_kernel<d>. */
 const char *rehyat_attn_kernel_name(int d);
 
 /* Text of the last HIP error seen by this library ("" if none). */
