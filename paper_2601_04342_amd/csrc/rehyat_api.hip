@@ -44,9 +44,9 @@ std::mutex g_mu;
 char g_hip_err[256] = "";
 std::atomic<unsigned> g_xcd_mask{0xFFu};   // rehyat_debug_set_xcd_mask
 
-// rehyat_step runs the state update of a chunk beside its attention kernel: a second stream
-// per device, forked from and joined to the caller's stream with two events (all at the
-// default priority; created on first use, kept until the process ends).
+// A rehyat_step whose attention launch does not take the state update (see there) runs it beside the
+// attention kernel on a second stream per device, forked from and joined to the caller's stream
+// with two events (all at the default priority; created on first use, kept until the process ends).
 struct SideStream {
   hipStream_t s = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
@@ -1083,29 +1083,43 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   // The read-out of this chunk uses the caller's state as it is (Eq. 16): slot 0 <- S, z.  The
   // tokens that leave the window are absorbed afterwards (Eq. 17-18: state kernel in pieces,
   // then S, z += the pieces, in place and in the caller's layout); the attention kernel does
-  // not depend on that and runs beside it when a second stream is at hand.
+  // not depend on that.
   const int qtile = attn_query_tile(d);
   const int attn_wgs = B * H * ((n_q + qtile - 1) / qtile);   // 64-row tiles of the queries fit an int
-  // An attention launch that leaves CUs free absorbs beside its own work, in the same launch;
-  // otherwise on a second stream when one is at hand.
-  const bool joint = n_absorb > 0 && attn_wgs <= kCUs;
+  // The absorbed rows are one segment, cut into pieces for `free_cus` CUs: one workgroup of the
+  // state kernel fills a CU, and a piece pays the workgroup's set-up (its weight slices into
+  // registers) once (25 pieces of one tile each were 30 % slower at the 480p shape, 12 heads).
+  const int max_pieces = (n_absorb + 63) / 64;
+  auto pieces_for = [&](int free_cus) {
+    if (free_cus < kCUs / 4) free_cus = kCUs / 4;
+    int n = free_cus / (B * H);
+    if (n < 1) n = 1;
+    if (n > c.sl.partial) n = c.sl.partial;
+    return n < max_pieces ? n : max_pieces;
+  };
+  // Up to one attention workgroup per CU the launch absorbs beside its own work (attn_split_kernel),
+  // otherwise a second stream does when one is at hand (and attn_kernel runs).  Whole steps, joint
+  // against forked, 136 sampled of up to 256 tiles and 2,700 keys at both head widths: joint was never
+  // slower, also where the pieces do not fit the CUs left over and start when attention workgroups
+  // end, and where the window alone would not be split (2 tiles of 64 keys 21 against 54 us, 96 tiles
+  // 45 against 55, 156 tiles of 3,120 keys, all absorbed, 68 against 79, 256 tiles of 256 (batch, head)
+  // with 2,048 keys, all absorbed, 253 against 258; d = 64: 252 tiles 32 against 60).  With long
+  // windows at d = 64 the fork costs nothing any more, and pieces that start late cost more than the
+  // split gains once they are long: 252 tiles, 5,376 keys, all absorbed, joint 96 and forked 84 us;
+  // 240 tiles, a third of 9,000 absorbed, 139 and 126; but a third of 5,376 in pieces of six tiles 82
+  // and 82, and at 3,000 keys 59 and 58, 63 and 67.
+  int nsplit = n_absorb > 0 ? pieces_for(kCUs - attn_wgs) : 0;
+  const bool late_and_long = d == 64 && n_win >= 4096 && attn_wgs + B * H * nsplit > kCUs && max_pieces > 10 * nsplit;
+  const bool joint = n_absorb > 0 && attn_wgs <= kCUs && !late_and_long;
   SideStream* side = n_absorb > 0 && !joint ? side_stream(st) : nullptr;
   hipStream_t upd = side ? side->s : st;   // stream of the state update
   StateArgs s{};
   if (n_absorb > 0) {
-    // One segment only, cut into pieces: one workgroup of the state kernel fills a CU, and a
-    // piece pays the workgroup's set-up (its weight slices into registers) once.  Beside the
-    // attention kernel, which spreads its workgroups over as many CUs, the pieces should fit
-    // the CUs it leaves free; alone, three quarters of the chip measured best (480p shape,
-    // 12 heads: 8 pieces beside the attention kernel, 16 serial; 25 pieces of one tile each
-    // were 30 % slower).
-    int free_cus = joint || side ? kCUs - attn_wgs : 3 * kCUs / 4;
-    if (free_cus < kCUs / 4) free_cus = kCUs / 4;
-    int nsplit = free_cus / (B * H);
-    if (nsplit < 1) nsplit = 1;
-    if (nsplit > c.sl.partial) nsplit = c.sl.partial;
-    const int max_pieces = (n_absorb + 63) / 64;
-    if (nsplit > max_pieces) nsplit = max_pieces;
+    // In the attention launch a sixteenth of the rows always takes less time than the attention over
+    // the window that holds them, and further pieces only lengthen the addition after it (2 heads of 64,
+    // 5,376 rows: 64 pieces 83 us, 16 pieces 70 us).  Alone, three quarters of the chip measured best.
+    if (joint) nsplit = nsplit < 16 ? nsplit : 16;
+    else if (!side) nsplit = pieces_for(3 * kCUs / 4);
     s.k = (const bf16_t*)k_win;
     s.v = (const bf16_t*)v_win;
     s.w1_k = (const bf16_t*)phi->w1_k;
@@ -1192,7 +1206,7 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   a.n_short = 0;
   {
     ProfScope prof(true, 2, st);
-    e = launch_attn(a, joint ? &s : nullptr, d, joint || attn_splits(attn_wgs, n_win, d, true), st);
+    e = launch_attn(a, joint ? &s : nullptr, d, joint || (n_absorb == 0 && attn_splits(attn_wgs, n_win, d, true)), st);
   }
   if (e != hipSuccess) return hip_fail(e, "attention kernel launch");
   if (joint) {   // state += pieces

@@ -150,3 +150,35 @@ def test_step_with_more_query_tiles_than_compute_units(B, H, T, HW, d, chunk, ov
     again = stream(dq, dk, dv, dphi, T, HW, chunk, overlap, absorb_all_at_end=True)
     for x, y in zip((out, S, z), again):
         assert torch.equal(x, y)
+
+
+@pytest.mark.parametrize("H,n_q,n_win,n_absorb,state_launches", [
+    (128, 129, 4200, 700, 1),    # 256 tiles, one piece of 11 key tiles per head: on the second stream
+    (128, 129, 4200, 640, 0),    # pieces of 10 tiles: in the attention launch
+    (2, 300, 4200, 4200, 0),     # as many CUs free as there are tiles: 16 pieces per head
+])
+def test_step_with_a_long_window_at_d64(H, n_q, n_win, n_absorb, state_launches):
+    """Where the state update of a long window runs, and that it gives the oracle's state and output."""
+    d = 64
+    q, _, _ = synth.make_qkv(1, H, n_q, d, seed=25)
+    _, k, v = synth.make_qkv(1, H, n_win, d, seed=26)
+    phi = synth.make_phi(H, d, seed=27, gain=3.0)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    dk, dv = k.to("cuda", torch.bfloat16), v.to("cuda", torch.bfloat16)
+    S, z = torch.zeros(1, H, 2 * d, d, device="cuda"), torch.zeros(1, H, 2 * d, device="cuda")
+    binding.step(dq, dk, dv, dphi, S, z, n_absorb)    # the second stream exists before the launches are counted
+    S.zero_()
+    z.zero_()
+    binding.profile_enable(True)
+    try:
+        out = binding.step(dq, dk, dv, dphi, S, z, n_absorb)
+        launches = binding.profile_read()["state"][1]
+    finally:
+        binding.profile_enable(False)
+    assert launches == state_launches
+    for h in (0, H - 1):
+        check_state(k[:, h:h + 1], v[:, h:h + 1], {n: p[h:h + 1] for n, p in phi.items()}, n_absorb,
+                    S[:, h:h + 1], z[:, h:h + 1], f"state of head {h}")
+        s = q[0, h].double() @ k[0, h].double().T / d ** 0.5     # the state before the step is zero
+        want = torch.softmax(s, dim=-1) @ v[0, h].double()
+        assert (out[0, h].double().cpu() - want).abs().max() <= parity.OUT_MAX_ABS, h
