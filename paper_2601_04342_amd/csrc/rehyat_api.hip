@@ -196,32 +196,52 @@ int check_phi(const rehyat_phi_params* p, int d) {
   return REHYAT_OK;
 }
 
+// Chunks per window of the bidirectional form with `fwin` frames in the partial slots: as many as
+// there are state slots; frames that are summed again must fit the partial slots together (resident
+// ones are there already: 6 heads of 64, 10 frames of 800 in chunks of three in one attention
+// launch 109 us, in two 148 us).
+int bidir_window(int T, int chunk, int overlap, int fwin, int state_slots) {
+  int cw = T <= fwin ? state_slots : (fwin - overlap) / chunk;
+  if (cw < 1) cw = 1;
+  return cw < state_slots ? cw : state_slots;
+}
+
+// The model by which cuts are chosen, from what was measured on the 480p and 320x480 shapes (12 heads
+// of 128): a state workgroup takes about 10 us to load its weights and store its sums and 4 us per
+// 64-token tile (at d = 64 1.5 us alone on a CU and 2.1 us beside another one); each partial sum
+// is read once more by the prefix pass; each further window of chunks costs its own launches, and the
+// attention launch of a window ends on a partly empty round (about half of a workgroup's time).
+//
+// A state launch of `segs` segments of `seg_tokens` tokens per (b, h), each in `ns` pieces, and the
+// reading of its sums:
+double state_launch_us(int BH, int segs, int64_t seg_tokens, int d, int ns) {
+  const int slots = d == 128 ? kCUs : 2 * kCUs;      // state workgroups resident at once
+  const double wgs = (double)BH * segs * ns;
+  // 3.2 us for every tile at d = 64 cut short segments into one-tile pieces that doubled the
+  // workgroups of a CU: 24 (batch, head) x 10 frames of 95 tokens 21.3 us whole, 23.2 us in halves
+  const double tile_us = d == 128 ? 4.0 : wgs <= kCUs ? 1.5 : 2.1;
+  const double piece_tiles = (double)(((seg_tokens + ns - 1) / ns + 63) / 64);
+  const double partial_us = (double)BH * (d * 2 * d + 2 * d) * sizeof(float) / 4e6;   // at 4 TB/s
+  return std::ceil(wgs / slots) * (10.0 + piece_tiles * tile_us) + segs * ns * partial_us;
+}
+double window_us(int64_t keys) { return 25.0 + 0.9 * (double)((keys + 63) / 64); }
+
 // How the chunk-state work of a call is cut: every segment into `nsplit` pieces, the chunks into
 // windows of `win` whose pieces fit the partial slots together.
 struct Cut {
   int nsplit, win;
 };
 
-// The cheapest cut by a model of what was measured on the 480p and 320x480 shapes (12 heads of
-// 128): a state workgroup takes about 10 us to load its weights and store its sums and 4 us per
-// 64-token tile (at d = 64 1.5 us alone on a CU and 2.1 us beside another one); each partial sum
-// is read once more by the prefix pass; each further window costs its own launches, and the
-// attention launch of a window ends on a partly empty round (about half of a workgroup's time).
-// `n` chunks (or frames) are windowed, at most `limit` to a window; `n_seg` of them (n or n - 1)
-// have a segment; `most_pieces` bounds the pieces of a segment.  What the
-// windows cost is why fewer pieces can win: 34 chunks of 1,800 tokens took 1,600 us cut into
-// seven pieces each (least state time, four windows) and take 1,300 us in two windows of 17.
-Cut choose_cut(int BH, int n, int n_seg, int64_t seg_tokens, int64_t keys, int d, int partial_slots, int limit,
-               int most_pieces) {
+// The cheapest cut.  `n` chunks (or frames) are windowed, at most `limit` to a window; `n_seg` of
+// them (n or n - 1) have a segment.  What the windows cost is why fewer pieces can win: 34 chunks
+// of 1,800 tokens took 1,600 us cut into seven pieces each (least state time, four windows) and
+// take 1,300 us in two windows of 17.
+Cut choose_cut(int BH, int n, int n_seg, int64_t seg_tokens, int64_t keys, int d, int partial_slots, int limit) {
   Cut best{1, 1};
   if (n < 1) return best;
-  const int slots = d == 128 ? kCUs : 2 * kCUs;      // state workgroups resident at once
-  const double setup_us = 10.0;
-  const double window_us = 25.0 + 0.9 * (double)((keys + 63) / 64);
-  const double partial_us = (double)BH * (d * 2 * d + 2 * d) * sizeof(float) / 4e6;   // at 4 TB/s
   const int64_t tiles = (seg_tokens + 63) / 64;
   double best_cost = 1e30;
-  for (int ns = 1; ns <= most_pieces && ns <= partial_slots; ++ns) {
+  for (int ns = 1; ns <= kMaxSplit && ns <= partial_slots; ++ns) {
     if (ns > 1 && ns > tiles) break;                 // a piece is at least one tile
     int win = partial_slots / ns;
     if (win > limit) win = limit;
@@ -231,18 +251,34 @@ Cut choose_cut(int BH, int n, int n_seg, int64_t seg_tokens, int64_t keys, int d
     const bool last_alone = n_seg == (windows - 1) * win;
     if (!last_alone) win = (n + windows - 1) / windows;
     const int segs = win < n_seg ? win : n_seg;
-    const double wgs = (double)BH * segs * ns;
-    const double rounds = std::ceil(wgs / slots);
-    // 3.2 us for every tile at d = 64 cut short segments into one-tile pieces that doubled the
-    // workgroups of a CU: 24 (batch, head) x 10 frames of 95 tokens 21.3 us whole, 23.2 us in halves
-    const double tile_us = d == 128 ? 4.0 : wgs <= kCUs ? 1.5 : 2.1;
-    const double piece_tiles = (double)(((seg_tokens + ns - 1) / ns + 63) / 64);
-    const double cost = (last_alone ? windows - 1 : windows) *
-                            (rounds * (setup_us + piece_tiles * tile_us) + segs * ns * partial_us) +
-                        (windows - 1) * window_us;
+    const double cost = (last_alone ? windows - 1 : windows) * state_launch_us(BH, segs, seg_tokens, d, ns) +
+                        (windows - 1) * window_us(keys);
     if (cost < best_cost * 0.98) {
       best_cost = cost;
       best = Cut{ns, win};
+    }
+  }
+  return best;
+}
+
+// Pieces of a frame of the bidirectional form: the frames are summed once for their total, and a
+// second time window by window when their sums do not all stay in the partial slots.  `win_frames`
+// is what the window of one chunk spans; its frames must fit the slots together.
+int choose_frame_pieces(int BH, int T, int HW, int d, int chunk, int overlap, int win_frames, Slots sl) {
+  const int nc = num_chunks(T, chunk);
+  int best = 1;
+  double best_cost = 1e30;
+  for (int ns = 1; ns <= kMaxSplit && ns * win_frames <= sl.partial; ++ns) {
+    if (ns > 1 && ns > (HW + 63) / 64) break;
+    const int fwin = sl.partial / ns, passes = (T + fwin - 1) / fwin;
+    double cost = (passes - 1) * state_launch_us(BH, fwin, HW, d, ns) +
+                  state_launch_us(BH, T - (passes - 1) * fwin, HW, d, ns);
+    const int cw = bidir_window(T, chunk, overlap, fwin, sl.state), windows = (nc + cw - 1) / cw;
+    if (T > fwin) cost += windows * state_launch_us(BH, cw * chunk + overlap < T ? cw * chunk + overlap : T, HW, d, ns);
+    cost += (windows - 1) * window_us((int64_t)win_frames * HW);
+    if (cost < best_cost * 0.98) {
+      best_cost = cost;
+      best = ns;
     }
   }
   return best;
@@ -372,9 +408,7 @@ int forward_bidirectional(const Ctx& c, const void* q, const void* k, const void
   int win_frames = chunk + overlap;  // frames one window can span (both are <= T here)
   if (win_frames > T) win_frames = T;
   if (win_frames > c.sl.partial) return REHYAT_E_UNSUPPORTED;
-  // the frames of one window must fit the partial slots together
-  const int nsplit = choose_cut(B * H, T, T, HW, (int64_t)win_frames * HW, d, c.sl.partial, c.sl.partial,
-                                c.sl.partial / win_frames < kMaxSplit ? c.sl.partial / win_frames : kMaxSplit).nsplit;
+  const int nsplit = choose_frame_pieces(B * H, T, HW, d, chunk, overlap, win_frames, c.sl);
   const int fwin = c.sl.partial / nsplit;  // frames whose sums fit the partial slots
 
   // pass 1: total over all frames, left in the carry
@@ -387,12 +421,8 @@ int forward_bidirectional(const Ctx& c, const void* q, const void* k, const void
   }
   const bool resident = T <= fwin;  // every F(f) is still in the partial slots
 
-  // pass 2: windows of chunks, as many as there are state slots; frames that are summed again must
-  // fit the partial slots together (resident ones are there already: 6 heads of 64, 10 frames of 800
-  // in chunks of three in one attention launch 109 us, in two 148 us)
-  int cw = resident ? c.sl.state : (fwin - overlap) / chunk;
-  if (cw < 1) cw = 1;
-  if (cw > c.sl.state) cw = c.sl.state;
+  // pass 2: windows of chunks
+  const int cw = bidir_window(T, chunk, overlap, fwin, c.sl.state);
   for (int c0 = 0; c0 < nc; c0 += cw) {
     const int c1 = (c0 + cw < nc) ? c0 + cw : nc;
     int F0 = c0 * chunk - overlap;
@@ -474,7 +504,7 @@ int forward_core(const Ctx& c, const void* q, const void* k, const void* v,
                                  stab_mode);
   const int nc = num_chunks(T, chunk);
   const Cut cut = choose_cut(B * H, nc, nc - 1, (int64_t)chunk * HW, (int64_t)(chunk + overlap) * HW, d, c.sl.partial,
-                             c.sl.state, kMaxSplit);
+                             c.sl.state);
   const int nsplit = cut.nsplit, win = cut.win;
   const int qtile = attn_query_tile(d);
   const int qtiles = (int)(((int64_t)chunk * HW + qtile - 1) / qtile);
@@ -515,8 +545,7 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   const size_t BH = (size_t)B * H, N = (size_t)T * HW;
   P.nc = num_chunks(T, chunk);
   P.n_seg = P.nc > 1 ? P.nc - 1 : 1;
-  P.nsplit = choose_cut((int)BH, P.n_seg, P.n_seg, (int64_t)chunk * HW, 0, d, kMaxSplit * P.nc, P.n_seg,
-                        kMaxSplit).nsplit;
+  P.nsplit = choose_cut((int)BH, P.n_seg, P.n_seg, (int64_t)chunk * HW, 0, d, kMaxSplit * P.nc, P.n_seg).nsplit;
   P.sl = Slots{P.n_seg * P.nsplit, P.nc};
   P.F = ws_layout(B, H, d, dp, P.sl);
   // weight-gradient kernels: one (b, h) token range cut so that the pieces about fill the chip
@@ -1247,7 +1276,7 @@ int rehyat_state(const void* k, const void* v, const rehyat_phi_params* phi, flo
   rc = ensure_workspace(c.L.total, st, &c.ws);
   if (rc != REHYAT_OK) return rc;
   // one frame per chunk, no overlap: segment f is frame f
-  const Cut cut = choose_cut(B * H, upto_frames, upto_frames, HW, 0, d, c.sl.partial, c.sl.state, kMaxSplit);
+  const Cut cut = choose_cut(B * H, upto_frames, upto_frames, HW, 0, d, c.sl.partial, c.sl.state);
   const int nsplit = cut.nsplit, win = cut.win;
   for (int c0 = 0; c0 < upto_frames; c0 += win) {
     const int n_seg = (upto_frames - c0 < win) ? upto_frames - c0 : win;
