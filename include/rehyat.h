@@ -27,6 +27,10 @@
  *    a workspace 256-byte aligned; otherwise REHYAT_E_SHAPE (REHYAT_E_WORKSPACE
  *    for a workspace).
  *  - Results are deterministic: repeated calls give bit-identical outputs.
+ *    Calls of different B, H, T or n_q may cut the sums of a row differently,
+ *    so the last bits of a row can depend on the size of the call that
+ *    computes it, also where Eq. 13 makes its value independent of the rest
+ *    (appended frames).
  *  - Calls that share a workspace must be ordered on one stream.  Entry points
  *    without a workspace argument share the one the library holds and are
  *    serialised by an internal lock; rehyat_forward_ws takes its workspace per
@@ -289,7 +293,8 @@ int rehyat_phi_backward(const void *q, const void *k, const void *v,
  * The state update (the pieces of Eq. 17-18 and their addition to S and z) does
  * not feed this chunk's output.  With at most 256 tiles of 128 queries over all
  * (batch, head) the pieces are computed by further workgroups of the attention
- * launch, on `stream`.  With more they run beside the attention kernel on a
+ * launch, on `stream`.  With more (and at d = 64 over windows of 4,096 tokens and
+ * more where long pieces would start late) they run beside the attention kernel on a
  * second stream that the library creates per device on first use (default
  * priority, kept until the process ends), forked from `stream` after the state
  * has been copied for the read-out and joined to it before the call's work on

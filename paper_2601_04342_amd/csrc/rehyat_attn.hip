@@ -747,8 +747,9 @@ attn_kernel(AttnArgs a) {
 //
 // What bounds it: as attn_kernel (per-wave chains of score products, exponentials and numerator
 // products), but a launch of at most 256 attn_kernel workgroups leaves one wave on a SIMD, which
-// runs a tile in 2,650 cycles where two waves run two in 2,930.  Here every SIMD that has work
-// has two waves, each with half of the tiles: 0.82 us per key tile and workgroup instead of 1.02
+// runs a tile in nearly the cycles in which two waves run two (2,650 and 2,930).  Here every SIMD
+// that has work has two waves, each with half of the tiles, at the price of the meeting and of a
+// lower clock: 0.82 us per key tile and workgroup instead of 1.02
 // (streaming step at the 480p shape with T_o = 1, 156 items: 59.6 instead of 67.4 us without the
 // state update).  0.14 of the 0.82 us goes away with the tile loads: tiles are requested three
 // half-steps ahead because one trip ahead, in lockstep, took 0.89 us.

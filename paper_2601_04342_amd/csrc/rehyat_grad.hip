@@ -187,7 +187,8 @@ hipError_t launch_transpose(const TransposeArgs& a, hipStream_t stream) {
 // squared half and for rows past the end, a conversion per stored element).  The two halves of
 // the features and the ragged tile now have code of their own, elements are converted in pairs, the
 // bias is the accumulators' start and the key side leaves out the sum it does not need: 168 -> 147
-// us (queries) and 167 -> 131 us (keys) at the 480p shape.
+// us (queries) and 167 -> 131 us (keys) at the 480p shape.  The two loops cost the query side nine
+// spilled registers, stored and reloaded outside them.
 // Two waves per SIMD, also where a workgroup has four waves: with the whole register file to use the
 // compiler keeps accumulators in AGPRs and copies each one out before vector work.
 template <int D, int NW, bool TW>

@@ -17,14 +17,12 @@
 // are one XOR away from a per-lane base and are derived per tile).
 //
 // K and V tiles arrive by direct global->LDS loads (chunk-swizzled rows) into two
-// buffers each, picked by the parity of the tile, and are requested two tile
-// steps ahead of their use: K and V are read exactly once, so every tile comes
-// from HBM, whose latency is far longer than the half tile step a single buffer
-// allows.  The K tile of step t+2 is requested once every wave is past the first
-// half of step t (its buffer is free then), the V tile of step t+2 once step t
-// is complete.  The loads are issued through tile_load_fast (see tile_load_asm:
-// with buffers picked at run time the compiler must not see them) and ordered
-// against the reads by counted waits.
+// buffers each, picked by the parity of the tile: K and V are read exactly once,
+// so every tile comes from HBM.  Step t (second half of tile t, first half of
+// tile t+1) requests the K tile of t+2 and the V tile of t+1 when it begins, one
+// step before they are read.  The loads are issued through tile_load_fast (see
+// tile_load_asm: with buffers picked at run time the compiler must not see them)
+// and have landed at the barrier that begins the next step.
 #include "rehyat_state_body.h"
 
 namespace rehyat {

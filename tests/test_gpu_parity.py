@@ -198,10 +198,10 @@ def test_state_and_normaliser_weigh_a_token_alike(d):
         assert ((S.double() - z.double()[..., None]).abs() <= N * 2.0 ** -24 * z.double()[..., None]).all()
 
 
-@pytest.mark.parametrize("T,HW", [(2, 130), (9, 40), (10, 40), (18, 500), (33, 20)])
+@pytest.mark.parametrize("T,HW", [(2, 40), (2, 130), (9, 40), (10, 40), (18, 500), (33, 20)])
 def test_states_around_whole_batches_of_pieces(T, HW):
-    """The prefix pass loads eight pieces at a time: one piece, eight, nine, pieces of split segments
-    and a second window, each state read by a chunk."""
+    """The prefix pass loads eight pieces at a time: one piece, the pieces of one split segment, eight,
+    nine, pieces of many split segments and a second window, each state read by a chunk."""
     parity.run_case(1, 1, T, HW, 64, 1, 0, 0, 3.0, seed=T + HW)
 
 
@@ -216,6 +216,20 @@ def test_causal_prefix_consistency_on_gpu():
     part = binding.forward(dq[:, :, :n4].contiguous(), dk[:, :, :n4].contiguous(),
                            dv[:, :, :n4].contiguous(), dphi, 4, HW, 2, overlap=1)
     assert torch.equal(full[:, :, :n4], part)
+
+
+def test_causal_prefix_consistency_across_launch_sizes():
+    """Chunk 0 alone (208 workgroups, keys shared by two groups of waves) and with two more chunks
+    appended (624, not shared): the same rows up to the rounding of their sums."""
+    B, H, HW, d = 1, 16, 1600, 128
+    q, k, v = synth.make_qkv(B, H, 3 * HW, d, seed=14)
+    phi = synth.make_phi(H, d, gain=3.0)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    full = binding.forward(dq, dk, dv, dphi, 3, HW, 1)[:, :, :HW].float()
+    part = binding.forward(*(x[:, :, :HW].contiguous() for x in (dq, dk, dv)), dphi, 1, HW, 1).float()
+    torch.cuda.synchronize()
+    err = (full - part).abs()
+    assert err.max() <= parity.OUT_MAX_ABS and err.mean() <= parity.OUT_MEAN_ABS
 
 
 def test_per_call_workspaces_on_two_streams():
