@@ -1,8 +1,8 @@
 // Fused hybrid-attention output kernel for gfx950.
 //
-// One workgroup (4 waves) owns 32*QB*4 consecutive query tokens of one chunk of
-// one (batch, head); each wave owns 32*QB of them and keeps, per query, the
-// running softmax maximum and sum and the d-wide numerator in MFMA accumulators.
+// One workgroup (4 waves) owns 128 consecutive query tokens of one chunk of one (batch, head); each
+// wave owns 32 of them and keeps, per query, the running softmax maximum and sum and the d-wide
+// numerator in MFMA accumulators.
 //
 //   phase S (Eq. 6, 8): exponents K Q^T over the chunk's softmax window
 //            (Eq. 12), online maximum/sum, numerator V^T P.
@@ -19,10 +19,10 @@
 //
 // All operands that are shared by the four waves (K and V tiles, then W1, W2
 // and the chunk state) travel global -> LDS with direct loads into four LDS
-// tile buffers, issued one or more steps ahead of their use.
+// tile buffers, issued one or more steps ahead of their use (as inline asm: the
+// compiler must not order LDS reads behind loads into other buffers).
 #include <cstdio>
 #include <type_traits>
-#include <utility>
 
 #include "rehyat_device.h"
 #include "rehyat_kernels.h"
@@ -39,200 +39,328 @@ constexpr float kLazyMax = 8.0f;
 // Where the reference starts: finite, so that a row whose first key tiles score -inf (or a group
 // of waves that sees no key of a row) weighs them exp2(-inf - reference) = 0, not a NaN.
 constexpr float kLowest = -3.402823466e38f;
-// Query blocks of 32 per wave.  1 -> 128-query workgroups, two resident per CU, whose
-// waves share each SIMD and fill each other's stalls; 2 (one wave per SIMD with twice the
-// registers, half the LDS operand traffic per MFMA) measured 30 % slower at the 480p shape.
-constexpr int kAttnQB = 1;
-constexpr int kAttnNW = 4;   // waves per workgroup; queries per workgroup = 32 * kAttnQB * kAttnNW
+constexpr int kAttnNW = 4;                      // waves that share the 128 queries of a workgroup
+constexpr int kQueryTile = 32 * kAttnNW;
 
-template <int D, int QB, int NWV = 4>
+template <int D>
 struct AttnShape {
   static constexpr int HID = 2 * D;
   static constexpr int DP = 2 * D;
   static constexpr int KS = D / 16;    // k-steps across the head dimension
   static constexpr int DB = D / 32;    // 32-row blocks across the head dimension
-  static constexpr int NW = NWV;       // waves per workgroup
-  static constexpr int NT = 64 * NWV;  // threads
-  static constexpr int QW = 32 * QB;   // queries per wave
-  static constexpr int QT = NWV * QW;  // queries per workgroup
-  static constexpr int KT = 64;        // keys per tile
   static constexpr int TILE_BYTES = 64 * D * 2;  // one LDS tile: 64 rows of 2D bytes
-  static constexpr int LPT = TILE_BYTES / (1024 * NWV);  // direct-load instructions per wave per tile
 };
 
-// per-lane byte offsets of the fragment reads inside a K / V tile
-template <int D>
-struct FragOffsets {
-  int k[D / 16];        // A fragment of K rows r (+32 per key block), k-step ks
-  int v_lo[D / 32];     // transposing read, tokens 4g..4g+3 of a 16-token step, features 32db..
-  int v_hi[D / 32];     // same, tokens 8+4g..
+// Fragment reads inside a K / V tile.  K rows r (+32 per key block), k-step ks: `k` ^ 32 ks.
+// Transposing reads of V, tokens 4g..4g+3 of a 16-token step, features 32 db..: `v` ^ 64 db, and
+// tokens 8+4g..: ^ 32 of that, eight rows further down.  (The chunk permutation of a row is an
+// exclusive-or that looks at the low four bits of the row only.)
+struct FragBase {
+  int k, v;
 };
-
 template <int D>
-__device__ __forceinline__ FragOffsets<D> make_frag_offsets(int lane) {
-  FragOffsets<D> f;
-  const int g = lane >> 5, r = lane & 31, i = lane & 15;
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ++ks) f.k[ks] = tile_off<2 * D>(r, 16 * ks + 8 * g);
-#pragma unroll
-  for (int db = 0; db < D / 32; ++db) {
-    const int col = 32 * db + 16 * (r >> 4) + 4 * (i & 3);
-    f.v_lo[db] = tile_off<2 * D>(4 * g + (i >> 2), col);
-    f.v_hi[db] = tile_off<2 * D>(8 + 4 * g + (i >> 2), col);
-  }
+__device__ __forceinline__ FragBase make_frag_base(int lane) {
+  FragBase f;
+  f.k = tile_off<2 * D>(lane & 31, 8 * (lane >> 5));
+  f.v = tile_off<2 * D>(4 * (lane >> 5) + ((lane & 15) >> 2), 16 * ((lane & 31) >> 4) + 4 * (lane & 3));
   return f;
 }
-
-// One 64-key tile of the softmax part for the wave's 32*QB queries (Eq. 6, 8) in two steps:
-// softmax_scores forms the exponents K Q^T, softmax_weights the online row maximum and sum and
-// numerator += V^T P.  E[kb][qb] register 4i+j = (key 32kb + 8i + 4g + j, query 32qb + r).
-// LDS reads are issued one batch ahead of the MFMAs that consume them; the
-// scheduling barriers keep the compiler from collapsing that order.
 template <int D>
-__device__ __forceinline__ void read_v_step(const char* Vs, const FragOffsets<D>& fo, int step, bf16x8 (&vf)[D / 32]) {
-  constexpr int STEP_BYTES = 16 * D * 2;   // 16 rows further down the tile
+__device__ __forceinline__ bf16x8 k_fragment(const char* Ks, const FragBase& fo, int ks, int kb) {
+  return *reinterpret_cast<const bf16x8*>(Ks + (fo.k ^ (32 * ks)) + kb * (32 * D * 2));
+}
+template <int D>
+__device__ __forceinline__ bf16x8 v_fragment(const char* Vs, const FragBase& fo, int step, int db) {
+  const char* const p = Vs + step * (16 * D * 2);
+  return join_tr(lds_read_tr(reinterpret_cast<const bf16_t*>(p + (fo.v ^ (64 * db)))),
+                 lds_read_tr(reinterpret_cast<const bf16_t*>(p + (fo.v ^ (64 * db) ^ 32) + 8 * 2 * D)));
+}
+
+// Fragments of A operands that a wave keeps ahead of its products.
+constexpr int kAhead = 4;
+
+// What a wave keeps of its 32 queries (one per lane, both lane halves) over the key tiles.
+template <int D>
+struct SoftmaxRows {
+  f32x16 O[D / 32];   // numerator: O[db] register 4i+j = (row d = 32db + 8i + 4g + j, query r)
+  float ref;          // reference of the exponentials (log2 units), lags the running maximum
+  float max;          // running maximum of exponent * log2(e)/sqrt(d)
+  float sum;          // this lane half's share of the sum
+};
+
+template <int D>
+__device__ __forceinline__ void softmax_rescale(SoftmaxRows<D>& s, float tile_max) {
+  s.max = fmaxf(s.max, tile_max);
+  const bool grow = tile_max > s.ref + kLazyMax;
+  if (__any(grow)) {
+    const float ref = grow ? tile_max : s.ref;
+    const float alpha = __builtin_amdgcn_exp2f(s.ref - ref);
+    s.ref = ref;
+    s.sum *= alpha;
 #pragma unroll
-  for (int db = 0; db < D / 32; ++db) {
-    i16x4 lo = lds_read_tr(reinterpret_cast<const bf16_t*>(Vs + fo.v_lo[db] + step * STEP_BYTES));
-    i16x4 hi = lds_read_tr(reinterpret_cast<const bf16_t*>(Vs + fo.v_hi[db] + step * STEP_BYTES));
-    vf[db] = join_tr(lo, hi);
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) s.O[db][e] *= alpha;
   }
 }
 
-// `last` runs with the last batch of products (a place for the LDS reads of what follows).
-template <int D, int QB, typename Last>
-__device__ __forceinline__ void softmax_scores(const char* Ks, const FragOffsets<D>& fo, const bf16x8 (&Qr)[QB][D / 16],
-                                               f32x16 (&E)[2][QB], Last last) {
-  constexpr int KS = D / 16;
-  constexpr int KB_BYTES = 32 * D * 2;   // 32 rows further down the tile
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  // batches of two k-steps (4 fragments)
-  bf16x8 kf[2][2][2];  // [batch parity][k-step in batch][key block]
-  auto read_k = [&](int b, int par) {
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-        kf[par][t][kb] = *reinterpret_cast<const bf16x8*>(Ks + fo.k[2 * b + t] + kb * KB_BYTES);
+// Exponents K Q^T of one 64-key tile (Eq. 6): E[kb] register 4i+j = (key 32kb + 8i + 4g + j, query r).
+template <int D>
+__device__ __forceinline__ void softmax_scores(const char* Ks, const FragBase& fo, const bf16x8 (&Qr)[D / 16],
+                                               f32x16 (&E)[2]) {
+  constexpr int NM = D / 8;
+  bf16x8 fr[kAhead];
+  static_for<kAhead>([&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    fr[m] = k_fragment<D>(Ks, fo, m / 2, m & 1);
+  });
+  static_for<NM>([&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    E[m & 1] = mfma(fr[m % kAhead], Qr[m / 2], m < 2 ? f32x16{} : E[m & 1]);
+    if constexpr (m + kAhead < NM) fr[m % kAhead] = k_fragment<D>(Ks, fo, (m + kAhead) / 2, (m + kAhead) & 1);
+    __builtin_amdgcn_sched_barrier(0);
+  });
+}
+
+// One 64-key tile t of the softmax part (Eq. 6, 8) for the wave's 32 queries, together with the
+// exponents of tile t+1: online maximum and sum of E, numerator += V^T P, and En = K(t+1) Q^T.
+//
+// A wave's own chain over one tile (scores, maximum, exponentials, numerator) leaves the matrix
+// unit idle for more than half of its time, and a second wave on the SIMD cannot fill all of that: both
+// chains have the same gaps.  Here the products of the next tile's scores run over the maximum
+// and the first exponentials of this one, and the numerator's over the rest.  The order is written out
+// slot by slot -- a slot is one product, one fragment read kAhead products ahead, its share of
+// the vector work -- and fenced, because the compiler's own order waits for every LDS read right
+// after issuing it.
+// What bounds it: on a filled chip power (products with the same mix of other work and nothing
+// else: 23 ns per product and SIMD with all CUs busy, 14.5 with 32; here 28 - 30, 25 without the tile
+// loads); with CUs to spare the issue of some 300 instructions per tile and wave.  Against the tile
+// loop that ran the four phases one after the other: 1,488 -> 1,389 us summed over the 480p, 720p and
+// three-frame-chunk guidance-pair launches, streaming step at 480p with T_o = 1 60 -> 55 us, d = 64
+// at 480p 441 -> 430 us.
+//
+// The one barrier per tile stands where the last K fragment of tile t+1 has been read and kAhead
+// products are still to be issued, so that its wait and the first V fragments' latency lie under
+// those; the first K fragments of tile t+2 are read under the last products of the numerator.  At the barrier
+// K(t+2) and V(t) have landed, and everyone is done with K(t+1) and V(t-1): `issue(i)`, i <
+// 2 LPT, requests K(t+3) and V(t+1), spread over the slots that follow (a wave that issues its
+// loads in one go stalls until the address unit has taken them all).
+// fr: the first kAhead K fragments of tile t+1 on entry, of tile t+2 on exit.
+template <int D, int LPT, typename Issue>
+__device__ __forceinline__ void softmax_trip(const char* Kn, const char* Kn2, const char* Vc, const FragBase& fo,
+                                             const bf16x8 (&Qr)[D / 16], f32x16 (&E)[2], f32x16 (&En)[2],
+                                             bf16x8 (&fr)[kAhead], SoftmaxRows<D>& rows, float sc, Issue issue) {
+  constexpr int KS = D / 16, DB = D / 32;
+  constexpr int NQ = 2 * KS, NV = 4 * DB, NM = NQ + NV;
+  static_assert(NM % kAhead == 0, "the fragment ring closes over a trip");
+  constexpr int BAR = NQ - kAhead;                  // slot that the barrier precedes
+  constexpr int MS = D == 128 ? 4 : 2;              // slots of the maximum
+  constexpr int S0 = MS + 3;                        // slot of the first exponential
+  constexpr int W = NQ + 3 * DB - 1 - S0;           // .. and how many slots they spread over
+  constexpr int LS = 2;                             // slots per load
+  static_assert(BAR + 1 + LS * (2 * LPT - 1) < NM, "the loads fit behind the barrier");
+  uint32_t pw[16];
+  float sum = 0.f, mx[2], pe[8];
+  auto fetch = [&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    if constexpr (m < NQ) fr[m % kAhead] = k_fragment<D>(Kn, fo, m / 2, m & 1);
+    else if constexpr (m < NM) fr[m % kAhead] = v_fragment<D>(Vc, fo, (m - NQ) / DB, (m - NQ) % DB);
+    else fr[m % kAhead] = k_fragment<D>(Kn2, fo, (m - NM) / 2, m & 1);
   };
-  read_k(0, 0);
-#pragma unroll
-  for (int b = 0; b < KS / 2; ++b) {
-    if (b + 1 < KS / 2) read_k(b + 1, (b + 1) & 1);
-    else last();
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-          E[kb][qb] = mfma(kf[b & 1][t][kb], Qr[qb][2 * b + t], (b == 0 && t == 0) ? zero : E[kb][qb]);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-}
-
-// vf[0] holds the V fragments of step 0.
-template <int D, int QB, bool TAIL>
-__device__ __forceinline__ void softmax_weights(const char* Vs, const FragOffsets<D>& fo, f32x16 (&E)[2][QB],
-                                                bf16x8 (&vf)[2][D / 32], f32x16 (&O)[D / 32][QB], float (&mrun)[QB],
-                                                float (&mtru)[QB], float (&lrun)[QB], float sc, int valid_keys,
-                                                int lane) {
-  constexpr int DB = D / 32;
-  const int g = lane >> 5;
-
-  // ---- online softmax: new maximum, rescale of the running sums --------------------
-  float mnew[QB], alpha[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    if (TAIL) {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (32 * kb + 8 * (e >> 2) + 4 * g + (e & 3) >= valid_keys) E[kb][qb][e] = -INFINITY;
+  auto product = [&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    if constexpr (m < NQ) {
+      En[m & 1] = mfma(fr[m % kAhead], Qr[m / 2], m < 2 ? f32x16{} : En[m & 1]);
+    } else {
+      constexpr int step = (m - NQ) / DB, db = (m - NQ) % DB;
+      const u32x4 w = {pw[4 * step], pw[4 * step + 1], pw[4 * step + 2], pw[4 * step + 3]};
+      rows.O[db] = mfma(fr[m % kAhead], __builtin_bit_cast(bf16x8, w), rows.O[db]);
     }
-    float mx = fmaxf(E[0][qb][0], E[1][qb][0]);
+  };
+  // element i of the tile is register i & 15 of key block i >> 4; eight of them make the operand of a
+  // 16-key step.  Its exponential stands in slot_of(i), its sum and rounding one slot later.
+  auto slot_of = [](int i) { return S0 + i * W / 32; };
+  static_for<NM>([&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    if constexpr (m == BAR) wait_loads_and_barrier<0>();
+    product(MC);
+    fetch(std::integral_constant<int, m + kAhead>{});
+    if constexpr (m > BAR && (m - BAR - 1) % LS == 0 && (m - BAR - 1) / LS < 2 * LPT)
+      issue(std::integral_constant<int, (m - BAR - 1) / LS>{});
+    if constexpr (m < MS) {
 #pragma unroll
-    for (int e = 1; e < 16; ++e) mx = fmaxf(mx, fmaxf(E[0][qb][e], E[1][qb][e]));
-    mx = half_swap_max(mx);
+      for (int e = m * 16 / MS; e < (m + 1) * 16 / MS; e += 2)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+          const float pair = fmaxf(E[kb][e], E[kb][e + 1]);
+          mx[kb] = e == 0 ? pair : fmaxf(mx[kb], pair);
+        }
+    }
     // exponents are kept unscaled; sc = log2(e)/sqrt(d) > 0 is folded into the exp2 argument
-    const float mt = mx * sc;
-    mtru[qb] = fmaxf(mtru[qb], mt);
-    alpha[qb] = 1.0f;
-    const bool grow = mt > mrun[qb] + kLazyMax;
-    if (__any(grow)) {
-      const float mref = grow ? mt : mrun[qb];
-      alpha[qb] = __builtin_amdgcn_exp2f(mrun[qb] - mref);
-      mrun[qb] = mref;
-#pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) O[db][qb][e] *= alpha[qb];
-    }
-    mnew[qb] = mrun[qb];
-  }
-  __builtin_amdgcn_sched_barrier(0);
-
-  // ---- numerator += V^T P, one 16-key step at a time.  The weights of a step (8 per
-  // lane: registers 8(step&1).. of key block step>>1) are exponentiated just before its
-  // products, so that the products of one step can run under the exponentials of the next
-  // (one scheduling region; the group barriers below ask for that interleave).
-  float sum[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) sum[qb] = 0.f;
-#pragma unroll
-  for (int step = 0; step < 4; ++step) {
-    if (step + 1 < 4) read_v_step<D>(Vs, fo, step + 1, vf[(step + 1) & 1]);
-    bf16x8 pf[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-#pragma unroll
-      for (int e = 8 * (step & 1); e < 8 * (step & 1) + 8; ++e) {
-        float p = __builtin_amdgcn_exp2f(__builtin_fmaf(E[step >> 1][qb][e], sc, -mnew[qb]));
-        E[step >> 1][qb][e] = p;
-        sum[qb] += p;
+    if constexpr (m == MS + 1) mx[0] = half_swap_max(fmaxf(mx[0], mx[1])) * sc;
+    if constexpr (m == MS + 2) softmax_rescale<D>(rows, mx[0]);
+    static_for<32>([&](auto IC) {
+      constexpr int i = decltype(IC)::value;
+      if constexpr (slot_of(i) + 1 == m) {
+        sum += pe[i & 7];
+        if constexpr (i & 1) pw[i >> 1] = pack_bf16(pe[(i & 7) - 1], pe[i & 7]);
       }
-      pf[qb] = acc_to_operand(E[step >> 1][qb], step & 1);
-    }
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) O[db][qb] = mfma(vf[step & 1][db], pf[qb], O[db][qb]);
-  }
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) lrun[qb] = lrun[qb] * alpha[qb] + sum[qb];
-  if (QB == 1 && DB == 4) {
-    // step 0's weights first, then each product followed by a share of the next step's work
-    __builtin_amdgcn_sched_group_barrier(0x100, 8, 0);   // V fragments of step 1
-    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
-    __builtin_amdgcn_sched_group_barrier(0x400, 8, 0);
-    __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);
-#pragma unroll
-    for (int s2 = 0; s2 < 3; ++s2)
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-        if (s2 < 2) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x400, 2, 0);
-        __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
-      }
-    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
-  }
-  __builtin_amdgcn_sched_barrier(0);
+    });
+    static_for<32>([&](auto IC) {
+      constexpr int i = decltype(IC)::value;
+      if constexpr (slot_of(i) == m)
+        pe[i & 7] = __builtin_amdgcn_exp2f(__builtin_fmaf(E[i >> 4][i & 15], sc, -rows.ref));
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  rows.sum += sum;
 }
 
-template <int D, int QB, bool TAIL>
-__device__ __forceinline__ void softmax_tile(const char* Ks, const char* Vs, const FragOffsets<D>& fo,
-                                             const bf16x8 (&Qr)[QB][D / 16], f32x16 (&O)[D / 32][QB],
-                                             float (&mrun)[QB], float (&mtru)[QB], float (&lrun)[QB],
-                                             float sc, int valid_keys, int lane) {
-  f32x16 E[2][QB];
-  bf16x8 vf[2][D / 32];   // [step parity][feature block]
-  softmax_scores<D, QB>(Ks, fo, Qr, E, [&] { read_v_step<D>(Vs, fo, 0, vf[0]); });
-  softmax_weights<D, QB, TAIL>(Vs, fo, E, vf, O, mrun, mtru, lrun, sc, valid_keys, lane);
+// The last tile: keys outside [first, first + count) of it are not in the window.
+template <int D>
+__device__ __forceinline__ void softmax_last(const char* Vc, const FragBase& fo, f32x16 (&E)[2], SoftmaxRows<D>& rows,
+                                             float sc, int first, int count, int lane) {
+  constexpr int DB = D / 32, NM = 4 * DB;
+  const int g = lane >> 5;
+  bf16x8 fr[kAhead];
+  static_for<kAhead>([&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    fr[m] = v_fragment<D>(Vc, fo, m / DB, m % DB);
+  });
+  float mx = -INFINITY;
+#pragma unroll
+  for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      if ((unsigned)(32 * kb + 8 * (e >> 2) + 4 * g + (e & 3) - first) >= (unsigned)count) E[kb][e] = -INFINITY;
+      mx = fmaxf(mx, E[kb][e]);
+    }
+  softmax_rescale<D>(rows, half_swap_max(mx) * sc);
+  float sum = 0.f;
+  uint32_t pw[4];
+  static_for<NM>([&](auto MC) {
+    constexpr int m = decltype(MC)::value, step = m / DB;
+    if constexpr (m % DB == 0) {
+#pragma unroll
+      for (int i = 0; i < 8; i += 2) {
+        float p[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          p[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(E[step >> 1][8 * (step & 1) + i + j], sc, -rows.ref));
+          sum += p[j];
+        }
+        pw[i >> 1] = pack_bf16(p[0], p[1]);
+      }
+    }
+    const u32x4 w = {pw[0], pw[1], pw[2], pw[3]};
+    rows.O[m % DB] = mfma(fr[m % kAhead], __builtin_bit_cast(bf16x8, w), rows.O[m % DB]);
+    if constexpr (m + kAhead < NM)
+      fr[m % kAhead] = v_fragment<D>(Vc, fo, (m + kAhead) / DB, (m + kAhead) % DB);
+  });
+  rows.sum += sum;
 }
+
+// The softmax part over a wave's key tiles 0 .. n-1 (tile t of it is tile first_tile + t * stride
+// of the window): four waves share K in buffers 0/1 and V in 2/3 of `tiles`, picked by the parity of
+// t.  Meets n + 1 barriers.  A ragged last tile holds the last 64 keys of the window, those of
+// the tile before it left out by softmax_last; only a window of fewer than 64 keys re-reads its
+// last row.  Waves that are not live move their share of the tiles and compute nothing.
+template <int D>
+struct SoftmaxTiles {
+  static constexpr int TB = 64 * D * 2;
+  static constexpr int LPT = TB / (1024 * 4);
+  u32x4 K, V;
+  uint32_t lds;        // address of the four buffers, of the wave's first block in them
+  const char* tiles;
+  int n_keys, first_tile, stride, n;
+  int wave, lane, voff;
+
+  __device__ __forceinline__ int soff(int t) const {   // byte offset of tile t in the window
+    const int row = 64 * (first_tile + t * stride), last = n_keys - 64;
+    return __builtin_amdgcn_readfirstlane((row < last ? row : last) * (2 * D));
+  }
+  // block i of the wave's share of a tile at `so` (bytes) into the buffer at `dst` (its first block)
+  template <int I>
+  __device__ __forceinline__ void load(u32x4 rsrc, int so, uint32_t dst) const {
+    int tmp;
+    asm volatile("s_add_i32 m0, %1, %5\n\ts_add_i32 %0, %4, %5\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds"
+                 : "=&s"(tmp)
+                 : "s"(dst), "v"(voff), "s"(rsrc), "s"(so), "n"(4096 * I)
+                 : "memory", "scc");
+  }
+  __device__ __forceinline__ void load_first(u32x4 rsrc, int t, int buf) const {   // before the loop
+    if (n_keys < 64) {
+      tile_load_asm<2 * D, TB, 4>(rsrc, 0, lds + buf * TB - wave * 1024, wave, lane, n_keys);
+      return;
+    }
+    const int so = soff(t);
+    const uint32_t dst = lds + buf * TB;
+    static_for<LPT>([&](auto IC) { load<decltype(IC)::value>(rsrc, so, dst); });
+  }
+  __device__ __forceinline__ void request() const {   // what has to be there before run()
+    if (n > 0) {
+      load_first(K, 0, 0);
+      load_first(V, 0, 2);
+    }
+    if (n > 1) load_first(K, 1, 1);
+  }
+  template <bool LIVE>
+  __device__ __forceinline__ void run(const bf16x8 (&Qr)[D / 16], SoftmaxRows<D>& rows, float sc) const {
+    FragBase fo = make_frag_base<D>(lane);
+    const char *const K0 = tiles, *const K1 = tiles + TB, *const V0 = tiles + 2 * TB, *const V1 = tiles + 3 * TB;
+    f32x16 E0[2], E1[2];
+    bf16x8 fr[kAhead];
+    if constexpr (LIVE) {
+      softmax_scores<D>(K0, fo, Qr, E0);
+      static_for<kAhead>([&](auto MC) {
+        constexpr int m = decltype(MC)::value;
+        fr[m] = k_fragment<D>(K1, fo, m / 2, m & 1);
+      });
+    }
+    lds_barrier();
+    if (n > 2) load_first(K, 2, 0);
+    auto trip = [&](int t, const char* Kn, const char* Kn2, const char* Vc, int kbuf, int vbuf, f32x16 (&E)[2],
+                    f32x16 (&En)[2]) {
+      // past the last tile the descriptor is empty and nothing is fetched: a branch around each
+      // load would let the compiler move vector work out of its slot
+      u32x4 Kd = K;
+      Kd[2] = t + 3 < n ? K[2] : 0u;
+      const int ks = soff(t + 3), vs = soff(t + 1);
+      const uint32_t kd = lds + kbuf * TB, vd = lds + vbuf * TB;
+      auto issue = [&](auto IC) {
+        constexpr int i = decltype(IC)::value;
+        if constexpr (i < LPT) load<i>(Kd, ks, kd);
+        else load<i - LPT>(V, vs, vd);
+      };
+      if constexpr (LIVE) {
+        softmax_trip<D, LPT>(Kn, Kn2, Vc, fo, Qr, E, En, fr, rows, sc, issue);
+      } else {
+        wait_loads_and_barrier<0>();
+        static_for<2 * LPT>([&](auto IC) { issue(IC); });
+      }
+    };
+    int t = 0;
+    for (; t + 2 < n; t += 2) {
+      trip(t, K1, K0, V0, 1, 3, E0, E1);
+      trip(t + 1, K0, K1, V1, 0, 2, E1, E0);
+    }
+    const char* Vl = V0;
+    if (t + 1 < n) {
+      trip(t, K1, K0, V0, 1, 3, E0, E1);
+      if constexpr (LIVE) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) E0[kb] = E1[kb];
+      }
+      Vl = V1;
+      ++t;
+    }
+    wait_loads_and_barrier<0>();
+    if constexpr (LIVE) {
+      const int row = 64 * (first_tile + t * stride), over = row + 64 - n_keys;   // keys short of a full tile
+      softmax_last<D>(Vl, fo, E0, rows, sc, over > 0 && n_keys >= 64 ? over : 0, over > 0 ? 64 - over : 64, lane);
+    }
+  }
+};
 
 // ---------------------------------------------------------------------------
 // Phase L operand tiles and the order in which they stream through the four
@@ -299,20 +427,143 @@ struct LinSched<64> {    // 2 W1 steps, then 4 feature-block steps
   }
 };
 
+// Requests of phase L tiles by NW waves (kinds as above), one per-lane offset for all blocks a wave
+// moves: W1 and S rows are contiguous or evenly strided, a W2 tile is two halves of 32 rows.
+template <int D, int NW>
+struct LinTiles {
+  static constexpr int TB = 64 * D * 2;
+  static constexpr int LPT = TB / (1024 * NW);   // direct loads per wave per tile
+  static constexpr int CPR = 2 * D / 16, RPB = 1024 / (2 * D);
+  u32x4 W1, W2, S;
+  uint32_t lds;
+  int wave, lane;
+
+  __device__ __forceinline__ void issue(int kind, int idx, int buf) const {
+    const int jr = lane / CPR, cw = ((lane % CPR) ^ swz<2 * D>(wave * RPB + jr)) << 4;
+    const int js = lane >> 3, cs = ((lane & 7) ^ swz<128>(wave * 8 + js)) << 4;
+#pragma unroll
+    for (int n = 0; n < LPT; ++n) {
+      const int blk = wave + NW * n, R = blk * RPB;
+      const uint32_t dst = lds + buf * TB + blk * 1024;
+      if (kind == kW1)
+        direct_load_16(W1, jr * (2 * D) + cw, idx * TB + blk * 1024, dst);
+      else if (kind == kW2)
+        direct_load_16(W2, jr * (4 * D) + cw, idx * 32 * (4 * D) + (R & 31) * (4 * D) + (R >> 5) * (2 * D), dst);
+      else
+        direct_load_16(S, js * (4 * D) + cs, idx * 128 + blk * 8 * (4 * D), dst);
+    }
+  }
+};
+
+// The 32 rows of a W1 / W2 block are read in "quad-swapped" order (lane r takes block row sigma(r),
+// sigma exchanging bits 2 and 3 of r), so that the accumulator of one product is, register for
+// register, the B operand of the next one in natural k order and no operand needs a permuted copy
+// in memory.  Accumulator register 4i+j of lane half g is block row 8i+4g+j, which after the row
+// permutation is unit 16(i>>1) + 8g + 4(i&1) + j of the block.
+template <int D>
+__device__ __forceinline__ int lin_row_base(int lane) {   // k-step ks of the lane's row at ^ 32 ks
+  const int r = lane & 31;
+  return tile_off<2 * D>((r & 0x13) | ((r & 4) << 1) | ((r & 8) >> 1), 8 * (lane >> 5));
+}
+__device__ __forceinline__ void lin_vector(const float* v, int g, f32x16& x) {   // 32 units in accumulator order
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f32x4 q = *reinterpret_cast<const f32x4*>(v + 16 * (i >> 1) + 8 * g + 4 * (i & 1));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) x[4 * i + j] = q[j];
+  }
+}
+
+// U^T = relu(W1 Q^T + b1) of NB blocks of 32 hidden units: Ub[2 nb], Ub[2 nb + 1] as B operands.  Fragments
+// are read kAhead products ahead, a block is rectified under the products of the next one.
+template <int D, int NB>
+__device__ __forceinline__ void lin_hidden(const char* Ws, int wbase, const float* bias, int g,
+                                           const bf16x8 (&Qr)[D / 16], bf16x8* Ub) {
+  constexpr int KS = D / 16, NM = NB * KS;
+  f32x16 acc[2];
+  bf16x8 fr[kAhead];
+  auto fetch = [&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    if constexpr (m < NM) {
+      if constexpr (m % KS == 0) lin_vector(bias + 32 * (m / KS), g, acc[(m / KS) & 1]);
+      fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(Ws + (wbase ^ (32 * (m % KS))) + (m / KS) * (32 * 2 * D));
+    }
+  };
+  auto finish = [&](int nb, int half) {   // one of the two operands of block nb
+    f32x16& x = acc[nb & 1];
+#pragma unroll
+    for (int e = 8 * half; e < 8 * half + 8; ++e) x[e] = fmaxf(x[e], 0.f);
+    Ub[2 * nb + half] = acc_to_operand(x, half);
+  };
+  asm volatile("" : "+v"(wbase));
+  static_for<kAhead>([&](auto MC) { fetch(MC); });
+  static_for<NM>([&](auto MC) {
+    constexpr int m = decltype(MC)::value, nb = m / KS;
+    acc[nb & 1] = mfma(fr[m % kAhead], Qr[m % KS], acc[nb & 1]);
+    // before the fetch that refills the other accumulator (bias of the next block)
+    if constexpr (nb > 0 && m % KS == (KS > kAhead ? 1 : 0)) finish(nb - 1, 0);
+    if constexpr (nb > 0 && m % KS == (KS > kAhead ? 2 : 0)) finish(nb - 1, 1);
+    fetch(std::integral_constant<int, m + kAhead>{});
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  finish(NB - 1, 0);
+  finish(NB - 1, 1);
+}
+
+// One block of 32 features: psi^T = relu(W2 U^T + b2), phi (SQ: squared), its share of n^L, and
+// O += S^T phi with the block's 32 columns of the S tile (the upper half of its 64 if `upper`).
+template <int D, bool SQ>
+__device__ __forceinline__ float lin_features(const char* Ws, const char* Ss, int wbase, int sbase, bool upper,
+                                              const float* bias, const float* z, int g, float lin_scale,
+                                              const bf16x8 (&Ub)[D / 8], f32x16 (&O)[D / 32]) {
+  constexpr int KS = D / 16, DB = D / 32, NW = 2 * KS, NM = NW + 2 * DB;
+  f32x16 acc, zv;
+  bf16x8 fr[kAhead], fb[2];
+  float part = 0.f;
+  asm volatile("" : "+v"(wbase), "+v"(sbase));
+  if (upper) sbase ^= 64;
+  auto fetch = [&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    if constexpr (m < NW)
+      fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(Ws + (wbase ^ (32 * (m % KS))) + (m / KS) * (32 * 2 * D));
+    else if constexpr (m < NM)
+      fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(Ss + (sbase ^ (32 * ((m - NW) / DB))) + (m - NW) % DB * (32 * 128));
+  };
+  lin_vector(bias, g, acc);
+  static_for<kAhead>([&](auto MC) { fetch(MC); });
+  static_for<NM>([&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    if constexpr (m < NW) {
+      acc = mfma(fr[m % kAhead], Ub[m], acc);
+    } else {
+      if constexpr (m == NW) {
+        // the read-out rounds phi to bf16 (MFMA operand); the normaliser takes it unrounded: the
+        // 256 rounding errors of a row have random signs and relative size 2^-9, far below the
+        // bar on n^L, and the rounding costs two instructions per feature
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+          float x = fmaxf(acc[e], 0.f);
+          if (SQ) x = x * x;
+          x = x * lin_scale;
+          acc[e] = x;
+          part += x * zv[e];
+        }
+        fb[0] = acc_to_operand(acc, 0);
+        fb[1] = acc_to_operand(acc, 1);
+      }
+      O[(m - NW) % DB] = mfma(fr[m % kAhead], fb[(m - NW) / DB], O[(m - NW) % DB]);
+    }
+    if constexpr (m == NW - 6) lin_vector(z, g, zv);
+    fetch(std::integral_constant<int, m + kAhead>{});
+    __builtin_amdgcn_sched_barrier(0);
+  });
+  return part;
+}
+
 template <int D, int ST>
 struct LinStepC { static constexpr LinStep value = LinSched<D>::step(ST); };
 template <int D, int I>
 struct LinProC { static constexpr LinStep value = LinSched<D>::pro(I); };
-
-// compile-time loop: f(integral_constant<int, 0>) ... f(integral_constant<int, N-1>)
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_impl(f, std::make_integer_sequence<int, N>{});
-}
 
 // Which (batch*head, chunk of the window, query tile) this workgroup computes; false: none.
 __device__ __forceinline__ bool attn_item(const AttnArgs& a, int& bh, int& tc, int& qt) {
@@ -365,20 +616,15 @@ __device__ __forceinline__ ChunkRange attn_range(const AttnArgs& a, int t) {
   return cr;
 }
 
-// second bound: waves per SIMD the register budget is sized for
-template <int D, int QB, int NWV>
-__global__ void __launch_bounds__(64 * NWV, (QB == 1 ? 2 : 1))
+// second bound: waves per SIMD that the register budget is sized for
+template <int D>
+__global__ void __launch_bounds__(64 * kAttnNW, D == 64 ? 3 : 2)
 attn_kernel(AttnArgs a) {
-  using C = AttnShape<D, QB, NWV>;
-  constexpr int HID = C::HID, DP = C::DP, KS = C::KS, DB = C::DB, NT = C::NT;
-  constexpr int TB = C::TILE_BYTES, LPT = C::LPT;
-  // Four tile buffers, declared as separate objects so that a pending direct
-  // load into one of them does not make the compiler wait before reads of
-  // another.  Phase S: K tiles in A0/A1, V tiles in A2/A3 (even/odd tile).
-  __shared__ __attribute__((aligned(1024))) char A0[TB];
-  __shared__ __attribute__((aligned(1024))) char A1[TB];
-  __shared__ __attribute__((aligned(1024))) char A2[TB];
-  __shared__ __attribute__((aligned(1024))) char A3[TB];
+  using C = AttnShape<D>;
+  constexpr int HID = C::HID, DP = C::DP, KS = C::KS, DB = C::DB, NT = 64 * kAttnNW;
+  constexpr int TB = C::TILE_BYTES;
+  // four tile buffers; phase S: K tiles in 0/1, V tiles in 2/3
+  __shared__ __attribute__((aligned(1024))) char tiles[4 * TB];
   __shared__ __attribute__((aligned(16))) float sb1[HID];
   __shared__ __attribute__((aligned(16))) float sb2[DP];
   __shared__ __attribute__((aligned(16))) float sz[DP];
@@ -396,7 +642,7 @@ attn_kernel(AttnArgs a) {
   const int t = a.chunk0 + tc;
   const int h = bh % a.H;
   const ChunkRange cr = attn_range(a, t);
-  const int64_t q0 = cr.q_lo + (int64_t)qt * C::QT;
+  const int64_t q0 = cr.q_lo + (int64_t)qt * kQueryTile;
   if (q0 >= cr.q_hi) return;   // never with the item counts of the host layer; without it the code before
                                // the first loads is ordered worse (24 heads x 11 chunks of 63 tokens
                                // 47.0 us a call, 45.1 with it)
@@ -408,62 +654,33 @@ attn_kernel(AttnArgs a) {
   const bool has_linear = cr.l_hi > 0;
 
   // ---- queries of this wave, held as B operands ---------------------------
-  const int64_t qw0 = q0 + wave * C::QW;
+  const int64_t qw0 = q0 + wave * 32;
+  const int64_t row = qw0 + r;   // this lane's query
   // a wave whose 32 queries all lie beyond the chunk (last query tile) still moves its
   // share of every tile and meets every barrier, but computes nothing
   const bool wave_live = qw0 < cr.q_hi;
-  bf16x8 Qr[QB][KS];
+  bf16x8 Qr[KS];
+  {
+    const bf16_t* p = Qg + (row < cr.q_hi ? row : cr.q_hi - 1) * D + 8 * g;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    int64_t row = qw0 + 32 * qb + r;
-    if (row > cr.q_hi - 1) row = cr.q_hi - 1;
-    const bf16_t* p = Qg + row * D + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-      Qr[qb][ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
+    for (int ks = 0; ks < KS; ++ks) Qr[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
   }
-
-  // numerator: O[db][qb] register 4i+j = (row d = 32db + 8i + 4g + j, query 32qb + r)
-  f32x16 O[DB][QB];
+  SoftmaxRows<D> rows;
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) O[db][qb][e] = 0.f;
-  float mrun[QB];  // reference of the exponentials (log2 units), lags the running maximum
-  float mtru[QB];  // running maximum of exponent * log2(e)/sqrt(d)
-  float lrun[QB];  // this lane half's share of the sum
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    mrun[qb] = kLowest;
-    mtru[qb] = -INFINITY;
-    lrun[qb] = 0.f;
-  }
-  const float sc = a.scale_log2e;
+  for (int db = 0; db < DB; ++db) rows.O[db] = f32x16{};
+  rows.ref = kLowest;
+  rows.max = -INFINITY;
+  rows.sum = 0.f;
 
   // =========================== phase S =====================================
   {
-    const FragOffsets<D> fo = make_frag_offsets<D>(lane);
-    const int64_t s_lo = cr.s_lo, s_hi = cr.s_hi;
-    const int n_full = (int)((s_hi - s_lo) / 64);
-    const int rem = (int)((s_hi - s_lo) - 64 * (int64_t)((s_hi - s_lo) / 64));  // keys in the ragged last tile
-    const char* const Kb = reinterpret_cast<const char*>(Kg + s_lo * D);
-    const char* const Vb = reinterpret_cast<const char*>(Vg + s_lo * D);
-    auto contiguous = [](int R) { return R * (2 * D); };
-    // K and V of tile `it` into the given buffers
-    auto run_tile = [&](auto TAILC, const char* Kt, const char* Vt, int valid) {
-      constexpr bool TAIL = decltype(TAILC)::value;
-      softmax_tile<D, QB, TAIL>(Kt, Vt, fo, Qr, O, mrun, mtru, lrun, sc, valid, lane);
-    };
-    const __amdgpu_buffer_rsrc_t Kr = make_rsrc(Kb), Vr = make_rsrc(Vb);
-    auto issue_kv = [&](int it, char* kd, char* vd) {
-      tile_load_buffer<2 * D, TB, NWV>(Kr, it * TB, kd, wave, lane, contiguous);
-      tile_load_buffer<2 * D, TB, NWV>(Vr, it * TB, vd, wave, lane, contiguous);
-    };
-    if (n_full > 0) issue_kv(0, A0, A2);
-      // per-head vectors of phase L (their loads complete long before phase L, whose
-      // counted waits must see tile loads only)
+    const int n_keys = (int)(cr.s_hi - cr.s_lo);
+    const SoftmaxTiles<D> st{make_rsrc_words(Kg + cr.s_lo * D), make_rsrc_words(Vg + cr.s_lo * D), lds_address(tiles) + wave * 1024,
+                             tiles, n_keys, 0, 1, (n_keys + 63) / 64, wave, lane,
+                             tile_voff_full<2 * D, 4>(wave, lane) + wave * 1024};
+    st.request();
+    // per-head vectors of phase L (their loads complete long before phase L, whose
+    // counted waits must see tile loads only)
     if (has_linear) {
       const float* zt = a.state_z + ((int64_t)bh * a.state_slots + tc) * DP;
       for (int i = tid; i < HID; i += NT) sb1[i] = a.b1_q[(int64_t)h * HID + i];
@@ -472,65 +689,45 @@ attn_kernel(AttnArgs a) {
         sz[i] = zt[i];
       }
     }
+    settle(Qr);
     wait_loads_and_barrier<0>();   // also publishes the bias vectors
-    // Two tiles per trip so that buffer choice is static.  The loads of tile
-    // it+1 go into the other buffer pair, whose last readers (tile it-1) all
-    // passed the barrier that ended the previous tile; they must have landed,
-    // for every wave, by the barrier that ends tile it.
-    for (int it = 0; it < n_full; it += 2) {
-      if (it + 1 < n_full) issue_kv(it + 1, A1, A3);
-      if (wave_live) run_tile(std::false_type{}, A0, A2, 64);
-      wait_loads_and_barrier<0>();
-      if (it + 1 < n_full) {
-        if (it + 2 < n_full) issue_kv(it + 2, A0, A2);
-        if (wave_live) run_tile(std::false_type{}, A1, A3, 64);
-        wait_loads_and_barrier<0>();
-      }
-    }
-    if (rem > 0) {
-      // ragged last tile, outside the loop so that its index math is not kept
-      // live in it; rows beyond the window re-read the last valid row (finite
-      // values) and their keys are masked
-      const int64_t goff = (int64_t)((s_hi - s_lo) / 64) * TB;
-      auto clamped = [rem](int R) { return (R < rem ? R : rem - 1) * (2 * D); };
-      tile_load_direct<2 * D, TB, NWV>(Kb + goff, A0, wave, lane, clamped);
-      tile_load_direct<2 * D, TB, NWV>(Vb + goff, A2, wave, lane, clamped);
-      wait_loads_and_barrier<0>();
-      if (wave_live) run_tile(std::true_type{}, A0, A2, rem);
-      wait_loads_and_barrier<0>();
-    }
+    if (wave_live) st.template run<true>(Qr, rows, a.scale_log2e);
+    else st.template run<false>(Qr, rows, a.scale_log2e);
+    lds_barrier();   // all K/V tiles are dead
   }
 
+  // =========================== phase L: first tiles =========================
+  using SCH = LinSched<D>;
+  const LinTiles<D, kAttnNW> lt{make_rsrc_words(a.w1_q + (int64_t)h * HID * D), make_rsrc_words(a.w2_q + (int64_t)h * DP * HID),
+                                make_rsrc_words(a.state_s + ((int64_t)bh * a.state_slots + tc) * (int64_t)D * DP),
+                                lds_address(tiles), wave, lane};
+  auto issue_all = [&](auto SD) {   // the tiles a step (or the prologue) issues
+    constexpr LinStep sd = decltype(SD)::value;
+    if constexpr (sd.n_issue > 0) lt.issue(sd.kind[0], sd.idx[0], sd.buf[0]);
+    if constexpr (sd.n_issue > 1) lt.issue(sd.kind[1], sd.idx[1], sd.buf[1]);
+  };
   // complete the softmax normaliser across the two lane halves
-  // All sums are relative to 2^-mrun; the components are reported relative to the
-  // true maximum: dscale = 2^(mrun - mtru) <= 1.
-  float nS[QB], dscale[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    nS[qb] = half_swap_sum(lrun[qb]);
-    dscale[qb] = __builtin_amdgcn_exp2f(mrun[qb] - mtru[qb]);
-  }
+  // All sums are relative to 2^-ref; the components are reported relative to the
+  // true maximum: dscale = 2^(ref - max) <= 1.
+  const float nS = half_swap_sum(rows.sum);
+  const float dscale = __builtin_amdgcn_exp2f(rows.ref - rows.max);
 
   // debug: softmax components
   if (a.dbg_m || a.dbg_nS || a.dbg_aS) {
+    if (row < cr.q_hi) {
+      const int64_t o = (int64_t)bh * N + row;
+      if (g == 0) {
+        if (a.dbg_m) a.dbg_m[o] = rows.max * 0.6931471805599453f;  // back from base 2
+        if (a.dbg_nS) a.dbg_nS[o] = nS * dscale;
+      }
+      if (a.dbg_aS) {
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      const int64_t row = qw0 + 32 * qb + r;
-      if (row < cr.q_hi) {
-        const int64_t o = (int64_t)bh * N + row;
-        if (g == 0) {
-          if (a.dbg_m) a.dbg_m[o] = mtru[qb] * 0.6931471805599453f;  // back from base 2
-          if (a.dbg_nS) a.dbg_nS[o] = nS[qb] * dscale[qb];
-        }
-        if (a.dbg_aS) {
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              f32x4 x = {O[db][qb][4 * i], O[db][qb][4 * i + 1], O[db][qb][4 * i + 2], O[db][qb][4 * i + 3]};
-              *reinterpret_cast<f32x4*>(a.dbg_aS + o * D + 32 * db + 8 * i + 4 * g) = x * dscale[qb];
-            }
-        }
+          for (int i = 0; i < 4; ++i) {
+            f32x4 x = {rows.O[db][4 * i], rows.O[db][4 * i + 1], rows.O[db][4 * i + 2], rows.O[db][4 * i + 3]};
+            *reinterpret_cast<f32x4*>(a.dbg_aS + o * D + 32 * db + 8 * i + 4 * g) = x * dscale;
+          }
       }
     }
     // the counted waits of phase L must see tile loads only
@@ -538,202 +735,60 @@ attn_kernel(AttnArgs a) {
   }
 
   // =========================== phase L =====================================
-  // The 32 rows of a W1 / W2 block are read in "quad-swapped" order (lane r takes
-  // block row sigma(r), sigma exchanging bits 2 and 3 of r), so that the
-  // accumulator of one product is, register for register, the B operand of the
-  // next one in natural k order and no operand needs a permuted copy in memory.
-  float nL[QB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) nL[qb] = 0.f;
+  float nL = 0.f;
   if (has_linear) {
-    using SCH = LinSched<D>;
+    static_for<SCH::NPRO>([&](auto I) { issue_all(LinProC<D, decltype(I)::value>{}); });
     constexpr int NW1 = HID / 64, NPB = DP / 32;
-    const char* W1 = reinterpret_cast<const char*>(a.w1_q + (int64_t)h * HID * D);
-    const char* W2 = reinterpret_cast<const char*>(a.w2_q + (int64_t)h * DP * HID);
-    const char* St = reinterpret_cast<const char*>(a.state_s + ((int64_t)bh * a.state_slots + tc) * (int64_t)D * DP);
-
-    const __amdgpu_buffer_rsrc_t W1r = make_rsrc(W1), W2r = make_rsrc(W2), Str = make_rsrc(St);
-    auto issue_tile = [&](auto KIND, int idx, char* dst) {
-      constexpr int kind = decltype(KIND)::value;
-      if constexpr (kind == kW1) {
-        tile_load_buffer<2 * D, TB, NWV>(W1r, idx * TB, dst, wave, lane, [](int R) { return R * (2 * D); });
-      } else if constexpr (kind == kW2) {
-        tile_load_buffer<2 * D, TB, NWV>(W2r, idx * 32 * (4 * D), dst, wave, lane,
-                                       [](int R) { return (R & 31) * (4 * D) + (R >> 5) * (2 * D); });
-      } else {
-        tile_load_buffer<128, TB, NWV>(Str, idx * 128, dst, wave, lane, [](int R) { return R * (4 * D); });
-      }
-    };
-    auto buf = [&](auto I) -> char* {
-      constexpr int i = decltype(I)::value;
-      if constexpr (i == 0) return A0;
-      else if constexpr (i == 1) return A1;
-      else if constexpr (i == 2) return A2;
-      else return A3;
-    };
-    auto issue_all = [&](auto SD) {   // the tiles a step (or the prologue) issues
-      constexpr LinStep sd = decltype(SD)::value;
-      if constexpr (sd.n_issue > 0)
-        issue_tile(std::integral_constant<int, sd.kind[0]>{}, sd.idx[0], buf(std::integral_constant<int, sd.buf[0]>{}));
-      if constexpr (sd.n_issue > 1)
-        issue_tile(std::integral_constant<int, sd.kind[1]>{}, sd.idx[1], buf(std::integral_constant<int, sd.buf[1]>{}));
-    };
-    // all K/V tiles are dead: the softmax loop ended with a barrier
-    static_for<SCH::NPRO>([&](auto I) {
-      issue_all(LinProC<D, decltype(I)::value>{});
-    });
-
-    // The softmax sums are relative to 2^-mrun: with c_i = row maximum (Eq. 6, 8) the
-    // linear terms weigh 2^(mtru - mrun) beside them, with c = 0 they weigh 2^-mrun.
-    float lin_scale[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-      lin_scale[qb] = __builtin_amdgcn_exp2f((a.stab_mode == 1 ? 0.f : mtru[qb]) - mrun[qb]);
-
-    // per-lane byte offsets inside a W tile: block row sigma(r), k-step ks
-    const int sr = (r & 0x13) | ((r & 4) << 1) | ((r & 8) >> 1);
-    int woff[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) woff[ks] = tile_off<2 * D>(sr, 16 * ks + 8 * g);
-    // accumulator register 4i+j of lane half g is block row 8i+4g+j, which after
-    // the row permutation is unit 16(i>>1) + 8g + 4(i&1) + j of the block
-    auto unit_of = [&](int i) { return 16 * (i >> 1) + 8 * g + 4 * (i & 1); };
-
-    bf16x8 Ub[QB][HID / 16];  // U^T = relu(W1 Q^T + b1) as B operands, natural k order
+    // The softmax sums are relative to 2^-ref: with c_i = row maximum (Eq. 6, 8) the
+    // linear terms weigh 2^(max - ref) beside them, with c = 0 they weigh 2^-ref.
+    const float lin_scale = __builtin_amdgcn_exp2f((a.stab_mode == 1 ? 0.f : rows.max) - rows.ref);
+    const int wbase = lin_row_base<D>(lane), sbase = tile_off<128>(r, 8 * g);
+    bf16x8 Ub[HID / 16];  // U^T = relu(W1 Q^T + b1) as B operands, natural k order
     static_for<NW1 + NPB>([&](auto ST) {
       constexpr int st = decltype(ST)::value;
       constexpr LinStep sd = LinStepC<D, st>::value;
-      wait_loads_and_barrier<sd.younger * LPT>();
+      wait_loads_and_barrier<sd.younger * LinTiles<D, kAttnNW>::LPT>();
       issue_all(LinStepC<D, st>{});
       if (!wave_live) return;  // this step of this wave only (the lambda is one step)
       if constexpr (st < NW1) {
-        // ---- two 32-row blocks of hidden units ------------------------------------
-        const char* Ws = buf(std::integral_constant<int, sd.buf_w>{});
-#pragma unroll
-        for (int hb2 = 0; hb2 < 2; ++hb2) {
-          const int hb = 2 * st + hb2;
-          f32x16 acc[QB];
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            f32x4 bias = *reinterpret_cast<const f32x4*>(sb1 + 32 * hb + unit_of(i));
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-              for (int qb = 0; qb < QB; ++qb) acc[qb][4 * i + j] = bias[j];
-          }
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks) {
-            bf16x8 wf = *reinterpret_cast<const bf16x8*>(Ws + hb2 * (32 * 2 * D) + woff[ks]);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) acc[qb] = mfma(wf, Qr[qb][ks], acc[qb]);
-          }
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb) {
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc[qb][e] = fmaxf(acc[qb][e], 0.f);
-            Ub[qb][2 * hb + 0] = acc_to_operand(acc[qb], 0);
-            Ub[qb][2 * hb + 1] = acc_to_operand(acc[qb], 1);
-          }
-        }
+        lin_hidden<D, 2>(tiles + sd.buf_w * TB, wbase, sb1 + 64 * st, g, Qr, Ub + 4 * st);
       } else {
-        // ---- 32 features: psi^T = relu(W2 U^T + b2), phi, read-out ------------------
-        const int pb = st - NW1;
-        const char* Ws = buf(std::integral_constant<int, sd.buf_w>{});
-        const char* Ss = buf(std::integral_constant<int, sd.buf_s>{});
-        f32x16 acc[QB];
-        float zv[16];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          f32x4 bias = *reinterpret_cast<const f32x4*>(sb2 + 32 * pb + unit_of(i));
-          f32x4 zz = *reinterpret_cast<const f32x4*>(sz + 32 * pb + unit_of(i));
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) acc[qb][4 * i + j] = bias[j];
-            zv[4 * i + j] = zz[j];
-          }
-        }
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks) {
-            bf16x8 wf = *reinterpret_cast<const bf16x8*>(Ws + half * (32 * 2 * D) + woff[ks]);
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) acc[qb] = mfma(wf, Ub[qb][half * KS + ks], acc[qb]);
-          }
-        }
-        const bool squared = (32 * pb >= DP / 2);
-        bf16x8 Fb[QB][2];
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-          float part = 0.f;
-#pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            float x = fmaxf(acc[qb][e], 0.f);
-            if (squared) x = x * x;
-            // the read-out below rounds x to bf16 (MFMA operand); the normaliser takes it
-            // unrounded: the 256 rounding errors of a row have random signs and relative size
-            // 2^-9, far below the bar on n^L, and the rounding costs two instructions per feature
-            x = x * lin_scale[qb];
-            acc[qb][e] = x;
-            part += x * zv[e];
-          }
-          nL[qb] += part;
-          Fb[qb][0] = acc_to_operand(acc[qb], 0);
-          Fb[qb][1] = acc_to_operand(acc[qb], 1);
-        }
-        // S tile: rows d, 64 columns = two feature blocks; this block's 32 columns
-        // start at 32(pb&1), k-step sidx of it is chunk 4(pb&1) + 2 sidx + g
-#pragma unroll
-        for (int sidx = 0; sidx < 2; ++sidx) {
-#pragma unroll
-          for (int db = 0; db < DB; ++db) {
-            const int row = 32 * db + r;
-            const int c = (4 * (pb & 1) + 2 * sidx) | g;
-            bf16x8 sf = *reinterpret_cast<const bf16x8*>(Ss + row * 128 + ((c ^ swz<128>(row)) << 4));
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb) O[db][qb] = mfma(sf, Fb[qb][sidx], O[db][qb]);
-          }
-        }
+        constexpr int pb = st - NW1;
+        nL += lin_features<D, (32 * pb >= DP / 2)>(tiles + sd.buf_w * TB, tiles + sd.buf_s * TB, wbase, sbase, pb & 1,
+                                                   sb2 + 32 * pb, sz + 32 * pb, g, lin_scale, Ub, rows.O);
       }
     });
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) nL[qb] = half_swap_sum(nL[qb]);
+    nL = half_swap_sum(nL);
   }
 
   // =========================== merge (Eq. 5) ================================
+  if (row >= cr.q_hi) return;
+  const int64_t o = (int64_t)bh * N + row;
+  if (g == 0 && a.dbg_nL) a.dbg_nL[o] = nL * dscale;
+  const float inv = 1.0f / (nS + nL);
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int64_t row = qw0 + 32 * qb + r;
-    if (row >= cr.q_hi) continue;
-    const int64_t o = (int64_t)bh * N + row;
-    if (g == 0 && a.dbg_nL) a.dbg_nL[o] = nL[qb] * dscale[qb];
-    const float inv = 1.0f / (nS[qb] + nL[qb]);
+  for (int db = 0; db < DB; ++db) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
+    for (int i = 0; i < 4; ++i) {
+      const int col = 32 * db + 8 * i + 4 * g;
+      if (a.dbg_aL) {
+        f32x4 as = {0.f, 0.f, 0.f, 0.f};
+        if (a.dbg_aS) as = *reinterpret_cast<const f32x4*>(a.dbg_aS + o * D + col);
+        f32x4 x;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int col = 32 * db + 8 * i + 4 * g;
-        if (a.dbg_aL) {
-          f32x4 as = {0.f, 0.f, 0.f, 0.f};
-          if (a.dbg_aS) as = *reinterpret_cast<const f32x4*>(a.dbg_aS + o * D + col);
-          const float ds = dscale[qb];
-          f32x4 x;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            // the product is rounded as it was when a^S was stored (no fused multiply-subtract),
-            // so an empty linear set reports exactly zero
-            float t = O[db][qb][4 * i + j] * ds;
-            asm volatile("" : "+v"(t));
-            x[j] = t - as[j];
-          }
-          *reinterpret_cast<f32x4*>(a.dbg_aL + o * D + col) = x;
+        for (int j = 0; j < 4; ++j) {
+          // the product is rounded as it was when a^S was stored (no fused multiply-subtract),
+          // so an empty linear set reports exactly zero
+          float t = rows.O[db][4 * i + j] * dscale;
+          asm volatile("" : "+v"(t));
+          x[j] = t - as[j];
         }
-        u32x2 pk;
-        pk[0] = pack_bf16(O[db][qb][4 * i] * inv, O[db][qb][4 * i + 1] * inv);
-        pk[1] = pack_bf16(O[db][qb][4 * i + 2] * inv, O[db][qb][4 * i + 3] * inv);
-        *reinterpret_cast<u32x2*>(Og + row * D + col) = pk;
+        *reinterpret_cast<f32x4*>(a.dbg_aL + o * D + col) = x;
       }
+      u32x2 pk;
+      pk[0] = pack_bf16(rows.O[db][4 * i] * inv, rows.O[db][4 * i + 1] * inv);
+      pk[1] = pack_bf16(rows.O[db][4 * i + 2] * inv, rows.O[db][4 * i + 3] * inv);
+      *reinterpret_cast<u32x2*>(Og + row * D + col) = pk;
     }
   }
 }
@@ -745,33 +800,28 @@ attn_kernel(AttnArgs a) {
 // phase L; the two numerators and normalisers are brought to one reference after phase S and
 // added through LDS at the end.
 //
-// What bounds it: as attn_kernel (per-wave chains of score products, exponentials and numerator
-// products), but a launch of at most 256 attn_kernel workgroups leaves one wave on a SIMD, which
-// runs a tile in nearly the cycles in which two waves run two (2,650 and 2,930).  Here every SIMD
-// that has work has two waves, each with half of the tiles, at the price of the meeting and of a
-// lower clock: 0.82 us per key tile and workgroup instead of 1.02
-// (streaming step at the 480p shape with T_o = 1, 156 items: 59.6 instead of 67.4 us without the
-// state update).  0.14 of the 0.82 us goes away with the tile loads: tiles are requested three
-// half-steps ahead because one trip ahead, in lockstep, took 0.89 us.
+// What bounds it: the same loop as attn_kernel, but a launch of at most 256 attn_kernel workgroups
+// leaves one wave on a SIMD, whose instruction stream alone does not fill it.  Here every SIMD that
+// has work has two waves, each with half of the tiles, at the price of the meeting and of a lower
+// clock (streaming step at the 480p shape with T_o = 1, 156 items: 52 us, 38 of them for 25 trips
+// of two tiles, 3.9 before the first and 9.7 after the last).
 // 128 KB of tile buffers (K and V of two tiles per group): one workgroup per CU, which is why
 // attn_kernel stays the better one as soon as its own launch fills the chip (attn_splits).
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(512, 2)
 attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
-  using C = AttnShape<D, 1, 4>;
+  using C = AttnShape<D>;
   constexpr int HID = C::HID, DP = C::DP, KS = C::KS, DB = C::DB;
   constexpr int TB = C::TILE_BYTES;
   constexpr int NT = 512;
   constexpr int GB = 4 * TB;             // tile buffers of one group: K 0/1, V 0/1
-  constexpr int L4 = TB / (1024 * 4);    // direct loads per wave per tile moved by one group
-  constexpr int L8 = TB / (1024 * 8);    // direct loads per wave per tile moved by all eight waves
   using SL = StateLds<D>;
   __shared__ __attribute__((aligned(1024))) char tiles[2 * GB > SL::XV + SL::US ? 2 * GB : SL::XV + SL::US];
   __shared__ __attribute__((aligned(256))) float sb1[HID];
   __shared__ __attribute__((aligned(16))) float sb2[DP];
   __shared__ __attribute__((aligned(16))) float sz[DP];
-  __shared__ float xref[2][C::QT], xmax[2][C::QT], xsum[2][C::QT], xlin[2][C::QT];
+  __shared__ float xref[2][kQueryTile], xmax[2][kQueryTile], xsum[2][kQueryTile], xlin[2][kQueryTile];
 
   // streaming step: the workgroups beyond the attention items absorb the tokens that leave the
   // window (pieces of the chunk-state increment) on CUs that the attention items leave free
@@ -794,7 +844,7 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   if (!attn_item(a, bh, tc, qt)) return;
   const int h = bh % a.H;
   const ChunkRange cr = attn_range(a, a.chunk0 + tc);
-  const int64_t q0 = cr.q_lo + (int64_t)qt * C::QT;
+  const int64_t q0 = cr.q_lo + (int64_t)qt * kQueryTile;
   if (q0 >= cr.q_hi) return;   // as in attn_kernel
   const int64_t N = (int64_t)a.T * a.HW;
   const bf16_t* Qg = a.q + (int64_t)bh * a.q_bh_stride;
@@ -805,49 +855,26 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
 
   const int64_t row = q0 + 32 * qg + r;            // this lane's query
   const bool wave_live = q0 + 32 * qg < cr.q_hi;   // else: moves tiles and meets barriers only
-  bf16x8 Qr[1][KS];
+  bf16x8 Qr[KS];
   {
     const bf16_t* p = Qg + (row < cr.q_hi ? row : cr.q_hi - 1) * D + 8 * g;
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) Qr[0][ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
+    for (int ks = 0; ks < KS; ++ks) Qr[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
   }
-  f32x16 O[DB][1];
+  SoftmaxRows<D> rows;
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) O[db][0][e] = 0.f;
-  float mrun[1] = {kLowest}, mtru[1] = {-INFINITY}, lrun[1] = {0.f};
+  for (int db = 0; db < DB; ++db) rows.O[db] = f32x16{};
+  rows.ref = kLowest;
+  rows.max = -INFINITY;
+  rows.sum = 0.f;
 
   // =========================== phase S =====================================
   {
-    FragOffsets<D> fo = make_frag_offsets<D>(lane);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) fo.k[ks] += kg * GB;
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      fo.v_lo[db] += kg * GB;
-      fo.v_hi[db] += kg * GB;
-    }
-    const int n_full = (int)((cr.s_hi - cr.s_lo) / 64);
-    const int rem = (int)((cr.s_hi - cr.s_lo) - 64 * (int64_t)n_full);
-    const int n_tiles = n_full + (rem > 0 ? 1 : 0);
-    const int trips = (n_tiles + 1) / 2;
-    const u32x4 Kr = make_rsrc_words(Kg + cr.s_lo * D), Vr = make_rsrc_words(Vg + cr.s_lo * D);
-    const uint32_t group_lds = __builtin_amdgcn_readfirstlane(lds_address(tiles) + kg * GB);
-    const int voff_full = tile_voff_full<2 * D, 4>(qg, lane);
-    // This group's K or V tile of trip j into the buffer of the trip's parity.  Past the end the
-    // last tile is moved again (never read), so that every wave always has the same number of
-    // loads behind the one it waits for.
-    auto load = [&](u32x4 rsrc, int j, int which) {
-      const int want = 2 * j + kg, it = want < n_tiles ? want : n_tiles - 1;
-      tile_load_fast<2 * D, TB, 4>(rsrc, __builtin_amdgcn_readfirstlane(it * TB), group_lds + (which + (j & 1)) * TB, qg,
-                                   lane, it < n_full ? 64 : rem, voff_full);
-    };
-    auto load_k = [&](int j) { load(Kr, j, 0); };
-    auto load_v = [&](int j) { load(Vr, j, 2); };
-    load_k(0);
-    load_v(0);
-    load_k(1);
+    const int n_keys = (int)(cr.s_hi - cr.s_lo), n_tiles = (n_keys + 63) / 64;
+    const SoftmaxTiles<D> st{make_rsrc_words(Kg + cr.s_lo * D), make_rsrc_words(Vg + cr.s_lo * D),
+                             (uint32_t)__builtin_amdgcn_readfirstlane(lds_address(tiles) + kg * GB + qg * 1024), tiles + kg * GB, n_keys, kg, 2,
+                             (n_tiles + 1 - kg) / 2, qg, lane, tile_voff_full<2 * D, 4>(qg, lane) + qg * 1024};
+    st.request();
     if (has_linear) {
       const float* zt = a.state_z + ((int64_t)bh * a.state_slots + tc) * DP;
       for (int i = tid; i < HID; i += NT) sb1[i] = a.b1_q[(int64_t)h * HID + i];
@@ -856,41 +883,16 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
         sz[i] = zt[i];
       }
     }
-    settle(Qr[0]);
+    settle(Qr);
     wait_loads_and_barrier<0>();   // also publishes the bias vectors
-    auto k_tile = [&](int j) -> const char* { return tiles + (j & 1) * TB; };
-    auto v_tile = [&](int j) -> const char* { return tiles + (2 + (j & 1)) * TB; };
-    // A trip has two half-steps, scores and weights, each ended by a barrier; group 1 runs one
-    // half-step behind, so that the two waves of a SIMD are in different ones.  A buffer is
-    // refilled as soon as the half-step that read it is over: every tile is requested three
-    // half-steps ahead, and two younger tiles may be in flight when it has to be there.
-    f32x16 E[2][1];
-    bf16x8 vf[2][DB];
-    if (kg == 1) lds_barrier();
-    for (int j = 0; j + 1 < trips; ++j) {   // every tile of the trips before the last one is full
-      load_v(j + 1);
-      if (wave_live) softmax_scores<D, 1>(k_tile(j), fo, Qr, E, [] {});
-      wait_loads_and_barrier<2 * L4>();
-      load_k(j + 2);
-      if (wave_live) {
-        read_v_step<D>(v_tile(j), fo, 0, vf[0]);
-        softmax_weights<D, 1, false>(v_tile(j), fo, E, vf, O, mrun, mtru, lrun, a.scale_log2e, 64, lane);
-      }
-      wait_loads_and_barrier<2 * L4>();
+    int met = 0;
+    if (st.n > 0) {
+      if (wave_live) st.template run<true>(Qr, rows, a.scale_log2e);
+      else st.template run<false>(Qr, rows, a.scale_log2e);
+      met = st.n + 1;
     }
-    {
-      const int j = trips - 1, it = 2 * j + kg;   // a full tile, the ragged one, or none
-      const bool work = wave_live && it < n_tiles;
-      if (work) softmax_scores<D, 1>(k_tile(j), fo, Qr, E, [] {});
-      wait_loads_and_barrier<0>();
-      if (work) {
-        read_v_step<D>(v_tile(j), fo, 0, vf[0]);
-        softmax_weights<D, 1, true>(v_tile(j), fo, E, vf, O, mrun, mtru, lrun, a.scale_log2e,
-                                    it < n_full ? 64 : rem, lane);
-      }
-    }
+    for (; met < (n_tiles + 1) / 2 + 1; ++met) lds_barrier();   // group 1 may have a tile less, or none
     lds_barrier();
-    if (kg == 0) lds_barrier();
   }
 
   // Phase L streams through the eight tile buffers: W1 tiles into 0 .. NW1-1, then sets of two
@@ -898,58 +900,30 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   // 4, 5, 6 and 0, 1, 2.  Tile kinds as in LinStep.
   constexpr int NW1 = HID / 64, NP = DP / 64;
   static_assert(NW1 <= 4, "the W1 tiles and the first set share the eight buffers");
-  const uint32_t tiles_lds = lds_address(tiles);
-  const u32x4 W1r = make_rsrc_words(a.w1_q + (int64_t)h * HID * D), W2r = make_rsrc_words(a.w2_q + (int64_t)h * DP * HID),
-              Str = make_rsrc_words(a.state_s + ((int64_t)bh * a.state_slots + tc) * (int64_t)D * DP);
-  constexpr int RPB = 1024 / (2 * D);   // rows of W1 / W2 tiles per 1 KB block
-  auto issue_w1 = [&](int idx, int buf) {
-    const int voff = tile_voff_full<2 * D, 8>(wave, lane);
-#pragma unroll
-    for (int n = 0; n < L8; ++n) {
-      const int blk = wave + 8 * n;
-      direct_load_16(W1r, voff, idx * TB + blk * 1024, tiles_lds + buf * TB + blk * 1024);
-    }
-  };
-  auto issue_w2 = [&](int pb, int buf) {   // rows 32pb ..: first k-half in tile rows 0..31, second in 32..63
-    constexpr int CPR = 2 * D / 16;
-    const int jr = lane / CPR;
-    const int voff = jr * (4 * D) + (((lane % CPR) ^ swz<2 * D>(wave * RPB + jr)) << 4);
-#pragma unroll
-    for (int n = 0; n < L8; ++n) {
-      const int blk = wave + 8 * n, R = blk * RPB;
-      direct_load_16(W2r, voff, pb * 32 * (4 * D) + (R & 31) * (4 * D) + (R >> 5) * (2 * D),
-                     tiles_lds + buf * TB + blk * 1024);
-    }
-  };
-  auto issue_s = [&](int pp, int buf) {    // S_t^T columns 64pp .. of all D rows
-    const int jr = lane >> 3;
-    const int voff = jr * (4 * D) + (((lane & 7) ^ swz<128>(wave * 8 + jr)) << 4);
-#pragma unroll
-    for (int n = 0; n < L8; ++n) {
-      const int blk = wave + 8 * n;
-      direct_load_16(Str, voff, pp * 128 + blk * 8 * (4 * D), tiles_lds + buf * TB + blk * 1024);
-    }
-  };
+  const LinTiles<D, 8> lt{make_rsrc_words(a.w1_q + (int64_t)h * HID * D), make_rsrc_words(a.w2_q + (int64_t)h * DP * HID),
+                          make_rsrc_words(a.state_s + ((int64_t)bh * a.state_slots + tc) * (int64_t)D * DP),
+                          lds_address(tiles), wave, lane};
+  constexpr int L8 = LinTiles<D, 8>::LPT;
   auto issue_set = [&](int p) {
     const int b = (p & 1) ? 0 : 4;
-    issue_w2(2 * p, b);
-    issue_w2(2 * p + 1, b + 1);
-    issue_s(p, b + 2);
+    lt.issue(kW2, 2 * p, b);
+    lt.issue(kW2, 2 * p + 1, b + 1);
+    lt.issue(kS, p, b + 2);
   };
   const bool dbg_soft = a.dbg_m || a.dbg_nS || a.dbg_aS;
   auto prologue = [&]() {
 #pragma unroll
-    for (int i = 0; i < NW1; ++i) issue_w1(i, i);
+    for (int i = 0; i < NW1; ++i) lt.issue(kW1, i, i);
     issue_set(0);
   };
   if (has_linear && !dbg_soft) prologue();
 
   // ---- one reference for both groups -------------------------------------------------
   {
-    const float part = half_swap_sum(lrun[0]);
+    const float part = half_swap_sum(rows.sum);
     if (g == 0) {
-      xref[kg][32 * qg + r] = mrun[0];
-      xmax[kg][32 * qg + r] = mtru[0];
+      xref[kg][32 * qg + r] = rows.ref;
+      xmax[kg][32 * qg + r] = rows.max;
       xsum[kg][32 * qg + r] = part;
     }
   }
@@ -958,21 +932,21 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   {
     const float r0 = xref[0][32 * qg + r], r1 = xref[1][32 * qg + r];
     const float mref = fmaxf(r0, r1);
-    mtru[0] = fmaxf(xmax[0][32 * qg + r], xmax[1][32 * qg + r]);
+    rows.max = fmaxf(xmax[0][32 * qg + r], xmax[1][32 * qg + r]);
     nS = xsum[0][32 * qg + r] * __builtin_amdgcn_exp2f(r0 - mref) +
          xsum[1][32 * qg + r] * __builtin_amdgcn_exp2f(r1 - mref);
-    const float f = __builtin_amdgcn_exp2f(mrun[0] - mref);
-    mrun[0] = mref;
+    const float f = __builtin_amdgcn_exp2f(rows.ref - mref);
+    rows.ref = mref;
 #pragma unroll
     for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) O[db][0][e] *= f;
-    dscale = __builtin_amdgcn_exp2f(mrun[0] - mtru[0]);
+      for (int e = 0; e < 16; ++e) rows.O[db][e] *= f;
+    dscale = __builtin_amdgcn_exp2f(rows.ref - rows.max);
   }
   // numerator registers 4i .. 4i+3 of feature block db, exchanged at 16 bytes per lane
   auto slot = [&](int q, int n) { return reinterpret_cast<f32x4*>(tiles + (q * (4 * DB) + n) * 1024 + lane * 16); };
   auto quad = [&](int db, int i) {
-    f32x4 x = {O[db][0][4 * i], O[db][0][4 * i + 1], O[db][0][4 * i + 2], O[db][0][4 * i + 3]};
+    f32x4 x = {rows.O[db][4 * i], rows.O[db][4 * i + 1], rows.O[db][4 * i + 2], rows.O[db][4 * i + 3]};
     return x;
   };
   if (dbg_soft) {   // component outputs: the two softmax parts are added for them alone
@@ -986,7 +960,7 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
     if (kg == 0 && row < cr.q_hi) {
       const int64_t o = (int64_t)bh * N + row;
       if (g == 0) {
-        if (a.dbg_m) a.dbg_m[o] = mtru[0] * 0.6931471805599453f;   // back from base 2
+        if (a.dbg_m) a.dbg_m[o] = rows.max * 0.6931471805599453f;   // back from base 2
         if (a.dbg_nS) a.dbg_nS[o] = nS * dscale;
       }
       if (a.dbg_aS) {
@@ -1007,80 +981,19 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   // =========================== phase L =====================================
   float nL = 0.f;
   if (has_linear) {
-    const float lin_scale = __builtin_amdgcn_exp2f((a.stab_mode == 1 ? 0.f : mtru[0]) - mrun[0]);
-    const int sr = (r & 0x13) | ((r & 4) << 1) | ((r & 8) >> 1);
-    int woff[KS];
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) woff[ks] = tile_off<2 * D>(sr, 16 * ks + 8 * g);
-    auto unit_of = [&](int i) { return 16 * (i >> 1) + 8 * g + 4 * (i & 1); };
+    const float lin_scale = __builtin_amdgcn_exp2f((a.stab_mode == 1 ? 0.f : rows.max) - rows.ref);
+    const int wbase = lin_row_base<D>(lane), sbase = tile_off<128>(r, 8 * g);
     bf16x8 Ub[HID / 16];
     wait_loads_and_barrier<3 * L8>();   // W1 has landed, the first set may be in flight
-    if (wave_live) {
-#pragma unroll
-      for (int hb = 0; hb < HID / 32; ++hb) {
-        f32x16 acc;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const f32x4 bias = *reinterpret_cast<const f32x4*>(sb1 + 32 * hb + unit_of(i));
-#pragma unroll
-          for (int jj = 0; jj < 4; ++jj) acc[4 * i + jj] = bias[jj];
-        }
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          acc = mfma(*reinterpret_cast<const bf16x8*>(tiles + hb * (32 * 2 * D) + woff[ks]), Qr[0][ks], acc);
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[e] = fmaxf(acc[e], 0.f);
-        Ub[2 * hb] = acc_to_operand(acc, 0);
-        Ub[2 * hb + 1] = acc_to_operand(acc, 1);
-      }
-    }
+    if (wave_live) lin_hidden<D, HID / 32>(tiles, wbase, sb1, g, Qr, Ub);
     static_for<NP>([&](auto PC) {
-      constexpr int p = decltype(PC)::value;
+      constexpr int p = decltype(PC)::value, base = (p & 1) ? 0 : 4;
       wait_loads_and_barrier<0>();      // set p has landed; everyone is done with the other buffers
       if constexpr (p + 1 < NP) issue_set(p + 1);
       if (!wave_live) return;
-      constexpr int base = (p & 1) ? 0 : 4;
-      const char* const Ws = tiles + base * TB + kg * TB;
-      const char* const Ss = tiles + (base + 2) * TB;
       const int pb = 2 * p + kg;
-      f32x16 acc;
-      float zv[16];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const f32x4 bias = *reinterpret_cast<const f32x4*>(sb2 + 32 * pb + unit_of(i));
-        const f32x4 zz = *reinterpret_cast<const f32x4*>(sz + 32 * pb + unit_of(i));
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-          acc[4 * i + jj] = bias[jj];
-          zv[4 * i + jj] = zz[jj];
-        }
-      }
-#pragma unroll
-      for (int half = 0; half < 2; ++half)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-          acc = mfma(*reinterpret_cast<const bf16x8*>(Ws + half * (32 * 2 * D) + woff[ks]), Ub[half * KS + ks], acc);
-      constexpr bool squared = (64 * p >= DP / 2);
-      float part = 0.f;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        float x = fmaxf(acc[e], 0.f);
-        if (squared) x = x * x;
-        x = x * lin_scale;   // unrounded in the normaliser, as in attn_kernel
-        acc[e] = x;
-        part += x * zv[e];
-      }
-      nL += part;
-#pragma unroll
-      for (int sidx = 0; sidx < 2; ++sidx) {
-        const bf16x8 fb = acc_to_operand(acc, sidx);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const int rw = 32 * db + r;
-          const int c = (4 * kg + 2 * sidx) | g;
-          O[db][0] = mfma(*reinterpret_cast<const bf16x8*>(Ss + rw * 128 + ((c ^ swz<128>(rw)) << 4)), fb, O[db][0]);
-        }
-      }
+      nL += lin_features<D, (64 * p >= DP / 2)>(tiles + (base + kg) * TB, tiles + (base + 2) * TB, wbase, sbase, kg,
+                                                sb2 + 32 * pb, sz + 32 * pb, g, lin_scale, Ub, rows.O);
     });
     nL = half_swap_sum(nL);
     lds_barrier();   // the last set has been read
@@ -1143,12 +1056,12 @@ bool attn_splits(int64_t n_items, int64_t n_keys, int d, bool read_out) {
   return read_out ? n_keys >= (d == 128 ? 448 : 1536) : n_keys >= (d == 128 ? 1536 : 2560);
 }
 
-int attn_query_tile(int d) { return AttnShape<128, kAttnQB, kAttnNW>::QT; }
+int attn_query_tile(int) { return kQueryTile; }
 
 const char* attn_kernel_name(int d) {
   static char name[2][48];
   char* n = name[d == 128 ? 0 : 1];
-  snprintf(n, sizeof(name[0]), "attn_kernel<%d, %d, %d>", d == 128 ? 128 : 64, kAttnQB, kAttnNW);
+  snprintf(n, sizeof(name[0]), "attn_kernel<%d>", d == 128 ? 128 : 64);
   return n;
 }
 
@@ -1161,9 +1074,9 @@ hipError_t launch_attn(const AttnArgs& a, const StateArgs* absorb, int d, bool s
     if (d == 128) hipLaunchKernelGGL(attn_split_kernel<128>, dim3(blocks), dim3(512), 0, stream, a, s, grid);
     else hipLaunchKernelGGL(attn_split_kernel<64>, dim3(blocks), dim3(512), 0, stream, a, s, grid);
   } else if (d == 128) {
-    hipLaunchKernelGGL((attn_kernel<128, kAttnQB, kAttnNW>), dim3(grid), dim3(64 * kAttnNW), 0, stream, a);
+    hipLaunchKernelGGL(attn_kernel<128>, dim3(grid), dim3(64 * kAttnNW), 0, stream, a);
   } else {
-    hipLaunchKernelGGL((attn_kernel<64, kAttnQB, kAttnNW>), dim3(grid), dim3(64 * kAttnNW), 0, stream, a);
+    hipLaunchKernelGGL(attn_kernel<64>, dim3(grid), dim3(64 * kAttnNW), 0, stream, a);
   }
   return hipGetLastError();
 }
