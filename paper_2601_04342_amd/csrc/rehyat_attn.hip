@@ -262,47 +262,25 @@ __device__ __forceinline__ void softmax_last(const char* Vc, const FragBase& fo,
 
 // The softmax part over a wave's key tiles 0 .. n-1 (tile t of it is tile first_tile + t * stride
 // of the window): four waves share K in buffers 0/1 and V in 2/3 of `tiles`, picked by the parity of
-// t.  Meets n + 1 barriers.  A ragged last tile holds the last 64 keys of the window, those of
-// the tile before it left out by softmax_last; only a window of fewer than 64 keys re-reads its
-// last row.  Waves that are not live move their share of the tiles and compute nothing.
+// t.  Meets n + 1 barriers.  Waves that are not live move their share of the tiles and compute nothing.
 template <int D>
 struct SoftmaxTiles {
-  static constexpr int TB = 64 * D * 2;
-  static constexpr int LPT = TB / (1024 * 4);
+  using R = RangeTiles<2 * D, 4>;
+  static constexpr int TB = R::TB, LPT = R::LPT;
   u32x4 K, V;
-  uint32_t lds;        // address of the four buffers, of the wave's first block in them
+  uint32_t lds;        // address of the four buffers
   const char* tiles;
-  int n_keys, first_tile, stride, n;
-  int wave, lane, voff;
+  R range;             // the window
+  int first_tile, stride, n;
+  int lane;
 
-  __device__ __forceinline__ int soff(int t) const {   // byte offset of tile t in the window
-    const int row = 64 * (first_tile + t * stride), last = n_keys - 64;
-    return __builtin_amdgcn_readfirstlane((row < last ? row : last) * (2 * D));
-  }
-  // block i of the wave's share of a tile at `so` (bytes) into the buffer at `dst` (its first block)
-  template <int I>
-  __device__ __forceinline__ void load(u32x4 rsrc, int so, uint32_t dst) const {
-    int tmp;
-    asm volatile("s_add_i32 m0, %1, %5\n\ts_add_i32 %0, %4, %5\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds"
-                 : "=&s"(tmp)
-                 : "s"(dst), "v"(voff), "s"(rsrc), "s"(so), "n"(4096 * I)
-                 : "memory", "scc");
-  }
-  __device__ __forceinline__ void load_first(u32x4 rsrc, int t, int buf) const {   // before the loop
-    if (n_keys < 64) {
-      tile_load_asm<2 * D, TB, 4>(rsrc, 0, lds + buf * TB - wave * 1024, wave, lane, n_keys);
-      return;
-    }
-    const int so = soff(t);
-    const uint32_t dst = lds + buf * TB;
-    static_for<LPT>([&](auto IC) { load<decltype(IC)::value>(rsrc, so, dst); });
-  }
+  __device__ __forceinline__ int row(int t) const { return 64 * (first_tile + t * stride); }
   __device__ __forceinline__ void request() const {   // what has to be there before run()
     if (n > 0) {
-      load_first(K, 0, 0);
-      load_first(V, 0, 2);
+      range.fill(K, row(0), lds);
+      range.fill(V, row(0), lds + 2 * TB);
     }
-    if (n > 1) load_first(K, 1, 1);
+    if (n > 1) range.fill(K, row(1), lds + TB);
   }
   template <bool LIVE>
   __device__ __forceinline__ void run(const bf16x8 (&Qr)[D / 16], SoftmaxRows<D>& rows, float sc) const {
@@ -318,19 +296,16 @@ struct SoftmaxTiles {
       });
     }
     lds_barrier();
-    if (n > 2) load_first(K, 2, 0);
+    if (n > 2) range.fill(K, row(2), lds);
     auto trip = [&](int t, const char* Kn, const char* Kn2, const char* Vc, int kbuf, int vbuf, f32x16 (&E)[2],
                     f32x16 (&En)[2]) {
-      // past the last tile the descriptor is empty and nothing is fetched: a branch around each
-      // load would let the compiler move vector work out of its slot
-      u32x4 Kd = K;
-      Kd[2] = t + 3 < n ? K[2] : 0u;
-      const int ks = soff(t + 3), vs = soff(t + 1);
+      const u32x4 Kd = rsrc_if(K, t + 3 < n);
+      const int ks = range.soff(row(t + 3)), vs = range.soff(row(t + 1));
       const uint32_t kd = lds + kbuf * TB, vd = lds + vbuf * TB;
       auto issue = [&](auto IC) {
         constexpr int i = decltype(IC)::value;
-        if constexpr (i < LPT) load<i>(Kd, ks, kd);
-        else load<i - LPT>(V, vs, vd);
+        if constexpr (i < LPT) range.template load<i>(Kd, ks, kd);
+        else range.template load<i - LPT>(V, vs, vd);
       };
       if constexpr (LIVE) {
         softmax_trip<D, LPT>(Kn, Kn2, Vc, fo, Qr, E, En, fr, rows, sc, issue);
@@ -356,8 +331,7 @@ struct SoftmaxTiles {
     }
     wait_loads_and_barrier<0>();
     if constexpr (LIVE) {
-      const int row = 64 * (first_tile + t * stride), over = row + 64 - n_keys;   // keys short of a full tile
-      softmax_last<D>(Vl, fo, E0, rows, sc, over > 0 && n_keys >= 64 ? over : 0, over > 0 ? 64 - over : 64, lane);
+      softmax_last<D>(Vl, fo, E0, rows, sc, range.first(row(t)), range.count(row(t)), lane);
     }
   }
 };
@@ -675,9 +649,8 @@ attn_kernel(AttnArgs a) {
   // =========================== phase S =====================================
   {
     const int n_keys = (int)(cr.s_hi - cr.s_lo);
-    const SoftmaxTiles<D> st{make_rsrc_words(Kg + cr.s_lo * D), make_rsrc_words(Vg + cr.s_lo * D), lds_address(tiles) + wave * 1024,
-                             tiles, n_keys, 0, 1, (n_keys + 63) / 64, wave, lane,
-                             tile_voff_full<2 * D, 4>(wave, lane) + wave * 1024};
+    const SoftmaxTiles<D> st{make_rsrc_words(Kg + cr.s_lo * D), make_rsrc_words(Vg + cr.s_lo * D), lds_address(tiles),
+                             tiles, RangeTiles<2 * D, 4>(n_keys, wave, lane), 0, 1, (n_keys + 63) / 64, lane};
     st.request();
     // per-head vectors of phase L (their loads complete long before phase L, whose
     // counted waits must see tile loads only)
@@ -872,8 +845,8 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   {
     const int n_keys = (int)(cr.s_hi - cr.s_lo), n_tiles = (n_keys + 63) / 64;
     const SoftmaxTiles<D> st{make_rsrc_words(Kg + cr.s_lo * D), make_rsrc_words(Vg + cr.s_lo * D),
-                             (uint32_t)__builtin_amdgcn_readfirstlane(lds_address(tiles) + kg * GB + qg * 1024), tiles + kg * GB, n_keys, kg, 2,
-                             (n_tiles + 1 - kg) / 2, qg, lane, tile_voff_full<2 * D, 4>(qg, lane) + qg * 1024};
+                             (uint32_t)__builtin_amdgcn_readfirstlane(lds_address(tiles) + kg * GB), tiles + kg * GB,
+                             RangeTiles<2 * D, 4>(n_keys, qg, lane), kg, 2, (n_tiles + 1 - kg) / 2, lane};
     st.request();
     if (has_linear) {
       const float* zt = a.state_z + ((int64_t)bh * a.state_slots + tc) * DP;

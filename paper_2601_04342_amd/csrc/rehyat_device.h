@@ -100,23 +100,17 @@ __device__ __forceinline__ bf16x8 acc_to_operand(const f32x16& c, int s) {
   return __builtin_bit_cast(bf16x8, p);
 }
 
-// c + the eight elements of an operand, in fp32.  DOT: as products with 1, one instruction for two
-// elements; it rounds each pair once (2^20 draws: at most 9.9e-8 of the sum off, two fp32 additions
-// 1.2e-7) and keeps denormals.  Otherwise each element is unpacked and added.
+// c + the two bf16 elements of a word, in fp32.  DOT: as products with 1, one instruction; it rounds
+// the pair once (2^20 draws: at most 9.9e-8 of the sum off, two fp32 additions 1.2e-7) and keeps
+// denormals.  Otherwise each element is unpacked and added.
 template <bool DOT>
-__device__ __forceinline__ float sum_operand(bf16x8 x, float c) {
-  const u32x4 w = __builtin_bit_cast(u32x4, x);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t pair = w[i];   // by value: a bit cast of w[i] itself reads element 0 each time
-    if (DOT) {
-      const bf16x2 one = __builtin_bit_cast(bf16x2, 0x3f803f80u);
-      c = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), one, c, false);
-    } else {
-      c += __builtin_bit_cast(float, pair << 16);
-      c += __builtin_bit_cast(float, pair & 0xffff0000u);
-    }
+__device__ __forceinline__ float sum_pair(uint32_t pair, float c) {
+  if (DOT) {
+    const bf16x2 one = __builtin_bit_cast(bf16x2, 0x3f803f80u);
+    return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), one, c, false);
   }
+  c += __builtin_bit_cast(float, pair << 16);
+  c += __builtin_bit_cast(float, pair & 0xffff0000u);
   return c;
 }
 
@@ -230,6 +224,16 @@ __device__ __forceinline__ void direct_load_16(u32x4 rsrc, int voff, int soff, u
                ::"s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff)
                : "memory");
 }
+// The same OFF bytes further on both sides, for the blocks of a tile: two scalar additions, of which
+// the second stands between the write of m0 and its use.
+template <int OFF>
+__device__ __forceinline__ void direct_load_16_at(u32x4 rsrc, int voff, int soff, uint32_t lds_addr) {
+  int tmp;
+  asm volatile("s_add_i32 m0, %1, %5\n\ts_add_i32 %0, %4, %5\n\tbuffer_load_dwordx4 %2, %3, %0 offen lds"
+               : "=&s"(tmp)
+               : "s"(lds_addr), "v"(voff), "s"(rsrc), "s"(soff), "n"(OFF)
+               : "memory", "scc");
+}
 // Four bytes per lane: lane i writes bytes [4 i, 4 i + 4) of the 256-byte block at lds_addr.
 __device__ __forceinline__ void direct_load_4(u32x4 rsrc, int voff, int soff, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dword %1, %2, %3 offen lds"
@@ -293,6 +297,47 @@ __device__ __forceinline__ void tile_load_fast(u32x4 rsrc, int soff, uint32_t ld
   }
 }
 
+// The tiles of 64 rows of ROWBYTES of a token range, moved by NW waves through direct_load_16_at, one
+// instruction at a time so that a kernel can spread them over its products.  A ragged last tile
+// holds the last 64 rows of the range (`first()` of them belong to the tile before it), so that every
+// load of a loop is the same; only a range of fewer than 64 rows re-reads its last row, and is moved
+// by fill() alone.
+template <int ROWBYTES, int NW>
+struct RangeTiles {
+  static constexpr int TB = 64 * ROWBYTES;
+  static constexpr int LPT = TB / (1024 * NW);   // loads per wave and tile
+  int rows, wave, lane, voff;
+
+  __device__ __forceinline__ RangeTiles(int rows, int wave, int lane)
+      : rows(rows), wave(wave), lane(lane), voff(tile_voff_full<ROWBYTES, NW>(wave, lane) + wave * 1024) {}
+  // byte offset of the tile that starts at row `row`
+  __device__ __forceinline__ int soff(int row) const {
+    return __builtin_amdgcn_readfirstlane((row < rows - 64 ? row : rows - 64) * ROWBYTES);
+  }
+  // load I of the tile at `so` into the LDS tile at `lds`
+  template <int I>
+  __device__ __forceinline__ void load(u32x4 rsrc, int so, uint32_t lds) const {
+    direct_load_16_at<1024 * NW * I>(rsrc, voff, so, lds + wave * 1024);
+  }
+  __device__ __forceinline__ void fill(u32x4 rsrc, int row, uint32_t lds) const {
+    if (rows < 64) {
+      tile_load_asm<ROWBYTES, TB, NW>(rsrc, 0, lds, wave, lane, rows);
+      return;
+    }
+    const int so = soff(row);
+    static_for<LPT>([&](auto IC) { load<decltype(IC)::value>(rsrc, so, lds); });
+  }
+  // rows [first, first + count) of the tile that starts at `row` belong to it
+  __device__ __forceinline__ int first(int row) const { return rows >= 64 && row > rows - 64 ? row + 64 - rows : 0; }
+  __device__ __forceinline__ int count(int row) const { return row > rows - 64 ? rows - row : 64; }
+};
+// The descriptor, or one that fetches nothing: a branch around loads that are spread over products
+// would let the compiler move vector work out of its place.
+__device__ __forceinline__ u32x4 rsrc_if(u32x4 rsrc, bool on) {
+  rsrc[2] = on ? rsrc[2] : 0u;
+  return rsrc;
+}
+
 // Makes the compiler wait here for the loads that filled these operands.  Without it the wait
 // goes to their first use inside the tile loop and stays there for every tile, as a count of
 // outstanding loads in which the direct loads issued as inline asm are not known: it then
@@ -303,6 +348,13 @@ __device__ __forceinline__ void settle(bf16x8 (&x)[N]) {
   for (int i = 0; i < N; ++i) asm volatile("" : "+v"(x[i]));
 }
 __device__ __forceinline__ void settle(float& x) { asm volatile("" : "+v"(x)); }
+
+// Keeps the value's computation where it stands between fenced products.  A running sum that is read
+// only at the end of a tile is otherwise computed there, and its sixteen terms stay in registers.
+template <typename T>
+__device__ __forceinline__ void pin(T& x) {
+  asm volatile("" : "+v"(x));
+}
 
 // Wait until at most N of this wave's direct loads are outstanding (and all of
 // its LDS accesses are done), then workgroup barrier.  Written as one asm block:

@@ -19,10 +19,9 @@
 // K and V tiles arrive by direct global->LDS loads (chunk-swizzled rows) into two
 // buffers each, picked by the parity of the tile: K and V are read exactly once,
 // so every tile comes from HBM.  Step t (second half of tile t, first half of
-// tile t+1) requests the K tile of t+2 and the V tile of t+1 when it begins, one
-// step before they are read.  The loads are issued through tile_load_fast (see
-// tile_load_asm: with buffers picked at run time the compiler must not see them)
-// and have landed at the barrier that begins the next step.
+// tile t+1) requests the K tile of t+2 and the V tile of t+1 when it begins; they
+// have landed at its barrier.  The loads are inline asm (with buffers picked at run time
+// the compiler must not see them, or it orders every LDS read behind all of them).
 #include "rehyat_state_body.h"
 
 namespace rehyat {

@@ -69,8 +69,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   const int64_t len = seg_hi - seg_lo;
   const int64_t lo = seg_lo + (len * sp) / a.nsplit;
   const int64_t hi = seg_lo + (len * (sp + 1)) / a.nsplit;
-  const int n_full = (int)((hi - lo) / 64);
-  const int rem = (int)((hi - lo) - 64 * (int64_t)n_full);
+  const int n_tokens = (int)(hi - lo), n_tiles = (n_tokens + 63) / 64;
 
   const char* Kb = reinterpret_cast<const char*>(a.k + (int64_t)bh * a.kv_bh_stride + lo * D);
   const char* Vb = reinterpret_cast<const char*>(a.v + (int64_t)bh * a.kv_bh_stride + lo * D);
@@ -94,20 +93,11 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
 #pragma unroll
     for (int ks = 0; ks < KS2; ++ks) w2f[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
   }
-  // tile `it` of K or V into the buffer of its parity; rows at or beyond the end of the range
-  // re-read the last valid row
+  // tile `it` of K or V goes into the buffer of its parity
   const u32x4 Kr = make_rsrc_words(Kb), Vr = make_rsrc_words(Vb);
-  const uint32_t xv_lds = lds_address(XV);
-  const int n_tiles = n_full + (rem > 0 ? 1 : 0);
-  const int voff_full = tile_voff_full<2 * D, NW>(wave, lane);
-  auto issue_k = [&](int it) {
-    tile_load_fast<2 * D, TB, NW>(Kr, __builtin_amdgcn_readfirstlane(it * TB), xv_lds + (it & 1) * TB, wave, lane,
-                                  it < n_full ? 64 : rem, voff_full);
-  };
-  auto issue_v = [&](int it) {
-    tile_load_fast<2 * D, TB, NW>(Vr, __builtin_amdgcn_readfirstlane(it * TB), xv_lds + (2 + (it & 1)) * TB, wave,
-                                  lane, it < n_full ? 64 : rem, voff_full);
-  };
+  const uint32_t k_lds = lds_address(XV), v_lds = k_lds + 2 * TB;
+  using R = RangeTiles<2 * D, NW>;
+  const R range(n_tokens, wave, lane);
   const int uwbase = r * UPAD + wave * 64 + 8 * g;   // write: token r, units 32w + 8i + 4g .. +3 at + 16 i
   const int urbase = r * UPAD + 16 * g;              // read: A fragment of token r, k-step ks at + 32 ks
 
@@ -118,134 +108,178 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[db][e] = 0.f;
   float zacc = 0.f;
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-  // fragment of row lr, k-step ks of a K tile = xbase ^ 32 ks (the chunk bits of the permuted
-  // layout do not overlap the row bits)
-  // first half of tile `it`: U^T slice = relu(W1[slice] X^T + b1[slice]) -> U[token][hidden] in
-  // the buffer of the tile's parity
-  auto first_half = [&](int it, int xbase) {
-    const char* const Xs = XV + (it & 1) * TB;
-    char* const Ud = Us + (it & 1) * (64 * UPAD);
+  // U^T slice of a tile = relu(W1[slice] X^T + b1[slice]) -> U[token][hidden]: accumulators that start
+  // from the bias (no addition per element), rectified and stored four units at a time
+  auto u_start = [&]() {
+    f32x16 u;
 #pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-      f32x16 u;   // starts from the bias: no addition per element
+    for (int i = 0; i < 4; ++i) {
+      const f32x4 bb = *reinterpret_cast<const f32x4*>(b1rows + 8 * i);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const f32x4 bb = *reinterpret_cast<const f32x4*>(b1rows + 8 * i);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) u[4 * i + j] = bb[j];
-      }
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        bf16x8 xf = *reinterpret_cast<const bf16x8*>(Xs + (xbase ^ (32 * ks)) + tb * (32 * 2 * D));
-        u = mfma(w1f[ks], xf, u);
-      }
-      // register 4i+j = (hidden 32w+8i+4g+j, token 32tb+r)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        u32x2 pk;
-        pk[0] = pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f));
-        pk[1] = pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f));
-        *reinterpret_cast<u32x2*>(Ud + uwbase + 16 * i + tb * (32 * UPAD)) = pk;
-      }
+      for (int j = 0; j < 4; ++j) u[4 * i + j] = bb[j];
     }
+    return u;
+  };
+  auto u_store = [&](const f32x16& u, int i, char* Ud, int tb) {   // register 4i+j = (hidden 32w+8i+4g+j, token 32tb+r)
+    u32x2 pk;
+    pk[0] = pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f));
+    pk[1] = pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f));
+    *reinterpret_cast<u32x2*>(Ud + uwbase + 16 * i + tb * (32 * UPAD)) = pk;
   };
   auto opaque_lane = [&]() {   // offsets derived from it are recomputed per tile, not held in registers
     int ln = lane;
     asm volatile("" : "+v"(ln));
     return ln;
   };
+  // fragment of token row r, k-step ks of a K tile: ^ 32 ks (the chunk bits of the permuted layout do
+  // not overlap the row bits)
+  auto x_base = [&](int ln) { return tile_off<2 * D>(ln & 31, 8 * (ln >> 5)); };
+  // transposing reads of V: columns 32 db .. at ^ 64 db, tokens eight rows further down at ^ 32 there
+  auto v_base = [&](int ln) {
+    return tile_off<2 * D>(4 * (ln >> 5) + ((ln & 15) >> 2), 16 * ((ln & 31) >> 4) + 4 * (ln & 3));
+  };
+  auto u_fragment = [&](const char* Uc, int tb, int ks) {
+    return *reinterpret_cast<const bf16x8*>(Uc + urbase + 32 * ks + tb * (32 * UPAD));
+  };
 
-  // Step `it` runs the second half of tile `it` together with the first half of tile it+1
-  // (independent instruction streams inside every wave), so one barrier per tile is enough:
-  // it publishes U of tile it+1 and frees the buffers of tile `it`.  K runs two tiles ahead
-  // of V's use, both are requested one step before they are read.
+  constexpr int PD = 4;   // fragments read ahead of their products
+  bf16x8 fr[PD];
   if (n_tiles > 0) {
-    issue_k(0);
-    issue_v(0);
+    range.fill(Kr, 0, k_lds);
+    range.fill(Vr, 0, v_lds);
+    if (n_tiles > 1) range.fill(Kr, 64, k_lds + TB);
   }
   settle(w1f);
   settle(w2f);
   settle(b2v);
   if (n_tiles > 0) {
     wait_loads_and_barrier<0>();   // also: the bias is in LDS
-    if (n_tiles > 1) issue_k(1);
-    const int ln = opaque_lane();
-    first_half(0, tile_off<2 * D>(ln & 31, 8 * (ln >> 5)));
-  }
-
-  auto tile_step = [&](auto TAILC, auto SQC, int it) {
-    constexpr bool TAIL = decltype(TAILC)::value;
-    constexpr bool squared = decltype(SQC)::value;
-    const char* const Vs = XV + (2 + (it & 1)) * TB;
-    const char* const Uc = Us + (it & 1) * (64 * UPAD);
-    // K of tile it+1 and V of tile `it` have landed (the only loads in flight); U of tile `it`
-    // is complete; every wave is done with tile it-1
-    wait_loads_and_barrier<0>();
-    if (it + 2 < n_tiles) issue_k(it + 2);
-    if (it + 1 < n_tiles) issue_v(it + 1);
-    const int ln = opaque_lane();
-    const int lr = ln & 31, lg = ln >> 5, li = ln & 15;
-    int voff_lo[DB], voff_hi[DB];                        // transposing reads of V, see softmax kernel
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const int col = 32 * db + 16 * (lr >> 4) + 4 * (li & 3);
-      voff_lo[db] = tile_off<2 * D>(4 * lg + (li >> 2), col);
-      voff_hi[db] = tile_off<2 * D>(8 + 4 * lg + (li >> 2), col);
-    }
-    if (it + 1 < n_tiles) first_half(it + 1, tile_off<2 * D>(lr, 8 * lg));
-    // ---- second half ---------------------------------------------------------------
+    const int xbase = x_base(opaque_lane());
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
-      // psi slice = relu(U W2[slice]^T + b2): rows = tokens, columns = features
-      f32x16 ps = zero;
+      f32x16 u = u_start();
 #pragma unroll
-      for (int ks = 0; ks < KS2; ++ks) {
-        bf16x8 uf = *reinterpret_cast<const bf16x8*>(Uc + urbase + 32 * ks + tb * (32 * UPAD));
-        ps = mfma(uf, w2f[ks], ps);
-      }
+      for (int ks = 0; ks < KS; ++ks)
+        u = mfma(w1f[ks], *reinterpret_cast<const bf16x8*>(XV + (xbase ^ (32 * ks)) + tb * (32 * 2 * D)), u);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        float x = fmaxf(ps[e] + b2v, 0.f);
-        if (squared) x = x * x;
-        if (TAIL) {
-          if (32 * tb + 8 * (e >> 2) + 4 * g + (e & 3) >= rem) x = 0.f;   // token beyond the range
-        }
-        ps[e] = x;
-      }
-      // The normaliser sums the features as rounded for the product below: with unrounded ones S
-      // and z weigh a token differently, and for keys that resemble each other the differences
-      // add up (equal keys: error of y against fp64 up to 30 % larger, of gradients 40 %).
-      const bf16x8 fbs[2] = {acc_to_operand(ps, 0), acc_to_operand(ps, 1)};
-      float part = 0.f;
-#pragma unroll
-      for (int s = 0; s < 2; ++s) part = sum_operand<kDotSum>(fbs[s], part);
-      zacc += part;
-      // state slice += V^T phi, two 16-token steps
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        const bf16x8 fb = fbs[s];
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const int so = (2 * tb + s) * (16 * 2 * D);
-          i16x4 vlo = lds_read_tr(reinterpret_cast<const bf16_t*>(Vs + voff_lo[db] + so));
-          i16x4 vhi = lds_read_tr(reinterpret_cast<const bf16_t*>(Vs + voff_hi[db] + so));
-          acc[db] = mfma(join_tr(vlo, vhi), fb, acc[db]);
-        }
-      }
+      for (int i = 0; i < 4; ++i) u_store(u, i, Us, tb);
     }
+    lds_barrier();   // U of tile 0 is complete
+    static_for<PD>([&](auto MC) { fr[decltype(MC)::value] = u_fragment(Us, 0, decltype(MC)::value); });
+  }
+
+  // Step `it` runs the second half of tile `it` -- psi, phi and V^T phi -- together with the first
+  // half of tile it+1 (independent instruction streams inside every wave), in this order of
+  // products: psi of tokens 0..31, U(it+1) of 0..31, psi of 32..63, U(it+1) of 32..63, the state
+  // products of both.  Each group's vector work lies under the products of the next group and every
+  // operand is read PD products ahead; the order is fenced slot by slot, because the compiler waits
+  // for each LDS read right after issuing it otherwise.
+  // One barrier per tile, with PD products still to be issued: U(it+1) is complete, every wave has
+  // read its last operands of tile `it`, and K(it+2) and V(it+1), requested as the step began, have landed.
+  auto tile_step = [&](auto MOREC, auto SQC, int it) {
+    constexpr bool MORE = decltype(MOREC)::value;        // a tile follows; this one is full
+    constexpr bool squared = decltype(SQC)::value;
+    const char* const Vs = XV + (2 + (it & 1)) * TB;
+    const char* const Xs = XV + ((it + 1) & 1) * TB;
+    const char* const Uc = Us + (it & 1) * (64 * UPAD);
+    char* const Ud = Us + ((it + 1) & 1) * (64 * UPAD);
+    const int ln = opaque_lane();
+    const int xbase = x_base(ln), vbase = v_base(ln);
+    const int first = range.first(64 * it), count = range.count(64 * it);   // tokens of the last tile
+    const u32x4 Kd = rsrc_if(Kr, it + 2 < n_tiles);
+    const int ks = range.soff(64 * (it + 2)), vs = range.soff(64 * (it + 1));
+    const uint32_t kd = k_lds + (it & 1) * TB, vd = v_lds + ((it + 1) & 1) * TB;
+    constexpr int LP = KS2, LF = MORE ? KS : 0, LS = 2 * DB;
+    constexpr int F0 = LP, P1 = LP + LF, F1 = P1 + LP, S0 = F1 + LF, S1 = S0 + LS, NM = S1 + LS;
+    static_assert(NM % PD == 0, "the fragment ring closes over a step");
+    f32x16 u[2], ps[2];
+    uint32_t fb[2][8];   // phi as operands
+    float part[2] = {0.f, 0.f};
+    auto fetch = [&](auto MC) {   // the LDS operand of product m
+      constexpr int m = decltype(MC)::value;
+      if constexpr (m >= NM) {
+        if constexpr (MORE) fr[m % PD] = u_fragment(Ud, 0, m - NM);   // psi of the next tile
+      } else if constexpr (m < F0 || (m >= P1 && m < F1)) {
+        fr[m % PD] = u_fragment(Uc, m >= P1, m - (m >= P1 ? P1 : 0));
+      } else if constexpr (m < S0) {
+        constexpr int tb = m >= F1, ks = m - (tb ? F1 : F0);
+        if constexpr (ks == 0) u[tb] = u_start();
+        fr[m % PD] = *reinterpret_cast<const bf16x8*>(Xs + (xbase ^ (32 * ks)) + tb * (32 * 2 * D));
+      } else {
+        constexpr int tb = m >= S1, n = m - (tb ? S1 : S0), s = n / DB, db = n % DB;
+        const char* const p = Vs + (2 * tb + s) * (16 * 2 * D);
+        fr[m % PD] = join_tr(lds_read_tr(reinterpret_cast<const bf16_t*>(p + (vbase ^ (64 * db)))),
+                             lds_read_tr(reinterpret_cast<const bf16_t*>(p + (vbase ^ (64 * db) ^ 32) + 8 * 2 * D)));
+      }
+    };
+    auto product = [&](auto MC) {
+      constexpr int m = decltype(MC)::value;
+      if constexpr (m < F0 || (m >= P1 && m < F1)) {
+        constexpr int tb = m >= P1, ks = m - (tb ? P1 : 0);   // rows = tokens, columns = features
+        ps[tb] = mfma(fr[m % PD], w2f[ks], ks == 0 ? f32x16{} : ps[tb]);
+      } else if constexpr (m < S0) {
+        constexpr int tb = m >= F1, ks = m - (tb ? F1 : F0);
+        u[tb] = mfma(w1f[ks], fr[m % PD], u[tb]);
+      } else {
+        constexpr int tb = m >= S1, n = m - (tb ? S1 : S0), s = n / DB, db = n % DB;
+        const u32x4 w = {fb[tb][4 * s], fb[tb][4 * s + 1], fb[tb][4 * s + 2], fb[tb][4 * s + 3]};
+        acc[db] = mfma(fr[m % PD], __builtin_bit_cast(bf16x8, w), acc[db]);
+      }
+    };
+    auto phi = [&](auto TBC, auto IC) {   // elements 2i, 2i+1 of psi
+      constexpr int tb = decltype(TBC)::value, i = decltype(IC)::value;
+      float x[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int e = 2 * i + j;
+        x[j] = fmaxf(ps[tb][e] + b2v, 0.f);
+        if (squared) x[j] = x[j] * x[j];
+        if (!MORE && (unsigned)(32 * tb + 8 * (e >> 2) + 4 * g + (e & 3) - first) >= (unsigned)count) x[j] = 0.f;
+      }
+      fb[tb][i] = pack_bf16(x[0], x[1]);
+      // The normaliser sums the features as rounded for the product: with unrounded ones S and z
+      // weigh a token differently, and for keys that resemble each other the differences add up
+      // (equal keys: error of y against fp64 up to 30 % larger, of gradients 40 %).
+      part[tb] = sum_pair<kDotSum>(fb[tb][i], part[tb]);
+      pin(part[tb]);
+      pin(fb[tb][i]);
+    };
+    constexpr int kPairs = 8 / LS;   // element pairs per slot
+    static_for<NM>([&](auto MC) {
+      constexpr int m = decltype(MC)::value;
+      if constexpr (MORE && m == NM - PD) wait_loads_and_barrier<0>();
+      product(MC);
+      fetch(std::integral_constant<int, m + PD>{});
+      if constexpr (MORE && m % 2 == 1 && m < 4 * R::LPT) {
+        constexpr int i = m / 2;
+        if constexpr (i < R::LPT) range.template load<i>(Kd, ks, kd);
+        else range.template load<i - R::LPT>(Vr, vs, vd);
+      }
+      static_for<2>([&](auto TBC) {
+        constexpr int tb = decltype(TBC)::value;
+        constexpr int p = m - (tb ? F1 : F0) - 2;   // two products behind the group's last one
+        if constexpr (p >= 0 && kPairs * p < 8)
+          static_for<kPairs>([&](auto JC) { phi(TBC, std::integral_constant<int, kPairs * p + decltype(JC)::value>{}); });
+        constexpr int q = m - (tb ? S0 : P1) - LS / 2;
+        if constexpr (MORE && q >= 0 && q < LS && q % (LS / 4) == 0) u_store(u[tb], q / (LS / 4), Ud, tb);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    zacc += part[0];
+    zacc += part[1];
   };
 
   // A loop for each half of the features: decided per element, squaring costs a select each (the
-  // waves of both loops meet at the same number of barriers).  With the bias in the first
-  // product and z summed from the operands of the second this takes the vector work of a tile from
-  // 290 to 190 instructions per wave at d = 128: 105 -> 102 us at the 480p shape, where the LDS latency
-  // of eight waves in step bounds a tile, 81 -> 65 us at 24 heads of 64 (with the accumulators out of
-  // the AGPRs).
+  // waves of both loops meet at the same number of barriers).
+  // What bounds a tile: products at the rate that power allows with all CUs busy (26.6 ns each per SIMD
+  // against 22.5 in a loop of nothing else with this mix), at d = 64 vector work.  With the groups one
+  // after the other and each LDS read waited for as it was issued: 480p and 320x480 launches of 12
+  // heads of 128 together 68.4 us, now 66.3; 24 heads of 64 at 480p 70.3, now 64.5; 2 x 3 heads of
+  // 333-token frames 19.5, now 18.1.  (d = 128: four registers are spilled outside the loops.)
   auto all_tiles = [&](auto SQC) {
-    for (int it = 0; it < n_full; ++it) tile_step(std::false_type{}, SQC, it);
-    if (rem > 0) tile_step(std::true_type{}, SQC, n_full);
+    for (int it = 0; it + 1 < n_tiles; ++it) tile_step(std::true_type{}, SQC, it);
+    if (n_tiles > 0) tile_step(std::false_type{}, SQC, n_tiles - 1);
   };
   if (wave * 32 >= DP / 2) all_tiles(std::true_type{});
   else all_tiles(std::false_type{});
