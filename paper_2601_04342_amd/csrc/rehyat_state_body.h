@@ -193,6 +193,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
     constexpr int LP = KS2, LF = MORE ? KS : 0, LS = 2 * DB;
     constexpr int F0 = LP, P1 = LP + LF, F1 = P1 + LP, S0 = F1 + LF, S1 = S0 + LS, NM = S1 + LS;
     static_assert(NM % PD == 0, "the fragment ring closes over a step");
+    static_assert(S0 + 3 < NM - PD, "U is stored before the barrier that publishes it");
     f32x16 u[2], ps[2];
     uint32_t fb[2][8];   // phi as operands
     float part[2] = {0.f, 0.f};
@@ -261,8 +262,11 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
         constexpr int p = m - (tb ? F1 : F0) - 2;   // two products behind the group's last one
         if constexpr (p >= 0 && kPairs * p < 8)
           static_for<kPairs>([&](auto JC) { phi(TBC, std::integral_constant<int, kPairs * p + decltype(JC)::value>{}); });
-        constexpr int q = m - (tb ? S0 : P1) - LS / 2;
-        if constexpr (MORE && q >= 0 && q < LS && q % (LS / 4) == 0) u_store(u[tb], q / (LS / 4), Ud, tb);
+        constexpr int q = m - (tb ? S0 : P1) - 2;   // two quads of units per slot: done before the barrier
+        if constexpr (MORE && q >= 0 && q < 2) {
+          u_store(u[tb], 2 * q, Ud, tb);
+          u_store(u[tb], 2 * q + 1, Ud, tb);
+        }
       });
       __builtin_amdgcn_sched_barrier(0);
     });
@@ -276,7 +280,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   // against 22.5 in a loop of nothing else with this mix), at d = 64 vector work.  With the groups one
   // after the other and each LDS read waited for as it was issued: 480p and 320x480 launches of 12
   // heads of 128 together 68.4 us, now 66.3; 24 heads of 64 at 480p 70.3, now 64.5; 2 x 3 heads of
-  // 333-token frames 19.5, now 18.1.  (d = 128: four registers are spilled outside the loops.)
+  // 333-token frames 19.5, now 18.1.  (d = 128: a few registers are spilled, outside the loops.)
   auto all_tiles = [&](auto SQC) {
     for (int it = 0; it + 1 < n_tiles; ++it) tile_step(std::true_type{}, SQC, it);
     if (n_tiles > 0) tile_step(std::false_type{}, SQC, n_tiles - 1);

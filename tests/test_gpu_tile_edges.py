@@ -4,6 +4,7 @@ rows, at both head widths, against the oracle with every component."""
 import pytest
 import torch
 
+from paper_2601_04342_amd import binding, synth
 from tests import parity
 
 pytestmark = pytest.mark.gpu
@@ -22,3 +23,17 @@ def test_key_tiles(HW, d):
     """Softmax windows of one to seven key tiles (below 448 keys: one group of waves), and chunk
     states over as many tiles."""
     parity.run_case(1, 1, 3, HW, d, 1, 0, 0, 4.0, seed=HW + d)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_chunk_states_are_reproducible(d):
+    """Every CU runs state pieces of three and more tiles several times over: the same bits each time
+    (a barrier that publishes a tile too early shows as rare differences)."""
+    H, T, HW = 48, 4, 1300
+    q, k, v = synth.make_qkv(1, H, T * HW, d, seed=d)
+    phi = synth.make_phi(H, d, seed=1, gain=4.0)
+    _, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    first = binding.state(dk, dv, dphi, T, HW, T)
+    for i in range(20):
+        again = binding.state(dk, dv, dphi, T, HW, T)
+        assert all(torch.equal(a, b) for a, b in zip(again, first)), i
