@@ -535,8 +535,9 @@ struct BwdPlan {
   WsLayout F;
   int nc, n_seg;     // chunks; segments (= chunks that read a state)
   int nsplit;        // pieces per segment (state and activation-gradient kernels)
-  int nsplit_g;      // pieces per (b, h) of the weight-gradient kernels
-  size_t yhat, nS, nL, u, tokw, Rt, rz, w2t_q, w2t_k, dpsi, p_w2, p_w1, p_b2, p_dz, total;
+  int n2, n1;        // pieces per side and (b, h) of the weight gradients: dW2, dW1
+  size_t yhat, nS, nL, u, tokw, Rt, rz, w2t, total;
+  size_t dpsi[2], signs[2], p_w2[2], p_w1[2], p_b2[2], p_dz;   // queries, keys
 };
 
 BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
@@ -548,12 +549,15 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   P.nsplit = choose_cut((int)BH, P.n_seg, P.n_seg, (int64_t)chunk * HW, 0, d, kMaxSplit * P.nc, P.n_seg).nsplit;
   P.sl = Slots{P.n_seg * P.nsplit, P.nc};
   P.F = ws_layout(B, H, d, dp, P.sl);
-  // weight-gradient kernels: one (b, h) token range cut so that the pieces about fill the chip
-  int ns = (int)(kCUs / BH);
-  if (ns < 1) ns = 1;
+  // Weight gradients: one launch for both sides and both layers, cut so that its workgroups about
+  // fill the chip.  A tile costs nearly the same for either layer (12 heads, 10 pieces per side and (b, h):
+  // five and five 102 us at 320x480, 340 us at 480p; four and six 120 and 396; six and four 106 and 341).
   const size_t tiles = (N + 63) / 64;
-  if ((size_t)ns > tiles) ns = (int)tiles;
-  P.nsplit_g = ns;
+  const int pieces = (int)((d == 128 ? kCUs : 2 * kCUs) / (2 * BH));   // per side and (b, h)
+  P.n2 = pieces > 1 ? (pieces + 1) / 2 : 1;
+  P.n1 = pieces > 1 ? pieces / 2 : 1;
+  if ((size_t)P.n2 > tiles) P.n2 = (int)tiles;
+  if ((size_t)P.n1 > tiles) P.n1 = (int)tiles;
   size_t off = P.F.total;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -567,33 +571,34 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   P.tokw = take(BH * N * sizeof(float));
   P.Rt = take(BH * P.nc * (size_t)dp * d * sizeof(bf16_t));
   P.rz = take(BH * P.nc * (size_t)dp * sizeof(float));
-  P.w2t_q = take((size_t)H * hid * dp * sizeof(bf16_t));
-  P.w2t_k = take((size_t)H * hid * dp * sizeof(bf16_t));
-  P.dpsi = take(BH * N * dp * sizeof(bf16_t));
-  P.p_w2 = take(BH * ns * (size_t)dp * hid * sizeof(float));
-  P.p_w1 = take(BH * ns * ((size_t)d * hid + hid) * sizeof(float));
-  P.p_b2 = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
+  P.w2t = take(2 * (size_t)H * hid * dp * sizeof(bf16_t));
+  for (int side = 0; side < 2; ++side) {
+    P.dpsi[side] = take(BH * N * dp * sizeof(bf16_t));
+    P.signs[side] = take(BH * N * (hid / 32) * sizeof(uint32_t));
+    P.p_w2[side] = take(BH * P.n2 * (size_t)dp * hid * sizeof(float));
+    P.p_w1[side] = take(BH * P.n1 * ((size_t)d * hid + hid) * sizeof(float));
+    P.p_b2[side] = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
+  }
   P.p_dz = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
   P.total = off;
   return P;
 }
 
-struct SideParams {   // one feature map and where its gradients go
-  const void *w1, *b1, *w2, *b2;
+// One feature map: its input and weights, where its gradients go, and the token range [lo, hi) of
+// every (b, h) that its segments cover.
+struct SideParams {
+  const void *x, *w1, *b1, *w2, *b2;
   float *g_w1, *g_b1, *g_w2, *g_b2;
+  int64_t lo, hi;
 };
 
-// Activation gradients, then the weight gradients, of one side.  `x` is q or k, `vec` is u or
-// v, `M`/`zv` the per-segment matrices of dPhi = M vec + tokw zv; [lo, hi) is the token range
-// of every (b, h) that the segments cover.
-int backward_side(char* ws, const BwdPlan& P, hipStream_t st, const void* x, const void* vec,
-                  const float* tokw, const SideParams& sp, const bf16_t* w2t, const bf16_t* M,
-                  const float* zv, bool query_side, float* dz_part, int B, int H, int T, int HW,
-                  int d, int chunk, int overlap, int64_t lo, int64_t hi) {
-  const int dp = 2 * d, hid = 2 * d;
-  const int BH = B * H;
+// Activation gradients of one side.  `vec` is u or v, `M`/`zv` the per-segment matrices of dPhi = M vec +
+// tokw zv.
+int activation_gradients(char* ws, const BwdPlan& P, hipStream_t st, int side, const SideParams& sp, const void* vec,
+                         const float* tokw, const bf16_t* M, const float* zv, float* dz_part, int BH, int H, int T, int HW,
+                         int d, int chunk, int overlap) {
   ActGradArgs g;
-  g.x = (const bf16_t*)x;
+  g.x = (const bf16_t*)sp.x;
   g.vec = (const bf16_t*)vec;
   g.tokw = tokw;
   g.w1 = (const bf16_t*)sp.w1;
@@ -602,98 +607,90 @@ int backward_side(char* ws, const BwdPlan& P, hipStream_t st, const void* x, con
   g.b2 = (const float*)sp.b2;
   g.M = M;
   g.zv = zv;
-  g.dpsi = (bf16_t*)(ws + P.dpsi);
-  g.db2_part = (float*)(ws + P.p_b2);
+  g.dpsi = (bf16_t*)(ws + P.dpsi[side]);
+  g.signs = (uint32_t*)(ws + P.signs[side]);
+  g.db2_part = (float*)(ws + P.p_b2[side]);
   g.dz_part = dz_part;
   g.H = H;
   g.T = T;
   g.HW = HW;
   g.chunk = chunk;
   g.overlap = overlap;
-  g.query_side = query_side ? 1 : 0;
+  g.query_side = side == 0 ? 1 : 0;
   g.n_seg = P.n_seg;
   g.nsplit = P.nsplit;
   g.slots = P.nc;
   g.n_items = BH * P.n_seg * P.nsplit;
   g.items_per_xcd = (g.n_items + 7) / 8;
   hipError_t e = launch_act_grad(g, d, g.items_per_xcd * 8, st);
-  if (e != hipSuccess) return hip_fail(e, "activation-gradient kernel launch");
+  return e == hipSuccess ? REHYAT_OK : hip_fail(e, "activation-gradient kernel launch");
+}
 
-  const int n_items = BH * P.nsplit_g;
-  TnGemmArgs t;
-  t.dpsi = (const bf16_t*)(ws + P.dpsi);
-  t.x = (const bf16_t*)x;
-  t.w1 = (const bf16_t*)sp.w1;
-  t.b1 = (const float*)sp.b1;
-  t.part = (float*)(ws + P.p_w2);
-  t.H = H;
-  t.N = (int64_t)T * HW;
-  t.lo = lo;
-  t.hi = hi;
-  t.nsplit = P.nsplit_g;
-  t.n_items = n_items;
-  t.items_per_xcd = (n_items + 7) / 8;
-  e = launch_tn_gemm(t, d, t.items_per_xcd * 8, st);
-  if (e != hipSuccess) return hip_fail(e, "second-layer gradient kernel launch");
-
-  HidGradArgs hg;
-  hg.dpsi = (const bf16_t*)(ws + P.dpsi);
-  hg.x = (const bf16_t*)x;
-  hg.w1 = (const bf16_t*)sp.w1;
-  hg.b1 = (const float*)sp.b1;
-  hg.w2t = w2t;
-  hg.part = (float*)(ws + P.p_w1);
-  hg.H = H;
-  hg.N = (int64_t)T * HW;
-  hg.lo = lo;
-  hg.hi = hi;
-  hg.nsplit = P.nsplit_g;
-  hg.n_items = n_items;
-  hg.items_per_xcd = (n_items + 7) / 8;
-  e = launch_hid_grad(hg, d, hg.items_per_xcd * 8, st);
-  if (e != hipSuccess) return hip_fail(e, "first-layer gradient kernel launch");
-
-  // the four gradient tensors of this side from their partial sums, one launch
+// The weight gradients of both sides from their activation gradients, and the sums over batch and
+// pieces.
+int weight_gradients(char* ws, const BwdPlan& P, hipStream_t st, const SideParams (&sides)[2], int B, int H, int T, int HW,
+                     int d) {
+  const int dp = 2 * d, hid = 2 * d, BH = B * H;
+  WeightGradArgs w;
+  w.H = H;
+  w.BH = BH;
+  w.N = (int64_t)T * HW;
+  w.n2 = P.n2;
+  w.n1 = P.n1;
+  w.n_items = 2 * BH * (P.n2 + P.n1);
+  w.items_per_xcd = (w.n_items + 7) / 8;
   ReduceJobs jobs;
-  jobs.n = 4;
-  for (int j = 0; j < 4; ++j) {
-    jobs.job[j].B = B;
-    jobs.job[j].H = H;
-    jobs.job[j].part_off = 0;
-    jobs.job[j].transpose = 0;
+  jobs.n = 8;
+  for (int side = 0; side < 2; ++side) {
+    const SideParams& sp = sides[side];
+    WeightGradSide& s = w.side[side];
+    s.dpsi = (const bf16_t*)(ws + P.dpsi[side]);
+    s.x = (const bf16_t*)sp.x;
+    s.signs = (const uint32_t*)(ws + P.signs[side]);
+    s.w1 = (const bf16_t*)sp.w1;
+    s.b1 = (const float*)sp.b1;
+    s.w2t = (const bf16_t*)(ws + P.w2t) + (size_t)side * H * hid * dp;
+    s.part_w2 = (float*)(ws + P.p_w2[side]);
+    s.part_w1 = (float*)(ws + P.p_w1[side]);
+    s.lo = sp.lo;
+    s.hi = sp.hi;
+
+    ReduceArgs* const job = jobs.job + 4 * side;
+    for (int j = 0; j < 4; ++j) {
+      job[j].B = B;
+      job[j].H = H;
+      job[j].part_off = 0;
+      job[j].transpose = 0;
+    }
+    job[0].part = s.part_w2;
+    job[0].out = sp.g_w2;
+    job[0].per_bh = P.n2;
+    job[0].part_stride = (int64_t)dp * hid;
+    job[0].R = dp;
+    job[0].C = hid;
+    job[1].part = s.part_w1;   // partial is dW1^T [d][hidden]
+    job[1].out = sp.g_w1;
+    job[1].per_bh = P.n1;
+    job[1].part_stride = (int64_t)d * hid + hid;
+    job[1].R = d;
+    job[1].C = hid;
+    job[1].transpose = 1;
+    job[2] = job[1];
+    job[2].out = sp.g_b1;
+    job[2].part_off = (int64_t)d * hid;
+    job[2].R = 1;
+    job[2].transpose = 0;
+    job[3].part = (const float*)(ws + P.p_b2[side]);
+    job[3].out = sp.g_b2;
+    job[3].per_bh = P.n_seg * P.nsplit;
+    job[3].part_stride = dp;
+    job[3].R = 1;
+    job[3].C = dp;
   }
-  ReduceArgs& rw2 = jobs.job[0];
-  rw2.part = (const float*)(ws + P.p_w2);
-  rw2.out = sp.g_w2;
-  rw2.per_bh = P.nsplit_g;
-  rw2.part_stride = (int64_t)dp * hid;
-  rw2.R = dp;
-  rw2.C = hid;
-  ReduceArgs& rw1 = jobs.job[1];   // partial is dW1^T [d][hidden]
-  rw1.part = (const float*)(ws + P.p_w1);
-  rw1.out = sp.g_w1;
-  rw1.per_bh = P.nsplit_g;
-  rw1.part_stride = (int64_t)d * hid + hid;
-  rw1.R = d;
-  rw1.C = hid;
-  rw1.transpose = 1;
-  ReduceArgs& rb1 = jobs.job[2];
-  rb1 = rw1;
-  rb1.out = sp.g_b1;
-  rb1.part_off = (int64_t)d * hid;
-  rb1.R = 1;
-  rb1.C = hid;
-  rb1.transpose = 0;
-  ReduceArgs& rb2 = jobs.job[3];
-  rb2.part = (const float*)(ws + P.p_b2);
-  rb2.out = sp.g_b2;
-  rb2.per_bh = P.n_seg * P.nsplit;
-  rb2.part_stride = dp;
-  rb2.R = 1;
-  rb2.C = dp;
+  hipError_t e = launch_weight_grad(w, d, w.items_per_xcd * 8, st);
+  if (e != hipSuccess) return hip_fail(e, "weight-gradient kernel launch");
   e = launch_reduce(jobs, st);
-  if (e != hipSuccess) return hip_fail(e, "reduce kernel launch");
-  return REHYAT_OK;
+  return e == hipSuccess ? REHYAT_OK : hip_fail(e, "reduce kernel launch");
 }
 
 // Largest slot counts whose layout fits `bytes` (equal partial and state slots, at most the
@@ -942,9 +939,9 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
   tr.R = dp;
   tr.C = hid;
   tr.in = (const bf16_t*)phi->w2_q;
-  tr.out = (bf16_t*)(ws + P.w2t_q);
+  tr.out = (bf16_t*)(ws + P.w2t);
   tr.in2 = (const bf16_t*)phi->w2_k;
-  tr.out2 = (bf16_t*)(ws + P.w2t_k);
+  tr.out2 = tr.out + (size_t)H * hid * dp;
   e = launch_transpose(tr, st);
   if (e != hipSuccess) return hip_fail(e, "transpose kernel launch");
 
@@ -989,14 +986,15 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
     if (e != hipSuccess) return hip_fail(e, "state-gradient kernel launch");
   }
 
-  // ---- query side ----------------------------------------------------------------------
-  SideParams sq{phi->w1_q, phi->b1_q, phi->w2_q, phi->b2_q,
-                (float*)grads->w1_q, (float*)grads->b1_q, (float*)grads->w2_q, (float*)grads->b2_q};
-  const ChunkRange c1 = chunk_range(T, HW, chunk, overlap, 1);
-  rc = backward_side(ws, P, st, q, ws + P.u, (const float*)(ws + P.tokw), sq,
-                     (const bf16_t*)(ws + P.w2t_q), (const bf16_t*)(ws + P.F.state_s),
-                     (const float*)(ws + P.F.state_z), true, (float*)(ws + P.p_dz), B, H, T, HW, d,
-                     chunk, overlap, c1.q_lo, N);
+  const ChunkRange c1 = chunk_range(T, HW, chunk, overlap, 1), cl = chunk_range(T, HW, chunk, overlap, nc - 1);
+  const SideParams sides[2] = {
+      {q, phi->w1_q, phi->b1_q, phi->w2_q, phi->b2_q, (float*)grads->w1_q, (float*)grads->b1_q, (float*)grads->w2_q,
+       (float*)grads->b2_q, c1.q_lo, N},
+      {k, phi->w1_k, phi->b1_k, phi->w2_k, phi->b2_k, (float*)grads->w1_k, (float*)grads->b1_k, (float*)grads->w2_k,
+       (float*)grads->b2_k, 0, cl.s_lo}};
+  rc = activation_gradients(ws, P, st, 0, sides[0], ws + P.u, (const float*)(ws + P.tokw),
+                            (const bf16_t*)(ws + P.F.state_s), (const float*)(ws + P.F.state_z), (float*)(ws + P.p_dz), BH, H,
+                            T, HW, d, chunk, overlap);
   if (rc != REHYAT_OK) return rc;
 
   // ---- R_tau, r_tau ------------------------------------------------------------------
@@ -1017,13 +1015,10 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
   e = launch_suffix(sa, st);
   if (e != hipSuccess) return hip_fail(e, "suffix kernel launch");
 
-  // ---- key side ------------------------------------------------------------------------
-  SideParams sk{phi->w1_k, phi->b1_k, phi->w2_k, phi->b2_k,
-                (float*)grads->w1_k, (float*)grads->b1_k, (float*)grads->w2_k, (float*)grads->b2_k};
-  const ChunkRange cl = chunk_range(T, HW, chunk, overlap, nc - 1);
-  return backward_side(ws, P, st, k, v, nullptr, sk, (const bf16_t*)(ws + P.w2t_k),
-                       (const bf16_t*)(ws + P.Rt), (const float*)(ws + P.rz), false, nullptr, B, H, T,
-                       HW, d, chunk, overlap, 0, cl.s_lo);
+  rc = activation_gradients(ws, P, st, 1, sides[1], v, nullptr, (const bf16_t*)(ws + P.Rt), (const float*)(ws + P.rz),
+                            nullptr, BH, H, T, HW, d, chunk, overlap);
+  if (rc != REHYAT_OK) return rc;
+  return weight_gradients(ws, P, st, sides, B, H, T, HW, d);
 }
 
 int rehyat_debug_set_xcd_mask(unsigned mask) {

@@ -10,20 +10,20 @@
 //   dL/dPhi_k,j = R_tau v_j + r_tau,  R_tau = sum_{t > tau} dL/dS_t        (keys j of segment tau)
 // and then through phi = [psi_1, psi_2^2], psi = relu(W2 U + b2), U = relu(W1 x + b1).
 //
-// Kernels, in launch order for one side (queries, then keys):
-//   prep_kernel       u, w per token (HBM-bound)
-//   state_kernel      (rehyat_state.hip, query segments) dL/dS_t partial sums
-//   act_grad_kernel   recomputes U and psi, forms dPhi and dpsi per token; writes dpsi
-//                     token-major, and the partial sums of db2 and dL/dz_t
-//   suffix_kernel     R_tau, r_tau from the partial sums
-//   tn_gemm_kernel    dW2 = dpsi^T U over tokens (U recomputed from x)
-//   hid_grad_kernel   dU = (dpsi W2) [U > 0]; dW1 = dU^T x, db1 = sum dU (sign of U recomputed)
-//   reduce_kernel     sums the per-workgroup partials over batch and pieces
+// Kernels, in launch order (queries, then keys, where there are two):
+//   prep_kernel        u, w per token (HBM-bound)
+//   state_kernel       (rehyat_state.hip, query segments) dL/dS_t partial sums
+//   act_grad_kernel    recomputes U and psi, forms dPhi and dpsi per token; writes dpsi token-major, the
+//                      signs of U, and the partial sums of db2 and dL/dz_t
+//   suffix_kernel      R_tau, r_tau from the partial sums (between the two activation gradients)
+//   weight_grad_kernel of both sides: dW2 = dpsi^T U over tokens (U recomputed from x);
+//                      dU = (dpsi W2) [U > 0], dW1 = dU^T x, db1 = sum dU
+//   reduce_kernel      sums the per-workgroup partials over batch and pieces
 // The contraction kernels follow the chunk-state kernel's scheme: wave w owns 32 hidden
 // units or features, weights of its slice live in registers as MFMA B operands, tiles of 64
 // tokens arrive by direct global->LDS loads, products are computed with tokens in the
 // accumulator rows so that an accumulator is directly the B operand of the token
-// contraction that follows.
+// contraction that follows, and their order is written out and fenced.
 #include <type_traits>
 
 #include "rehyat_device.h"
@@ -173,22 +173,20 @@ hipError_t launch_transpose(const TransposeArgs& a, hipStream_t stream) {
 // Activation gradients.  Wave w owns hidden units and features [32w, 32w + 32); its rows of
 // W1, W2 and of the segment's matrix M stay in registers as MFMA operands for the whole token
 // range.  Per tile of 64 tokens:
-//   first half   U^T slice = relu(W1[slice] X^T + b1[slice]) -> LDS as U[token][hidden];
-//   second half  psi slice = U W2[slice]^T + b2 and dPhi slice = Vec M[slice]^T, both with
-//                tokens in accumulator rows and the wave's 32 features in lanes;
-//                dpsi = dPhi + w zv, times 2 psi in the squared half, zero where psi = 0;
-//                dpsi goes through a wave-private LDS patch so that it leaves in 16-byte stores.
-// The x and vec tiles (and the 64 token weights) of tile t+2 are requested when tile t is
-// finished, into the buffers tile t used; they are ordered against the reads by counted
-// waits.  Vector memory operations of a wave complete in the order issued, stores included,
-// so "at most n outstanding" after n younger stores means every older load has landed.
+//   psi slice = U W2[slice]^T + b2 and dPhi slice = Vec M[slice]^T, both with tokens in accumulator
+//   rows and the wave's 32 features in lanes; dpsi = dPhi + w zv, times 2 psi in the squared half,
+//   zero where psi = 0; dpsi goes through a wave-private LDS patch so that it leaves in 16-byte stores;
+//   U^T slice of the next tile = relu(W1[slice] X^T + b1[slice]) -> LDS as U[token][hidden], and
+//   the signs of its 32 hidden units as one word per token, which the first-layer gradient takes as gates.
+// Order of products: psi and dPhi of tokens 0..31, of 32..63, then U(it+1); a half's vector work lies
+// under the products that follow it, operands are read PD products ahead, one barrier per tile.
+// x(it+2), vec(it+1) and the token weights of it+1 are requested as a step begins.  At its barrier
+// they have landed: vector memory operations of a wave complete in the order issued, stores included,
+// and the step's stores (four of dpsi, one of signs) are younger than its loads.
 // ------------------------------------------------------------------------------------
-// The kernel was bound by vector work (18 instructions per feature and token: selects for the
-// squared half and for rows past the end, a conversion per stored element).  The two halves of
-// the features and the ragged tile now have code of their own, elements are converted in pairs, the
-// bias is the accumulators' start and the key side leaves out the sum it does not need: 168 -> 147
-// us (queries) and 167 -> 131 us (keys) at the 480p shape.  The two loops cost the query side nine
-// spilled registers, stored and reloaded outside them.
+// Bound by memory: 1.06 KB per token read and written, 3.8 TB/s at the 480p shape (108 us for the queries,
+// 103 for the keys) against 4.75 of a plain copy; the order of the products made no difference to that,
+// the sign words cost 2 - 5 us and save the first-layer gradient a quarter of its products.
 // Two waves per SIMD, also where a workgroup has four waves: with the whole register file to use the
 // compiler keeps accumulators in AGPRs and copies each one out before vector work.
 template <int D, int NW, bool TW>
@@ -199,10 +197,7 @@ act_grad_kernel(ActGradArgs a) {
   constexpr int KS2 = HID / 16;
   constexpr int TB = 64 * 2 * D;  // bytes of an x or vec tile
   constexpr int UROW = HID * 2;
-  constexpr int LPT = TB / (1024 * NW);
-  constexpr int LG = 2 * LPT + (TW ? 1 : 0);  // direct loads per wave per tile
   constexpr int SROW = 80;        // bytes per token row of the dpsi patch: 32 features + padding
-  constexpr int NST = 4;          // dpsi stores per lane per full tile
   // U[token][hidden] with 16 bytes of padding per row: consecutive rows start four banks apart,
   // so fragment reads and writes are conflict-free without a chunk permutation and every
   // k-step is an immediate offset from one per-lane address
@@ -210,7 +205,7 @@ act_grad_kernel(ActGradArgs a) {
   static_assert(DP / NW == 32, "each wave owns 32 features");
 
   __shared__ __attribute__((aligned(1024))) char XV[4 * TB];   // x tiles 0/1, then vec tiles 0/1
-  __shared__ __attribute__((aligned(1024))) char Us[64 * UPAD];
+  __shared__ __attribute__((aligned(1024))) char Us[2 * 64 * UPAD];
   __shared__ __attribute__((aligned(1024))) char Stg[NW * 32 * SROW];
   __shared__ __attribute__((aligned(256))) float Tws[2 * 64];
   __shared__ __attribute__((aligned(256))) float B1s[HID];
@@ -245,21 +240,20 @@ act_grad_kernel(ActGradArgs a) {
   const int64_t len = seg_hi - seg_lo;
   const int64_t lo = seg_lo + (len * sp) / a.nsplit;
   const int64_t hi = seg_lo + (len * (sp + 1)) / a.nsplit;
-  const int n_full = (int)((hi - lo) / 64);
-  const int rem = (int)((hi - lo) - 64 * (int64_t)n_full);
-  const int n_tiles = n_full + (rem > 0 ? 1 : 0);
+  const int n_tokens = (int)(hi - lo), n_tiles = (n_tokens + 63) / 64;
 
   const int64_t row0 = (int64_t)bh * N + lo;  // first token of this piece, over all (b, h)
   char* Pg = reinterpret_cast<char*>(a.dpsi + row0 * DP);
+  uint32_t* const Sgn = a.signs + ((int64_t)bh * NW + wave) * N + lo;   // this wave's word of a token
 
   // ---- resident operands ----------------------------------------------------
   // first-layer bias in LDS: accumulator register 4i+j is hidden unit 32w + 8i + 4g + j, so a
   // lane reads its four rows of block i with one 16-byte read
   if (tid < HID) B1s[tid] = a.b1[(int64_t)h * HID + tid];
   const float* const b1rows = B1s + wave * 32 + 4 * g;
-  const int unit = wave * 32 + r;  // this lane's hidden unit (first half) and feature (second half)
-  const float b2v = a.b2[(int64_t)h * DP + unit];
-  const float zvv = a.zv[((int64_t)bh * a.slots + slot) * DP + unit];
+  const int unit = wave * 32 + r;  // this lane's hidden unit (U) and feature (psi, dPhi)
+  float b2v = a.b2[(int64_t)h * DP + unit];
+  float zvv = a.zv[((int64_t)bh * a.slots + slot) * DP + unit];
   bf16x8 w1f[KS];   // A operands: row = hidden unit, k = head dimension
   {
     const bf16_t* p = a.w1 + ((int64_t)h * HID + unit) * D + 8 * g;
@@ -292,137 +286,219 @@ act_grad_kernel(ActGradArgs a) {
 
   const u32x4 Xr = make_rsrc_words(a.x + row0 * D), Vr = make_rsrc_words(a.vec + row0 * D);
   const u32x4 Twr = make_rsrc_words(TW ? (const void*)(a.tokw + row0) : (const void*)a.x);
-  const uint32_t xv_lds = lds_address(XV), tw_lds = lds_address(Tws);
-  const int voff_full = tile_voff_full<2 * D, NW>(wave, lane);
-  auto issue = [&](int it) {   // tile `it` into the buffers of its parity
-    const int valid = it < n_full ? 64 : rem;
-    const int soff = __builtin_amdgcn_readfirstlane(it * TB);
-    tile_load_fast<2 * D, TB, NW>(Xr, soff, xv_lds + (it & 1) * TB, wave, lane, valid, voff_full);
-    if (TW) {
-      const int t = lane < valid ? lane : valid - 1;
-      direct_load_4(Twr, 4 * t, __builtin_amdgcn_readfirstlane(it * 256), tw_lds + (it & 1) * 256);
-    }
-    tile_load_fast<2 * D, TB, NW>(Vr, soff, xv_lds + (2 + (it & 1)) * TB, wave, lane, valid, voff_full);
+  const uint32_t x_lds = lds_address(XV), v_lds = x_lds + 2 * TB, tw_lds = lds_address(Tws);
+  using R = RangeTiles<2 * D, NW>;
+  const R range(n_tokens, wave, lane);
+  auto load_tw = [&](int it) {   // the tile's 64 token weights, moved by every wave alike
+    const int row = n_tokens < 64 ? 0 : 64 * it < n_tokens - 64 ? 64 * it : n_tokens - 64;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    direct_load_4(Twr, 4 * (ln < n_tokens ? ln : n_tokens - 1), __builtin_amdgcn_readfirstlane(4 * row),
+                  tw_lds + (it & 1) * 256);
   };
-
-  // ---- per-lane LDS byte offsets (as in the chunk-state kernel) -----------------
-  // fragment of token row r, k-step ks inside an x or vec tile: chunk 2 ks + g, permuted by the
-  // row -- the chunk bits do not overlap the row bits, so the offset is one XOR away from a
-  // per-lane constant
-  // (derived per tile from an opaque copy of the lane index: held across the loop, the eight
-  // offsets and the addresses of the dpsi patch would push resident operands out of registers)
   const int uwbase = r * UPAD + wave * 64 + 8 * g;   // write: token r, units 32w + 8i + 4g .. +3 at + 16 i
   const int urbase = r * UPAD + 16 * g;              // read: A fragment of token r, k-step ks at + 32 ks
   char* const Sg = Stg + wave * (32 * SROW);   // this wave's patch: [32 tokens][32 features]
 
-  float db2acc = 0.f, dzacc = 0.f;
-  const int valid_last = rem;   // rows of the ragged last tile
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-
-  if (n_tiles > 0) issue(0);
-  if (n_tiles > 1) {
-    issue(1);
-    wait_loads_and_barrier<LG>();   // tile 0 has landed, tile 1 may be in flight
-  } else {
-    wait_loads_and_barrier<0>();
-  }
-
-  auto tile = [&](auto TAILC, auto SQC, int it) {
-    constexpr bool TAIL = decltype(TAILC)::value;      // fewer than 64 rows count
-    constexpr bool squared = decltype(SQC)::value;     // Phi = psi^2, psi = relu(.) otherwise
-    const char* const Xs = XV + (it & 1) * TB;
-    const char* const Vs = XV + (2 + (it & 1)) * TB;
-    const float* const tws = Tws + (it & 1) * 64;
+  auto u_start = [&]() {   // starts from the bias: no addition per element
+    f32x16 u;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const f32x4 bb = *reinterpret_cast<const f32x4*>(b1rows + 8 * i);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) u[4 * i + j] = bb[j];
+    }
+    return u;
+  };
+  // four hidden units of the lane's token: rectified into U, their signs (u > 0) into `s` from the right
+  auto u_store = [&](const f32x16& u, int i, int it, int tb, uint32_t& s) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      s = __builtin_amdgcn_alignbit(s, __builtin_bit_cast(uint32_t, 0.f - u[4 * i + j]), 31);
+    pin(s);
+    u32x2 pk;
+    pk[0] = pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f));
+    pk[1] = pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f));
+    *reinterpret_cast<u32x2*>(Us + (it & 1) * (64 * UPAD) + uwbase + 16 * i + tb * (32 * UPAD)) = pk;
+  };
+  // one word per token: unit 8i + 4g + j of the slice is bit 16 g + 15 - (4i + j); lane half g stores
+  // the tokens of half tile g
+  auto sign_word = [&](const uint32_t (&s)[2]) {
+    uint32_t w[2];
+#pragma unroll
+    for (int tb = 0; tb < 2; ++tb) {
+      float lo = __builtin_bit_cast(float, s[tb]), hi = lo;
+      half_swap(lo, hi);
+      w[tb] = __builtin_bit_cast(uint32_t, lo) | (__builtin_bit_cast(uint32_t, hi) << 16);
+    }
+    return g ? w[1] : w[0];
+  };
+  auto tile_row = [&](int it) {   // first token of the tile's 64 rows in the piece
+    return n_tokens < 64 ? 0 : 64 * it < n_tokens - 64 ? 64 * it : n_tokens - 64;
+  };
+  auto opaque_lane = [&]() {
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    const int xbase = tile_off<2 * D>(ln & 31, 8 * (ln >> 5));
+    return ln;
+  };
+  // fragment of token row r, k-step ks inside an x or vec tile: ^ 32 ks
+  auto x_base = [&](int ln) { return tile_off<2 * D>(ln & 31, 8 * (ln >> 5)); };
 
-    // ---- first half ----------------------------------------------------------
+  float db2acc = 0.f, dzacc = 0.f;
+  constexpr int PD = 4;
+  bf16x8 fr[PD];
+  if (n_tiles > 0) {
+    range.fill(Xr, 0, x_lds);
+    if (TW) load_tw(0);
+    range.fill(Vr, 0, v_lds);
+    if (n_tiles > 1) range.fill(Xr, 64, x_lds + TB);
+  }
+  settle(w1f);
+  settle(w2f);
+  settle(mf);
+  settle(b2v);
+  settle(zvv);
+  if (n_tiles > 0) {
+    wait_loads_and_barrier<0>();   // also: the bias is in LDS
+    const int xbase = x_base(opaque_lane());
+    uint32_t s[2] = {0u, 0u};
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
-      f32x16 u;   // starts from the bias: no addition per element
+      f32x16 u = u_start();
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const f32x4 bb = *reinterpret_cast<const f32x4*>(b1rows + 8 * i);
+      for (int ks = 0; ks < KS; ++ks)
+        u = mfma(w1f[ks], *reinterpret_cast<const bf16x8*>(XV + (xbase ^ (32 * ks)) + tb * (32 * 2 * D)), u);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) u[4 * i + j] = bb[j];
-      }
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        bf16x8 xf = *reinterpret_cast<const bf16x8*>(Xs + (xbase ^ (32 * ks)) + tb * (32 * 2 * D));
-        u = mfma(w1f[ks], xf, u);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        u32x2 pk;
-        pk[0] = pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f));
-        pk[1] = pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f));
-        *reinterpret_cast<u32x2*>(Us + uwbase + 16 * i + tb * (32 * UPAD)) = pk;
-      }
+      for (int i = 0; i < 4; ++i) u_store(u, i, 0, tb, s[tb]);
     }
-    lds_barrier();   // U complete
+    const uint32_t word = sign_word(s);
+    if (lane < n_tokens) Sgn[lane] = word;
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // U of tile 0 is complete
+    static_for<PD>([&](auto MC) {
+      fr[decltype(MC)::value] = *reinterpret_cast<const bf16x8*>(Us + urbase + 32 * decltype(MC)::value);
+    });
+  }
 
-    // ---- second half ---------------------------------------------------------
-#pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-      f32x16 ps = zero, dphi = zero;
-#pragma unroll
-      for (int ks = 0; ks < KS2; ++ks) {
-        bf16x8 uf = *reinterpret_cast<const bf16x8*>(Us + urbase + 32 * ks + tb * (32 * UPAD));
-        ps = mfma(uf, w2f[ks], ps);
+  auto tile_step = [&](auto MOREC, auto SQC, int it) {
+    constexpr bool MORE = decltype(MOREC)::value;      // a tile follows; this one is full
+    constexpr bool squared = decltype(SQC)::value;     // Phi = psi^2, psi = relu(.) otherwise
+    const char* const Vs = XV + (2 + (it & 1)) * TB;
+    const char* const Xs = XV + ((it + 1) & 1) * TB;
+    const char* const Uc = Us + (it & 1) * (64 * UPAD);
+    const float* const tws = Tws + (it & 1) * 64;
+    const int ln = opaque_lane();
+    const int xbase = x_base(ln);
+    const int first = range.first(64 * it), count = range.count(64 * it), row = tile_row(it);
+    const u32x4 Xd = rsrc_if(Xr, it + 2 < n_tiles);
+    const int xs = range.soff(64 * (it + 2)), vs = range.soff(64 * (it + 1));
+    const uint32_t xd = x_lds + (it & 1) * TB, vd = v_lds + ((it + 1) & 1) * TB;
+    constexpr int LH = KS2 + KS, F0 = 2 * LH, LF = MORE ? KS : 0, NM = F0 + 2 * LF;
+    static_assert(NM % PD == 0, "the fragment ring closes over a step");
+    f32x16 ps[2], dphi[2], u[2];
+    uint32_t sgn[2] = {0u, 0u};
+    float pdb[2] = {0.f, 0.f}, pdz[2] = {0.f, 0.f};   // a half's own sums: short chains of additions in fp32
+    auto fetch = [&](auto MC) {
+      constexpr int m = decltype(MC)::value;
+      if constexpr (m >= NM) {
+      } else if constexpr (m < F0) {
+        constexpr int tb = m / LH, n = m % LH;
+        if constexpr (n < KS2) fr[m % PD] = *reinterpret_cast<const bf16x8*>(Uc + urbase + 32 * n + tb * (32 * UPAD));
+        else fr[m % PD] = *reinterpret_cast<const bf16x8*>(Vs + (xbase ^ (32 * (n - KS2))) + tb * (32 * 2 * D));
+      } else {
+        constexpr int tb = (m - F0) / KS, n = (m - F0) % KS;
+        if constexpr (n == 0) u[tb] = u_start();
+        fr[m % PD] = *reinterpret_cast<const bf16x8*>(Xs + (xbase ^ (32 * n)) + tb * (32 * 2 * D));
       }
+    };
+    auto elements = [&](auto TBC, auto IC) {   // tokens 8 i + 4 g .. + 3 of the half, in two pairs
+      constexpr int tb = decltype(TBC)::value, q = decltype(IC)::value, i = q / 2;
+      float dp[2];
+      f32x2 tw = {1.f, 1.f};   // weights of zv
+      if (TW) tw = *reinterpret_cast<const f32x2*>(tws + 32 * tb + 8 * i + 4 * g + 2 * (q & 1));
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        bf16x8 vf = *reinterpret_cast<const bf16x8*>(Vs + (xbase ^ (32 * ks)) + tb * (32 * 2 * D));
-        dphi = mfma(vf, mf[ks], dphi);
+      for (int j = 0; j < 2; ++j) {
+        const int e = 2 * q + j;
+        const bool live = MORE || (unsigned)(32 * tb + 8 * i + 4 * g + (e & 3) - first) < (unsigned)count;
+        const float psi = fmaxf(ps[tb][e] + b2v, 0.f);
+        const float base = TW ? dphi[tb][e] + tw[j] * zvv : dphi[tb][e] + zvv;   // dL/dPhi
+        dp[j] = squared ? (psi + psi) * base : (psi > 0.f ? base : 0.f);
+        pdb[tb] += live ? dp[j] : 0.f;
+        // dL/dz_t is a sum over queries only
+        if (TW) pdz[tb] += live ? tw[j] * (squared ? psi * psi : psi) : 0.f;
       }
-      float pdb = 0.f, pdz = 0.f;   // the block's own sums: short chains of additions in fp32
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        f32x4 tw = {1.f, 1.f, 1.f, 1.f};   // weights of zv for tokens 32 tb + 8 i + 4 g + j
-        if (TW) tw = *reinterpret_cast<const f32x4*>(tws + 32 * tb + 8 * i + 4 * g);
-        float dp[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int e = 4 * i + j;
-          const bool live = !TAIL || 32 * tb + 8 * i + 4 * g + j < valid_last;
-          const float psi = fmaxf(ps[e] + b2v, 0.f);
-          const float base = TW ? dphi[e] + tw[j] * zvv : dphi[e] + zvv;   // dL/dPhi
-          dp[j] = squared ? (psi + psi) * base : (psi > 0.f ? base : 0.f);
-          pdb += live ? dp[j] : 0.f;
-          // dL/dz_t is a sum over queries only
-          if (TW) pdz += live ? tw[j] * (squared ? psi * psi : psi) : 0.f;
-        }
-#pragma unroll
-        for (int j = 0; j < 4; j += 2) {
-          const uint32_t pk = pack_bf16(dp[j], dp[j + 1]);
-          char* const w = Sg + (8 * i + 4 * g + j) * SROW + 2 * r;
-          *reinterpret_cast<bf16_t*>(w) = (bf16_t)pk;
-          *reinterpret_cast<bf16_t*>(w + SROW) = (bf16_t)(pk >> 16);
-        }
-      }
-      db2acc += pdb;
-      if (TW) dzacc += pdz;
-      // the patch leaves token-major: 4 chunks of 16 bytes per token row, two per lane
+      pin(pdb[tb]);
+      if (TW) pin(pdz[tb]);
+      const uint32_t pk = pack_bf16(dp[0], dp[1]);
+      char* const w = Sg + (8 * i + 4 * g + 2 * (q & 1)) * SROW + 2 * r;
+      *reinterpret_cast<bf16_t*>(w) = (bf16_t)pk;
+      *reinterpret_cast<bf16_t*>(w + SROW) = (bf16_t)(pk >> 16);
+    };
+    // the patch leaves token-major: 4 chunks of 16 bytes per token row, two per lane
+    auto leave = [&](int tb) {
 #pragma unroll
       for (int n = 0; n < 2; ++n) {
-        const int idx = ln + 64 * n;
-        const int row = idx >> 2, c = idx & 3;
-        const u32x4 val = *reinterpret_cast<const u32x4*>(Sg + row * SROW + 16 * c);
-        if (!TAIL || 32 * tb + row < valid_last)
-          *reinterpret_cast<u32x4*>(Pg + ((int64_t)it * 64 + 32 * tb + row) * (DP * 2) + wave * 64 + 16 * c) = val;
+        const int idx = ln + 64 * n, rw = idx >> 2, c = idx & 3;
+        const u32x4 val = *reinterpret_cast<const u32x4*>(Sg + rw * SROW + 16 * c);
+        if (MORE || (unsigned)(32 * tb + rw - first) < (unsigned)count)
+          *reinterpret_cast<u32x4*>(Pg + ((int64_t)row + 32 * tb + rw) * (DP * 2) + wave * 64 + 16 * c) = val;
       }
+    };
+    constexpr int kQ = 2;   // element pairs per slot
+    static_assert(!MORE || F0 + 2 + 8 / kQ < NM, "the second half leaves before the barrier");
+    static_for<NM>([&](auto MC) {
+      constexpr int m = decltype(MC)::value;
+      if constexpr (m < F0) {
+        constexpr int tb = m / LH, n = m % LH;
+        if constexpr (n < KS2) ps[tb] = mfma(fr[m % PD], w2f[n], n == 0 ? f32x16{} : ps[tb]);
+        else dphi[tb] = mfma(fr[m % PD], mf[n - KS2], n == KS2 ? f32x16{} : dphi[tb]);
+      } else {
+        constexpr int tb = (m - F0) / KS, n = (m - F0) % KS;
+        u[tb] = mfma(w1f[n], fr[m % PD], u[tb]);
+      }
+      fetch(std::integral_constant<int, m + PD>{});
+      if constexpr (MORE && m % 2 == 1 && m / 2 < 2 * R::LPT) {
+        constexpr int i = m / 2;
+        if constexpr (i < R::LPT) range.template load<i>(Xd, xs, xd);
+        else range.template load<i - R::LPT>(Vr, vs, vd);
+      }
+      if constexpr (MORE && TW && m == 4 * R::LPT + 1) load_tw(it + 1);
+      static_for<2>([&](auto TBC) {
+        constexpr int tb = decltype(TBC)::value, p = m - (tb + 1) * LH - 2;
+        if constexpr (p >= 0 && p * kQ < 8) {
+          static_for<kQ>([&](auto JC) { elements(TBC, std::integral_constant<int, p * kQ + decltype(JC)::value>{}); });
+        }
+        if constexpr (p == 8 / kQ) leave(tb);
+      });
+      if constexpr (MORE) {
+        constexpr int q = m - F0 - KS - 2;   // U of tokens 0..31 under the products of 32..63
+        if constexpr (D == 128 && q >= 0 && q < 4) u_store(u[0], q, it + 1, 0, sgn[0]);
+        if constexpr (D == 64 && m == NM - 1) static_for<4>([&](auto IC) { u_store(u[0], decltype(IC)::value, it + 1, 0, sgn[0]); });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    if constexpr (MORE) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) u_store(u[1], i, it + 1, 1, sgn[1]);
+      Sgn[tile_row(it + 1) + opaque_lane()] = sign_word(sgn);
+      wait_loads_and_barrier<5>();
+      static_for<PD>([&](auto MC) {
+        fr[decltype(MC)::value] = *reinterpret_cast<const bf16x8*>(Us + ((it + 1) & 1) * (64 * UPAD) + urbase +
+                                                                  32 * decltype(MC)::value);
+      });
+    } else {
+      static_for<8>([&](auto IC) { elements(std::integral_constant<int, 1>{}, IC); });
+      leave(1);
     }
-    if (it + 1 < n_tiles) {
-      // tile it+1 has landed: it is older than this (full) tile's NST stores; every wave is done
-      // with this tile's buffers and with U
-      wait_loads_and_barrier<NST>();
-      if (it + 2 < n_tiles) issue(it + 2);
+    db2acc += pdb[0];
+    db2acc += pdb[1];
+    if (TW) {
+      dzacc += pdz[0];
+      dzacc += pdz[1];
     }
   };
   auto all_tiles = [&](auto SQC) {   // the waves of both instances meet at the same barriers
-    for (int it = 0; it < n_full; ++it) tile(std::false_type{}, SQC, it);
-    if (rem > 0) tile(std::true_type{}, SQC, n_full);
+    for (int it = 0; it + 1 < n_tiles; ++it) tile_step(std::true_type{}, SQC, it);
+    if (n_tiles > 0) tile_step(std::false_type{}, SQC, n_tiles - 1);
   };
   if (wave * 32 >= DP / 2) all_tiles(std::true_type{});
   else all_tiles(std::false_type{});
@@ -446,21 +522,16 @@ hipError_t launch_act_grad(const ActGradArgs& a, int d, int grid, hipStream_t st
   return hipGetLastError();
 }
 
-// token range of piece sp of nsplit: whole tiles of 64 from `lo`, the last tile ragged
+// token range of piece sp of nsplit: whole tiles of 64 from `lo`, the last one ragged
 struct Piece {
   int64_t tok0;
-  int n_tiles;    // tiles of this piece
-  int last_rows;  // valid rows of its last tile (64 unless it is the range's last tile)
+  int tokens;
 };
 __device__ __forceinline__ Piece piece_of(int64_t lo, int64_t hi, int sp, int nsplit) {
   const int64_t nt = (hi - lo + 63) / 64;
   const int64_t t0 = nt * sp / nsplit, t1 = nt * (sp + 1) / nsplit;
-  Piece p;
-  p.tok0 = lo + 64 * t0;
-  p.n_tiles = (int)(t1 - t0);
-  p.last_rows = 64;
-  if (t1 == nt && nt > 0) p.last_rows = (int)((hi - lo) - 64 * (nt - 1));
-  return p;
+  const int64_t end = lo + 64 * t1 < hi ? lo + 64 * t1 : hi;
+  return Piece{lo + 64 * t0, (int)(end - (lo + 64 * t0))};
 }
 
 // first-layer bias of the wave's accumulator rows: register 4i+j is hidden unit
@@ -480,45 +551,66 @@ __device__ __forceinline__ BiasRows load_bias_rows(const float* bp) {
   return b;
 }
 
+// Per-lane offsets into the tiles, recomputed per tile from an opaque copy of the lane index: held
+// across a loop they would push resident operands out of registers.
+template <int D>
+struct GradOffsets {
+  int p, x, v;   // dpsi row, x row (k-step ks at ^ 32 ks), transposing reads of x (column block db at ^ 64 db)
+  __device__ __forceinline__ explicit GradOffsets(int lane) {
+    asm volatile("" : "+v"(lane));
+    const int r = lane & 31, g = lane >> 5;
+    p = tile_off<4 * D>(r, 8 * g);
+    x = tile_off<2 * D>(r, 8 * g);
+    v = tile_off<2 * D>(4 * g + ((lane & 15) >> 2), 16 * (r >> 4) + 4 * (lane & 3));
+  }
+};
+// transposing read of 16 tokens x 32 columns; the second half lies eight rows further down
+template <int ROWBYTES>
+__device__ __forceinline__ bf16x8 tr_fragment(const char* p, int off) {
+  return join_tr(lds_read_tr(reinterpret_cast<const bf16_t*>(p + off)),
+                 lds_read_tr(reinterpret_cast<const bf16_t*>(p + (off ^ 32) + 8 * ROWBYTES)));
+}
+
 // ------------------------------------------------------------------------------------
-// dW2 partial: part[f][hid] = sum_tok dpsi[tok][f] U[tok][hid].  Per tile the waves first
-// rebuild U = relu(W1 x + b1) in LDS (token-major, as the chunk-state kernel does; 16 MFMAs per
-// wave against 512 bytes per token that U would cost through HBM); then both operands are
-// token-major LDS tiles read with transposing loads (tokens become the contraction index).
-// Each wave owns 64 rows f and half of the columns.  The dpsi and x tiles of tile t+1 are
-// requested at the start of tile t.
+// dW2 partial: part[f][hid] = sum_tok dpsi[tok][f] U[tok][hid].  The waves rebuild U = relu(W1 x + b1)
+// of tile it+1 in LDS (token-major, as the chunk-state kernel does; 16 MFMAs per wave against 512
+// bytes per token that U would cost through HBM) while they multiply tile `it`; both operands
+// are token-major LDS tiles read with transposing loads (tokens become the contraction index).
+// Each wave owns 64 rows f and half of the columns.
+// Order of products: 16 tokens of dW2, U of 32 tokens, 16 tokens, U, 16, 16 -- U is rectified and stored
+// under the products that follow it.  Operands are read kLook reads ahead into a ring of kRing; one
+// barrier per tile, behind the last read of it.  X(it+2) and dpsi(it+1) are requested as a
+// step begins and have landed at its barrier.
 // ------------------------------------------------------------------------------------
 template <int D, int NW>
-__global__ void __launch_bounds__(64 * NW, 2)
-tn_gemm_kernel(TnGemmArgs a) {
+__device__ __forceinline__ void tn_body(const WeightGradSide& a, int H, int64_t N, int bh, int sp, int nsplit, char* Ts) {
   constexpr int W = 2 * D;          // features = hidden units
   constexpr int KS = D / 16;
   constexpr int ROWB = 2 * W;       // bytes per token row of dpsi and of U
   constexpr int TBY = 64 * ROWB;    // dpsi tile
   constexpr int TB = 64 * 2 * D;    // x tile
-  constexpr int SET = TBY + TB;
-  constexpr int NT = 64 * NW;
   constexpr int HB = W / 64;        // 32-column blocks per wave (half of the columns)
   static_assert(W / 64 == NW / 2, "waves form a (W/64) x 2 grid");
   static_assert(W / NW == 32, "each wave rebuilds 32 hidden units");
-
-  __shared__ __attribute__((aligned(1024))) char Ts[2 * SET];   // (dpsi tile, x tile) x 2
-  __shared__ __attribute__((aligned(1024))) char Us[2 * TBY];   // U of the current and of the next tile
+  char* const Pt = Ts;              // dpsi tiles 0/1
+  char* const Xt = Ts + 2 * TBY;    // x tiles 0/1
+  char* const Us = Xt + 2 * TB;     // U of the current and of the next tile
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, r = lane & 31, i16 = lane & 15;
   const int wf = wave >> 1, wh = wave & 1;
-
-  const int item = xcd_swizzle(blockIdx.x, a.items_per_xcd);
-  if (item >= a.n_items) return;
-  const int sp = item % a.nsplit;
-  const int bh = item / a.nsplit;
-  const int h = bh % a.H;
-  const Piece pc = piece_of(a.lo, a.hi, sp, a.nsplit);
-  const int64_t row0 = (int64_t)bh * a.N + pc.tok0;
+  const int h = bh % H;
+  const Piece pc = piece_of(a.lo, a.hi, sp, nsplit);
+  const int n_tiles = (pc.tokens + 63) / 64;
+  const int64_t row0 = (int64_t)bh * N + pc.tok0;
   const u32x4 Pr = make_rsrc_words(a.dpsi + row0 * W), Xr = make_rsrc_words(a.x + row0 * D);
+  const uint32_t p_lds = lds_address(Pt), x_lds = lds_address(Xt);
+  using RP = RangeTiles<ROWB, NW>;
+  using RX = RangeTiles<2 * D, NW>;
+  const RP prange(pc.tokens, wave, lane);
+  const RX xrange(pc.tokens, wave, lane);
 
   const BiasRows b1 = load_bias_rows(a.b1 + (int64_t)h * W + wave * 32);
   bf16x8 w1f[KS];   // A operands: row = hidden unit 32 wave + r, k = head dimension
@@ -527,115 +619,145 @@ tn_gemm_kernel(TnGemmArgs a) {
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) w1f[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
   }
-  int xoff[KS];
-#pragma unroll
-  for (int ks = 0; ks < KS; ++ks) xoff[ks] = tile_off<2 * D>(r, 16 * ks + 8 * g);
-  int uwoff[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) uwoff[i] = r * ROWB + (((wave * 4 + i) ^ swz<256>(r)) << 4) + 8 * g;
-
-  int xlo[2], xhi[2], ylo[HB], yhi[HB];
-#pragma unroll
-  for (int fb = 0; fb < 2; ++fb) {
-    const int col = 64 * wf + 32 * fb + 16 * (r >> 4) + 4 * (i16 & 3);
-    xlo[fb] = tile_off<ROWB>(4 * g + (i16 >> 2), col);
-    xhi[fb] = tile_off<ROWB>(8 + 4 * g + (i16 >> 2), col);
-  }
-#pragma unroll
-  for (int hb = 0; hb < HB; ++hb) {
-    const int col = (W / 2) * wh + 32 * hb + 16 * (r >> 4) + 4 * (i16 & 3);
-    ylo[hb] = tile_off<ROWB>(4 * g + (i16 >> 2), col);
-    yhi[hb] = tile_off<ROWB>(8 + 4 * g + (i16 >> 2), col);
-  }
-
   f32x16 acc[2][HB];
 #pragma unroll
   for (int fb = 0; fb < 2; ++fb)
 #pragma unroll
-    for (int hb = 0; hb < HB; ++hb)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[fb][hb][e] = 0.f;
+    for (int hb = 0; hb < HB; ++hb) acc[fb][hb] = f32x16{};
 
-  const uint32_t ts_lds = lds_address(Ts);
-  const int pvoff = tile_voff_full<ROWB, NW>(wave, lane), xvoff = tile_voff_full<2 * D, NW>(wave, lane);
-  auto valid_of = [&](int it) { return (it + 1 < pc.n_tiles) ? 64 : pc.last_rows; };
-  auto issue_p = [&](int it) {
-    tile_load_fast<ROWB, TBY, NW>(Pr, __builtin_amdgcn_readfirstlane(it * TBY), ts_lds + (it & 1) * SET, wave, lane,
-                                  valid_of(it), pvoff);
+  if (n_tiles > 0) {
+    xrange.fill(Xr, 0, x_lds);
+    prange.fill(Pr, 0, p_lds);
+    if (n_tiles > 1) xrange.fill(Xr, 64, x_lds + TB);
+  }
+  settle(w1f);
+  auto u_start = [&]() {
+    f32x16 u;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) u[e] = g ? b1.hi[e] : b1.lo[e];
+    return u;
   };
-  auto issue_x = [&](int it) {
-    tile_load_fast<2 * D, TB, NW>(Xr, __builtin_amdgcn_readfirstlane(it * TB), ts_lds + (it & 1) * SET + TBY, wave,
-                                  lane, valid_of(it), xvoff);
+  // U of tile `it`: tokens that are not of this tile (ragged last one) store zeros
+  auto u_store = [&](const f32x16& u, int i, int it, int tb) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int tok = ln & 31;
+    const bool live = (unsigned)(32 * tb + tok - xrange.first(64 * it)) < (unsigned)xrange.count(64 * it);
+    u32x2 pk;
+    pk[0] = live ? pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f)) : 0u;
+    pk[1] = live ? pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f)) : 0u;
+    *reinterpret_cast<u32x2*>(Us + (it & 1) * TBY + tb * (32 * ROWB) + tok * ROWB + (((wave * 4 + i) ^ swz<ROWB>(tok)) << 4) +
+                              8 * (ln >> 5)) = pk;
   };
-  // U^T slice of tile `it` = relu(W1[slice] X^T + b1[slice]) -> U[token][hidden] in the buffer of
-  // the tile's parity
-  auto build_u = [&](int it) {
-    const char* const Xs = Ts + (it & 1) * SET + TBY;
-    char* const Ud = Us + (it & 1) * TBY;
+  auto x_fragment = [&](int it, const GradOffsets<D>& o, int tb, int ks) {
+    return *reinterpret_cast<const bf16x8*>(Xt + (it & 1) * TB + (o.x ^ (32 * ks)) + tb * (32 * 2 * D));
+  };
+  constexpr int kRing = 8, kLook = D == 128 ? 3 : 4;
+  bf16x8 fr[kRing];
+  // column of the wave's first 32 of dpsi (rows of dW2) and of U
+  auto f_base = [&](const GradOffsets<D>&, int col) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    return tile_off<ROWB>(4 * (ln >> 5) + ((ln & 15) >> 2), col + 16 * ((ln & 31) >> 4) + 4 * (ln & 3));
+  };
+  // read q of the dW2 part of a tile: per 16 tokens two blocks of 32 rows, then HB blocks of 32 columns
+  auto s_read = [&](int it, int pb, int ub, int s, int q) {
+    if (q < 2) return tr_fragment<ROWB>(Pt + (it & 1) * TBY + s * 16 * ROWB, pb ^ (64 * q));
+    return tr_fragment<ROWB>(Us + (it & 1) * TBY + s * 16 * ROWB, ub ^ (64 * (q - 2)));
+  };
+  if (n_tiles > 0) {
+    wait_loads_and_barrier<0>();
+    const GradOffsets<D> o(lane);
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
-      f32x16 u;
+      f32x16 u = u_start();
 #pragma unroll
-      for (int e = 0; e < 16; ++e) u[e] = g ? b1.hi[e] : b1.lo[e];
+      for (int ks = 0; ks < KS; ++ks) u = mfma(w1f[ks], x_fragment(0, o, tb, ks), u);
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        bf16x8 xf = *reinterpret_cast<const bf16x8*>(Xs + xoff[ks] + tb * (32 * 2 * D));
-        u = mfma(w1f[ks], xf, u);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        u32x2 pk;
-        pk[0] = pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f));
-        pk[1] = pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f));
-        *reinterpret_cast<u32x2*>(Ud + uwoff[i] + tb * (32 * ROWB)) = pk;
-      }
+      for (int i = 0; i < 4; ++i) u_store(u, i, 0, tb);
     }
+    lds_barrier();   // U of tile 0 is complete
+    const int pb = f_base(o, 64 * wf), ub = f_base(o, (W / 2) * wh);
+    static_for<kLook>([&](auto QC) { fr[decltype(QC)::value] = s_read(0, pb, ub, 0, decltype(QC)::value); });
+  }
+  auto tile_step = [&](auto MOREC, int it) {
+    constexpr bool MORE = decltype(MOREC)::value;
+    const GradOffsets<D> o(lane);
+    const int pb = f_base(o, 64 * wf), ub = f_base(o, (W / 2) * wh);
+    const u32x4 Xd = rsrc_if(Xr, it + 2 < n_tiles);
+    const int xs = xrange.soff(64 * (it + 2)), ps = prange.soff(64 * (it + 1));
+    const uint32_t xd = x_lds + (it & 1) * TB, pd = p_lds + ((it + 1) & 1) * TBY;
+    // groups of products: S0 U0 S1 U1 S2 S3; a group S has LS products on RS reads, a group U KS on KS
+    constexpr int LS = 2 * HB, RS = 2 + HB, LU = MORE ? KS : 0;
+    constexpr int NM = 4 * LS + 2 * LU, NR = 4 * RS + 2 * LU;
+    static_assert(!MORE || NR % kRing == 0, "the ring closes over a step");
+    // group of product m (0..5), its first product and its first read
+    auto group = [](int m) {
+      return m < LS ? 0 : m < LS + LU ? 1 : m < 2 * LS + LU ? 2 : m < 2 * LS + 2 * LU ? 3 : m < 3 * LS + 2 * LU ? 4 : 5;
+    };
+    auto s_of = [](int gr) { return gr == 5 ? 3 : gr / 2; };
+    auto is_u = [](int gr) { return gr == 1 || gr == 3; };
+    f32x16 u[2];
+    auto base_m = [](int gr) {   // products before group gr
+      const int sg = gr == 0 ? 0 : gr == 1 ? 1 : gr == 2 ? 1 : gr == 3 ? 2 : gr == 4 ? 2 : 3;
+      const int ug = gr <= 1 ? 0 : gr <= 3 ? 1 : 2;
+      return sg * LS + ug * LU;
+    };
+    auto base_r = [](int gr) {   // reads before group gr
+      const int sg = gr == 0 ? 0 : gr == 1 ? 1 : gr == 2 ? 1 : gr == 3 ? 2 : gr == 4 ? 2 : 3;
+      const int ug = gr <= 1 ? 0 : gr <= 3 ? 1 : 2;
+      return sg * RS + ug * LU;
+    };
+    auto need = [=](int m) {     // last read that product m takes
+      const int gr = group(m), n = m - base_m(gr);
+      return base_r(gr) + (is_u(gr) ? n : 2 + n / 2);
+    };
+    auto read = [&](auto QC) {
+      constexpr int q = decltype(QC)::value;
+      if constexpr (q >= NR) {
+        if constexpr (MORE) fr[q % kRing] = s_read(it + 1, pb, ub, 0, q - NR);
+      } else {
+        constexpr int gr = q < base_r(1) ? 0 : q < base_r(2) ? 1 : q < base_r(3) ? 2 : q < base_r(4) ? 3 : q < base_r(5) ? 4 : 5;
+        constexpr int n = q - base_r(gr);
+        if constexpr (is_u(gr)) {
+          fr[q % kRing] = x_fragment(it + 1, o, gr / 2, n);
+        } else {
+          fr[q % kRing] = s_read(it, pb, ub, s_of(gr), n);
+        }
+      }
+    };
+    // the barrier stands behind the last read of the tile and before the first of the next one
+    constexpr int BAR = base_m(5) + (need(base_m(5) - 1) + 1 + kLook < NR ? 1 : 0);
+    static_assert(need(BAR - 1) + 1 + kLook == NR, "all of the tile has been read at the barrier");
+    static_assert(base_m(4) + 6 <= BAR + (D == 64 ? 2 : 0), "U is stored before the barrier that publishes it");
+    static_for<NM>([&](auto MC) {
+      constexpr int m = decltype(MC)::value, gr = group(m), n = m - base_m(gr), rb = base_r(gr);
+      if constexpr (MORE && m == BAR) wait_loads_and_barrier<0>();
+      if constexpr (is_u(gr) && n == 0) u[gr / 2] = u_start();
+      if constexpr (is_u(gr)) u[gr / 2] = mfma(w1f[n], fr[(rb + n) % kRing], u[gr / 2]);
+      else acc[n & 1][n / 2] = mfma(fr[(rb + (n & 1)) % kRing], fr[(rb + 2 + n / 2) % kRing], acc[n & 1][n / 2]);
+      constexpr int from = m == 0 ? kLook : need(m - 1) + 1 + kLook, to = need(m) + 1 + kLook;
+      static_for<(to > from ? to - from : 0)>([&](auto JC) { read(std::integral_constant<int, from + decltype(JC)::value>{}); });
+      if constexpr (MORE && m % 2 == 1 && m / 2 < RX::LPT + RP::LPT) {
+        constexpr int i = m / 2;
+        if constexpr (i < RX::LPT) xrange.template load<i>(Xd, xs, xd);
+        else prange.template load<i - RX::LPT>(Pr, ps, pd);
+      }
+      static_for<2>([&](auto TBC) {   // U goes to LDS under the group behind it
+        constexpr int tb = decltype(TBC)::value, q = m - base_m(tb ? 4 : 2) - 2;
+        if constexpr (MORE && D == 128 && q >= 0 && q < 4) u_store(u[tb], q, it + 1, tb);
+        if constexpr (MORE && D == 64 && q >= 0 && q < 2) {
+          u_store(u[tb], 2 * q, it + 1, tb);
+          u_store(u[tb], 2 * q + 1, it + 1, tb);
+        }
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
   };
-  // One barrier per tile: in step `it` the waves rebuild U of tile it+1 while they multiply
-  // tile it, so the two phases overlap inside every wave.  x runs one tile ahead of dpsi.
-  if (pc.n_tiles > 0) {
-    issue_x(0);
-    issue_p(0);
-    settle(w1f);
-    wait_loads_and_barrier<0>();
-    if (pc.n_tiles > 1) issue_x(1);
-    build_u(0);
-  }
-  for (int it = 0; it < pc.n_tiles; ++it) {
-    const int valid = valid_of(it);
-    char* const Ps = Ts + (it & 1) * SET;
-    const char* const Uc = Us + (it & 1) * TBY;
-    // dpsi of tile `it` and x of tile it+1 have landed (the only loads in flight); U of tile
-    // `it` is complete; every wave is done with tile it-1
-    wait_loads_and_barrier<0>();
-    if (it + 1 < pc.n_tiles) issue_p(it + 1);
-    if (it + 2 < pc.n_tiles) issue_x(it + 2);
-    if (valid < 64) {  // rows past the range hold copies of the last row: clear them in dpsi
-      const u32x4 z4 = {0u, 0u, 0u, 0u};
-      for (int o = valid * ROWB + tid * 16; o < TBY; o += NT * 16) *reinterpret_cast<u32x4*>(Ps + o) = z4;
-      lds_barrier();
-    }
-    if (it + 1 < pc.n_tiles) build_u(it + 1);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int so = s * 16 * ROWB;
-      bf16x8 af[2], bfr[HB];
-#pragma unroll
-      for (int fb = 0; fb < 2; ++fb)
-        af[fb] = join_tr(lds_read_tr(reinterpret_cast<const bf16_t*>(Ps + xlo[fb] + so)),
-                         lds_read_tr(reinterpret_cast<const bf16_t*>(Ps + xhi[fb] + so)));
-#pragma unroll
-      for (int hb = 0; hb < HB; ++hb)
-        bfr[hb] = join_tr(lds_read_tr(reinterpret_cast<const bf16_t*>(Uc + ylo[hb] + so)),
-                          lds_read_tr(reinterpret_cast<const bf16_t*>(Uc + yhi[hb] + so)));
-#pragma unroll
-      for (int fb = 0; fb < 2; ++fb)
-#pragma unroll
-        for (int hb = 0; hb < HB; ++hb) acc[fb][hb] = mfma(af[fb], bfr[hb], acc[fb][hb]);
-    }
-  }
+  for (int it = 0; it + 1 < n_tiles; ++it) tile_step(std::true_type{}, it);
+  if (n_tiles > 0) tile_step(std::false_type{}, n_tiles - 1);
 
-  float* P = a.part + (int64_t)item * W * W;
+  float* P = a.part_w2 + ((int64_t)bh * nsplit + sp) * W * W;
 #pragma unroll
   for (int fb = 0; fb < 2; ++fb)
 #pragma unroll
@@ -647,146 +769,156 @@ tn_gemm_kernel(TnGemmArgs a) {
       }
 }
 
-hipError_t launch_tn_gemm(const TnGemmArgs& a, int d, int grid, hipStream_t stream) {
-  if (d == 128) hipLaunchKernelGGL((tn_gemm_kernel<128, 8>), dim3(grid), dim3(512), 0, stream, a);
-  else hipLaunchKernelGGL((tn_gemm_kernel<64, 4>), dim3(grid), dim3(256), 0, stream, a);
-  return hipGetLastError();
-}
-
 // ------------------------------------------------------------------------------------
-// First-layer gradients.  Wave w owns hidden units [32w, 32w + 32): its rows of W1 and of
-// W2^T stay in registers as B operands.  Per tile, with tokens in accumulator rows and the
-// wave's hidden units in lanes: U slice = X W1[slice]^T + b1 (only its sign is needed),
-// dU slice = dpsi W2[:, slice], zero where U <= 0; then x^T dU into the wave's [d][32] slice
-// of dW1^T, exactly as the chunk-state kernel accumulates V^T phi.
+// First-layer gradients.  Wave w owns hidden units [32w, 32w + 32): its rows of W2^T stay in
+// registers as B operands.  Per tile, with tokens in accumulator rows and the wave's hidden units in
+// lanes: dU slice = dpsi W2[:, slice], zero where U <= 0 (the sign words of act_grad_kernel; with U formed
+// again for its sign alone, 16 of 64 products per tile and 32 registers, nothing was left to read
+// ahead into); then x^T dU into the wave's [d][32] slice of dW1^T, exactly as the chunk-state kernel
+// accumulates V^T phi.
+// Order of products: dU of tokens 0..31, of 32..63, x^T dU of both; the gates of a half lie under
+// the products that follow it.
 // ------------------------------------------------------------------------------------
 template <int D, int NW>
-__global__ void __launch_bounds__(64 * NW, 2)
-hid_grad_kernel(HidGradArgs a) {
+__device__ __forceinline__ void hid_body(const WeightGradSide& a, int H, int64_t N, int bh, int sp, int nsplit, char* Ts,
+                                         uint32_t* Sw) {
   constexpr int HID = 2 * D, DP = 2 * D;
-  constexpr int KS = D / 16;
   constexpr int KS2 = DP / 16;      // k-steps across the features
   constexpr int DB = D / 32;
   constexpr int TB = 64 * 2 * D;    // x tile
   constexpr int UROW = DP * 2;      // bytes of a dpsi row
   constexpr int TBU = 64 * UROW;
-  constexpr int SET = TBU + TB;
   static_assert(HID / NW == 32, "each wave owns 32 hidden units");
-
-  __shared__ __attribute__((aligned(1024))) char Ts[2 * SET];   // (dpsi tile, x tile) x 2
+  char* const Pt = Ts;              // dpsi tiles 0/1
+  char* const Xt = Ts + 2 * TBU;    // x tiles 0/1
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, r = lane & 31, i16 = lane & 15;
-
-  const int item = xcd_swizzle(blockIdx.x, a.items_per_xcd);
-  if (item >= a.n_items) return;
-  const int sp = item % a.nsplit;
-  const int bh = item / a.nsplit;
-  const int h = bh % a.H;
-  const Piece pc = piece_of(a.lo, a.hi, sp, a.nsplit);
-  const int64_t row0 = (int64_t)bh * a.N + pc.tok0;
+  const int g = lane >> 5, r = lane & 31;
+  const int h = bh % H;
+  const Piece pc = piece_of(a.lo, a.hi, sp, nsplit);
+  const int n_tiles = (pc.tokens + 63) / 64;
+  const int64_t row0 = (int64_t)bh * N + pc.tok0;
   const u32x4 Pr = make_rsrc_words(a.dpsi + row0 * DP), Xr = make_rsrc_words(a.x + row0 * D);
+  const u32x4 Sr = make_rsrc_words(a.signs + ((int64_t)bh * NW + wave) * N + pc.tok0);
+  const uint32_t p_lds = lds_address(Pt), x_lds = lds_address(Xt);
+  uint32_t* const sw = Sw + wave * 128;   // this wave's words of two tiles
+  const uint32_t s_lds = lds_address(Sw) + wave * 512;
+  using RP = RangeTiles<UROW, NW>;
+  using RX = RangeTiles<2 * D, NW>;
+  const RP prange(pc.tokens, wave, lane);
+  const RX xrange(pc.tokens, wave, lane);
+  auto load_signs = [&](int it) {
+    const int row = pc.tokens < 64 ? 0 : 64 * it < pc.tokens - 64 ? 64 * it : pc.tokens - 64;
+    direct_load_4(Sr, 4 * (lane < pc.tokens ? lane : pc.tokens - 1), __builtin_amdgcn_readfirstlane(4 * row),
+                  s_lds + (it & 1) * 256);
+  };
 
   const int unit = wave * 32 + r;   // this lane's hidden unit
-  float b1v = a.b1[(int64_t)h * HID + unit];
-  bf16x8 w1f[KS];                   // B operands: column = hidden unit, k = head dimension
-  {
-    const bf16_t* p = a.w1 + ((int64_t)h * HID + unit) * D + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) w1f[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-  }
+  // where its sign stands in a word: unit 8i + 4g + j of the slice is bit 16 g + 15 - (4i + j)
+  const int bit = 16 * ((r >> 2) & 1) + 15 - (4 * (r >> 3) + (r & 3));
   bf16x8 w2tf[KS2];                 // B operands: column = hidden unit, k = feature
   {
     const bf16_t* p = a.w2t + ((int64_t)h * HID + unit) * DP + 8 * g;
 #pragma unroll
     for (int ks = 0; ks < KS2; ++ks) w2tf[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
   }
-  // Fragment offsets inside the tiles are one XOR away from a per-lane constant (the chunk bits
-  // do not overlap the row bits).  They are derived per tile from an opaque copy of the lane
-  // index: held across the loop they would push resident operands out of registers.
-
   f32x16 acc[DB];
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
-#pragma unroll
-    for (int e = 0; e < 16; ++e) acc[db][e] = 0.f;
+  for (int db = 0; db < DB; ++db) acc[db] = f32x16{};
   float dbacc = 0.f;
-  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-  const uint32_t ts_lds = lds_address(Ts);
-  const int pvoff = tile_voff_full<UROW, NW>(wave, lane), xvoff = tile_voff_full<2 * D, NW>(wave, lane);
-  auto issue = [&](int it) {   // requested one tile step ahead of its use
-    const int valid = (it + 1 < pc.n_tiles) ? 64 : pc.last_rows;
-    const uint32_t base = ts_lds + (it & 1) * SET;
-    tile_load_fast<UROW, TBU, NW>(Pr, __builtin_amdgcn_readfirstlane(it * TBU), base, wave, lane, valid, pvoff);
-    tile_load_fast<2 * D, TB, NW>(Xr, __builtin_amdgcn_readfirstlane(it * TB), base + TBU, wave, lane, valid, xvoff);
-  };
-  if (pc.n_tiles > 0) issue(0);
-  settle(w1f);
-  settle(w2tf);
-  settle(b1v);
-  for (int it = 0; it < pc.n_tiles; ++it) {
-    const int valid = (it + 1 < pc.n_tiles) ? 64 : pc.last_rows;
-    const char* const Ps = Ts + (it & 1) * SET;
-    const char* const Xs = Ps + TBU;
-    // tile `it` has landed (the only loads in flight) and every wave is done with tile it-1
-    wait_loads_and_barrier<0>();
-    if (it + 1 < pc.n_tiles) issue(it + 1);
-    int ln = lane;
-    asm volatile("" : "+v"(ln));
-    const int lr = ln & 31, lg = ln >> 5, li = ln & 15;
-    const int pbase = lr * UROW + ((lg ^ swz<256>(lr)) << 4);   // dpsi row lr, chunk 2 ks + g at ^ 32 ks
-    const int xbase = tile_off<2 * D>(lr, 8 * lg);             // x row lr, k-step ks at ^ 32 ks
-    int voff_lo[DB], voff_hi[DB];                              // transposing reads of x
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const int col = 32 * db + 16 * (lr >> 4) + 4 * (li & 3);
-      voff_lo[db] = tile_off<2 * D>(4 * lg + (li >> 2), col);
-      voff_hi[db] = tile_off<2 * D>(8 + 4 * lg + (li >> 2), col);
-    }
-#pragma unroll
-    for (int tb = 0; tb < 2; ++tb) {
-      f32x16 uu, du = zero;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) uu[e] = b1v;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        bf16x8 xf = *reinterpret_cast<const bf16x8*>(Xs + (xbase ^ (32 * ks)) + tb * (32 * 2 * D));
-        uu = mfma(xf, w1f[ks], uu);
-      }
-#pragma unroll
-      for (int ks = 0; ks < KS2; ++ks) {
-        bf16x8 pf = *reinterpret_cast<const bf16x8*>(Ps + (pbase ^ (32 * ks)) + tb * (32 * UROW));
-        du = mfma(pf, w2tf[ks], du);
-      }
-      float part = 0.f;
-#pragma unroll
-      for (int e = 0; e < 16; ++e) {
-        const int t = 32 * tb + 8 * (e >> 2) + 4 * g + (e & 3);
-        float x = du[e];
-        if (!(uu[e] > 0.f) || t >= valid) x = 0.f;
-        x = bf16_round(x);
-        du[e] = x;
-        part += x;
-      }
-      dbacc += part;
-#pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        bf16x8 fb = acc_to_operand(du, s);
-#pragma unroll
-        for (int db = 0; db < DB; ++db) {
-          const int so = (2 * tb + s) * (16 * 2 * D);
-          i16x4 vlo = lds_read_tr(reinterpret_cast<const bf16_t*>(Xs + voff_lo[db] + so));
-          i16x4 vhi = lds_read_tr(reinterpret_cast<const bf16_t*>(Xs + voff_hi[db] + so));
-          acc[db] = mfma(join_tr(vlo, vhi), fb, acc[db]);
-        }
-      }
-    }
+  if (n_tiles > 0) {
+    prange.fill(Pr, 0, p_lds);
+    xrange.fill(Xr, 0, x_lds);
+    load_signs(0);
   }
+  settle(w2tf);
+  constexpr int PD = 4;   // fragments read ahead of their products
+  bf16x8 fr[PD];
+  auto p_fragment = [&](int it, const GradOffsets<D>& o, int tb, int ks) {
+    return *reinterpret_cast<const bf16x8*>(Pt + (it & 1) * TBU + (o.p ^ (32 * ks)) + tb * (32 * UROW));
+  };
+  if (n_tiles > 0) {
+    wait_loads_and_barrier<0>();
+    const GradOffsets<D> o(lane);
+    static_for<PD>([&](auto MC) { fr[decltype(MC)::value] = p_fragment(0, o, 0, decltype(MC)::value); });
+  }
+  auto tile_step = [&](auto MOREC, int it) {
+    constexpr bool MORE = decltype(MOREC)::value;
+    const GradOffsets<D> o(lane);
+    const int first = xrange.first(64 * it), count = xrange.count(64 * it);
+    const int xs = xrange.soff(64 * (it + 1)), ps = prange.soff(64 * (it + 1));
+    const uint32_t xd = x_lds + ((it + 1) & 1) * TB, pd = p_lds + ((it + 1) & 1) * TBU;
+    constexpr int LH = KS2, LA = 2 * DB, A0 = 2 * LH, NM = A0 + 2 * LA;
+    static_assert(NM % PD == 0, "the fragment ring closes over a step");
+    f32x16 du[2];
+    uint32_t fb[2][8];
+    u32x4 words;
+    float part[2] = {0.f, 0.f};
+    auto fetch = [&](auto MC) {
+      constexpr int m = decltype(MC)::value;
+      if constexpr (m >= NM) {
+        if constexpr (MORE) fr[m % PD] = p_fragment(it + 1, o, 0, m - NM);
+      } else if constexpr (m < A0) {
+        fr[m % PD] = p_fragment(it, o, m / LH, m % LH);
+      } else {
+        constexpr int n = m - A0;   // 16-token step n / DB, column block n % DB
+        fr[m % PD] = tr_fragment<2 * D>(Xt + (it & 1) * TB + n / DB * (16 * 2 * D), o.v ^ (64 * (n % DB)));
+      }
+    };
+    auto gate = [&](auto TBC, auto IC) {   // elements 2i, 2i+1: tokens 8 (i/2) + 4g + 2 (i%2) ..
+      constexpr int tb = decltype(TBC)::value, i = decltype(IC)::value;
+      if constexpr (i % 2 == 0)
+        words = *reinterpret_cast<const u32x4*>(sw + (it & 1) * 64 + 32 * tb + 8 * (i / 2) + 4 * g);
+      float x[2];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int e = 2 * i + j;
+        const int open = __builtin_amdgcn_sbfe((int)words[e & 3], bit, 1);   // 0 or all ones
+        const float d = du[tb][e];   // by value: a bit cast of du[tb][e] itself reads element 0
+        x[j] = __builtin_bit_cast(float, __builtin_bit_cast(int, d) & open);
+        if (!MORE && (unsigned)(32 * tb + 8 * (e >> 2) + 4 * g + (e & 3) - first) >= (unsigned)count) x[j] = 0.f;
+      }
+      fb[tb][i] = pack_bf16(x[0], x[1]);
+      part[tb] = sum_pair<false>(fb[tb][i], part[tb]);   // db1 sums what dW1 sums
+      pin(part[tb]);
+      pin(fb[tb][i]);
+    };
+    constexpr int kPairs = 8 / LA;   // element pairs per slot
+    static_for<NM>([&](auto MC) {
+      constexpr int m = decltype(MC)::value;
+      if constexpr (MORE && m == NM - PD) wait_loads_and_barrier<0>();
+      if constexpr (m < A0) {
+        constexpr int tb = m / LH, n = m % LH;
+        du[tb] = mfma(fr[m % PD], w2tf[n], n == 0 ? f32x16{} : du[tb]);
+      } else {
+        constexpr int tb = (m - A0) / LA, n = (m - A0) % LA, s = n / DB;
+        const u32x4 w = {fb[tb][4 * s], fb[tb][4 * s + 1], fb[tb][4 * s + 2], fb[tb][4 * s + 3]};
+        acc[n % DB] = mfma(fr[m % PD], __builtin_bit_cast(bf16x8, w), acc[n % DB]);
+      }
+      fetch(std::integral_constant<int, m + PD>{});
+      if constexpr (MORE && m % 2 == 1 && m / 2 < RX::LPT + RP::LPT) {
+        constexpr int i = m / 2;
+        if constexpr (i < RX::LPT) xrange.template load<i>(Xr, xs, xd);
+        else prange.template load<i - RX::LPT>(Pr, ps, pd);
+      }
+      if constexpr (MORE && m == 2 * (RX::LPT + RP::LPT) + 1) load_signs(it + 1);
+      static_for<2>([&](auto TBC) {
+        constexpr int tb = decltype(TBC)::value, p = m - (tb ? A0 : LH) - 2;
+        if constexpr (p >= 0 && kPairs * p < 8)
+          static_for<kPairs>([&](auto JC) { gate(TBC, std::integral_constant<int, kPairs * p + decltype(JC)::value>{}); });
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    dbacc += part[0];
+    dbacc += part[1];
+  };
+  for (int it = 0; it + 1 < n_tiles; ++it) tile_step(std::true_type{}, it);
+  if (n_tiles > 0) tile_step(std::false_type{}, n_tiles - 1);
 
-  float* P = a.part + (int64_t)item * (D * HID + HID);
+  float* P = a.part_w1 + ((int64_t)bh * nsplit + sp) * (D * HID + HID);
 #pragma unroll
   for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -798,9 +930,29 @@ hid_grad_kernel(HidGradArgs a) {
   if (g == 0) P[D * HID + unit] = tot;
 }
 
-hipError_t launch_hid_grad(const HidGradArgs& a, int d, int grid, hipStream_t stream) {
-  if (d == 128) hipLaunchKernelGGL((hid_grad_kernel<128, 8>), dim3(grid), dim3(512), 0, stream, a);
-  else hipLaunchKernelGGL((hid_grad_kernel<64, 4>), dim3(grid), dim3(256), 0, stream, a);
+// Both kinds of weight gradient of both sides in one launch: per side and (b, h), n2 pieces of
+// the tokens for dW2 and n1 for dW1.  Four launches (dW2 and dW1 of the queries, then of the keys), each
+// with its weights to load, its last tile to wait for and 21 partial sums per (b, h), took 436 us at
+// the 480p shape and 157 at 320x480; this one takes 340 and 103, half as many partial sums, and the two
+// kinds share what they read in the last-level cache.  Bound by memory and by the products about
+// alike: 1.15 GB of operands through the caches at 480p, 0.87 PFLOP/s.
+template <int D, int NW>
+__global__ void __launch_bounds__(64 * NW, 2)
+weight_grad_kernel(WeightGradArgs a) {
+  // dW2: two dpsi, x and U tiles (all of the CU's LDS at d = 128); dW1: two dpsi and x tiles, sign words
+  __shared__ __attribute__((aligned(1024))) char Ts[2 * 64 * (4 * D + 2 * D + 4 * D)];
+  const int item = xcd_swizzle(blockIdx.x, a.items_per_xcd);
+  if (item >= a.n_items) return;
+  const int per = a.n2 + a.n1, which = item / per, j = item % per;
+  const int bh = which % a.BH;
+  const WeightGradSide& s = a.side[which / a.BH];
+  if (j < a.n2) tn_body<D, NW>(s, a.H, a.N, bh, j, a.n2, Ts);
+  else hid_body<D, NW>(s, a.H, a.N, bh, j - a.n2, a.n1, Ts, reinterpret_cast<uint32_t*>(Ts + 2 * 64 * 6 * D));
+}
+
+hipError_t launch_weight_grad(const WeightGradArgs& a, int d, int grid, hipStream_t stream) {
+  if (d == 128) hipLaunchKernelGGL((weight_grad_kernel<128, 8>), dim3(grid), dim3(512), 0, stream, a);
+  else hipLaunchKernelGGL((weight_grad_kernel<64, 4>), dim3(grid), dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -182,6 +182,7 @@ struct ActGradArgs {
   const bf16_t* M;      // [BH, slots, d, dp]  S_t (query side) or R_tau (key side), transposed
   const float* zv;      // [BH, slots, dp]     z_t or r_tau
   bf16_t* dpsi;         // [BH, N, dp]
+  uint32_t* signs;      // [BH, 2d/32, N]  which hidden units of a token are positive, 32 to a word
   float* db2_part;      // [n_items, dp]  sum over the item's tokens of dpsi
   float* dz_part;       // [n_items, dp]  sum of tokw * phi (query side), or null
   int H, T, HW, chunk, overlap;
@@ -189,31 +190,27 @@ struct ActGradArgs {
   int n_seg, nsplit, slots, n_items, items_per_xcd;
 };
 
-// dW2 partial sums: part[f][hid] = sum over a token range of dpsi[tok][f] * U[tok][hid], with
-// U = relu(W1 x + b1) recomputed from x (cheaper than moving it through HBM)
-struct TnGemmArgs {
+// Weight gradients of both sides.  dW2 partial sums: part_w2[f][hid] = sum over a token range of
+// dpsi[tok][f] * U[tok][hid], with U = relu(W1 x + b1) recomputed from x (cheaper than moving it through
+// HBM).  First layer: dU = (dpsi W2) * [U > 0] (signs from act_grad_kernel); part_w1 = x^T dU ([d][hidden]), then the column sums of
+// dU ([hidden]).
+struct WeightGradSide {
   const bf16_t* dpsi;   // [BH, N, 2d]
   const bf16_t* x;      // [BH, N, d]
+  const uint32_t* signs;   // [BH, 2d/32, N]
   const bf16_t* w1;     // [H, 2d, d]
   const float* b1;      // [H, 2d]
-  float* part;          // [BH * nsplit, 2d, 2d]
-  int H;
-  int64_t N, lo, hi;    // token range [lo, hi) of every (b, h)
-  int nsplit, n_items, items_per_xcd;
-};
-
-// First-layer gradients: dU = (dpsi W2) * [U > 0] with U recomputed from x;
-// part = x^T dU ([d][hidden]), then the column sums of dU ([hidden])
-struct HidGradArgs {
-  const bf16_t* dpsi;   // [BH, N, dp]
-  const bf16_t* x;      // [BH, N, d]
-  const bf16_t* w1;     // [H, hidden, d]
-  const float* b1;      // [H, hidden]
   const bf16_t* w2t;    // [H, hidden, dp]  W2 transposed
-  float* part;          // [BH * nsplit, d*hidden + hidden]
-  int H;
-  int64_t N, lo, hi;
-  int nsplit, n_items, items_per_xcd;
+  float* part_w2;       // [BH * n2, 2d, 2d]
+  float* part_w1;       // [BH * n1, d*hidden + hidden]
+  int64_t lo, hi;       // token range [lo, hi) of every (b, h)
+};
+struct WeightGradArgs {
+  WeightGradSide side[2];   // queries, keys
+  int H, BH;
+  int64_t N;
+  int n2, n1;               // pieces per side and (b, h) for dW2 and for dW1
+  int n_items, items_per_xcd;
 };
 
 // out[h][..] = sum over b and the per_bh partials of (b, h) of an [R][C] block found at
@@ -225,9 +222,9 @@ struct ReduceArgs {
   int64_t part_stride, part_off;
   int R, C, transpose;
 };
-// up to four such sums in one launch (one per gradient tensor of a side)
+// up to eight such sums in one launch (one per gradient tensor)
 struct ReduceJobs {
-  ReduceArgs job[4];
+  ReduceArgs job[8];
   int n;
 };
 
@@ -235,8 +232,7 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t stream);
 hipError_t launch_suffix(const SuffixArgs& a, hipStream_t stream);
 hipError_t launch_transpose(const TransposeArgs& a, hipStream_t stream);
 hipError_t launch_act_grad(const ActGradArgs& a, int d, int grid, hipStream_t stream);
-hipError_t launch_tn_gemm(const TnGemmArgs& a, int d, int grid, hipStream_t stream);
-hipError_t launch_hid_grad(const HidGradArgs& a, int d, int grid, hipStream_t stream);
+hipError_t launch_weight_grad(const WeightGradArgs& a, int d, int grid, hipStream_t stream);
 hipError_t launch_reduce(const ReduceJobs& jobs, hipStream_t stream);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t stream);
 
