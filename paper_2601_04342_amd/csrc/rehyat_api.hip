@@ -379,6 +379,7 @@ int launch_attn_window(const Ctx& c, const void* q, const void* k, const void* v
   }
   a.q_bh_stride = a.kv_bh_stride = (int64_t)T * HW * d;
   a.step_nq = a.step_nwin = 0;
+  a.step_S = a.step_z = nullptr;
   a.all_linear = bidir ? 1 : 0;
   a.xcd_mask = g_xcd_mask.load();
   hipError_t e;
@@ -934,18 +935,7 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
   }
 
   hipError_t e;
-  TransposeArgs tr;   // W2 [dp][hidden] -> [hidden][dp] of both maps
-  tr.n = H;
-  tr.R = dp;
-  tr.C = hid;
-  tr.in = (const bf16_t*)phi->w2_q;
-  tr.out = (bf16_t*)(ws + P.w2t);
-  tr.in2 = (const bf16_t*)phi->w2_k;
-  tr.out2 = tr.out + (size_t)H * hid * dp;
-  e = launch_transpose(tr, st);
-  if (e != hipSuccess) return hip_fail(e, "transpose kernel launch");
-
-  // ---- u, w per token ---------------------------------------------------------------
+  // ---- u, w per token; W2 [dp][hidden] -> [hidden][dp] of both maps ---------------------------------------------------------------
   PrepArgs pa;
   pa.g = (const bf16_t*)grad_out;
   pa.y = (const bf16_t*)y;
@@ -953,7 +943,11 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
   pa.nL = nL;
   pa.u = (bf16_t*)(ws + P.u);
   pa.tokw = (float*)(ws + P.tokw);
+  pa.w2_q = (const bf16_t*)phi->w2_q;
+  pa.w2_k = (const bf16_t*)phi->w2_k;
+  pa.w2t = (bf16_t*)(ws + P.w2t);
   pa.tokens = (int64_t)BH * N;
+  pa.H = H;
   pa.d = d;
   e = launch_prep(pa, st);
   if (e != hipSuccess) return hip_fail(e, "gradient preparation kernel launch");
@@ -1104,10 +1098,10 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   ss.dprime = dp;
   ss.partial_slots = c.sl.partial;
   ss.state_slots = c.sl.state;
-  // The read-out of this chunk uses the caller's state as it is (Eq. 16): slot 0 <- S, z.  The
-  // tokens that leave the window are absorbed afterwards (Eq. 17-18: state kernel in pieces,
-  // then S, z += the pieces, in place and in the caller's layout); the attention kernel does
-  // not depend on that.
+  // The read-out of this chunk uses the caller's state as it is (Eq. 16): the split kernel reads it,
+  // for attn_kernel it is copied first (slot 0 <- S, z).  The tokens that leave the window are
+  // absorbed afterwards (Eq. 17-18: state kernel in pieces, then S, z += the pieces, in place and
+  // in the caller's layout); the attention kernel does not depend on that.
   const int qtile = attn_query_tile(d);
   const int attn_wgs = B * H * ((n_q + qtile - 1) / qtile);   // 64-row tiles of the queries fit an int
   // The absorbed rows are one segment, cut into pieces for `free_cus` CUs: one workgroup of the
@@ -1135,6 +1129,7 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   int nsplit = n_absorb > 0 ? pieces_for(kCUs - attn_wgs) : 0;
   const bool late_and_long = d == 64 && n_win >= 4096 && attn_wgs + B * H * nsplit > kCUs && max_pieces > 10 * nsplit;
   const bool joint = n_absorb > 0 && attn_wgs <= kCUs && !late_and_long;
+  const bool split = joint || (n_absorb == 0 && attn_splits(attn_wgs, n_win, d, true));
   SideStream* side = n_absorb > 0 && !joint ? side_stream(st) : nullptr;
   hipStream_t upd = side ? side->s : st;   // stream of the state update
   StateArgs s{};
@@ -1188,10 +1183,10 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
     if (rc != REHYAT_OK) return rc;
     e = hipEventRecord(side->join, side->s);
     if (e != hipSuccess) return hip_fail(e, "hipEventRecord(join)");
-  } else if (joint || n_absorb == 0) {
-    rc = launch_slot(0, 1, st);   // slot 0 <- state
+  } else if (n_absorb == 0) {
+    if (!split) rc = launch_slot(0, 1, st);   // slot 0 <- state
     if (rc != REHYAT_OK) return rc;
-  } else {
+  } else if (!joint) {
     // one stream: pieces, then slot 0 <- state and state += pieces in one kernel
     rc = launch_pieces();
     if (rc != REHYAT_OK) return rc;
@@ -1225,12 +1220,14 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   a.kv_bh_stride = (int64_t)n_win * d;
   a.step_nq = n_q;
   a.step_nwin = n_win;
+  a.step_S = split ? S : nullptr;
+  a.step_z = split ? z : nullptr;
   a.all_linear = 0;
   a.xcd_mask = 0xFFu;   // the measurement hook covers whole-sequence calls only
   a.n_short = 0;
   {
     ProfScope prof(true, 2, st);
-    e = launch_attn(a, joint ? &s : nullptr, d, joint || (n_absorb == 0 && attn_splits(attn_wgs, n_win, d, true)), st);
+    e = launch_attn(a, joint ? &s : nullptr, d, split, st);
   }
   if (e != hipSuccess) return hip_fail(e, "attention kernel launch");
   if (joint) {   // state += pieces

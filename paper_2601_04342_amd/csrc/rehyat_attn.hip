@@ -781,7 +781,11 @@ attn_kernel(AttnArgs a) {
 // 128 KB of tile buffers (K and V of two tiles per group): one workgroup per CU, which is why
 // attn_kernel stays the better one as soon as its own launch fills the chip (attn_splits).
 // ---------------------------------------------------------------------------
-template <int D>
+// STEP (streaming step): explicit ranges; S and z are the caller's, in its layout and precision, so that no
+// launch has to prepare them (a kernel that wrote S as the bf16 operand that phase L reads stood
+// before this one: 4 of 64 us per step at the 480p shape); further workgroups absorb rows.  A
+// thread carries a block of 4 features x 4 columns of S through registers, rounded as that kernel did.
+template <int D, bool STEP>
 __global__ void __launch_bounds__(512, 2)
 attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   using C = AttnShape<D>;
@@ -790,7 +794,7 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   constexpr int NT = 512;
   constexpr int GB = 4 * TB;             // tile buffers of one group: K 0/1, V 0/1
   using SL = StateLds<D>;
-  __shared__ __attribute__((aligned(1024))) char tiles[2 * GB > SL::XV + SL::US ? 2 * GB : SL::XV + SL::US];
+  __shared__ __attribute__((aligned(1024))) char tiles[!STEP || 2 * GB > SL::XV + SL::US ? 2 * GB : SL::XV + SL::US];
   __shared__ __attribute__((aligned(256))) float sb1[HID];
   __shared__ __attribute__((aligned(16))) float sb2[DP];
   __shared__ __attribute__((aligned(16))) float sz[DP];
@@ -798,11 +802,13 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
 
   // streaming step: the workgroups beyond the attention items absorb the tokens that leave the
   // window (pieces of the chunk-state increment) on CUs that the attention items leave free
-  if ((int)blockIdx.x >= attn_blocks) {
-    constexpr int NW = D / 16;   // waves of the chunk-state body; the others are done
-    if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < NW)
-      state_body<D, NW>(sa, blockIdx.x - attn_blocks, tiles, tiles + SL::XV, sb1);
-    return;
+  if constexpr (STEP) {
+    if ((int)blockIdx.x >= attn_blocks) {
+      constexpr int NW = D / 16;   // waves of the chunk-state body; the others are done
+      if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) < NW)
+        state_body<D, NW>(sa, blockIdx.x - attn_blocks, tiles, tiles + SL::XV, sb1);
+      return;
+    }
   }
 
   const int tid = threadIdx.x;
@@ -849,7 +855,7 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
                              RangeTiles<2 * D, 4>(n_keys, qg, lane), kg, 2, (n_tiles + 1 - kg) / 2, lane};
     st.request();
     if (has_linear) {
-      const float* zt = a.state_z + ((int64_t)bh * a.state_slots + tc) * DP;
+      const float* zt = STEP ? a.step_z + (int64_t)bh * DP : a.state_z + ((int64_t)bh * a.state_slots + tc) * DP;
       for (int i = tid; i < HID; i += NT) sb1[i] = a.b1_q[(int64_t)h * HID + i];
       for (int i = tid; i < DP; i += NT) {
         sb2[i] = a.b2_q[(int64_t)h * DP + i];
@@ -874,20 +880,48 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   constexpr int NW1 = HID / 64, NP = DP / 64;
   static_assert(NW1 <= 4, "the W1 tiles and the first set share the eight buffers");
   const LinTiles<D, 8> lt{make_rsrc_words(a.w1_q + (int64_t)h * HID * D), make_rsrc_words(a.w2_q + (int64_t)h * DP * HID),
-                          make_rsrc_words(a.state_s + ((int64_t)bh * a.state_slots + tc) * (int64_t)D * DP),
+                          make_rsrc_words(STEP ? a.w1_q : a.state_s + ((int64_t)bh * a.state_slots + tc) * (int64_t)D * DP),
                           lds_address(tiles), wave, lane};
   constexpr int L8 = LinTiles<D, 8>::LPT;
+  // STEP: features 64p + 4 s_f .. of columns 4 s_d .. of S are requested into registers before set p's
+  // tiles and go to its S tile (64 features, i.e. 128 bytes, per column) after the work on the set before it
+  const int s_f = tid / (D / 4), s_d = tid % (D / 4);
+  const bool s_mover = tid < 4 * D;   // whole waves
+  f32x4 sreg[4];
+  auto request_s = [&](int p) {
+    if (STEP && s_mover) {
+      const float* const src = a.step_S + ((int64_t)bh * DP + 64 * p + 4 * s_f) * D + 4 * s_d;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sreg[i] = *reinterpret_cast<const f32x4_u*>(src + i * D);
+    }
+  };
+  auto place_s = [&](int p) {
+    if (STEP && s_mover) {
+      char* const Ss = tiles + ((p & 1) ? 2 : 6) * TB;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        u32x2 pk;
+        pk[0] = pack_bf16(sreg[0][j], sreg[1][j]);
+        pk[1] = pack_bf16(sreg[2][j], sreg[3][j]);
+        *reinterpret_cast<u32x2*>(Ss + tile_off<128>(4 * s_d + j, 4 * s_f)) = pk;
+      }
+    }
+  };
   auto issue_set = [&](int p) {
     const int b = (p & 1) ? 0 : 4;
+    request_s(p);
     lt.issue(kW2, 2 * p, b);
     lt.issue(kW2, 2 * p + 1, b + 1);
-    lt.issue(kS, p, b + 2);
+    if (!STEP) lt.issue(kS, p, b + 2);
   };
   const bool dbg_soft = a.dbg_m || a.dbg_nS || a.dbg_aS;
   auto prologue = [&]() {
+    if (STEP) request_s(0);   // the wait for W1 below counts the tiles behind it
 #pragma unroll
     for (int i = 0; i < NW1; ++i) lt.issue(kW1, i, i);
-    issue_set(0);
+    lt.issue(kW2, 0, 4);
+    lt.issue(kW2, 1, 5);
+    if (!STEP) lt.issue(kS, 0, 6);
   };
   if (has_linear && !dbg_soft) prologue();
 
@@ -957,16 +991,18 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
     const float lin_scale = __builtin_amdgcn_exp2f((a.stab_mode == 1 ? 0.f : rows.max) - rows.ref);
     const int wbase = lin_row_base<D>(lane), sbase = tile_off<128>(r, 8 * g);
     bf16x8 Ub[HID / 16];
-    wait_loads_and_barrier<3 * L8>();   // W1 has landed, the first set may be in flight
+    wait_loads_and_barrier<(STEP ? 2 : 3) * L8>();   // W1 has landed, the first set may be in flight
     if (wave_live) lin_hidden<D, HID / 32>(tiles, wbase, sb1, g, Qr, Ub);
+    place_s(0);
     static_for<NP>([&](auto PC) {
       constexpr int p = decltype(PC)::value, base = (p & 1) ? 0 : 4;
       wait_loads_and_barrier<0>();      // set p has landed; everyone is done with the other buffers
       if constexpr (p + 1 < NP) issue_set(p + 1);
-      if (!wave_live) return;
       const int pb = 2 * p + kg;
-      nL += lin_features<D, (64 * p >= DP / 2)>(tiles + (base + kg) * TB, tiles + (base + 2) * TB, wbase, sbase, kg,
-                                                sb2 + 32 * pb, sz + 32 * pb, g, lin_scale, Ub, rows.O);
+      if (wave_live)
+        nL += lin_features<D, (64 * p >= DP / 2)>(tiles + (base + kg) * TB, tiles + (base + 2) * TB, wbase, sbase, kg,
+                                                  sb2 + 32 * pb, sz + 32 * pb, g, lin_scale, Ub, rows.O);
+      if constexpr (p + 1 < NP) place_s(p + 1);
     });
     nL = half_swap_sum(nL);
     lds_barrier();   // the last set has been read
@@ -1044,8 +1080,10 @@ hipError_t launch_attn(const AttnArgs& a, const StateArgs* absorb, int d, bool s
     StateArgs s{};
     if (absorb) s = *absorb;
     const int blocks = grid + (absorb ? s.items_per_xcd * 8 : 0);
-    if (d == 128) hipLaunchKernelGGL(attn_split_kernel<128>, dim3(blocks), dim3(512), 0, stream, a, s, grid);
-    else hipLaunchKernelGGL(attn_split_kernel<64>, dim3(blocks), dim3(512), 0, stream, a, s, grid);
+    const bool step = a.step_S != nullptr;
+    auto kernel = d == 128 ? (step ? attn_split_kernel<128, true> : attn_split_kernel<128, false>)
+                           : (step ? attn_split_kernel<64, true> : attn_split_kernel<64, false>);
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(512), 0, stream, a, s, grid);
   } else if (d == 128) {
     hipLaunchKernelGGL(attn_kernel<128>, dim3(grid), dim3(64 * kAttnNW), 0, stream, a);
   } else {

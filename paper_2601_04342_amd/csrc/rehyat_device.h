@@ -16,6 +16,7 @@ typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(float)))) float f32x2;
+typedef f32x4 f32x4_u __attribute__((aligned(4)));   // in a caller's buffer aligned to single floats
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
@@ -84,12 +85,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
 
-__device__ __forceinline__ float bf16_round(float x) {
-  // value of x after round-to-nearest-even to bf16
-  uint32_t u = pack_bf16(x, 0.f) << 16;
-  return __builtin_bit_cast(float, u);
-}
-
 // Registers 8s .. 8s+7 of an accumulator -> one bf16 B operand.
 __device__ __forceinline__ bf16x8 acc_to_operand(const f32x16& c, int s) {
   u32x4 p;
@@ -146,62 +141,13 @@ __device__ __forceinline__ int tile_off(int row, int col) {
   return row * ROWBYTES + ((((col >> 3) ^ swz<ROWBYTES>(row)) << 4) | ((col & 7) << 1));
 }
 
-// Direct loads of one tile.  Wave w of NW moves the 1 KB blocks w, w+NW, ...; lane i of
-// a block fills LDS chunk slot i, so it fetches the global chunk that the
-// swizzle assigns to that slot.  `rowaddr(R)` gives the byte offset, from
-// `gbase`, of the global row segment that becomes tile row R.
-template <int ROWBYTES, int TILE_BYTES, int NW, typename RowAddr>
-__device__ __forceinline__ void tile_load_direct(const char* gbase, char* lds_tile, int wave, int lane,
-                                                 RowAddr rowaddr) {
-  constexpr int CPR = ROWBYTES / 16;     // chunks per row
-  constexpr int RPB = 1024 / ROWBYTES;   // rows per 1 KB block
-  constexpr int NBLK = TILE_BYTES / 1024;
-  static_assert(NBLK % NW == 0, "blocks of a tile are dealt evenly to the waves");
-#pragma unroll
-  for (int n = 0; n < NBLK / NW; ++n) {
-    const int blk = wave + NW * n;
-    const int R = blk * RPB + lane / CPR;
-    const int c = (lane % CPR) ^ swz<ROWBYTES>(R);
-    const char* src = gbase + (uint32_t)(rowaddr(R) + c * 16);
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                     (__attribute__((address_space(3))) void*)(lds_tile + blk * 1024), 16, 0, 0);
-  }
-}
-
-// Raw buffer descriptor for direct loads.  The hardware's range check covers only
-// the per-lane offset (never the scalar offset), so the descriptor is left open
-// ended and callers keep every access inside their tensors themselves.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, 0x7fffffff, 0x00020000);
-}
-
-// Same tile fill as tile_load_direct for row maps that split into a block part and a
-// row-in-block part, rowaddr(blk * RPB + j) == rowaddr(blk * RPB) + rowaddr(j) for j < RPB
-// (RPB = rows per 1 KB block): the per-lane offset is then the same for every block a
-// wave moves, and the block part, the tile offset `soff` (bytes from the descriptor's
-// base) and the LDS address are all wave-uniform, so a load costs no vector ALU work.
-// `wave` must be wave-uniform in the compiler's eyes (readfirstlane).
-template <int ROWBYTES, int TILE_BYTES, int NW, typename RowAddr>
-__device__ __forceinline__ void tile_load_buffer(__amdgpu_buffer_rsrc_t rsrc, int soff, char* lds_tile,
-                                                 int wave, int lane, RowAddr rowaddr) {
-  constexpr int CPR = ROWBYTES / 16;
-  constexpr int RPB = 1024 / ROWBYTES;
-  constexpr int NBLK = TILE_BYTES / 1024;
-  static_assert(NBLK % NW == 0, "blocks of a tile are dealt evenly to the waves");
-  const int j = lane / CPR;
-#pragma unroll
-  for (int n = 0; n < NBLK / NW; ++n) {
-    const int blk = wave + NW * n;
-    // the chunk swizzle looks at the low bits of the block index only: with NW a multiple
-    // of 4 every block of a wave shares one per-lane offset, otherwise two alternate
-    const int c = (lane % CPR) ^ swz<ROWBYTES>((NW % 4 == 0 ? wave : blk) * RPB + j);
-    const int voff = rowaddr(j) + c * 16;
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)(lds_tile + blk * 1024),
-                                             16, voff, soff + rowaddr(blk * RPB), 0, 0);
-  }
-}
-
-// The same direct load written as inline asm, for kernels that rotate tile buffers at run
+// Direct loads of a tile: wave w of NW moves the 1 KB blocks w, w+NW, ...; lane i of a block fills LDS
+// chunk slot i, so it fetches the global chunk that the swizzle assigns to that slot.  They go through
+// raw buffer descriptors, whose range check covers only the per-lane offset (never the scalar
+// offset): descriptors are left open ended and callers keep every access inside their tensors
+// themselves.
+//
+// The loads are inline asm, for kernels that rotate tile buffers at run
 // time.  The compiler orders every LDS read after any direct load it can see that might
 // write the same object, by waiting for ALL outstanding loads -- right for one buffer,
 // but with buffers picked by a run-time index it cannot tell the tile being read from the
@@ -215,7 +161,7 @@ __device__ __forceinline__ u32x4 make_rsrc_words(const void* base) {
   u32x4 w;
   w[0] = __builtin_amdgcn_readfirstlane((uint32_t)b);
   w[1] = __builtin_amdgcn_readfirstlane((uint32_t)(b >> 32) & 0xffffu);
-  w[2] = 0x7fffffffu;   // open ended, as in make_rsrc
+  w[2] = 0x7fffffffu;   // open ended
   w[3] = 0x00020000u;
   return w;
 }
@@ -264,12 +210,9 @@ __device__ __forceinline__ void tile_load_asm(u32x4 rsrc, int soff, uint32_t lds
   }
 }
 
-// tile_load_asm with one per-lane offset for every block a wave moves when the tile is full
-// (valid == 64): block b of a wave differs from its first block by whole multiples of 16
-// rows, which the chunk permutation does not see, so the block part goes into the scalar
-// offset and the per-lane offset is loop-invariant (one register per tile shape instead of
-// one per load).  `voff_full` is that offset, from tile_voff_full; a ragged tile takes the
-// general path.
+// The per-lane offset of a wave's first block of a full tile, which serves all of its blocks: block
+// b of a wave differs from its first block by whole multiples of 16 rows, which the chunk permutation
+// does not see, so the block part goes into the scalar offset.
 template <int ROWBYTES, int NW>
 __device__ __forceinline__ int tile_voff_full(int wave, int lane) {
   constexpr int CPR = ROWBYTES / 16;
@@ -278,25 +221,6 @@ __device__ __forceinline__ int tile_voff_full(int wave, int lane) {
   const int j = lane / CPR;
   return j * ROWBYTES + (((lane % CPR) ^ swz<ROWBYTES>(wave * RPB + j)) << 4);
 }
-template <int ROWBYTES, int TILE_BYTES, int NW>
-__device__ __forceinline__ void tile_load_fast(u32x4 rsrc, int soff, uint32_t lds_tile, int wave, int lane,
-                                               int valid, int voff_full) {
-  constexpr int NBLK = TILE_BYTES / 1024;
-  static_assert(NBLK % NW == 0, "blocks of a tile are dealt evenly to the waves");
-  if (valid >= 64) {
-#pragma unroll
-    for (int n = 0; n < NBLK / NW; ++n) {
-      const int blk = wave + NW * n;
-      direct_load_16(rsrc, voff_full, soff + blk * 1024, lds_tile + blk * 1024);
-    }
-  } else {
-    // at most once per token range: keep its per-load offsets from being computed ahead of
-    // the loop and held in registers (the empty asm hides that they are loop-invariant)
-    asm volatile("" : "+s"(valid), "+v"(lane));
-    tile_load_asm<ROWBYTES, TILE_BYTES, NW>(rsrc, soff, lds_tile, wave, lane, valid);
-  }
-}
-
 // The tiles of 64 rows of ROWBYTES of a token range, moved by NW waves through direct_load_16_at, one
 // instruction at a time so that a kernel can spread them over its products.  A ragged last tile
 // holds the last 64 rows of the range (`first()` of them belong to the tile before it), so that every

@@ -33,11 +33,33 @@ namespace rehyat {
 
 // ------------------------------------------------------------------------------------
 // u_i = G_i / den_i (bf16), w_i = -(G_i . y_i) / den_i.  Eight elements per thread, D/8
-// consecutive lanes per token.
+// consecutive lanes per token.  The last blocks of the launch transpose the second-layer weights of both
+// maps (32 x 32 per block, through a padded LDS tile): 5 us as a launch of their own, nothing beside
+// this one, which is bound by memory.
 // ------------------------------------------------------------------------------------
+__device__ __forceinline__ void transpose_block(const PrepArgs& a, int W, int block) {
+  __shared__ bf16_t tile[32][33];
+  const int nb = W / 32, m = block / (nb * nb), rc = block % (nb * nb);
+  const bool second = m >= a.H;
+  const int64_t off = (int64_t)(second ? m - a.H : m) * W * W;
+  const bf16_t* const in = (second ? a.w2_k : a.w2_q) + off;
+  bf16_t* const out = a.w2t + (second ? (int64_t)a.H * W * W : 0) + off;
+  const int r0 = rc / nb * 32, c0 = rc % nb * 32;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
+#pragma unroll
+  for (int j = 0; j < 4; ++j) tile[ty + 8 * j][tx] = in[(r0 + ty + 8 * j) * W + c0 + tx];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 4; ++j) out[(c0 + ty + 8 * j) * W + r0 + tx] = tile[tx][ty + 8 * j];
+}
+
 template <int D>
 __global__ void __launch_bounds__(256)
-prep_kernel(PrepArgs a) {
+prep_kernel(PrepArgs a, int token_blocks) {
+  if ((int)blockIdx.x >= token_blocks) {
+    transpose_block(a, 2 * D, blockIdx.x - token_blocks);
+    return;
+  }
   constexpr int LPT = D / 8;  // lanes per token
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   int64_t tok = gid / LPT;
@@ -66,11 +88,11 @@ prep_kernel(PrepArgs a) {
 }
 
 hipError_t launch_prep(const PrepArgs& a, hipStream_t stream) {
-  const int lpt = a.d / 8;
+  const int lpt = a.d / 8, nb = 2 * a.d / 32;
   const int64_t threads = a.tokens * lpt;
-  const unsigned grid = (unsigned)((threads + 255) / 256);
-  if (a.d == 128) hipLaunchKernelGGL(prep_kernel<128>, dim3(grid), dim3(256), 0, stream, a);
-  else hipLaunchKernelGGL(prep_kernel<64>, dim3(grid), dim3(256), 0, stream, a);
+  const unsigned tokens = (unsigned)((threads + 255) / 256), grid = tokens + 2 * a.H * nb * nb;
+  if (a.d == 128) hipLaunchKernelGGL(prep_kernel<128>, dim3(grid), dim3(256), 0, stream, a, (int)tokens);
+  else hipLaunchKernelGGL(prep_kernel<64>, dim3(grid), dim3(256), 0, stream, a, (int)tokens);
   return hipGetLastError();
 }
 
@@ -128,44 +150,6 @@ suffix_kernel(SuffixArgs a) {
 hipError_t launch_suffix(const SuffixArgs& a, hipStream_t stream) {
   dim3 grid((a.elems / 4 + 255) / 256, a.BH);
   hipLaunchKernelGGL(suffix_kernel, grid, dim3(256), 0, stream, a);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------
-// bf16 [n][R][C] -> [n][C][R] through a padded 32 x 32 LDS tile; optionally a second batch of n
-// matrices of the same shape in the same launch.
-// ------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-transpose_kernel(TransposeArgs a) {
-  __shared__ bf16_t tile[32][33];
-  int m = blockIdx.z;
-  const bf16_t* in = a.in;
-  bf16_t* out = a.out;
-  if (m >= a.n) {   // second batch of matrices
-    m -= a.n;
-    in = a.in2;
-    out = a.out2;
-  }
-  const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  in += (int64_t)m * a.R * a.C;
-  out += (int64_t)m * a.R * a.C;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int rr = r0 + ty + 8 * j, cc = c0 + tx;
-    if (rr < a.R && cc < a.C) tile[ty + 8 * j][tx] = in[(int64_t)rr * a.C + cc];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int cc = c0 + ty + 8 * j, rr = r0 + tx;
-    if (rr < a.R && cc < a.C) out[(int64_t)cc * a.R + rr] = tile[tx][ty + 8 * j];
-  }
-}
-
-hipError_t launch_transpose(const TransposeArgs& a, hipStream_t stream) {
-  dim3 grid((a.C + 31) / 32, (a.R + 31) / 32, a.in2 ? 2 * a.n : a.n);
-  hipLaunchKernelGGL(transpose_kernel, grid, dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -959,76 +943,84 @@ hipError_t launch_weight_grad(const WeightGradArgs& a, int d, int grid, hipStrea
 // ------------------------------------------------------------------------------------
 // Sum of the per-workgroup partials over batch and pieces, in a fixed order.
 // ------------------------------------------------------------------------------------
-// A block owns 256 elements; each of its four waves sums every fourth partial of them, 16 bytes
-// per lane and kReduceDepth partials in flight, and the four sums are combined in a fixed order.
-// Bound by reading the partials (100 MB per side at the 480p shape, written just before and
-// mostly still in the last-level cache).  A transposed job (dW1, whose partials are [d][hidden])
-// takes its 256 elements as 8 rows of 32, so that reads are whole 128-byte lines and the
-// stores leave in runs of 32 bytes.
-// Four bytes per lane, with a division per load and single-element transposed stores, took
-// 45 us per side at the 480p shape and 36 us at 320x480; this form 18 us
-// and 17 us.
-constexpr int kReduceDepth = 6;   // 21 partials per (b, h) at 12 heads: one batch per wave
+// A wave sums 256 elements, 16 bytes per lane and kReduceDepth partials in flight; a block holds four
+// such waves, or, for a tensor of no more elements (the biases, with up to a few hundred partials),
+// four waves of every fourth partial, combined in a fixed order.  A transposed job (dW1, whose
+// partials are [d][hidden]) takes its 256 elements as 8 rows of 32, so that reads are whole 128-byte
+// lines and the stores leave in runs of 32 bytes.
+// Bound by launching the blocks and one round trip to the partials (26 MB at 12 heads of 128, mostly in
+// the last-level cache): with a grid of 256 blocks for every tensor, most of them idle for the
+// biases, and the partials of every element split over four waves, 15 us; now 11.
+constexpr int kReduceDepth = 6;
 __global__ void __launch_bounds__(256)
 reduce_kernel(ReduceJobs jobs) {
   __shared__ __attribute__((aligned(16))) float sums[4][256];
-  const ReduceArgs& a = jobs.job[blockIdx.z];
+  int j = 0;
+  while (j + 1 < jobs.n && (int)blockIdx.x >= jobs.first[j + 1]) ++j;
+  const ReduceArgs& a = jobs.job[j];
   const int h = blockIdx.y;
   const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
   const int n = a.R * a.C;   // a multiple of 4 (of 256 with rows of whole 32s when transposed)
-  const int i0 = blockIdx.x * 256;
-  if (i0 >= n) return;
-  int i = i0 + 4 * lane, r0 = 0, c0 = 0;
-  if (a.transpose) {   // block (rb, cb) of 8 x 32 elements
+  const bool tall = n <= 256;
+  const int group = tall ? 0 : 4 * ((int)blockIdx.x - jobs.first[j]) + q;   // of 256 elements
+  int i = 256 * group + 4 * lane, r0 = 0, c0 = 0;
+  if (a.transpose) {   // 8 x 32 elements
     const int cbs = a.C / 32;
-    r0 = 8 * ((int)blockIdx.x / cbs);
-    c0 = 32 * ((int)blockIdx.x % cbs);
+    r0 = 8 * (group / cbs);
+    c0 = 32 * (group % cbs);
     i = (r0 + (lane >> 3)) * a.C + c0 + 4 * (lane & 7);
   }
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  if (i < n) {
-    const int total = a.B * a.per_bh;
+  if (256 * group + 4 * lane < n) {
+    const int total = a.B * a.per_bh, step = tall ? 4 : 1;
     const float* const p0 = a.part + a.part_off + i;
-    int b = 0, s = q;   // partial m = b * per_bh + s
-    for (int m = q; m < total; m += 4 * kReduceDepth) {
+    int b = 0, s = tall ? q : 0;   // partial m = b * per_bh + s
+    for (int m = s; m < total; m += step * kReduceDepth) {
       f32x4 x[kReduceDepth];
 #pragma unroll
       for (int u = 0; u < kReduceDepth; ++u) {
         x[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-        if (m + 4 * u < total) {
+        if (m + step * u < total) {
           while (s >= a.per_bh) {
             s -= a.per_bh;
             ++b;
           }
           x[u] = *reinterpret_cast<const f32x4*>(p0 + ((int64_t)(b * a.H + h) * a.per_bh + s) * a.part_stride);
-          s += 4;
+          s += step;
         }
       }
 #pragma unroll
       for (int u = 0; u < kReduceDepth; ++u) acc += x[u];
     }
   }
-  *reinterpret_cast<f32x4*>(&sums[q][4 * lane]) = acc;
-  __syncthreads();
-  const int t = threadIdx.x;
-  int e = t;          // element of the block
-  int64_t o = i0 + t; // where it goes
-  if (a.transpose) {
-    e = (t & 7) * 32 + (t >> 3);
-    o = (int64_t)(c0 + (t >> 3)) * a.R + r0 + (t & 7);
-  } else if (o >= n) {
+  float* const out = a.out + (int64_t)h * n;
+  if (!tall && !a.transpose) {
+    if (256 * group + 4 * lane < n) *reinterpret_cast<f32x4_u*>(out + i) = acc;
     return;
   }
-  a.out[(int64_t)h * n + o] = ((sums[0][e] + sums[1][e]) + sums[2][e]) + sums[3][e];
+  *reinterpret_cast<f32x4*>(&sums[q][4 * lane]) = acc;
+  __syncthreads();
+  if (tall) {
+    const int t = threadIdx.x;
+    if (t < n) out[t] = ((sums[0][t] + sums[1][t]) + sums[2][t]) + sums[3][t];
+    return;
+  }
+  if (256 * group >= n) return;
+  const int col = lane >> 1, row = 4 * (lane & 1);
+  const f32x4 y = {sums[q][row * 32 + col], sums[q][(row + 1) * 32 + col], sums[q][(row + 2) * 32 + col],
+                   sums[q][(row + 3) * 32 + col]};
+  *reinterpret_cast<f32x4_u*>(out + (int64_t)(c0 + col) * a.R + r0 + row) = y;
 }
 
-hipError_t launch_reduce(const ReduceJobs& jobs, hipStream_t stream) {
-  int most = 0;
-  for (int j = 0; j < jobs.n; ++j)
-    if (jobs.job[j].R * jobs.job[j].C > most) most = jobs.job[j].R * jobs.job[j].C;
-  dim3 grid((most + 255) / 256, jobs.job[0].H, jobs.n);
-  hipLaunchKernelGGL(reduce_kernel, grid, dim3(256), 0, stream, jobs);
+hipError_t launch_reduce(const ReduceJobs& given, hipStream_t stream) {
+  ReduceJobs jobs = given;
+  int blocks = 0;
+  for (int j = 0; j < jobs.n; ++j) {
+    jobs.first[j] = blocks;
+    blocks += (jobs.job[j].R * jobs.job[j].C + 1023) / 1024;
+  }
+  hipLaunchKernelGGL(reduce_kernel, dim3(blocks, jobs.job[0].H), dim3(256), 0, stream, jobs);
   return hipGetLastError();
 }
 

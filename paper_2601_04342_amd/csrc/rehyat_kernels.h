@@ -82,6 +82,8 @@ struct AttnArgs {
   int step_nq, step_nwin;  // step_nq > 0 (streaming step): queries are rows [0, step_nq) of q,
                            // the softmax window is rows [0, step_nwin) of k / v, the linear
                            // state is slot 0; the frame geometry above is then unused
+  const float *step_S, *step_z;   // streaming step with the split kernel: the caller's S [BH, dprime, d]
+                                  // and z [BH, dprime] (then no slot is read); otherwise null
   int all_linear;          // 1: every chunk reads a state (bidirectional sets of Eq. 11-12)
   unsigned xcd_mask;       // measurement hook: workgroups on XCD x (index % 8) run only if bit x is set
 };
@@ -145,8 +147,11 @@ struct PrepArgs {
   const float* nL;    // [tokens]
   bf16_t* u;          // [tokens, d]
   float* tokw;        // [tokens]
+  const bf16_t* w2_q; // [H, 2d, 2d]
+  const bf16_t* w2_k;
+  bf16_t* w2t;        // [2, H, 2d, 2d]  each matrix of w2_q, then of w2_k, transposed
   int64_t tokens;
-  int d;
+  int H, d;
 };
 
 // R_tau, r_tau: sums over the later chunks of the chunk-state gradients
@@ -157,15 +162,6 @@ struct SuffixArgs {
   float* r;             // [BH, slots, dp]
   int BH, n_seg, s_nsplit, s_slots, z_nsplit, slots;
   int elems, s_elems, dp;
-};
-
-// bf16 matrices [n][R][C] -> [n][C][R]; in2/out2 (nullable): a second batch of n such matrices
-struct TransposeArgs {
-  const bf16_t* in;
-  bf16_t* out;
-  const bf16_t* in2;
-  bf16_t* out2;
-  int n, R, C;
 };
 
 // Activation gradients of one side (queries or keys): recomputes U = relu(W1 x + b1) and
@@ -226,11 +222,11 @@ struct ReduceArgs {
 struct ReduceJobs {
   ReduceArgs job[8];
   int n;
+  int first[8];   // first block of each (set by launch_reduce)
 };
 
 hipError_t launch_prep(const PrepArgs& a, hipStream_t stream);
 hipError_t launch_suffix(const SuffixArgs& a, hipStream_t stream);
-hipError_t launch_transpose(const TransposeArgs& a, hipStream_t stream);
 hipError_t launch_act_grad(const ActGradArgs& a, int d, int grid, hipStream_t stream);
 hipError_t launch_weight_grad(const WeightGradArgs& a, int d, int grid, hipStream_t stream);
 hipError_t launch_reduce(const ReduceJobs& jobs, hipStream_t stream);
@@ -238,8 +234,8 @@ hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t stream);
 
 hipError_t launch_state(const StateArgs& a, int d, int grid, hipStream_t stream);
 hipError_t launch_prefix(const PrefixArgs& a, hipStream_t stream);
-// `split`: attn_split_kernel, otherwise attn_kernel.  `absorb` (with split only): chunk-state
-// pieces run by further workgroups of the launch.
+// `split`: attn_split_kernel, otherwise attn_kernel.  `absorb` (streaming step with split only):
+// chunk-state pieces run by further workgroups of the launch.
 hipError_t launch_attn(const AttnArgs& a, const StateArgs* absorb, int d, bool split, hipStream_t stream);
 // whether attn_split_kernel is the better one for a launch of n_items 128-query workgroups whose
 // softmax windows hold n_keys keys; `read_out`: some of them read a chunk state
