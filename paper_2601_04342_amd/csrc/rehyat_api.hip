@@ -1129,7 +1129,9 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   int nsplit = n_absorb > 0 ? pieces_for(kCUs - attn_wgs) : 0;
   const bool late_and_long = d == 64 && n_win >= 4096 && attn_wgs + B * H * nsplit > kCUs && max_pieces > 10 * nsplit;
   const bool joint = n_absorb > 0 && attn_wgs <= kCUs && !late_and_long;
-  const bool split = joint || (n_absorb == 0 && attn_splits(attn_wgs, n_win, d, true));
+  // A step that absorbs nothing takes the split kernel at any number of keys: the 1 - 2 us that it loses
+  // on short windows are less than the copy of the state that attn_kernel needs before it.
+  const bool split = joint || (n_absorb == 0 && attn_wgs <= kCUs);
   SideStream* side = n_absorb > 0 && !joint ? side_stream(st) : nullptr;
   hipStream_t upd = side ? side->s : st;   // stream of the state update
   StateArgs s{};

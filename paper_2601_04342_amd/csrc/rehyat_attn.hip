@@ -1051,18 +1051,17 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
 }
 
 // The split kernel holds one workgroup per CU (tile buffers of 128 KB), so it can only win while
-// its launch is a single round: at 256 items and fewer.  Measured whole calls, split against not, at
-// d = 128: 72 items of 39 key tiles 65.8 against 71.2 us, 144 of 15 tiles 55.7 against 57.7, 144 of
-// 8 tiles 49.9 against 50.7, 144 of 7 tiles 48.5 against 48.7; 312 items of 25 tiles 94 against 81,
-// 624 items 134 against 121.  At d = 64 (half the products per key, three attn_kernel
-// workgroups per CU): 72 items of 32 tiles 44.5 against 45.8, 20 tiles even, 8 tiles 28.1 against 27.6.
-// Without a read-out phase, half of which each group would take, the two groups' meeting has to be
-// paid by the keys alone: at d = 128 4 - 256 items of 8 tiles 15.4 - 18.3 against 13.4 - 16.2 us, of 16
-// tiles 21.8 - 26.2 against 21.4 - 25.4, of 25 tiles 28.6 - 33.9 against 29.9 - 34.8; at d = 64 of 24 tiles
-// 21.6 - 24.2 against 21.0 - 23.2, of 48 tiles 36.6 - 38.5 against 37.7 - 40.2.
+// its launch is a single round: at 256 items and fewer (with the loops before these, 312 items of 25 key
+// tiles took 94 against 81 us, 624 items 134 against 121).  Below that the keys decide, since the two
+// groups' meeting has to be paid by them.  Whole calls, split against not: d = 128 with a read-out 16 - 192
+// items of 64 - 640 keys 3 - 6 % slower, 126 of 800 48.4 and 48.0 us, 128 of 1,000 48.6 and 48.8, 144 of
+// 1,536 54.1 and 55.6, 96 of 2,000 60.2 and 63.6; d = 64 160 of 640 26.9 and 26.1, 128 of 1,000 26.9 and 27.2,
+// 189 of 2,600 42.5 and 46.1.  Without a read-out at d = 128 60 of 768 17.3 and 16.7, 80 of 1,024 19.8 and
+// 20.0, 120 of 1,536 25.8 and 27.2, 240 of 3,000 51.4 and 54.4; at d = 64 80 of 1,024 14.8 and 15.0, 150 of
+// 1,800 21.7 and 23.2 -- there the line lies higher than it has to, so that rows of fewer keys have the
+// same bits in every launch.
 bool attn_splits(int64_t n_items, int64_t n_keys, int d, bool read_out) {
-  if (n_items > 256) return false;
-  return read_out ? n_keys >= (d == 128 ? 448 : 1536) : n_keys >= (d == 128 ? 1536 : 2560);
+  return n_items <= 256 && n_keys >= (read_out || d == 128 ? 960 : 1664);
 }
 
 int attn_query_tile(int) { return kQueryTile; }

@@ -20,7 +20,7 @@ def _announce(request):
 @pytest.mark.parametrize("d", [128, 64])
 @pytest.mark.parametrize("HW", [1, 63, 64, 65, 127, 128, 130, 191, 193, 256, 319, 386])
 def test_key_tiles(HW, d):
-    """Softmax windows of one to seven key tiles (below 448 keys: one group of waves), and chunk
+    """Softmax windows of one to seven key tiles (one group of waves), and chunk
     states over as many tiles."""
     parity.run_case(1, 1, 3, HW, d, 1, 0, 0, 4.0, seed=HW + d)
 
