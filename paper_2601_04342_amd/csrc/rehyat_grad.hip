@@ -294,15 +294,19 @@ act_grad_kernel(ActGradArgs a) {
     }
     return u;
   };
-  // four hidden units of the lane's token: rectified into U, their signs (u > 0) into `s` from the right
+  // four hidden units of the lane's token: rectified into U, their signs (u > 0) into `s` from the right --
+  // of the rectified value, which is zero for a NaN
   auto u_store = [&](const f32x16& u, int i, int it, int tb, uint32_t& s) {
+    float rl[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      s = __builtin_amdgcn_alignbit(s, __builtin_bit_cast(uint32_t, 0.f - u[4 * i + j]), 31);
+    for (int j = 0; j < 4; ++j) {
+      rl[j] = fmaxf(u[4 * i + j], 0.f);
+      s = __builtin_amdgcn_alignbit(s, __builtin_bit_cast(uint32_t, 0.f - rl[j]), 31);
+    }
     pin(s);
     u32x2 pk;
-    pk[0] = pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f));
-    pk[1] = pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f));
+    pk[0] = pack_bf16(rl[0], rl[1]);
+    pk[1] = pack_bf16(rl[2], rl[3]);
     *reinterpret_cast<u32x2*>(Us + (it & 1) * (64 * UPAD) + uwbase + 16 * i + tb * (32 * UPAD)) = pk;
   };
   // one word per token: unit 8i + 4g + j of the slice is bit 16 g + 15 - (4i + j); lane half g stores

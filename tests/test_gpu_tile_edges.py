@@ -37,3 +37,25 @@ def test_chunk_states_are_reproducible(d):
     for i in range(20):
         again = binding.state(dk, dv, dphi, T, HW, T)
         assert all(torch.equal(a, b) for a, b in zip(again, first)), i
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_gate_of_a_nan_is_closed(d):
+    """A hidden unit that is NaN for every token is rectified to zero, and its gate is closed: the gradients are
+    those of a unit that is negative everywhere, bit for bit."""
+    B, H, T, HW = 1, 2, 3, 97
+    q, k, v = synth.make_qkv(B, H, T * HW, d, seed=d)
+    G = synth.make_grad_out(B, H, T * HW, d).to("cuda", torch.bfloat16)
+    _, dk, dv, dphi = parity.to_device(q, k, v, synth.make_phi(H, d, seed=1, gain=4.0))
+    dq = q.to("cuda", torch.bfloat16)
+    runs = []
+    for nan in (True, False):
+        phi = {n: t.clone() for n, t in dphi.items()}
+        for side in "qk":
+            for unit in (5, 2 * d - 1):
+                phi[f"w1_{side}"][0, unit] = float("nan") if nan else 0.0
+                phi[f"b1_{side}"][0, unit] = -1.0
+        runs.append(binding.phi_backward(dq, dk, dv, phi, G, T, HW, 1)[0])
+    for n in runs[0]:
+        assert torch.isfinite(runs[0][n]).all(), n
+        assert torch.equal(runs[0][n], runs[1][n]), n
