@@ -6,6 +6,7 @@ import torch
 
 from paper_2601_04342_amd import binding, synth
 from tests import parity
+from tests.test_gpu_backward import run_case
 
 pytestmark = pytest.mark.gpu
 
@@ -37,6 +38,14 @@ def test_chunk_states_are_reproducible(d):
     for i in range(20):
         again = binding.state(dk, dv, dphi, T, HW, T)
         assert all(torch.equal(a, b) for a, b in zip(again, first)), i
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("B,H,HW", [(1, 1, 32), (1, 1, 65), (16, 8, 33), (16, 8, 64), (16, 8, 97), (16, 8, 160)])
+def test_weight_gradient_tiles(B, H, HW, d):
+    """Weight gradients of pieces of one tile (one head; HW = 65 leaves a piece of two rows) and of two, four and
+    five tiles with a last one of 2 or 64 rows (128 (b, h), one piece each); bars as for the other gradients."""
+    run_case(B, H, 3, HW, d, 1, 0, 4.0, seed=HW + d)
 
 
 @pytest.mark.parametrize("d", [128, 64])
