@@ -262,6 +262,31 @@ __device__ __forceinline__ u32x4 rsrc_if(u32x4 rsrc, bool on) {
   return rsrc;
 }
 
+// Rows [first, first + count) of a 64-row tile belong to it; the others meet zeros in a product over rows, but
+// an infinity in them would make it NaN.  A product over rows 16 step .. + 15 is left out if none of
+// them belong, and its LDS operand keeps only the rows that do if not all of them.
+__device__ __forceinline__ bool step_is_out(int step, int first, int count) {
+  return 16 * step + 16 <= first || 16 * step >= first + count;
+}
+__device__ __forceinline__ bool step_is_cut(int step, int first, int count) {
+  return 16 * step < first || 16 * step + 16 > first + count;
+}
+// Element e of the operand of lane half g is row 16 step + 8 (e >> 2) + 4 g + (e & 3).
+__device__ __forceinline__ u32x4 rows_kept(int step, int g, int first, int count) {
+  u32x4 keep;
+  int base = 16 * step + 4 * g - first;
+  asm volatile("" : "+v"(base));   // comparisons of the same rows elsewhere are not kept for this
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = base + 8 * (i >> 1) + 2 * (i & 1);
+    keep[i] = ((unsigned)row < (unsigned)count ? 0xffffu : 0u) | ((unsigned)(row + 1) < (unsigned)count ? 0xffff0000u : 0u);
+  }
+  return keep;
+}
+__device__ __forceinline__ bf16x8 keep_rows(bf16x8 x, u32x4 keep) {
+  return __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, x) & keep);
+}
+
 // Makes the compiler wait here for the loads that filled these operands.  Without it the wait
 // goes to their first use inside the tile loop and stays there for every tile, as a count of
 // outstanding loads in which the direct loads issued as inline asm are not known: it then
@@ -278,6 +303,14 @@ __device__ __forceinline__ void settle(float& x) { asm volatile("" : "+v"(x)); }
 template <typename T>
 __device__ __forceinline__ void pin(T& x) {
   asm volatile("" : "+v"(x));
+}
+
+// The same for a whole tile in LDS, by NT threads; a barrier has to follow.
+template <int ROWBYTES, int NT>
+__device__ __forceinline__ void clear_other_rows(char* tile, int first, int count, int tid) {
+#pragma unroll
+  for (int o = tid * 16; o < 64 * ROWBYTES; o += NT * 16)
+    if ((unsigned)(o / ROWBYTES - first) >= (unsigned)count) *reinterpret_cast<u32x4*>(tile + o) = u32x4{0u, 0u, 0u, 0u};
 }
 
 // Wait until at most N of this wave's direct loads are outstanding (and all of

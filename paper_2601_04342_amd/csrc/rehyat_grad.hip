@@ -743,7 +743,17 @@ __device__ __forceinline__ void tn_body(const WeightGradSide& a, int H, int64_t 
     });
   };
   for (int it = 0; it + 1 < n_tiles; ++it) tile_step(std::true_type{}, it);
-  if (n_tiles > 0) tile_step(std::false_type{}, n_tiles - 1);
+  if (n_tiles > 0) {
+    const int it = n_tiles - 1, first = prange.first(64 * it), count = prange.count(64 * it);
+    if (count < 64) {   // then the fragments that were read ahead are read again
+      clear_other_rows<ROWB, 64 * NW>(Pt + (it & 1) * TBY, first, count, tid);
+      lds_barrier();
+      const GradOffsets<D> o(lane);
+      const int pb = f_base(o, 64 * wf), ub = f_base(o, (W / 2) * wh);
+      static_for<kLook>([&](auto QC) { fr[decltype(QC)::value] = s_read(it, pb, ub, 0, decltype(QC)::value); });
+    }
+    tile_step(std::false_type{}, it);
+  }
 
   float* P = a.part_w2 + ((int64_t)bh * nsplit + sp) * W * W;
 #pragma unroll

@@ -68,3 +68,53 @@ def test_gate_of_a_nan_is_closed(d):
     for n in runs[0]:
         assert torch.isfinite(runs[0][n]).all(), n
         assert torch.equal(runs[0][n], runs[1][n]), n
+
+
+@pytest.mark.parametrize("d,HW,row", [
+    (128, 97, 36), (64, 97, 36),        # the last tile holds rows 33 .. 96
+    (128, 1000, 939), (64, 1700, 1639),   # two groups of waves
+    (128, 40, 39), (64, 40, 39),        # fewer rows than a tile: the last one stands in for those beyond
+])
+def test_infinite_value_in_a_shared_row(d, HW, row):
+    """A ragged last key tile holds rows that an earlier tile has taken already.  An infinity in such a row of V
+    counts once: its column of the output is infinite, not NaN, and no other column changes."""
+    q, k, v = synth.make_qkv(1, 1, HW, d, seed=HW + d)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, synth.make_phi(1, d, seed=1))
+    want = binding.forward(dq, dk, dv, dphi, 1, HW, 1)
+    dv[0, 0, row, 5] = float("inf")
+    out = binding.forward(dq, dk, dv, dphi, 1, HW, 1)
+    assert (out[..., 5] == float("inf")).all()
+    rest = [c for c in range(d) if c != 5]
+    assert torch.equal(out[..., rest], want[..., rest])
+
+
+@pytest.mark.parametrize("d", [128, 64])
+def test_infinite_value_in_a_state(d):
+    """The same for chunk states, at every row: S is infinite where phi of the key is positive."""
+    HW = 97
+    _, k, v = synth.make_qkv(1, 1, HW, d, seed=d)
+    phi = synth.make_phi(1, d, seed=1, gain=4.0)
+    _, dk, dv, dphi = parity.to_device(k, k, v, phi)
+    p = {n: t.double()[0] for n, t in phi.items()}
+    psi = torch.relu(torch.relu(k[0, 0].double() @ p["w1_k"].T + p["b1_k"]) @ p["w2_k"].T + p["b2_k"])
+    for row in range(HW):
+        x = dv.clone()
+        x[0, 0, row, 5] = float("inf")
+        S, _ = binding.state(dk, x, dphi, 1, HW, 1)
+        on = psi[row] > 0.02 * psi[row].max()   # well above what bf16 makes of zero
+        assert (S[0, 0, :, 5].cpu()[on] == float("inf")).all(), row
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("row", [36, 96])
+def test_infinite_gradient_in_a_shared_row(d, row):
+    """An infinite dL/dy at a token whose row two tiles hold: the second layer's gradient keeps the infinities of
+    the features that it opens (NaN only where they meet a closed hidden unit)."""
+    B, H, T, HW = 16, 16, 2, 97
+    q, k, v = synth.make_qkv(B, H, T * HW, d, seed=d)
+    G = synth.make_grad_out(B, H, T * HW, d).to("cuda", torch.bfloat16)
+    G[0, 0, HW + row, 5] = float("inf")
+    _, dk, dv, dphi = parity.to_device(q, k, v, synth.make_phi(H, d, seed=1, gain=4.0))
+    grads, _ = binding.phi_backward(q.to("cuda", torch.bfloat16), dk, dv, dphi, G, T, HW, 1)
+    assert torch.isinf(grads["w2_q"][0]).any()
+    assert torch.isfinite(grads["w2_q"][1:]).all()
