@@ -361,10 +361,7 @@ act_grad_kernel(ActGradArgs a) {
     }
     const uint32_t word = sign_word(s);
     if (lane < n_tokens) Sgn[lane] = word;
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // U of tile 0 is complete
-    static_for<PD>([&](auto MC) {
-      fr[decltype(MC)::value] = *reinterpret_cast<const bf16x8*>(Us + urbase + 32 * decltype(MC)::value);
-    });
+    wait_loads_and_barrier<0>();   // U of tile 0 is complete
   }
 
   auto tile_step = [&](auto MOREC, auto SQC, int it) {
@@ -485,6 +482,12 @@ act_grad_kernel(ActGradArgs a) {
     }
   };
   auto all_tiles = [&](auto SQC) {   // the waves of both instances meet at the same barriers
+    // (fragments read before the branch would be kept, spilled, for the instance behind the other)
+    if (n_tiles > 0) {
+      static_for<PD>([&](auto MC) {
+        fr[decltype(MC)::value] = *reinterpret_cast<const bf16x8*>(Us + urbase + 32 * decltype(MC)::value);
+      });
+    }
     for (int it = 0; it + 1 < n_tiles; ++it) tile_step(std::true_type{}, SQC, it);
     if (n_tiles > 0) tile_step(std::false_type{}, SQC, n_tiles - 1);
   };

@@ -9,7 +9,7 @@ import pytest
 import torch
 
 from oracle import cref
-from paper_2601_04342_amd import binding
+from paper_2601_04342_amd import binding, build
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -253,3 +253,12 @@ def test_xcd_mask_hook_validation():
     assert lib.rehyat_debug_set_xcd_mask(0x100) == binding.E_SHAPE
     assert lib.rehyat_debug_set_xcd_mask(0x01) == binding.OK
     assert lib.rehyat_debug_set_xcd_mask(0xFF) == binding.OK
+
+
+def test_contraction_kernels_keep_their_registers():
+    """No kernel of the library spills a vector register: a value that is reloaded in front of or inside a tile loop
+    makes the compiler wait there for every load in flight, the direct loads that it does not know of among them."""
+    lib = open(build.LIB, "rb").read()
+    kernels = dict(re.findall(rb"\.symbol..?(_Z\w+)\.kd.*?\.vgpr_spill_count(\xcc.|.)", lib, re.S))
+    assert sum(b"state_kernel" in n or b"attn" in n or b"grad_kernel" in n for n in kernels) >= 14, sorted(kernels)
+    assert all(v[-1] == 0 for v in kernels.values()), {n: v[-1] for n, v in kernels.items() if v[-1]}
