@@ -1063,15 +1063,21 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
 // The split kernel holds one workgroup per CU (tile buffers of 128 KB), so it can only win while
 // its launch is a single round: at 256 items and fewer (with the loops before these, 312 items of 25 key
 // tiles took 94 against 81 us, 624 items 134 against 121).  Below that the keys decide, since the two
-// groups' meeting has to be paid by them.  Whole calls, split against not: d = 128 with a read-out 16 - 192
-// items of 64 - 640 keys 3 - 6 % slower, 126 of 800 48.4 and 48.0 us, 128 of 1,000 48.6 and 48.8, 144 of
-// 1,536 54.1 and 55.6, 96 of 2,000 60.2 and 63.6; d = 64 160 of 640 26.9 and 26.1, 128 of 1,000 26.9 and 27.2,
-// 189 of 2,600 42.5 and 46.1.  Without a read-out at d = 128 60 of 768 17.3 and 16.7, 80 of 1,024 19.8 and
-// 20.0, 120 of 1,536 25.8 and 27.2, 240 of 3,000 51.4 and 54.4; at d = 64 80 of 1,024 14.8 and 15.0, 150 of
-// 1,800 21.7 and 23.2 -- there the line lies higher than it has to, so that rows of fewer keys have the
-// same bits in every launch.
+// groups' meeting has to be paid by them.  Whole calls, split against not: d = 128 with a read-out 32
+// items of 448 keys 39.6 and 37.9 us, 200 of 512 47.2 and 45.3, 180 of 600 46.3 and 45.8, 168 of 800 50.8 and
+// 50.2, 128 of 1,000 48.6 and 48.8, 144 of 1,536 54.1 and 55.6, 96 of 2,000 60.2 and 63.6; d = 64 160 of 640
+// 26.9 and 26.1, 128 of 1,000 26.9 and 27.2, 189 of 2,600 42.5 and 46.1.  Without a read-out at d = 128 60 of
+// 768 17.3 and 16.7, 80 of 1,024 19.8 and 20.0, 120 of 1,536 25.8 and 27.2, 240 of 3,000 51.4 and 54.4; at
+// d = 64 80 of 1,024 14.8 and 15.0, 150 of 1,800 21.7 and 23.2.
+// Time alone would put every line at about 960 keys.  Two lie elsewhere:
+// - d = 128 with a read-out at 448: 1 - 4 % of the time buys an output that is 1.3 % nearer to fp64 (2.266e-3
+//   instead of 2.297e-3 of relative error at 4 heads of 333-token frames, T_o = 1, eight seeds, +- 3e-6: each
+//   group rounds its weights relative to a maximum of its own, whose weight of 1 is exact).  At d = 64 the
+//   split kernel is nearer by 0.6 %.
+// - d = 64 without a read-out at 1,664, 1 - 3 % slower up to there: softmax-only rows of 1,600 keys and fewer keep
+//   the same bits in a launch of any number of items.
 bool attn_splits(int64_t n_items, int64_t n_keys, int d, bool read_out) {
-  return n_items <= 256 && n_keys >= (read_out || d == 128 ? 960 : 1664);
+  return n_items <= 256 && n_keys >= (d == 128 ? (read_out ? 448 : 960) : read_out ? 960 : 1664);
 }
 
 int attn_query_tile(int) { return kQueryTile; }

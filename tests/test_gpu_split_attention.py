@@ -143,3 +143,18 @@ def test_short_softmax_only_rows_do_not_depend_on_the_launch(d, HW):
     out = binding.forward(*few, {n: p[:2].contiguous() for n, p in dphi.items()}, 1, HW, 1)
     torch.cuda.synchronize()
     assert torch.equal(out, many[:, :2])
+
+
+def test_error_of_short_windows_with_a_read_out():
+    """Windows of 448 - 959 keys at d = 128 go to the split kernel for its error: relative to fp64 over these eight
+    inputs 2.266e-3 (rounding y to bf16 alone is 1.65e-3), 2.297e-3 in attn_kernel, the mean of eight +- 3e-6."""
+    H, T, HW, d = 4, 5, 333, 128
+    errors = []
+    for seed in range(10, 18):
+        q, k, v = synth.make_qkv(1, H, T * HW, d, seed=seed)
+        phi = synth.make_phi(H, d, seed=seed + 1)
+        dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+        out = binding.forward(dq, dk, dv, dphi, T, HW, 1, overlap=1).double().cpu().numpy()
+        ref = cref.forward(*parity.oracle_inputs(q, k, v, phi), T, HW, 1, overlap=1).out
+        errors.append(((out - ref) ** 2).sum() ** 0.5 / (ref ** 2).sum() ** 0.5)
+    assert sum(errors) / 8 <= 2.282e-3, errors
