@@ -49,6 +49,34 @@ def test_weight_gradient_tiles(B, H, HW, d):
 
 
 @pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("nan", ["nan", "-nan", "inf - inf"])
+def test_gate_of_every_nan_is_closed(nan, d):
+    """As below, for NaN of either sign in the weights and for one that the products make."""
+    B, H, T, HW = 1, 2, 3, 97
+    q, k, v = synth.make_qkv(B, H, T * HW, d, seed=d)
+    G = synth.make_grad_out(B, H, T * HW, d).to("cuda", torch.bfloat16)
+    _, dk, dv, dphi = parity.to_device(q, k, v, synth.make_phi(H, d, seed=1, gain=4.0))
+    dq = q.to("cuda", torch.bfloat16)
+    runs = []
+    for on in (True, False):
+        phi = {n: t.clone() for n, t in dphi.items()}
+        for side in "qk":
+            phi[f"w1_{side}"][0, 5] = 0.0
+            phi[f"b1_{side}"][0, 5] = -1.0
+            if on and nan == "inf - inf":
+                phi[f"w1_{side}"][0, 5, :2] = torch.tensor([float("inf"), float("-inf")], device="cuda")
+                for x in (dq, dk):
+                    x[..., :2] = x[..., :2].abs() + 0.5
+                phi[f"b1_{side}"][0, 5] = 0.0
+            elif on:
+                phi[f"w1_{side}"][0, 5] = torch.tensor(0x7FC0 if nan == "nan" else -0x40, dtype=torch.int16).view(torch.bfloat16)
+        runs.append(binding.phi_backward(dq, dk, dv, phi, G, T, HW, 1)[0])
+    for n in runs[0]:
+        assert torch.isfinite(runs[0][n]).all(), n
+        assert torch.equal(runs[0][n], runs[1][n]), n
+
+
+@pytest.mark.parametrize("d", [128, 64])
 def test_gate_of_a_nan_is_closed(d):
     """A hidden unit that is NaN for every token is rectified to zero, and its gate is closed: the gradients are
     those of a unit that is negative everywhere, bit for bit."""
