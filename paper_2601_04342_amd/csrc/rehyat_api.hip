@@ -550,15 +550,7 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   P.nsplit = choose_cut((int)BH, P.n_seg, P.n_seg, (int64_t)chunk * HW, 0, d, kMaxSplit * P.nc, P.n_seg).nsplit;
   P.sl = Slots{P.n_seg * P.nsplit, P.nc};
   P.F = ws_layout(B, H, d, dp, P.sl);
-  // Weight gradients: one launch for both sides and both layers, cut so that its workgroups about
-  // fill the chip.  A tile costs nearly the same for either layer (12 heads, 10 pieces per side and (b, h):
-  // five and five 102 us at 320x480, 340 us at 480p; four and six 120 and 396; six and four 106 and 341).
-  const size_t tiles = (N + 63) / 64;
-  const int pieces = (int)((d == 128 ? kCUs : 2 * kCUs) / (2 * BH));   // per side and (b, h)
-  P.n2 = pieces > 1 ? (pieces + 1) / 2 : 1;
-  P.n1 = pieces > 1 ? pieces / 2 : 1;
-  if ((size_t)P.n2 > tiles) P.n2 = (int)tiles;
-  if ((size_t)P.n1 > tiles) P.n1 = (int)tiles;
+  weight_pieces((int)BH, (int64_t)((N + 63) / 64), d, &P.n2, &P.n1);
   size_t off = P.F.total;
   auto take = [&](size_t bytes) {
     const size_t o = off;

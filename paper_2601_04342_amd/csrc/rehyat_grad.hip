@@ -954,6 +954,39 @@ weight_grad_kernel(WeightGradArgs a) {
   else hid_body<D, NW>(s, a.H, a.N, bh, j - a.n2, a.n1, Ts, reinterpret_cast<uint32_t*>(Ts + 2 * 64 * 6 * D));
 }
 
+// The launch is cut to fill the chip once, twice or three times, whichever ends first, in even shares of both
+// kinds.  A tile takes 3.0 us for dW2 with every CU busy at d = 128 and 1.6 at d = 64, for dW1 a tenth less, and a
+// piece 20 and 10 us for its weights and its partial sums; in a single round what is left when some pieces have ended
+// runs faster, so it counts between its longest and its mean piece.  One round alone, rounded down to whole
+// pieces, leaves up to half of the chip idle behind the longest ones, or has a second round that is nearly empty.
+// Saved gradients, whole calls, one round and this rule:
+//   d = 128, 12,600 tokens: 33 heads 2 + 1 pieces 874 us, 4 + 3 831; 36 928 and 858; 65 1 + 1 1,976, 3 + 2 1,675; 96
+//   2,523 and 2,385; 24 stay at 3 + 2 (677; 5 + 5 689).  32,760 tokens: 24 heads 3 + 2 1,615, 8 + 8 1,579
+//   d = 64, 12,600 tokens: 72 heads 2 + 1 683, 4 + 3 628; 96 1 + 1 884, 4 + 4 824
+// Of all cuts tried at 44 such counts of heads and tokens the rule's was nowhere slower than one round's, and the best
+// or within 1 % of it but for four (1 - 6 % at 48, 72 and 130 heads of 64 and 36 of 128).
+void weight_pieces(int BH, int64_t tiles, int d, int* n2, int* n1) {
+  const int64_t slots = d == 128 ? 256 : 512;   // workgroups resident at once
+  const double tile2 = d == 128 ? 3.0 : 1.6, tile1 = 0.9 * tile2, piece = d == 128 ? 20.0 : 10.0;
+  double best = 1e300;
+  for (int rounds = 1; rounds <= 3; ++rounds) {
+    int64_t p = rounds * slots / (2 * (int64_t)BH);   // both kinds together
+    if (p < 2) p = 2;
+    int64_t c2 = (p + 1) / 2, c1 = p / 2;
+    if (c2 > tiles) c2 = tiles;
+    if (c1 > tiles) c1 = tiles;
+    const double t2 = piece + tile2 * (double)((tiles + c2 - 1) / c2), t1 = piece + tile1 * (double)((tiles + c1 - 1) / c1);
+    const double mean = (c2 * t2 + c1 * t1) / (double)(c2 + c1), longest = t2 > t1 ? t2 : t1;
+    const int64_t groups = 2 * (int64_t)BH * (c2 + c1), full = (groups + slots - 1) / slots - 1;
+    const double cost = full > 0 ? (double)full * mean + longest : 0.6 * longest + 0.4 * mean;
+    if (cost < 0.98 * best) {
+      best = cost;
+      *n2 = (int)c2;
+      *n1 = (int)c1;
+    }
+  }
+}
+
 hipError_t launch_weight_grad(const WeightGradArgs& a, int d, int grid, hipStream_t stream) {
   if (d == 128) hipLaunchKernelGGL((weight_grad_kernel<128, 8>), dim3(grid), dim3(512), 0, stream, a);
   else hipLaunchKernelGGL((weight_grad_kernel<64, 4>), dim3(grid), dim3(256), 0, stream, a);

@@ -229,6 +229,8 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t stream);
 hipError_t launch_suffix(const SuffixArgs& a, hipStream_t stream);
 hipError_t launch_act_grad(const ActGradArgs& a, int d, int grid, hipStream_t stream);
 hipError_t launch_weight_grad(const WeightGradArgs& a, int d, int grid, hipStream_t stream);
+// pieces of the tokens (`tiles` of 64) of each side and (b, h) in that launch: n2 for dW2, n1 for dW1
+void weight_pieces(int BH, int64_t tiles, int d, int* n2, int* n1);
 hipError_t launch_reduce(const ReduceJobs& jobs, hipStream_t stream);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t stream);
 

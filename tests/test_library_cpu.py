@@ -2,6 +2,7 @@
 every symbol the header declares, reproduces the hand-written chunk tables
 bit-exactly and turns bad arguments into error codes before any GPU work."""
 import ctypes
+import heapq
 import os
 import re
 
@@ -262,3 +263,21 @@ def test_contraction_kernels_keep_their_registers():
     kernels = dict(re.findall(rb"\.symbol..?(_Z\w+)\.kd.*?\.vgpr_spill_count(\xcc.|.)", lib, re.S))
     assert sum(b"state_kernel" in n or b"attn" in n or b"grad_kernel" in n for n in kernels) >= 14, sorted(kernels)
     assert all(v[-1] == 0 for v in kernels.values()), {n: v[-1] for n, v in kernels.items() if v[-1]}
+
+
+@pytest.mark.parametrize("tiles", [197, 512])
+@pytest.mark.parametrize("d,slots", [(128, 256), (64, 512)])
+def test_weight_gradient_pieces_keep_the_chip_busy(d, slots, tiles):
+    """The cut of the weight gradients over 1 - 260 (batch, head): dealt to the workgroups that are resident at once,
+    its pieces end within 1.5 times an even share of the tiles (one round, rounded down, took up to 1.97)."""
+    lib = ctypes.CDLL(build.LIB)
+    n2, n1 = ctypes.c_int(), ctypes.c_int()
+    for bh in range(1, 261):
+        lib._ZN6rehyat13weight_piecesEiliPiS0_(bh, ctypes.c_int64(tiles), d, ctypes.byref(n2), ctypes.byref(n1))
+        free = [0] * slots
+        for _ in range(2 * bh):
+            for n in (n2.value, n1.value):
+                assert 1 <= n <= tiles
+                for j in range(n):
+                    heapq.heappush(free, heapq.heappop(free) + tiles * (j + 1) // n - tiles * j // n)
+        assert max(free) <= 1.5 * 4 * bh * tiles / slots, (bh, n2.value, n1.value)
