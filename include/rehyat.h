@@ -232,12 +232,13 @@ int rehyat_forward_noalloc(const void *q, const void *k, const void *v,
  *             [H, dprime] for each map), summed over the batch; overwritten
  *   workspace DEVICE, 256-byte aligned, at least
  *             rehyat_phi_backward_workspace_bytes(...) bytes.  Unlike the
- *             forward workspace it grows with N: y_hat, dL/dy_hat / den and
- *             the gradient of the second layer's pre-activations are kept
- *             token by token, the latter for queries and keys (about 1.6 KB per
- *             token and head at d = 128), beside the per-workgroup partial sums
- *             of the weight gradients (at most 0.2 GB at d = 128 whenever B*H
- *             does not exceed 256).  Used only
+ *             forward workspace it grows with N: the gradients of the second
+ *             layer's pre-activations are kept token by token, for queries and
+ *             keys, the latter over y_hat and dL/dy_hat / den, which they
+ *             outlive (about 1.1 KB per token and head at d = 128), beside the
+ *             chunk states, over which the per-workgroup partial sums of the
+ *             weight gradients lie (at most 0.2 GB at d = 128 whenever B*H does
+ *             not exceed 256).  Used only
  *             for the duration of the enqueued work; no library state is
  *             touched.
  *

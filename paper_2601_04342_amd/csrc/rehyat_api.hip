@@ -551,27 +551,37 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   P.sl = Slots{P.n_seg * P.nsplit, P.nc};
   P.F = ws_layout(B, H, d, dp, P.sl);
   weight_pieces((int)BH, (int64_t)((N + 63) / 64), d, &P.n2, &P.n1);
-  size_t off = P.F.total;
+  // Areas that are not needed at the same time lie over each other (all launches are on one stream): the partial
+  // sums of the weight gradients over the states and R, which the key side's activation gradients read last,
+  // and what those write over what the query side has read.  480p at 12 heads of 128: 752 -> 498 MB.
+  size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
     off += align256(bytes);
     return o;
   };
-  P.yhat = take(BH * N * d * sizeof(bf16_t));
-  P.nS = take(BH * N * sizeof(float));
-  P.nL = take(BH * N * sizeof(float));
-  P.u = take(BH * N * d * sizeof(bf16_t));
-  P.tokw = take(BH * N * sizeof(float));
-  P.Rt = take(BH * P.nc * (size_t)dp * d * sizeof(bf16_t));
-  P.rz = take(BH * P.nc * (size_t)dp * sizeof(float));
-  P.w2t = take(2 * (size_t)H * hid * dp * sizeof(bf16_t));
   for (int side = 0; side < 2; ++side) {
-    P.dpsi[side] = take(BH * N * dp * sizeof(bf16_t));
-    P.signs[side] = take(BH * N * (hid / 32) * sizeof(uint32_t));
     P.p_w2[side] = take(BH * P.n2 * (size_t)dp * hid * sizeof(float));
     P.p_w1[side] = take(BH * P.n1 * ((size_t)d * hid + hid) * sizeof(float));
-    P.p_b2[side] = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
   }
+  const size_t sums = off;
+  off = P.F.total;
+  P.Rt = take(BH * P.nc * (size_t)dp * d * sizeof(bf16_t));
+  P.rz = take(BH * P.nc * (size_t)dp * sizeof(float));
+  if (off < sums) off = sums;
+  P.yhat = P.dpsi[1] = off;
+  take(BH * N * d * sizeof(bf16_t));
+  P.u = take(BH * N * d * sizeof(bf16_t));
+  P.nS = P.signs[1] = off;
+  take(BH * N * sizeof(float));
+  P.nL = take(BH * N * sizeof(float));
+  P.tokw = take(BH * N * sizeof(float));
+  const size_t signs = BH * N * (hid / 32) * sizeof(uint32_t);
+  if (off < P.signs[1] + align256(signs)) off = P.signs[1] + align256(signs);
+  P.dpsi[0] = take(BH * N * dp * sizeof(bf16_t));
+  P.signs[0] = take(signs);
+  P.w2t = take(2 * (size_t)H * hid * dp * sizeof(bf16_t));
+  for (int side = 0; side < 2; ++side) P.p_b2[side] = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
   P.p_dz = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
   P.total = off;
   return P;

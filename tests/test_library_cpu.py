@@ -281,3 +281,16 @@ def test_weight_gradient_pieces_keep_the_chip_busy(d, slots, tiles):
                 for j in range(n):
                     heapq.heappush(free, heapq.heappop(free) + tiles * (j + 1) // n - tiles * j // n)
         assert max(free) <= 1.5 * 4 * bh * tiles / slots, (bh, n2.value, n1.value)
+
+
+@pytest.mark.parametrize("B,H,T,HW,d,chunk,most", [
+    (1, 12, 21, 1560, 128, 1, 577_092_864),
+    (2, 12, 21, 1560, 128, 1, 1_046_959_872),
+    (1, 12, 21, 600, 128, 3, 300_880_128),
+    (1, 24, 21, 1560, 64, 1, 471_574_272),
+    (1, 2, 9, 1333, 128, 1, 143_992_064),
+])
+def test_phi_backward_workspace_does_not_grow(B, H, T, HW, d, chunk, most):
+    """What the gradients needed while each side had its own launches: a caller's buffer of that size still does.
+    (Both sides' activation gradients are kept at once now, over areas that are not needed by then.)"""
+    assert 0 < binding.phi_backward_workspace_bytes(B, H, T, HW, d, chunk) <= most
