@@ -269,7 +269,7 @@ __device__ __forceinline__ void softmax_last(const char* Vc, const FragBase& fo,
 
 // The softmax part over a wave's key tiles 0 .. n-1 (tile t of it is tile first_tile + t * stride
 // of the window): four waves share K in buffers 0/1 and V in 2/3 of `tiles`, picked by the parity of
-// t.  Meets n + 1 barriers, none with one tile.  Waves that are not live move their share of the tiles and compute nothing.
+// t.  Meets n + 1 barriers.  Waves that are not live move their share of the tiles and compute nothing.
 template <int D>
 struct SoftmaxTiles {
   using R = RangeTiles<2 * D, 4>;
@@ -295,7 +295,15 @@ struct SoftmaxTiles {
     const char *const K0 = tiles, *const K1 = tiles + TB, *const V0 = tiles + 2 * TB, *const V1 = tiles + 3 * TB;
     f32x16 E0[2], E1[2];
     bf16x8 fr[kAhead];
-    if constexpr (LIVE) softmax_scores<D>(K0, fo, Qr, E0);
+    if constexpr (LIVE) {
+      softmax_scores<D>(K0, fo, Qr, E0);
+      static_for<kAhead>([&](auto MC) {
+        constexpr int m = decltype(MC)::value;
+        fr[m] = k_fragment<D>(K1, fo, m / 2, m & 1);
+      });
+    }
+    lds_barrier();
+    if (n > 2) range.fill(K, row(2), lds);
     auto trip = [&](int t, const char* Kn, const char* Kn2, const char* Vc, int kbuf, int vbuf, f32x16 (&E)[2],
                     f32x16 (&En)[2]) {
       const u32x4 Kd = rsrc_if(K, t + 3 < n);
@@ -314,31 +322,21 @@ struct SoftmaxTiles {
       }
     };
     int t = 0;
-    const char* Vl = V0;
-    if (n > 1) {
-      if constexpr (LIVE) {
-        static_for<kAhead>([&](auto MC) {
-          constexpr int m = decltype(MC)::value;
-          fr[m] = k_fragment<D>(K1, fo, m / 2, m & 1);
-        });
-      }
-      lds_barrier();
-      if (n > 2) range.fill(K, row(2), lds);
-      for (; t + 2 < n; t += 2) {
-        trip(t, K1, K0, V0, 1, 3, E0, E1);
-        trip(t + 1, K0, K1, V1, 0, 2, E1, E0);
-      }
-      if (t + 1 < n) {
-        trip(t, K1, K0, V0, 1, 3, E0, E1);
-        if constexpr (LIVE) {
-#pragma unroll
-          for (int kb = 0; kb < 2; ++kb) E0[kb] = E1[kb];
-        }
-        Vl = V1;
-        ++t;
-      }
-      wait_loads_and_barrier<0>();
+    for (; t + 2 < n; t += 2) {
+      trip(t, K1, K0, V0, 1, 3, E0, E1);
+      trip(t + 1, K0, K1, V1, 0, 2, E1, E0);
     }
+    const char* Vl = V0;
+    if (t + 1 < n) {
+      trip(t, K1, K0, V0, 1, 3, E0, E1);
+      if constexpr (LIVE) {
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) E0[kb] = E1[kb];
+      }
+      Vl = V1;
+      ++t;
+    }
+    wait_loads_and_barrier<0>();
     if constexpr (LIVE) {
       softmax_last<D>(Vl, fo, E0, rows, sc, range.first(row(t)), range.count(row(t)), lane);
     }
@@ -877,10 +875,9 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
     if (st.n > 0) {
       if (wave_live) st.template run<true>(Qr, rows, a.scale_log2e);
       else st.template run<false>(Qr, rows, a.scale_log2e);
-      met = st.n > 1 ? st.n + 1 : 0;
+      met = st.n + 1;
     }
-    if (n_tiles > 2)   // group 1 may have a tile less
-      for (; met < (n_tiles + 1) / 2 + 1; ++met) lds_barrier();
+    for (; met < (n_tiles + 1) / 2 + 1; ++met) lds_barrier();   // group 1 may have a tile less, or none
     lds_barrier();
   }
 
