@@ -216,53 +216,46 @@ __device__ __forceinline__ void softmax_trip(const char* Kn, const char* Kn2, co
   rows.sum += sum;
 }
 
-// The last tile.  Keys outside [first, first + count) of it are not in the window: their weights are zero,
-// and their rows of V are cleared in the operands as well, where an infinity would make the product
-// NaN.  Steps of 16 keys without a key of the window are left out.
+// The last tile: keys outside [first, first + count) of it have been weighed already.
 template <int D>
 __device__ __forceinline__ void softmax_last(const char* Vc, const FragBase& fo, f32x16 (&E)[2], SoftmaxRows<D>& rows,
                                              float sc, int first, int count, int lane) {
-  constexpr int DB = D / 32;
-  bf16x8 fr[2][DB];   // by the parity of the step
+  constexpr int DB = D / 32, NM = 4 * DB;
+  const int g = lane >> 5;
+  bf16x8 fr[kAhead];
+  static_for<kAhead>([&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    fr[m] = v_fragment<D>(Vc, fo, m / DB, m % DB);
+  });
+  float mx = -INFINITY;   // of all 64 keys: the others stand in the window as well
 #pragma unroll
-  for (int db = 0; db < DB; ++db) fr[0][db] = v_fragment<D>(Vc, fo, 0, db);
-  const int base = 4 * (lane >> 5) - first;
-  auto in_window = [&](int e) { return (unsigned)(base + 8 * (e >> 2) + (e & 3)) < (unsigned)count; };
-  if (count < 64) {
+  for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-    for (int e = 0; e < 32; ++e)
-      if (!in_window(e)) E[e >> 4][e & 15] = -INFINITY;
-  }
-  float mx = -INFINITY;
-#pragma unroll
-  for (int e = 0; e < 32; ++e) mx = fmaxf(mx, E[e >> 4][e & 15]);
+    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, E[kb][e]);
   softmax_rescale<D>(rows, half_swap_max(mx) * sc);
+  const float again = kAgainLog2 - rows.ref;
   float sum = 0.f;
-  static_for<4>([&](auto SC) {
-    constexpr int step = decltype(SC)::value;
-    if constexpr (step < 3) {
+  uint32_t pw[4];
+  static_for<NM>([&](auto MC) {
+    constexpr int m = decltype(MC)::value, step = m / DB;
+    if constexpr (m % DB == 0) {
 #pragma unroll
-      for (int db = 0; db < DB; ++db) fr[(step + 1) & 1][db] = v_fragment<D>(Vc, fo, step + 1, db);
-    }
-    if (step_is_out(step, first, count)) return;   // this step only
-    u32x4 pw;
+      for (int i = 0; i < 8; i += 2) {
+        float p[2];
 #pragma unroll
-    for (int i = 0; i < 8; i += 2) {
-      float p[2];
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        p[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(E[step >> 1][8 * (step & 1) + i + j], sc, -rows.ref));
-        sum += p[j];
+        for (int j = 0; j < 2; ++j) {
+          const int e = 8 * (step & 1) + i + j;
+          const bool first_time = (unsigned)(32 * (step >> 1) + 8 * (e >> 2) + 4 * g + (e & 3) - first) < (unsigned)count;
+          p[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(E[step >> 1][e], sc, first_time ? -rows.ref : again));
+          sum += p[j];
+        }
+        pw[i >> 1] = pack_bf16(p[0], p[1]);
       }
-      pw[i >> 1] = pack_bf16(p[0], p[1]);
     }
-    if (step_is_cut(step, first, count)) {
-      const u32x4 keep = rows_kept(step, lane >> 5, first, count);
-#pragma unroll
-      for (int db = 0; db < DB; ++db) fr[step & 1][db] = keep_rows(fr[step & 1][db], keep);
-    }
-#pragma unroll
-    for (int db = 0; db < DB; ++db) rows.O[db] = mfma(fr[step & 1][db], __builtin_bit_cast(bf16x8, pw), rows.O[db]);
+    const u32x4 w = {pw[0], pw[1], pw[2], pw[3]};
+    rows.O[m % DB] = mfma(fr[m % kAhead], __builtin_bit_cast(bf16x8, w), rows.O[m % DB]);
+    if constexpr (m + kAhead < NM)
+      fr[m % kAhead] = v_fragment<D>(Vc, fo, (m + kAhead) / DB, (m + kAhead) % DB);
   });
   rows.sum += sum;
 }

@@ -251,40 +251,19 @@ struct RangeTiles {
     const int so = soff(row);
     static_for<LPT>([&](auto IC) { load<decltype(IC)::value>(rsrc, so, lds); });
   }
-  // rows [first, first + count) of the tile that starts at `row` belong to it
+  // Rows [first, first + count) of the tile that starts at `row` belong to it; the others are rows of the range that
+  // have been taken already (or, of a range of fewer than 64, its last row).
   __device__ __forceinline__ int first(int row) const { return rows >= 64 && row > rows - 64 ? row + 64 - rows : 0; }
   __device__ __forceinline__ int count(int row) const { return row > rows - 64 ? rows - row : 64; }
 };
+// What such a row weighs when it is met again.  Not zero, which would make NaN of an infinity that the sums hold
+// already; 2^-40 of its own contribution is 2^-16 of what fp32 rounds off beside that.
+constexpr float kAgainLog2 = -40.f, kAgain = 0x1p-40f;
 // The descriptor, or one that fetches nothing: a branch around loads that are spread over products
 // would let the compiler move vector work out of its place.
 __device__ __forceinline__ u32x4 rsrc_if(u32x4 rsrc, bool on) {
   rsrc[2] = on ? rsrc[2] : 0u;
   return rsrc;
-}
-
-// Rows [first, first + count) of a 64-row tile belong to it; the others meet zeros in a product over rows, but
-// an infinity in them would make it NaN.  A product over rows 16 step .. + 15 is left out if none of
-// them belong, and its LDS operand keeps only the rows that do if not all of them.
-__device__ __forceinline__ bool step_is_out(int step, int first, int count) {
-  return 16 * step + 16 <= first || 16 * step >= first + count;
-}
-__device__ __forceinline__ bool step_is_cut(int step, int first, int count) {
-  return 16 * step < first || 16 * step + 16 > first + count;
-}
-// Element e of the operand of lane half g is row 16 step + 8 (e >> 2) + 4 g + (e & 3).
-__device__ __forceinline__ u32x4 rows_kept(int step, int g, int first, int count) {
-  u32x4 keep;
-  int base = 16 * step + 4 * g - first;
-  asm volatile("" : "+v"(base));   // comparisons of the same rows elsewhere are not kept for this
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int row = base + 8 * (i >> 1) + 2 * (i & 1);
-    keep[i] = ((unsigned)row < (unsigned)count ? 0xffffu : 0u) | ((unsigned)(row + 1) < (unsigned)count ? 0xffff0000u : 0u);
-  }
-  return keep;
-}
-__device__ __forceinline__ bf16x8 keep_rows(bf16x8 x, u32x4 keep) {
-  return __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, x) & keep);
 }
 
 // Makes the compiler wait here for the loads that filled these operands.  Without it the wait
@@ -305,7 +284,8 @@ __device__ __forceinline__ void pin(T& x) {
   asm volatile("" : "+v"(x));
 }
 
-// The same for a whole tile in LDS, by NT threads; a barrier has to follow.
+// Clears the rows of a 64-row tile in LDS that do not belong to it, by NT threads; a barrier has to follow.
+// (For operands that meet zeros in those rows: an infinity there would make the product NaN.)
 template <int ROWBYTES, int NT>
 __device__ __forceinline__ void clear_other_rows(char* tile, int first, int count, int tid) {
 #pragma unroll

@@ -194,7 +194,6 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
     constexpr int LP = KS2, LF = MORE ? KS : 0, LS = 2 * DB;
     constexpr int F0 = LP, P1 = LP + LF, F1 = P1 + LP, S0 = F1 + LF, S1 = S0 + LS, NM = S1 + LS;
     static_assert(NM % PD == 0, "the fragment ring closes over a step");
-    static_assert(MORE || P1 <= S0 - PD, "V is cleared before it is read");
     static_assert(S0 + 3 < NM - PD, "U is stored before the barrier that publishes it");
     f32x16 u[2], ps[2];
     uint32_t fb[2][8];   // phi as operands
@@ -238,7 +237,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
         const int e = 2 * i + j;
         x[j] = fmaxf(ps[tb][e] + b2v, 0.f);
         if (squared) x[j] = x[j] * x[j];
-        if (!MORE && (unsigned)(32 * tb + 8 * (e >> 2) + 4 * g + (e & 3) - first) >= (unsigned)count) x[j] = 0.f;
+        if (!MORE && (unsigned)(32 * tb + 8 * (e >> 2) + 4 * g + (e & 3) - first) >= (unsigned)count) x[j] *= kAgain;
       }
       fb[tb][i] = pack_bf16(x[0], x[1]);
       // The normaliser sums the features as rounded for the product: with unrounded ones S and z
@@ -252,12 +251,6 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
     static_for<NM>([&](auto MC) {
       constexpr int m = decltype(MC)::value;
       if constexpr (MORE && m == NM - PD) wait_loads_and_barrier<0>();
-      if constexpr (!MORE && (m == 0 || m == P1)) {   // V is first read PD products before S0
-        if (count < 64) {
-          if (m == 0) clear_other_rows<2 * D, 64 * NW>(XV + (2 + (it & 1)) * TB, first, count, tid);
-          else lds_barrier();
-        }
-      }
       product(MC);
       fetch(std::integral_constant<int, m + PD>{});
       if constexpr (MORE && m % 2 == 1 && m < 4 * R::LPT) {
