@@ -6,6 +6,10 @@ v_cvt_pk_bf16_f32, v_mov_b32 streams; MFMA mixed with exponentials and FMAs (ME*
 workgroup per CU, 256 threads (one wave per SIMD) and 512 threads (two waves per SIMD).
 Prints, per pattern, the shader-clock cycles per iteration seen by a wave (clock64) and the
 wall time per iteration in cycles of the nominal 2.4 GHz clock.
+Then the mixes of the tile loops with their LDS reads, on random operands, two waves per SIMD: what one wave
+does per 64-key or 64-token tile in the attention kernels (ATTN128, ATTN64) and in the chunk-state kernel (STATE128,
+STATE64), without tile loads, barriers or dependences; and the same without vector work, without LDS reads, and the
+products alone; with all CUs busy and with 32.  Prints ns per product and SIMD.
 
     python gen_issue_rates.py && hipcc --offload-arch=gfx950 -O3 -o issue_rates issue_rates.hip && ./issue_rates
 """
@@ -102,5 +106,91 @@ for pi, n in enumerate(names):
         for th in (256, 512):
             src += f'  run<{pi}, {"true" if ag else "false"}>("{n}", d, dc, {th});\n'
 src += '  printf("issue done\\n");\n  return 0;\n}\n'
+
+def mix(nm, b128, tr, ops):
+    """nm products, each behind its share of LDS reads (fragments four ahead) and vector instructions."""
+    lines, done = [], [0, 0, 0]
+    for m in range(nm):
+        lines.append("s_waitcnt lgkmcnt(6)")
+        lines.append(f"v_mfma_f32_32x32x16_bf16 %{m % 4}, %{4 + m % 4}, %8, %{m % 4}")
+        for i, n in enumerate((b128, tr, len(ops))):
+            while done[i] < (m + 1) * n // nm:
+                j = done[i]
+                if i == 0: lines.append(f"ds_read_b128 %{4 + m % 4}, %22 offset:{j % 24 * 1024}")
+                elif i == 1: lines.append(f"ds_read_b64_tr_b16 %{9 + j % 4}, %22 offset:{j % 24 * 1024}")
+                else: lines.append(ops[j])
+                done[i] += 1
+    return lines + ["s_waitcnt lgkmcnt(0)"]
+def softmax_ops():   # 32 exponents of a lane: maximum, scale, exponential, sum, rounding
+    ops = [f"v_max3_f32 %20, %17, %18, %20" for _ in range(16)]
+    for e in range(32):
+        t = 13 + e % 4
+        ops += [f"v_fma_f32 %{t}, %17, %18, %19", f"v_exp_f32 %{t}, %{t}", f"v_add_f32 %20, %20, %{t}"]
+        if e % 2: ops.append(f"v_cvt_pk_bf16_f32 %21, %{t}, %{13 + (e - 1) % 4}")
+    return ops
+def state_ops():   # 32 units of U and 32 features of a lane: rectified, rounded; features summed
+    ops = []
+    for e in range(32):
+        t = 13 + e % 4
+        ops += [f"v_max_f32 %{t}, 0, %17", f"v_add_f32 %{t}, %{t}, %19", f"v_max_f32 %{t}, 0, %{t}", f"v_add_f32 %20, %20, %{t}"]
+        if e % 2: ops += [f"v_cvt_pk_bf16_f32 %21, %{t}, %{13 + (e - 1) % 4}"] * 2
+    return ops
+sm, so = softmax_ops(), state_ops()
+mixes = {'ATTN128': (32, 16, 32, sm), 'ATTN64': (16, 8, 16, sm), 'STATE128': (64, 48, 32, so), 'STATE64': (24, 16, 16, so)}
+full = {}
+for n, (nm, b, t, o) in mixes.items():
+    full[n] = (nm, mix(nm, b, t, o))
+    full[n + '-valu'] = (nm, mix(nm, b, t, []))
+    full[n + '-lds'] = (nm, mix(nm, 0, 0, o))
+full['PRODUCTS'] = (32, mix(32, 0, 0, []))
+head = r'''
+template <int PAT>
+__global__ void __launch_bounds__(512) kl(float* out, const float* rnd, int iters) {
+  __shared__ __attribute__((aligned(1024))) __bf16 lds[16384];   // 32 KB; reads stay below 24 KB + 8 KB
+  for (int i = threadIdx.x; i < 16384; i += 512) lds[i] = (__bf16)rnd[i];
+  __syncthreads();
+  bf16x8 r0, r1, r2, r3, b;
+  for (int e = 0; e < 8; ++e) {
+    r0[e] = lds[threadIdx.x * 8 + e]; r1[e] = lds[4096 + threadIdx.x * 8 + e]; r2[e] = lds[8192 + threadIdx.x * 8 + e];
+    r3[e] = lds[12288 + threadIdx.x * 8 + e]; b[e] = lds[(threadIdx.x * 8 + e + 777) & 16383];
+  }
+  f32x16 c0 = {0}, c1 = {0}, c2 = {0}, c3 = {0};
+  typedef __attribute__((__vector_size__(4 * sizeof(short)))) short i16x4;
+  i16x4 t0 = {0}, t1 = {0}, t2 = {0}, t3 = {0};
+  float y0 = 0, y1 = 0, y2 = 0, y3 = 0, x = -fabsf(rnd[threadIdx.x]), kk = 0.127f, k2 = -0.3f, s = 0, cv = 0;
+  const int addr = (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds + (threadIdx.x & 511) * 16;
+  for (int i = 0; i < iters; ++i) {
+'''
+for pi, (n, (nm, lines)) in enumerate(full.items()):
+    body = "\\n\\t".join(lines)
+    head += f'''    if (PAT == {pi}) asm volatile("{body}"
+      : "+v"(c0), "+v"(c1), "+v"(c2), "+v"(c3), "+v"(r0), "+v"(r1), "+v"(r2), "+v"(r3), "+v"(b), "+v"(t0), "+v"(t1), "+v"(t2), "+v"(t3),
+        "+v"(y0), "+v"(y1), "+v"(y2), "+v"(y3), "+v"(x), "+v"(kk), "+v"(k2), "+v"(s), "+v"(cv) : "v"(addr) : "memory");
+'''
+head += r'''  }
+  for (int r = 0; r < 16; ++r) s += c0[r] + c1[r] + c2[r] + c3[r];
+  out[blockIdx.x * 512 + threadIdx.x] = s + cv + y0 + y1 + y2 + y3 + t0[0] + t1[0] + t2[0] + t3[0];
+}
+template <int PAT>
+void run_mix(const char* name, float* d, const float* rnd, int products) {
+  const int iters = 4000;
+  hipEvent_t e0, e1; CK(hipEventCreate(&e0)); CK(hipEventCreate(&e1));
+  double ns[2];
+  for (int g = 0; g < 2; ++g) {
+    float ms = 0;
+    for (int rep = 0; rep < 3; ++rep) {
+      CK(hipEventRecord(e0));
+      kl<PAT><<<g ? 32 : 256, 512>>>(d, rnd, iters);
+      CK(hipEventRecord(e1)); CK(hipEventSynchronize(e1));
+      CK(hipEventElapsedTime(&ms, e0, e1));
+    }
+    ns[g] = ms * 1e6 / iters / (2 * products);
+  }
+  printf("%-14s %d products a wave and tile: %.1f ns per product and SIMD with 256 CUs, %.1f with 32\n", name, products, ns[0], ns[1]);
+}
+'''
+src = src.replace("int main() {", head + "int main() {\n  static float h_rnd[16384];\n  srand(1);\n  for (float& v : h_rnd) v = (float)((rand() % 2001) + (rand() % 2001) + (rand() % 2001) - 3000) / 1000.f;\n"
+                  "  float* rnd;\n  CK(hipMalloc(&rnd, sizeof(h_rnd)));\n  CK(hipMemcpy(rnd, h_rnd, sizeof(h_rnd), hipMemcpyHostToDevice));\n")
+src = src.replace('  printf("issue done', "".join(f'  run_mix<{pi}>("{n}", d, rnd, {nm});\n' for pi, (n, (nm, _)) in enumerate(full.items())) + '  printf("issue done')
 import os
 open(os.path.join(os.path.dirname(os.path.abspath(__file__)), 'issue_rates.hip'), 'w').write(src)

@@ -210,7 +210,9 @@ int bidir_window(int T, int chunk, int overlap, int fwin, int state_slots) {
 // of 128): a state workgroup takes about 10 us to load its weights and store its sums and 4 us per
 // 64-token tile (at d = 64 1.5 us alone on a CU and 2.1 us beside another one); each partial sum
 // is read once more by the prefix pass; each further window of chunks costs its own launches, and the
-// attention launch of a window ends on a partly empty round (about half of a workgroup's time).
+// attention launch of a window ends on a partly empty round (about half of a workgroup's time).  (The tile times are
+// those of the loops that ran a tile's phases one after the other; with the present ones a tile takes up to 8 %
+// less at d = 64 and 3 % at d = 128.)
 //
 // A state launch of `segs` segments of `seg_tokens` tokens per (b, h), each in `ns` pieces, and the
 // reading of its sums:
@@ -1119,15 +1121,14 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   };
   // Up to one attention workgroup per CU the launch absorbs beside its own work (attn_split_kernel),
   // otherwise a second stream does when one is at hand (and attn_kernel runs).  Whole steps, joint
-  // against forked, 136 sampled of up to 256 tiles and 2,700 keys at both head widths: joint was never
-  // slower, also where the pieces do not fit the CUs left over and start when attention workgroups
-  // end, and where the window alone would not be split (2 tiles of 64 keys 21 against 54 us, 96 tiles
-  // 45 against 55, 156 tiles of 3,120 keys, all absorbed, 68 against 79, 256 tiles of 256 (batch, head)
-  // with 2,048 keys, all absorbed, 253 against 258; d = 64: 252 tiles 32 against 60).  With long
-  // windows at d = 64 the fork costs nothing any more, and pieces that start late cost more than the
-  // split gains once they are long: 252 tiles, 5,376 keys, all absorbed, joint 96 and forked 84 us;
-  // 240 tiles, a third of 9,000 absorbed, 139 and 126; but a third of 5,376 in pieces of six tiles 82
-  // and 82, and at 3,000 keys 59 and 58, 63 and 67.
+  // against forked: joint is faster, also where the pieces do not fit the CUs left over and start when
+  // attention workgroups end, and where the window alone would not be split (d = 128: 2 tiles of 64 keys
+  // 21 against 59 us, 96 tiles of 1,024 keys 36 against 64, 156 tiles of 3,120 keys, all absorbed, 61 against
+  // 70, 256 tiles of 256 (batch, head) with 2,048 keys, all absorbed, 213 against 237; d = 64: 240 tiles of
+  // 1,280 keys 32 against 56, 252 of 3,000, all absorbed, 58 against 66).  With long windows at d = 64 the
+  // fork costs nothing any more, and pieces that start late cost more than the split gains once they are
+  // long: 252 tiles, 5,376 keys, all absorbed, joint 102 and forked 91 us; 4,500 keys 81 and 82; 240 tiles,
+  // a third of 9,000 absorbed, 108 and 110; a third of 5,376 in pieces of six tiles 75 and 73.
   int nsplit = n_absorb > 0 ? pieces_for(kCUs - attn_wgs) : 0;
   const bool late_and_long = d == 64 && n_win >= 4096 && attn_wgs + B * H * nsplit > kCUs && max_pieces > 10 * nsplit;
   const bool joint = n_absorb > 0 && attn_wgs <= kCUs && !late_and_long;
@@ -1140,7 +1141,7 @@ int rehyat_step(const void* q_t, const void* k_win, const void* v_win, const reh
   if (n_absorb > 0) {
     // In the attention launch a sixteenth of the rows always takes less time than the attention over
     // the window that holds them, and further pieces only lengthen the addition after it (2 heads of 64,
-    // 5,376 rows: 64 pieces 83 us, 16 pieces 70 us).  Alone, three quarters of the chip measured best.
+    // 5,376 rows: 64 pieces 69 us, 16 pieces 55, 8 pieces 53).  Alone, three quarters of the chip measured best.
     if (joint) nsplit = nsplit < 16 ? nsplit : 16;
     else if (!side) nsplit = pieces_for(3 * kCUs / 4);
     s.k = (const bf16_t*)k_win;

@@ -132,12 +132,12 @@ __device__ __forceinline__ void softmax_scores(const char* Ks, const FragBase& f
 // slot by slot -- a slot is one product, one fragment read kAhead products ahead, its share of
 // the vector work -- and fenced, because the compiler's own order waits for every LDS read right
 // after issuing it.
-// What bounds it: on a filled chip power (products with the same mix of other work and nothing
-// else: 23 ns per product and SIMD with all CUs busy, 14.5 with 32; here 28 - 30, 25 without the tile
-// loads); with CUs to spare the issue of some 300 instructions per tile and wave.  Against the tile
-// loop that ran the four phases one after the other: 1,488 -> 1,389 us summed over the 480p, 720p and
-// three-frame-chunk guidance-pair launches, streaming step at 480p with T_o = 1 60 -> 55 us, d = 64
-// at 480p 441 -> 430 us.
+// What bounds it: on a filled chip power (a loop of nothing but the same products, vector work and LDS reads,
+// on random operands: 23 - 25 ns per product and SIMD with all CUs busy, 14.5 with 32; here 28 - 30, 25 without
+// the tile loads), at d = 64 power and vector work (32 ns in such a loop, 23 with 32 CUs); with CUs to spare the
+// issue of some 300 instructions per tile and wave.  Against the tile loop that ran the four phases one after
+// the other: 1,488 -> 1,389 us summed over the 480p, 720p and three-frame-chunk guidance-pair launches,
+// streaming step at 480p with T_o = 1 60 -> 55 us, d = 64 at 480p 441 -> 430 us.
 //
 // The one barrier per tile stands where the last K fragment of tile t+1 has been read and kAhead
 // products are still to be issued, so that its wait and the first V fragments' latency lie under
@@ -1051,8 +1051,9 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
 }
 
 // The split kernel holds one workgroup per CU (tile buffers of 128 KB), so it can only win while
-// its launch is a single round: at 256 items and fewer (with the loops before these, 312 items of 25 key
-// tiles took 94 against 81 us, 624 items 134 against 121).  Below that the keys decide, since the two
+// its launch is a single round: at 256 items and fewer (split against not: d = 128 270 items of 1,100 keys 66.3 and
+// 62.8 us, 312 of 1,500 74.5 and 71.3, 576 of 1,500 112 and 108, 1,152 of 3,000 274 and 259; d = 64 312 of 1,500
+// 46.3 and 41.5, 1,152 of 3,000 164 and 148).  Below that the keys decide, since the two
 // groups' meeting has to be paid by them.  Whole calls, split against not: d = 128 with a read-out 32
 // items of 448 keys 39.6 and 37.9 us, 200 of 512 47.2 and 45.3, 180 of 600 46.3 and 45.8, 168 of 800 50.8 and
 // 50.2, 128 of 1,000 48.6 and 48.8, 144 of 1,536 54.1 and 55.6, 96 of 2,000 60.2 and 63.6; d = 64 160 of 640

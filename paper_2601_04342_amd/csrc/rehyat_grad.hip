@@ -593,7 +593,7 @@ __device__ __forceinline__ void tn_body(const WeightGradSide& a, int H, int64_t 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int g = lane >> 5, r = lane & 31, i16 = lane & 15;
+  const int g = lane >> 5, r = lane & 31;
   const int wf = wave >> 1, wh = wave & 1;
   const int h = bh % H;
   const Piece pc = piece_of(a.lo, a.hi, sp, nsplit);
@@ -649,7 +649,7 @@ __device__ __forceinline__ void tn_body(const WeightGradSide& a, int H, int64_t 
   constexpr int kRing = 8, kLook = D == 128 ? 3 : 4;
   bf16x8 fr[kRing];
   // column of the wave's first 32 of dpsi (rows of dW2) and of U
-  auto f_base = [&](const GradOffsets<D>&, int col) {
+  auto f_base = [&](int col) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
     return tile_off<ROWB>(4 * (ln >> 5) + ((ln & 15) >> 2), col + 16 * ((ln & 31) >> 4) + 4 * (ln & 3));
@@ -671,13 +671,13 @@ __device__ __forceinline__ void tn_body(const WeightGradSide& a, int H, int64_t 
       for (int i = 0; i < 4; ++i) u_store(u, i, 0, tb);
     }
     lds_barrier();   // U of tile 0 is complete
-    const int pb = f_base(o, 64 * wf), ub = f_base(o, (W / 2) * wh);
+    const int pb = f_base(64 * wf), ub = f_base((W / 2) * wh);
     static_for<kLook>([&](auto QC) { fr[decltype(QC)::value] = s_read(0, pb, ub, 0, decltype(QC)::value); });
   }
   auto tile_step = [&](auto MOREC, int it) {
     constexpr bool MORE = decltype(MOREC)::value;
     const GradOffsets<D> o(lane);
-    const int pb = f_base(o, 64 * wf), ub = f_base(o, (W / 2) * wh);
+    const int pb = f_base(64 * wf), ub = f_base((W / 2) * wh);
     const u32x4 Xd = rsrc_if(Xr, it + 2 < n_tiles);
     const int xs = xrange.soff(64 * (it + 2)), ps = prange.soff(64 * (it + 1));
     const uint32_t xd = x_lds + (it & 1) * TB, pd = p_lds + ((it + 1) & 1) * TBY;
@@ -755,7 +755,7 @@ __device__ __forceinline__ void tn_body(const WeightGradSide& a, int H, int64_t 
       clear_other_rows<ROWB, 64 * NW>(Pt + (it & 1) * TBY, first, count, tid);
       lds_barrier();
       const GradOffsets<D> o(lane);
-      const int pb = f_base(o, 64 * wf), ub = f_base(o, (W / 2) * wh);
+      const int pb = f_base(64 * wf), ub = f_base((W / 2) * wh);
       static_for<kLook>([&](auto QC) { fr[decltype(QC)::value] = s_read(it, pb, ub, 0, decltype(QC)::value); });
     }
     tile_step(std::false_type{}, it);

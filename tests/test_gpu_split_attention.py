@@ -2,11 +2,13 @@
 tiles and the features of a query block) at the sizes where it can go wrong: one key tile, an odd
 and an even number of them, a ragged last one on either group, query blocks without a query, chunks
 without a linear part, both head widths; and the streaming step that absorbs beside it."""
+import ctypes
+
 import pytest
 import torch
 
 from oracle import cref
-from paper_2601_04342_amd import binding, synth
+from paper_2601_04342_amd import binding, build, synth
 from tests import parity
 
 pytestmark = pytest.mark.gpu
@@ -20,8 +22,8 @@ def _announce(request):
 
 
 @pytest.mark.parametrize("case", [
-    # B, H, T, HW, d, chunk, overlap, stab, gain: whole-sequence calls, windows of 448 keys (1,536
-    # at d = 64) and more
+    # B, H, T, HW, d, chunk, overlap, stab, gain: whole-sequence calls, windows of 448 keys (960 at d = 64
+    # or without a read-out, 1,664 with neither) and more
     (1, 1, 2, 448, 128, 1, 0, 0, 4.0),     # the smallest window: 7 full tiles
     (1, 1, 2, 1024, 128, 1, 0, 0, 4.0),    # 16 full tiles
     (1, 1, 2, 1025, 128, 1, 0, 0, 4.0),    # 17 tiles: one key in the last, the second group has none
@@ -158,3 +160,18 @@ def test_error_of_short_windows_with_a_read_out():
         ref = cref.forward(*parity.oracle_inputs(q, k, v, phi), T, HW, 1, overlap=1).out
         errors.append(((out - ref) ** 2).sum() ** 0.5 / (ref ** 2).sum() ** 0.5)
     assert sum(errors) / 8 <= 2.282e-3, errors
+
+
+@pytest.mark.parametrize("T,HW,d,split", [
+    (2, 447, 128, False), (2, 448, 128, True),     # with a read-out: 7 tiles, the last one short or full
+    (2, 959, 64, False), (2, 960, 64, True), (2, 961, 64, True),   # 15 tiles, then 16
+    (1, 959, 128, False), (1, 960, 128, True),     # without one
+    (1, 1663, 64, False), (1, 1664, 64, True),     # 26 tiles
+])
+def test_both_sides_of_each_line(T, HW, d, split):
+    """The smallest windows that take the split kernel and the largest that do not, by the library's own rule."""
+    rule = ctypes.CDLL(build.LIB)._ZN6rehyat11attn_splitsEllib
+    rule.restype = ctypes.c_bool
+    takes = lambda keys: rule(ctypes.c_int64(T * -(-HW // 128)), ctypes.c_int64(keys), d, ctypes.c_bool(T > 1))
+    assert takes(HW) == split
+    parity.run_case(1, 1, T, HW, d, 1, 0, 0, 4.0 if T > 1 else 1.0, seed=HW + d)
