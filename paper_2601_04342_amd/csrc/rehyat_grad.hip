@@ -631,15 +631,13 @@ __device__ __forceinline__ void tn_body(const WeightGradSide& a, int H, int64_t 
     for (int e = 0; e < 16; ++e) u[e] = g ? b1.hi[e] : b1.lo[e];
     return u;
   };
-  // U of tile `it`: tokens that are not of this tile (ragged last one) store zeros
   auto u_store = [&](const f32x16& u, int i, int it, int tb) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int tok = ln & 31;
-    const bool live = (unsigned)(32 * tb + tok - xrange.first(64 * it)) < (unsigned)xrange.count(64 * it);
     u32x2 pk;
-    pk[0] = live ? pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f)) : 0u;
-    pk[1] = live ? pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f)) : 0u;
+    pk[0] = pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f));
+    pk[1] = pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f));
     *reinterpret_cast<u32x2*>(Us + (it & 1) * TBY + tb * (32 * ROWB) + tok * ROWB + (((wave * 4 + i) ^ swz<ROWB>(tok)) << 4) +
                               8 * (ln >> 5)) = pk;
   };
@@ -751,8 +749,12 @@ __device__ __forceinline__ void tn_body(const WeightGradSide& a, int H, int64_t 
   for (int it = 0; it + 1 < n_tiles; ++it) tile_step(std::true_type{}, it);
   if (n_tiles > 0) {
     const int it = n_tiles - 1, first = prange.first(64 * it), count = prange.count(64 * it);
-    if (count < 64) {   // then the fragments that were read ahead are read again
+    // Rows of dpsi and U that do not belong are cleared, both, so that an infinity in either meets no zero; the
+    // fragments that were read ahead are read again.  (U masked as it is stored cost every tile of the loop four
+    // instructions per store: 320x480 96 us a launch, this way 91.)
+    if (count < 64) {
       clear_other_rows<ROWB, 64 * NW>(Pt + (it & 1) * TBY, first, count, tid);
+      clear_other_rows<ROWB, 64 * NW>(Us + (it & 1) * TBY, first, count, tid);
       lds_barrier();
       const GradOffsets<D> o(lane);
       const int pb = f_base(64 * wf), ub = f_base((W / 2) * wh);
