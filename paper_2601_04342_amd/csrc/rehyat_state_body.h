@@ -98,6 +98,8 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   const uint32_t k_lds = lds_address(XV), v_lds = k_lds + 2 * TB;
   using R = RangeTiles<2 * D, NW>;
   const R range(n_tokens, wave, lane);
+  const int uwbase = r * UPAD + wave * 64 + 8 * g;   // write: token r, units 32w + 8i + 4g .. +3 at + 16 i
+  const int urbase = r * UPAD + 16 * g;              // read: A fragment of token r, k-step ks at + 32 ks
 
   // state slice: acc[db] register 4i+j = (row d = 32db+8i+4g+j, feature 32w+r)
   f32x16 acc[DB];
@@ -119,7 +121,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
     }
     return u;
   };
-  auto u_store = [&](const f32x16& u, int i, char* Ud, int uwbase, int tb) {   // register 4i+j = (hidden 32w+8i+4g+j, token 32tb+r)
+  auto u_store = [&](const f32x16& u, int i, char* Ud, int tb) {   // register 4i+j = (hidden 32w+8i+4g+j, token 32tb+r)
     u32x2 pk;
     pk[0] = pack_bf16(fmaxf(u[4 * i], 0.f), fmaxf(u[4 * i + 1], 0.f));
     pk[1] = pack_bf16(fmaxf(u[4 * i + 2], 0.f), fmaxf(u[4 * i + 3], 0.f));
@@ -137,10 +139,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   auto v_base = [&](int ln) {
     return tile_off<2 * D>(4 * (ln >> 5) + ((ln & 15) >> 2), 16 * ((ln & 31) >> 4) + 4 * (ln & 3));
   };
-  // U: written for token r, units 32w + 8i + 4g .. +3 at + 16 i; read as A fragment of token r, k-step ks at + 32 ks
-  auto uw_base = [&](int ln) { return (ln & 31) * UPAD + wave * 64 + 8 * (ln >> 5); };
-  auto ur_base = [&](int ln) { return (ln & 31) * UPAD + 16 * (ln >> 5); };
-  auto u_fragment = [&](const char* Uc, int urbase, int tb, int ks) {
+  auto u_fragment = [&](const char* Uc, int tb, int ks) {
     return *reinterpret_cast<const bf16x8*>(Uc + urbase + 32 * ks + tb * (32 * UPAD));
   };
 
@@ -157,7 +156,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   if (n_tiles > 0) {
     wait_loads_and_barrier<0>();   // also: the bias is in LDS
     const int ln = opaque_lane();
-    const int xbase = x_base(ln), uwbase = uw_base(ln);
+    const int xbase = x_base(ln);
 #pragma unroll
     for (int tb = 0; tb < 2; ++tb) {
       f32x16 u = u_start();
@@ -165,7 +164,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
       for (int ks = 0; ks < KS; ++ks)
         u = mfma(w1f[ks], *reinterpret_cast<const bf16x8*>(XV + (xbase ^ (32 * ks)) + tb * (32 * 2 * D)), u);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) u_store(u, i, Us, uwbase, tb);
+      for (int i = 0; i < 4; ++i) u_store(u, i, Us, tb);
     }
     lds_barrier();   // U of tile 0 is complete
   }
@@ -186,7 +185,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
     const char* const Uc = Us + (it & 1) * (64 * UPAD);
     char* const Ud = Us + ((it + 1) & 1) * (64 * UPAD);
     const int ln = opaque_lane();
-    const int xbase = x_base(ln), vbase = v_base(ln), uwbase = uw_base(ln), urbase = ur_base(ln);
+    const int xbase = x_base(ln), vbase = v_base(ln);
     const int first = range.first(64 * it), count = range.count(64 * it);   // tokens of the last tile
     const u32x4 Kd = rsrc_if(Kr, it + 2 < n_tiles);
     const int ks = range.soff(64 * (it + 2)), vs = range.soff(64 * (it + 1));
@@ -201,9 +200,9 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
     auto fetch = [&](auto MC) {   // the LDS operand of product m
       constexpr int m = decltype(MC)::value;
       if constexpr (m >= NM) {
-        if constexpr (MORE) fr[m % PD] = u_fragment(Ud, urbase, 0, m - NM);   // psi of the next tile
+        if constexpr (MORE) fr[m % PD] = u_fragment(Ud, 0, m - NM);   // psi of the next tile
       } else if constexpr (m < F0 || (m >= P1 && m < F1)) {
-        fr[m % PD] = u_fragment(Uc, urbase, m >= P1, m - (m >= P1 ? P1 : 0));
+        fr[m % PD] = u_fragment(Uc, m >= P1, m - (m >= P1 ? P1 : 0));
       } else if constexpr (m < S0) {
         constexpr int tb = m >= F1, ks = m - (tb ? F1 : F0);
         if constexpr (ks == 0) u[tb] = u_start();
@@ -265,8 +264,8 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
           static_for<kPairs>([&](auto JC) { phi(TBC, std::integral_constant<int, kPairs * p + decltype(JC)::value>{}); });
         constexpr int q = m - (tb ? S0 : P1) - 2;   // two quads of units per slot: done before the barrier
         if constexpr (MORE && q >= 0 && q < 2) {
-          u_store(u[tb], 2 * q, Ud, uwbase, tb);
-          u_store(u[tb], 2 * q + 1, Ud, uwbase, tb);
+          u_store(u[tb], 2 * q, Ud, tb);
+          u_store(u[tb], 2 * q + 1, Ud, tb);
         }
       });
       __builtin_amdgcn_sched_barrier(0);
@@ -286,8 +285,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
     // (Read here and not before the branch: there they were kept, spilled, for the loop behind the other one, whose
     // every step then waited for all loads in flight at their first use.)
     if (n_tiles > 0) {
-      const int urbase = ur_base(opaque_lane());
-      static_for<PD>([&](auto MC) { fr[decltype(MC)::value] = u_fragment(Us, urbase, 0, decltype(MC)::value); });
+      static_for<PD>([&](auto MC) { fr[decltype(MC)::value] = u_fragment(Us, 0, decltype(MC)::value); });
     }
     for (int it = 0; it + 1 < n_tiles; ++it) tile_step(std::true_type{}, SQC, it);
     if (n_tiles > 0) tile_step(std::false_type{}, SQC, n_tiles - 1);
