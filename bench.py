@@ -30,8 +30,8 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, published
 # and valid for the library version they were measured on (profiles/*_hbm_traffic_pmc.md).
 # Anything else reports null.
 ATTN_TRAFFIC = {
-    # 2.0 x 175,542 KiB + 1.0 x 98,280 KiB (profiles/wan480p_hbm_traffic_pmc.md)
-    ("wan480p", "forward", 306): 460_100_000,
+    # 2.0 x 174,820 KiB + 1.0 x 98,280 KiB (profiles/wan480p_hbm_traffic_pmc.md)
+    ("wan480p", "forward", 307): 458_700_000,
 }
 
 

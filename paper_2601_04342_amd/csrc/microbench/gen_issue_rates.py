@@ -136,7 +136,7 @@ def state_ops():   # 32 units of U and 32 features of a lane: rectified, rounded
         if e % 2: ops += [f"v_cvt_pk_bf16_f32 %21, %{t}, %{13 + (e - 1) % 4}"] * 2
     return ops
 sm, so = softmax_ops(), state_ops()
-mixes = {'ATTN128': (32, 16, 32, sm), 'ATTN64': (16, 8, 16, sm), 'STATE128': (64, 48, 32, so), 'STATE64': (24, 16, 16, so)}
+mixes = {'ATTN128': (32, 16, 32, sm), 'ATTN64': (16, 8, 16, sm), 'STATE128': (64, 48, 32, so), 'STATE64': (32, 24, 16, so)}
 full = {}
 for n, (nm, b, t, o) in mixes.items():
     full[n] = (nm, mix(nm, b, t, o))

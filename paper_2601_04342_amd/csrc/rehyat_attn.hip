@@ -133,8 +133,8 @@ __device__ __forceinline__ void softmax_scores(const char* Ks, const FragBase& f
 // the vector work -- and fenced, because the compiler's own order waits for every LDS read right
 // after issuing it.
 // What bounds it: on a filled chip power (a loop of nothing but the same products, vector work and LDS reads,
-// on random operands: 23 - 25 ns per product and SIMD with all CUs busy, 14.5 with 32; here 28 - 30, 25 without
-// the tile loads), at d = 64 power and vector work (32 ns in such a loop, 23 with 32 CUs); with CUs to spare the
+// on random operands: 23 - 27 ns per product and SIMD with all CUs busy, by box, 14.5 with 32; here 28 - 30, 25
+// without the tile loads), at d = 64 power and vector work (32 - 34 ns in such a loop, 23 with 32 CUs); with CUs to spare the
 // issue of some 300 instructions per tile and wave.  Against the tile loop that ran the four phases one after
 // the other: 1,488 -> 1,389 us summed over the 480p, 720p and three-frame-chunk guidance-pair launches,
 // streaming step at 480p with T_o = 1 60 -> 55 us, d = 64 at 480p 441 -> 430 us.

@@ -277,8 +277,8 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   // A loop for each half of the features: decided per element, squaring costs a select each (the
   // waves of both loops meet at the same number of barriers).
   // What bounds a tile: products at the rate that power allows with all CUs busy (26.6 ns each per SIMD; a
-  // loop of nothing but the same products, vector work and LDS reads 21 - 22.5, and 14.1 with 32 CUs), at
-  // d = 64 vector work as well (24 - 25 ns and 17).  With the groups one after the other and each LDS read waited
+  // loop of nothing but the same products, vector work and LDS reads 21 - 24.5, by box, and 14.1 with 32 CUs; at
+  // d = 64 33 ns against 25 and 14.2).  With the groups one after the other and each LDS read waited
   // for as it was issued: 480p and 320x480 launches of 12 heads of 128 together 68.4 us, now 66.3; 24 heads of 64
   // at 480p 70.3, now 64.5; 2 x 3 heads of 333-token frames 19.5, now 18.1.
   auto all_tiles = [&](auto SQC) {
