@@ -939,9 +939,10 @@ __device__ __forceinline__ void hid_body(const WeightGradSide& a, int H, int64_t
 // Both kinds of weight gradient of both sides in one launch: per side and (b, h), n2 pieces of
 // the tokens for dW2 and n1 for dW1.  Four launches (dW2 and dW1 of the queries, then of the keys), each
 // with its weights to load, its last tile to wait for and 21 partial sums per (b, h), took 436 us at
-// the 480p shape and 157 at 320x480; this one takes 340 and 103, half as many partial sums, and the two
-// kinds share what they read in the last-level cache.  Bound by memory and by the products about
-// alike: 1.15 GB of operands through the caches at 480p, 0.87 PFLOP/s.
+// the 480p shape and 157 at 320x480; this one 340 and 103 on that box, half as many partial sums, and the two
+// kinds share what they read in the last-level cache (on another 282 and 103, and 254 and 95 since U is not masked
+// in every tile).  Bound by memory and by the products about alike: 1.15 GB of operands through the caches at 480p
+// and 0.29 TFLOP, 4.5 TB/s and 1.14 PFLOP/s there.
 template <int D, int NW>
 __global__ void __launch_bounds__(64 * NW, 2)
 weight_grad_kernel(WeightGradArgs a) {
