@@ -193,7 +193,7 @@ __device__ __forceinline__ void softmax_trip(const char* Kn, const char* Kn2, co
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb) {
           const float pair = fmaxf(E[kb][e], E[kb][e + 1]);
-          mx[kb] = e == 0 ? pair : fmaxf(mx[kb], pair);
+          mx[kb] = e == 0 ? pair : fmaxf(pair, mx[kb]);
         }
     }
     // exponents are kept unscaled; sc = log2(e)/sqrt(d) > 0 is folded into the exp2 argument
