@@ -217,10 +217,12 @@ __device__ __forceinline__ void softmax_trip(const char* Kn, const char* Kn2, co
 }
 
 // The last tile: keys outside [first, first + count) of it have been weighed already.
-template <int D>
+// `issue(i)`, i < NI, requests tiles of the next phase, one load behind a product.
+template <int D, int NI, typename Issue>
 __device__ __forceinline__ void softmax_last(const char* Vc, const FragBase& fo, f32x16 (&E)[2], SoftmaxRows<D>& rows,
-                                             float sc, int first, int count, int lane) {
+                                             float sc, int first, int count, int lane, Issue issue) {
   constexpr int DB = D / 32, NM = 4 * DB;
+  static_assert(NI <= NM, "a load behind each product");
   const int g = lane >> 5;
   bf16x8 fr[kAhead];
   static_for<kAhead>([&](auto MC) {
@@ -256,13 +258,16 @@ __device__ __forceinline__ void softmax_last(const char* Vc, const FragBase& fo,
     rows.O[m % DB] = mfma(fr[m % kAhead], __builtin_bit_cast(bf16x8, w), rows.O[m % DB]);
     if constexpr (m + kAhead < NM)
       fr[m % kAhead] = v_fragment<D>(Vc, fo, (m + kAhead) / DB, (m + kAhead) % DB);
+    if constexpr (m < NI) issue(MC);
   });
   rows.sum += sum;
 }
 
 // The softmax part over a wave's key tiles 0 .. n-1 (tile t of it is tile first_tile + t * stride
 // of the window): four waves share K in buffers 0/1 and V in 2/3 of `tiles`, picked by the parity of
-// t.  Meets n + 1 barriers.  Waves that are not live move their share of the tiles and compute nothing.
+// t.  Meets n + 1 barriers.  Behind the last of them the K tiles are dead: with `last` the NI loads `issue(i)` go out
+// under the last tile.  EARLY: on entry K of tile 0 has landed, the rest of request() is waited for behind its scores.
+// Waves that are not live move their share of the tiles and compute nothing.
 template <int D>
 struct SoftmaxTiles {
   using R = RangeTiles<2 * D, 4>;
@@ -282,20 +287,24 @@ struct SoftmaxTiles {
     }
     if (n > 1) range.fill(K, row(1), lds + TB);
   }
-  template <bool LIVE>
-  __device__ __forceinline__ void run(const bf16x8 (&Qr)[D / 16], SoftmaxRows<D>& rows, float sc) const {
+  template <bool LIVE, bool EARLY, int NI, typename Issue>
+  __device__ __forceinline__ void run(const bf16x8 (&Qr)[D / 16], SoftmaxRows<D>& rows, float sc, bool last,
+                                      Issue issue) const {
     FragBase fo = make_frag_base<D>(lane);
     const char *const K0 = tiles, *const K1 = tiles + TB, *const V0 = tiles + 2 * TB, *const V1 = tiles + 3 * TB;
     f32x16 E0[2], E1[2];
     bf16x8 fr[kAhead];
-    if constexpr (LIVE) {
-      softmax_scores<D>(K0, fo, Qr, E0);
+    auto first_fragments = [&]() {
       static_for<kAhead>([&](auto MC) {
         constexpr int m = decltype(MC)::value;
         fr[m] = k_fragment<D>(K1, fo, m / 2, m & 1);
       });
-    }
-    lds_barrier();
+    };
+    if constexpr (LIVE) softmax_scores<D>(K0, fo, Qr, E0);
+    if constexpr (LIVE && !EARLY) first_fragments();
+    if constexpr (EARLY) wait_loads_and_barrier<0>();
+    else lds_barrier();
+    if constexpr (LIVE && EARLY) first_fragments();
     if (n > 2) range.fill(K, row(2), lds);
     auto trip = [&](int t, const char* Kn, const char* Kn2, const char* Vc, int kbuf, int vbuf, f32x16 (&E)[2],
                     f32x16 (&En)[2]) {
@@ -330,8 +339,12 @@ struct SoftmaxTiles {
       ++t;
     }
     wait_loads_and_barrier<0>();
-    if constexpr (LIVE) {
-      softmax_last<D>(Vl, fo, E0, rows, sc, range.first(row(t)), range.count(row(t)), lane);
+    const int first = range.first(row(t)), count = range.count(row(t));
+    if (NI > 0 && last) {
+      if constexpr (LIVE) softmax_last<D, NI>(Vl, fo, E0, rows, sc, first, count, lane, issue);
+      else static_for<NI>([&](auto IC) { issue(IC); });
+    } else if constexpr (LIVE) {
+      softmax_last<D, 0>(Vl, fo, E0, rows, sc, first, count, lane, issue);
     }
   }
 };
@@ -413,19 +426,22 @@ struct LinTiles {
   int wave, lane;
 
   __device__ __forceinline__ void issue(int kind, int idx, int buf) const {
+#pragma unroll
+    for (int n = 0; n < LPT; ++n) load(kind, idx, buf, n);
+  }
+  __device__ __forceinline__ void load(int kind, int idx, int buf, int n) const {
     const int jr = lane / CPR, cw = ((lane % CPR) ^ swz<2 * D>(wave * RPB + jr)) << 4;
     const int js = lane >> 3, cs = ((lane & 7) ^ swz<128>(wave * 8 + js)) << 4;
-#pragma unroll
-    for (int n = 0; n < LPT; ++n) {
-      const int blk = wave + NW * n, R = blk * RPB;
-      const uint32_t dst = lds + buf * TB + blk * 1024;
-      if (kind == kW1)
-        direct_load_16(W1, jr * (2 * D) + cw, idx * TB + blk * 1024, dst);
-      else if (kind == kW2)
-        direct_load_16(W2, jr * (4 * D) + cw, idx * 32 * (4 * D) + (R & 31) * (4 * D) + (R >> 5) * (2 * D), dst);
-      else
-        direct_load_16(S, js * (4 * D) + cs, idx * 128 + blk * 8 * (4 * D), dst);
-    }
+    const int blk = wave + NW * n, R = blk * RPB;
+    const uint32_t dst = __builtin_amdgcn_readfirstlane(lds + buf * TB + blk * 1024);
+    // (scalar also where the compiler has lost sight of that, in a branch for instance)
+    auto uniform = [](int x) { return __builtin_amdgcn_readfirstlane(x); };
+    if (kind == kW1)
+      direct_load_16(W1, jr * (2 * D) + cw, uniform(idx * TB + blk * 1024), dst);
+    else if (kind == kW2)
+      direct_load_16(W2, jr * (4 * D) + cw, uniform(idx * 32 * (4 * D) + (R & 31) * (4 * D) + (R >> 5) * (2 * D)), dst);
+    else
+      direct_load_16(S, js * (4 * D) + cs, uniform(idx * 128 + blk * 8 * (4 * D)), dst);
   }
 };
 
@@ -449,18 +465,21 @@ __device__ __forceinline__ void lin_vector(const float* v, int g, f32x16& x) {  
 }
 
 // U^T = relu(W1 Q^T + b1) of NB blocks of 32 hidden units: Ub[2 nb], Ub[2 nb + 1] as B operands.  Fragments
-// are read kAhead products ahead, a block is rectified under the products of the next one.
-template <int D, int NB>
+// are read kAhead products ahead, a block is rectified under the products of the next one.  The second half of
+// the blocks lies GAP bytes further on.  `issue(i)`, i < NI, requests tiles, one load behind every other product.
+template <int D, int NB, int GAP, int NI, typename Issue>
 __device__ __forceinline__ void lin_hidden(const char* Ws, int wbase, const float* bias, int g,
-                                           const bf16x8 (&Qr)[D / 16], bf16x8* Ub) {
+                                           const bf16x8 (&Qr)[D / 16], bf16x8* Ub, Issue issue) {
   constexpr int KS = D / 16, NM = NB * KS;
+  static_assert(2 * NI <= NM, "the loads fit");
   f32x16 acc[2];
   bf16x8 fr[kAhead];
   auto fetch = [&](auto MC) {
     constexpr int m = decltype(MC)::value;
     if constexpr (m < NM) {
       if constexpr (m % KS == 0) lin_vector(bias + 32 * (m / KS), g, acc[(m / KS) & 1]);
-      fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(Ws + (wbase ^ (32 * (m % KS))) + (m / KS) * (32 * 2 * D));
+      fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(Ws + (wbase ^ (32 * (m % KS))) + (m / KS) * (32 * 2 * D) +
+                                                        (m / KS >= NB / 2 ? GAP : 0));
     }
   };
   auto finish = [&](int nb, int half) {   // one of the two operands of block nb
@@ -478,6 +497,7 @@ __device__ __forceinline__ void lin_hidden(const char* Ws, int wbase, const floa
     if constexpr (nb > 0 && m % KS == (KS > kAhead ? 1 : 0)) finish(nb - 1, 0);
     if constexpr (nb > 0 && m % KS == (KS > kAhead ? 2 : 0)) finish(nb - 1, 1);
     fetch(std::integral_constant<int, m + kAhead>{});
+    if constexpr (m % 2 == 1 && m / 2 < NI) issue(std::integral_constant<int, m / 2>{});
     __builtin_amdgcn_sched_barrier(0);
   });
   finish(NB - 1, 0);
@@ -664,8 +684,9 @@ attn_kernel(AttnArgs a) {
     }
     settle(Qr);
     wait_loads_and_barrier<0>();   // also publishes the bias vectors
-    if (wave_live) st.template run<true>(Qr, rows, a.scale_log2e);
-    else st.template run<false>(Qr, rows, a.scale_log2e);
+    auto none = [](auto) {};
+    if (wave_live) st.template run<true, false, 0>(Qr, rows, a.scale_log2e, false, none);
+    else st.template run<false, false, 0>(Qr, rows, a.scale_log2e, false, none);
     lds_barrier();   // all K/V tiles are dead
   }
 
@@ -724,7 +745,7 @@ attn_kernel(AttnArgs a) {
       issue_all(LinStepC<D, st>{});
       if (!wave_live) return;  // this step of this wave only (the lambda is one step)
       if constexpr (st < NW1) {
-        lin_hidden<D, 2>(tiles + sd.buf_w * TB, wbase, sb1 + 64 * st, g, Qr, Ub + 4 * st);
+        lin_hidden<D, 2, 0, 0>(tiles + sd.buf_w * TB, wbase, sb1 + 64 * st, g, Qr, Ub + 4 * st, [](auto) {});
       } else {
         constexpr int pb = st - NW1;
         nL += lin_features<D, (32 * pb >= DP / 2)>(tiles + sd.buf_w * TB, tiles + sd.buf_s * TB, wbase, sbase, pb & 1,
@@ -776,9 +797,11 @@ attn_kernel(AttnArgs a) {
 // What bounds it: the same loop as attn_kernel, but a launch of at most 256 attn_kernel workgroups
 // leaves one wave on a SIMD, whose instruction stream alone does not fill it.  Here every SIMD that
 // has work has two waves, each with half of the tiles, at the price of the meeting and of a lower
-// clock (streaming step at the 480p shape with T_o = 1, 156 items: 52 us, 38 of them for 25 trips
-// of two tiles, 3.9 before the first and 9.7 after the last).
-// 128 KB of tile buffers (K and V of two tiles per group): one workgroup per CU, which is why
+// clock.  Streaming step at the 480p shape with T_o = 1, 156 items: 47 us from the first workgroup's start, 34 of them
+// for the tiles, 2.9 before the first and 9 after the last, 2.4 - 2.7 of those for each of the hidden layer (128 products
+// on a SIMD) and the merge's two round trips, 4.2 for the features; with phase L's first tiles requested
+// behind the last key tile and its blocks one after the other 50.1, 10.9 behind the tiles.
+// 144 KB of tile buffers (K and V of two tiles per group): one workgroup per CU, which is why
 // attn_kernel stays the better one as soon as its own launch fills the chip (attn_splits).
 // ---------------------------------------------------------------------------
 // STEP (streaming step): explicit ranges; S and z are the caller's, in its layout and precision, so that no
@@ -791,10 +814,10 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   using C = AttnShape<D>;
   constexpr int HID = C::HID, DP = C::DP, KS = C::KS, DB = C::DB;
   constexpr int TB = C::TILE_BYTES;
-  constexpr int NT = 512;
-  constexpr int GB = 4 * TB;             // tile buffers of one group: K 0/1, V 0/1
+  constexpr int GB = 4 * TB;   // tile buffers of one group: K 0/1, V 2/3; of group 1: K 4/5, V 6/7
+  constexpr int NBUF = D == 128 ? 9 : 8;   // one more for the first S tile where W1 takes all K buffers
   using SL = StateLds<D>;
-  __shared__ __attribute__((aligned(1024))) char tiles[!STEP || 2 * GB > SL::XV + SL::US ? 2 * GB : SL::XV + SL::US];
+  __shared__ __attribute__((aligned(1024))) char tiles[!STEP || NBUF * TB > SL::XV + SL::US ? NBUF * TB : SL::XV + SL::US];
   __shared__ __attribute__((aligned(256))) float sb1[HID];
   __shared__ __attribute__((aligned(16))) float sb2[DP];
   __shared__ __attribute__((aligned(16))) float sz[DP];
@@ -834,12 +857,6 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
 
   const int64_t row = q0 + 32 * qg + r;            // this lane's query
   const bool wave_live = q0 + 32 * qg < cr.q_hi;   // else: moves tiles and meets barriers only
-  bf16x8 Qr[KS];
-  {
-    const bf16_t* p = Qg + (row < cr.q_hi ? row : cr.q_hi - 1) * D + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) Qr[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-  }
   SoftmaxRows<D> rows;
 #pragma unroll
   for (int db = 0; db < DB; ++db) rows.O[db] = f32x16{};
@@ -847,57 +864,66 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   rows.max = -INFINITY;
   rows.sum = 0.f;
 
-  // =========================== phase S =====================================
-  {
-    const int n_keys = (int)(cr.s_hi - cr.s_lo), n_tiles = (n_keys + 63) / 64;
-    const SoftmaxTiles<D> st{make_rsrc_words(Kg + cr.s_lo * D), make_rsrc_words(Vg + cr.s_lo * D),
-                             (uint32_t)__builtin_amdgcn_readfirstlane(lds_address(tiles) + kg * GB), tiles + kg * GB,
-                             RangeTiles<2 * D, 4>(n_keys, qg, lane), kg, 2, (n_tiles + 1 - kg) / 2, lane};
-    st.request();
-    if (has_linear) {
-      const float* zt = STEP ? a.step_z + (int64_t)bh * DP : a.state_z + ((int64_t)bh * a.state_slots + tc) * DP;
-      for (int i = tid; i < HID; i += NT) sb1[i] = a.b1_q[(int64_t)h * HID + i];
-      for (int i = tid; i < DP; i += NT) {
-        sb2[i] = a.b2_q[(int64_t)h * DP + i];
-        sz[i] = zt[i];
-      }
-    }
-    settle(Qr);
-    wait_loads_and_barrier<0>();   // also publishes the bias vectors
-    int met = 0;
-    if (st.n > 0) {
-      if (wave_live) st.template run<true>(Qr, rows, a.scale_log2e);
-      else st.template run<false>(Qr, rows, a.scale_log2e);
-      met = st.n + 1;
-    }
-    for (; met < (n_tiles + 1) / 2 + 1; ++met) lds_barrier();   // group 1 may have a tile less, or none
-    lds_barrier();
-  }
-
-  // Phase L streams through the eight tile buffers: W1 tiles into 0 .. NW1-1, then sets of two
-  // W2 tiles (one per group) and the S tile of their 64 features, alternating between buffers
-  // 4, 5, 6 and 0, 1, 2.  Tile kinds as in LinStep.
+  const bool dbg_soft = a.dbg_m || a.dbg_nS || a.dbg_aS;
   constexpr int NW1 = HID / 64, NP = DP / 64;
-  static_assert(NW1 <= 4, "the W1 tiles and the first set share the eight buffers");
   const LinTiles<D, 8> lt{make_rsrc_words(a.w1_q + (int64_t)h * HID * D), make_rsrc_words(a.w2_q + (int64_t)h * DP * HID),
                           make_rsrc_words(STEP ? a.w1_q : a.state_s + ((int64_t)bh * a.state_slots + tc) * (int64_t)D * DP),
                           lds_address(tiles), wave, lane};
   constexpr int L8 = LinTiles<D, 8>::LPT;
-  // STEP: features 64p + 4 s_f .. of columns 4 s_d .. of S are requested into registers before set p's
-  // tiles and go to its S tile (64 features, i.e. 128 bytes, per column) after the work on the set before it
+  // Where the tiles of phase L lie.  W1 in the K buffers; set p is the W2 tiles of feature blocks 2p and 2p + 1 (one
+  // per group) and the S tile of their 64 features.
+  static_assert(NW1 <= 4 && NP <= 4, "schedule of the buffers");
+  constexpr int W1GAP = NW1 > 2 ? 2 * TB : 0;
+  auto w1_buf = [](int i) { return i < 2 ? i : i + 2; };
+  auto w2_buf = [](int p) { return p == 0 || p == 3 ? 2 : p == 1 ? 6 : 4; };
+  auto s_buf = [](int p) { return D == 64 ? 4 + p : p == 0 ? 8 : p == 3 ? 6 : p - 1; };
+  // load i of W1, and of the tiles of phase L behind it: W2 of sets 0 and 1 and S of what has a free buffer
+  // (under the hidden layer), W2 of 2 and S of 1 and 2 (under the first block), W2 of 3 and S of 3 (under the second)
+  constexpr int N1 = NW1 * L8;
+  auto load_w1 = [&](auto IC) {
+    constexpr int i = decltype(IC)::value;
+    lt.load(kW1, i / L8, w1_buf(i / L8), i % L8);
+  };
+  auto load_w2 = [&](int first, int i) {
+    const int tile = first + i / L8;
+    lt.load(kW2, tile, w2_buf(tile / 2) + tile % 2, i % L8);
+  };
+  auto load_s = [&](int first, int i) { lt.load(kS, first + i / L8, s_buf(first + i / L8), i % L8); };
+  constexpr int NS0 = STEP ? 0 : D == 64 ? 2 : 1;   // S tiles under the hidden layer
+  constexpr int N2 = (4 + NS0) * L8;
+  auto load_first = [&](auto IC) {
+    constexpr int i = decltype(IC)::value;
+    if constexpr (i < 4 * L8) load_w2(0, i);
+    else load_s(0, i - 4 * L8);
+  };
+  constexpr int N3 = NP > 2 ? (STEP ? 2 : 4) * L8 : 0;
+  auto load_second = [&](auto IC) {
+    constexpr int i = decltype(IC)::value;
+    if constexpr (i < 2 * L8) load_w2(4, i);
+    else load_s(1, i - 2 * L8);
+  };
+  constexpr int N4 = NP > 2 ? (STEP ? 2 : 3) * L8 : 0;
+  auto load_third = [&](auto IC) {
+    constexpr int i = decltype(IC)::value;
+    if constexpr (i < 2 * L8) load_w2(6, i);
+    else load_s(3, i - 2 * L8);
+  };
+  // STEP: features 64p + 4 s_f .. of columns 4 s_d .. of S are requested into registers ahead of the S tile
+  // (64 features, i.e. 128 bytes, per column) that they go to, rounded as the copy of the state was
   const int s_f = tid / (D / 4), s_d = tid % (D / 4);
-  const bool s_mover = tid < 4 * D;   // whole waves
+  const bool s_mover = 4 * D == 512 || tid < 4 * D;   // whole waves
   f32x4 sreg[4];
   auto request_s = [&](int p) {
     if (STEP && s_mover) {
-      const float* const src = a.step_S + ((int64_t)bh * DP + 64 * p + 4 * s_f) * D + 4 * s_d;
+      const float* const src = a.step_S + ((int64_t)bh * DP + 64 * p) * D;
+      const uint32_t off = 4 * s_f * D + 4 * s_d;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) sreg[i] = *reinterpret_cast<const f32x4_u*>(src + i * D);
+      for (int i = 0; i < 4; ++i) sreg[i] = *reinterpret_cast<const f32x4_u*>(src + i * D + off);
     }
   };
   auto place_s = [&](int p) {
     if (STEP && s_mover) {
-      char* const Ss = tiles + ((p & 1) ? 2 : 6) * TB;
+      char* const Ss = tiles + s_buf(p) * TB;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         u32x2 pk;
@@ -907,23 +933,60 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
       }
     }
   };
-  auto issue_set = [&](int p) {
-    const int b = (p & 1) ? 0 : 4;
-    request_s(p);
-    lt.issue(kW2, 2 * p, b);
-    lt.issue(kW2, 2 * p + 1, b + 1);
-    if (!STEP) lt.issue(kS, p, b + 2);
-  };
-  const bool dbg_soft = a.dbg_m || a.dbg_nS || a.dbg_aS;
-  auto prologue = [&]() {
-    if (STEP) request_s(0);   // the wait for W1 below counts the tiles behind it
+
+  // =========================== phase S =====================================
+  bf16x8 Qr[KS];
+  {
+    const int n_keys = (int)(cr.s_hi - cr.s_lo), n_tiles = (n_keys + 63) / 64;
+    const uint32_t lds = lds_address(tiles);
+    const SoftmaxTiles<D> st{make_rsrc_words(Kg + cr.s_lo * D), make_rsrc_words(Vg + cr.s_lo * D),
+                                (uint32_t)__builtin_amdgcn_readfirstlane(lds + kg * GB), tiles + kg * GB,
+                                RangeTiles<2 * D, 4>(n_keys, qg, lane), kg, 2, (n_tiles + 1 - kg) / 2, lane};
+    // The queries come through the V buffers of tile 1, whole rows to an instruction, once for both groups: read
+    // from memory as operands (32 rows of 32 bytes an instruction, by both groups) they held up the tiles behind
+    // them (K of tile 0 there 3.8 us after the workgroup's start, now 2.9).
+    const u32x4 Qd = make_rsrc_words(Qg + q0 * D);
+    const int q_rows = cr.q_hi - q0 < kQueryTile ? (int)(cr.q_hi - q0) : kQueryTile;
+    tile_load_asm<2 * D, TB, 8>(Qd, 0, lds + 3 * TB, wave, lane, q_rows < 64 ? q_rows : 64);
+    if (q_rows > 64) tile_load_asm<2 * D, TB, 8>(Qd, 64 * 2 * D, lds + 7 * TB, wave, lane, q_rows - 64);
+    st.request();
+    if (has_linear) {   // per-head vectors of phase L, 64 values to an instruction
+      const float* const zt = STEP ? a.step_z + (int64_t)bh * DP : a.state_z + ((int64_t)bh * a.state_slots + tc) * DP;
+      static_assert(HID == DP, "three vectors of one length");
+      for (int i = wave; i < 3 * (DP / 64); i += 8) {
+        const int which = i / (DP / 64), part = i % (DP / 64);
+        const float* const src = which == 0 ? a.b1_q + (int64_t)h * HID : which == 1 ? a.b2_q + (int64_t)h * DP : zt;
+        const uint32_t dst = lds_address(which == 0 ? sb1 : which == 1 ? sb2 : sz);
+        direct_load_4(make_rsrc_words(src), 4 * lane, 256 * part, __builtin_amdgcn_readfirstlane(dst + 256 * part));
+      }
+    }
+    // the queries and K of tile 0; with a second tile V and K of it are younger, and may be in flight
+    if (st.n > 1) wait_loads_and_barrier<2 * SoftmaxTiles<D>::LPT>();
+    else wait_loads_and_barrier<0>();
+    if (wave_live) {
+      const char* const Qs = tiles + (3 + 4 * (qg >> 1)) * TB + (qg & 1) * (32 * 2 * D);
+      const FragBase fo = make_frag_base<D>(lane);
 #pragma unroll
-    for (int i = 0; i < NW1; ++i) lt.issue(kW1, i, i);
-    lt.issue(kW2, 0, 4);
-    lt.issue(kW2, 1, 5);
-    if (!STEP) lt.issue(kS, 0, 6);
-  };
-  if (has_linear && !dbg_soft) prologue();
+      for (int ks = 0; ks < KS; ++ks) Qr[ks] = k_fragment<D>(Qs, fo, ks, 0);
+    }
+    // Group 1 may have a tile less than group 0, or none, and then meets its last barriers here.  Behind the last
+    // one that group 0's tiles need all K buffers are free, and W1 goes there under the last tile.
+    const int barriers = (n_tiles + 1) / 2 + 1;
+    const bool ahead = has_linear && !dbg_soft;
+    int met = 0;
+    if (st.n > 0) {
+      met = st.n + 1;
+      const bool last = ahead && met == barriers;
+      if (wave_live) st.template run<true, true, N1>(Qr, rows, a.scale_log2e, last, load_w1);
+      else st.template run<false, true, N1>(Qr, rows, a.scale_log2e, last, load_w1);
+    }
+    if (met < barriers) {
+      for (; met < barriers; ++met) wait_loads_and_barrier<0>();
+      if (ahead) static_for<N1>(load_w1);
+    }
+    if (ahead) request_s(0);
+    lds_barrier();   // the V buffers are free as well
+  }
 
   // ---- one reference for both groups -------------------------------------------------
   {
@@ -982,7 +1045,10 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
     // the parts have been read, a^S is in memory, and the counted waits of phase L see tile
     // loads only
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
-    if (has_linear) prologue();
+    if (has_linear) {
+      static_for<N1>(load_w1);
+      request_s(0);
+    }
   }
 
   // =========================== phase L =====================================
@@ -991,25 +1057,125 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
     const float lin_scale = __builtin_amdgcn_exp2f((a.stab_mode == 1 ? 0.f : rows.max) - rows.ref);
     const int wbase = lin_row_base<D>(lane), sbase = tile_off<128>(r, 8 * g);
     bf16x8 Ub[HID / 16];
-    wait_loads_and_barrier<(STEP ? 2 : 3) * L8>();   // W1 has landed, the first set may be in flight
-    if (wave_live) lin_hidden<D, HID / 32>(tiles, wbase, sb1, g, Qr, Ub);
+    wait_loads_and_barrier<0>();   // W1 has landed
+    if (wave_live) lin_hidden<D, HID / 32, W1GAP, N2>(tiles, wbase, sb1, g, Qr, Ub, load_first);
+    else static_for<N2>(load_first);
     place_s(0);
-    static_for<NP>([&](auto PC) {
-      constexpr int p = decltype(PC)::value, base = (p & 1) ? 0 : 4;
-      wait_loads_and_barrier<0>();      // set p has landed; everyone is done with the other buffers
-      if constexpr (p + 1 < NP) issue_set(p + 1);
-      const int pb = 2 * p + kg;
-      if (wave_live)
-        nL += lin_features<D, (64 * p >= DP / 2)>(tiles + (base + kg) * TB, tiles + (base + 2) * TB, wbase, sbase, kg,
-                                                  sb2 + 32 * pb, sz + 32 * pb, g, lin_scale, Ub, rows.O);
-      if constexpr (p + 1 < NP) place_s(p + 1);
-    });
+    wait_loads_and_barrier<0>();   // sets 0 and 1; W1 is dead
+    request_s(1);
+    // The wave's feature blocks 2p + kg, p = 0 .. NP-1, as one stream of products: psi of block 0, then psi of p + 1 and
+    // O += S^T phi of p in turn.  phi of a block lies under the psi of the next one (of the last: under the read-out of the
+    // one before it).  Both waves of a SIMD are in the same phase here, so that neither fills the other's gaps:
+    // block by block, each fragment read and each phi in the way of the products, it took 5.0 us (streaming step
+    // 5.7), now 3.3 (4.2).
+    // Barriers stand where tiles have to have landed, kAhead products before their own.
+    auto stream = [&](auto LIVEC) {
+      constexpr bool LIVE = decltype(LIVEC)::value;
+      constexpr int NW = 2 * KS, NS = 2 * DB, BL = NW + NS, NM = NP * BL;
+      struct Slot {
+        bool psi;
+        int p, n;   // product n of block p
+      };
+      auto slot = [](int m) {
+        if (m < NW) return Slot{true, 0, m};
+        const int q = (m - NW) / BL, n = (m - NW) % BL;
+        return q == NP - 1 ? Slot{false, q, n} : n < NW ? Slot{true, q + 1, n} : Slot{false, q, n - NW};
+      };
+      auto psi_at = [](int p) { return p == 0 ? 0 : NW + (p - 1) * BL; };
+      auto s_at = [](int p) { return NW + p * BL + (p == NP - 1 ? 0 : NW); };
+      // the slot of pair i of phi of block p
+      auto phi_at = [=](int p, int i) {
+        return p < NP - 1 ? psi_at(p + 1) + 2 + i * (NW - 4) / 8 : s_at(NP - 2) + 1 + i * (NS - 1) / 8;
+      };
+      int wk = wbase + kg * TB, sk = sbase ^ (kg * 64);
+      f32x16 ps[2];
+      // z of four features and of the next four; at d = 64 pairs of three quads stand in one slot
+      constexpr int ZR = D == 128 ? 2 : 4;
+      f32x4 zq[ZR];
+      uint32_t fb[2][8];
+      float part[2];
+      bf16x8 fr[kAhead];
+      auto fetch = [&](auto MC) {
+        constexpr int m = decltype(MC)::value;
+        if constexpr (m < NM) {
+          constexpr Slot t = slot(m);
+          if constexpr (t.psi)
+            fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(tiles + w2_buf(t.p) * TB + (wk ^ (32 * (t.n % KS))) +
+                                                              t.n / KS * (32 * 2 * D));
+          else
+            fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(tiles + s_buf(t.p) * TB + (sk ^ (32 * (t.n / DB))) +
+                                                              t.n % DB * (32 * 128));
+        }
+      };
+      auto phi = [&](auto PC, auto IC) {   // elements 2i, 2i+1; n^L takes them unrounded, as in lin_features
+        constexpr int p = decltype(PC)::value, i = decltype(IC)::value;
+        if constexpr (i == 0) part[p & 1] = 0.f;
+        float x[2];
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          x[j] = fmaxf(ps[p & 1][2 * i + j], 0.f);
+          if (64 * p >= DP / 2) x[j] = x[j] * x[j];
+          x[j] = x[j] * lin_scale;
+          part[p & 1] += x[j] * zq[(i >> 1) % ZR][2 * (i & 1) + j];
+        }
+        fb[p & 1][i] = pack_bf16(x[0], x[1]);
+        if constexpr (i == 7) nL += part[p & 1];
+      };
+      if constexpr (LIVE) {
+        lin_vector(sb2 + 32 * kg, g, ps[0]);
+        static_for<kAhead>([&](auto MC) { fetch(MC); });
+      }
+      static_for<NM>([&](auto MC) {
+        constexpr int m = decltype(MC)::value;
+        constexpr Slot t = slot(m);
+        if constexpr (t.n == 0) asm volatile("" : "+v"(wk), "+v"(sk));   // offsets of a block are not kept for the next
+        // before the psi of blocks 2 and 3, and before the last read-out, where everything but its S is dead
+        static_for<NP>([&](auto PC) {
+          constexpr int p = decltype(PC)::value;
+          if constexpr (p >= 1 && m + kAhead == (p + 1 < NP ? psi_at(p + 1) : s_at(p))) {
+            place_s(p);
+            wait_loads_and_barrier<0>();
+            if constexpr (p + 1 < NP) request_s(p + 1);
+          }
+        });
+        if constexpr (LIVE) {
+          if constexpr (t.psi) {
+            ps[t.p & 1] = mfma(fr[m % kAhead], Ub[t.n], ps[t.p & 1]);
+          } else {
+            constexpr int ks = t.n / DB, db = t.n % DB, b = t.p & 1;
+            const u32x4 w = {fb[b][4 * ks], fb[b][4 * ks + 1], fb[b][4 * ks + 2], fb[b][4 * ks + 3]};
+            rows.O[db] = mfma(fr[m % kAhead], __builtin_bit_cast(bf16x8, w), rows.O[db]);
+          }
+          fetch(std::integral_constant<int, m + kAhead>{});
+        }
+        if constexpr (m % 2 == 1 && m / 2 < N3) load_second(std::integral_constant<int, m / 2>{});
+        constexpr int b1 = NP > 2 ? psi_at(2) - kAhead : 0, i4 = (m - b1 - 1) / 2;
+        if constexpr (NP > 2 && m > b1 && (m - b1) % 2 == 1 && i4 < N4) load_third(std::integral_constant<int, i4>{});
+        if constexpr (LIVE) {
+          static_for<NP>([&](auto PC) {
+            constexpr int p = decltype(PC)::value;
+            if constexpr (p >= 1 && m + 2 == psi_at(p)) lin_vector(sb2 + 32 * (2 * p + kg), g, ps[p & 1]);
+            static_for<4>([&](auto QC) {   // four features of accumulator registers 4q .. 4q + 3, a slot ahead
+              constexpr int q = decltype(QC)::value;
+              if constexpr (m + 1 == phi_at(p, 2 * q))
+                zq[q % ZR] = *reinterpret_cast<const f32x4*>(sz + 32 * (2 * p + kg) + 16 * (q >> 1) + 8 * g + 4 * (q & 1));
+            });
+            static_for<8>([&](auto IC) {
+              if constexpr (phi_at(p, decltype(IC)::value) == m) phi(PC, IC);
+            });
+          });
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      });
+    };
+    if (wave_live) stream(std::true_type{});
+    else stream(std::false_type{});
     nL = half_swap_sum(nL);
-    lds_barrier();   // the last set has been read
   }
 
   // =========================== merge (Eq. 5) ================================
-  // each group hands the other half of its numerator over and finishes DB / 2 feature blocks
+  // each group hands the other half of its numerator over and finishes DB / 2 feature blocks (through buffers
+  // 0 .. 3, dead since the barrier before the last read-out)
   if (g == 0) xlin[kg][32 * qg + r] = nL;
   auto finish = [&](auto GC) {
     constexpr int own = decltype(GC)::value, other = 1 - own;
@@ -1050,23 +1216,19 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
   else finish(std::integral_constant<int, 1>{});
 }
 
-// The split kernel holds one workgroup per CU (tile buffers of 128 KB), so it can only win while
-// its launch is a single round: at 256 items and fewer (split against not: d = 128 270 items of 1,100 keys 66.3 and
-// 62.8 us, 312 of 1,500 74.5 and 71.3, 576 of 1,500 112 and 108, 1,152 of 3,000 274 and 259; d = 64 312 of 1,500
-// 46.3 and 41.5, 1,152 of 3,000 164 and 148).  Below that the keys decide, since the two
-// groups' meeting has to be paid by them.  Whole calls, split against not: d = 128 with a read-out 32
-// items of 448 keys 39.6 and 37.9 us, 200 of 512 47.2 and 45.3, 180 of 600 46.3 and 45.8, 168 of 800 50.8 and
-// 50.2, 128 of 1,000 48.6 and 48.8, 144 of 1,536 54.1 and 55.6, 96 of 2,000 60.2 and 63.6; d = 64 160 of 640
-// 26.9 and 26.1, 128 of 1,000 26.9 and 27.2, 189 of 2,600 42.5 and 46.1.  Without a read-out at d = 128 60 of
-// 768 17.3 and 16.7, 80 of 1,024 19.8 and 20.0, 120 of 1,536 25.8 and 27.2, 240 of 3,000 51.4 and 54.4; at
-// d = 64 80 of 1,024 14.8 and 15.0, 150 of 1,800 21.7 and 23.2.
-// Time alone would put every line at about 960 keys.  Two lie elsewhere:
-// - d = 128 with a read-out at 448: 1 - 4 % of the time buys an output that is 1.3 % nearer to fp64 (2.266e-3
-//   instead of 2.297e-3 of relative error at 4 heads of 333-token frames, T_o = 1, eight seeds, +- 3e-6: each
-//   group rounds its weights relative to a maximum of its own, whose weight of 1 is exact).  At d = 64 the
-//   split kernel is nearer by 0.6 %.
-// - d = 64 without a read-out at 1,664, 1 - 3 % slower up to there: softmax-only rows of 1,600 keys and fewer keep
-//   the same bits in a launch of any number of items.
+// The split kernel holds one workgroup per CU (144 KB of tile buffers), so it wins while its launch is a single
+// round: at 256 items and fewer (not split against split, whole calls: d = 128 300 items of 540 keys 49.7 and 55.0 us,
+// 405 of 1,100 72.4 and 70.0, 576 of 1,500 108.7 and 109.5; d = 64 260 of 1,600 29.2 and 34.2, 378 of 2,600 62.0 and
+// 66.4, 720 of 1,500 60.5 and 67.6).  Below that the two groups' meeting has to be paid by the keys: d = 128 with a
+// read-out 120 items of 192 keys 39.1 and 39.1 us, 24 of 256 34.1 and 32.8, 160 of 512 47.8 and 46.3, 225 of 600 48.1
+// and 47.0, 192 of 1,000 52.2 and 50.3, 144 of 2,000 63.2 and 59.0; d = 64 160 of 448 25.7 and 25.9, 200 of 640 27.1
+// and 26.5, 192 of 1,000 29.2 and 28.1.  Without a read-out at d = 128 48 of 512 14.6 and 14.5, 60 of 768 16.0 and
+// 15.2, 80 of 1,024 19.1 and 17.7; at d = 64 70 of 896 14.3 and 14.5, 110 of 1,400 18.0 and 16.2.
+// The lines lie where the two broke even before the split kernel's phase L was one stream (d = 128 with a read-out:
+// where its smaller error began to cost little, 2.266e-3 instead of 2.297e-3 relative to fp64 at 4 heads of 333-token
+// frames, T_o = 1: each group rounds its weights relative to a maximum of its own, whose weight of 1 is exact).  Time
+// alone would put them at about 200, 600, 560 and 1,000 keys now, for 2 - 4 % of the calls between (at d = 64 without
+// a read-out 10 %); they stay, so that a row of fewer keys has the same bits in a launch of any number of items.
 bool attn_splits(int64_t n_items, int64_t n_keys, int d, bool read_out) {
   return n_items <= 256 && n_keys >= (d == 128 ? (read_out ? 448 : 960) : read_out ? 960 : 1664);
 }
