@@ -414,15 +414,15 @@ int forward_bidirectional(const Ctx& c, const void* q, const void* k, const void
   const int nsplit = choose_frame_pieces(B * H, T, HW, d, chunk, overlap, win_frames, c.sl);
   const int fwin = c.sl.partial / nsplit;  // frames whose sums fit the partial slots
 
-  // pass 1: total over all frames, left in the carry
+  // pass 1: total over all frames, left in the carry (by the first launch of pass 2 when all frames stay)
+  const bool resident = T <= fwin;  // every F(f) is still in the partial slots
   for (int f0 = 0; f0 < T; f0 += fwin) {
     const int n = (T - f0 < fwin) ? T - f0 : fwin;
     int rc = launch_state_window(c, k, v, phi, B, H, T, HW, d, 1, 0, f0, n, nsplit);
     if (rc != REHYAT_OK) return rc;
-    rc = launch_prefix_window(c, B, H, d, dp, /*n_chunks=*/0, /*n_seg=*/n, nsplit, f0 == 0);
+    if (!resident) rc = launch_prefix_window(c, B, H, d, dp, /*n_chunks=*/0, /*n_seg=*/n, nsplit, f0 == 0);
     if (rc != REHYAT_OK) return rc;
   }
-  const bool resident = T <= fwin;  // every F(f) is still in the partial slots
 
   // pass 2: windows of chunks
   const int cw = bidir_window(T, chunk, overlap, fwin, c.sl.state);
@@ -438,7 +438,8 @@ int forward_bidirectional(const Ctx& c, const void* q, const void* k, const void
     }
     BidirArgs b;
     b.partial = (const float*)(c.ws + c.L.partial);
-    b.total = (const float*)(c.ws + c.L.carry);
+    b.total = (float*)(c.ws + c.L.carry);
+    b.sum_total = resident && c0 == 0 ? 1 : 0;
     b.state_s = (bf16_t*)(c.ws + c.L.state_s);
     b.state_z = (float*)(c.ws + c.L.state_z);
     b.BH = B * H;

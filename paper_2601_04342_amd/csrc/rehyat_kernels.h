@@ -99,10 +99,12 @@ struct StateOutArgs {
 // ---- bidirectional states: everything outside each chunk's softmax window -----------
 // state(c) = total - sum of the per-frame sums of the frames inside window c (Eq. 11-12);
 // the per-frame sums of frames [frame0, frame0 + n_frames) are in `partial`
-// (frame-major, nsplit pieces each), the total over all frames is in `total`.
+// (frame-major, nsplit pieces each), the total over all frames is in `total`, or (sum_total) is formed
+// here first, when all T frames are in `partial`, and left there.
 struct BidirArgs {
   const float* partial;
-  const float* total;    // [BH, d*dprime + dprime]
+  float* total;          // [BH, d*dprime + dprime]
+  int sum_total;
   bf16_t* state_s;       // [BH, state_slots, d, dprime]
   float* state_z;        // [BH, state_slots, dprime]
   int BH, T, chunk, overlap;

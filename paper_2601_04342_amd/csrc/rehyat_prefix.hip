@@ -57,36 +57,96 @@ prefix_kernel(PrefixArgs a) {
   *reinterpret_cast<f32x4*>(carry) = acc;
 }
 
+// Walks `total` pieces in order: add(load(0)), add(load(1)), ...  kScanDepth loads are in flight all the time; load(m) is
+// called with rising m, and beyond the last piece again with total - 1.  Every load is unconditional: behind a branch the
+// compiler does not know how many are in flight and waits for all of them (or for each one).
+template <typename Load, typename Add>
+__device__ __forceinline__ void scan_pieces(int total, Load load, Add add) {
+  if (total <= 0) return;
+  f32x4 x[kScanDepth], y[kScanDepth];
+  auto fill = [&](f32x4 (&r)[kScanDepth], int m) {
+#pragma unroll
+    for (int u = 0; u < kScanDepth; ++u) r[u] = load(m + u < total ? m + u : total - 1);
+  };
+  fill(x, 0);
+  int m = 0;
+  for (; m + 2 * kScanDepth <= total; m += kScanDepth) {
+#pragma unroll
+    for (int u = 0; u < kScanDepth; ++u) {
+      add(x[u]);
+      x[u] = load(m + kScanDepth + u);
+    }
+  }
+  if (m + kScanDepth < total) fill(y, m + kScanDepth);
+#pragma unroll
+  for (int u = 0; u < kScanDepth; ++u)
+    if (m + u < total) add(x[u]);
+#pragma unroll
+  for (int u = 0; u < kScanDepth; ++u)
+    if (m + kScanDepth + u < total) add(y[u]);
+}
+
+// state(c) = total - (frames of the softmax window of chunk c).  Bound by the round trips to the partial sums, which a
+// second reading finds in the caches: as two launches, with the windows' loads one after the other, 20.5 us at the 480p
+// shape, now 15.0.
 __global__ void __launch_bounds__(256)
 bidir_state_kernel(BidirArgs a) {
   const int bh = blockIdx.y;
   const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (idx >= a.elems) return;
   const float* part = a.partial + (int64_t)bh * a.partial_slots * a.elems + idx;
-  const f32x4 total = *reinterpret_cast<const f32x4*>(a.total + (int64_t)bh * a.elems + idx);
-  const bool is_s = idx < a.s_elems;
-  for (int c = 0; c < a.n_chunks; ++c) {
-    const int t = a.chunk0 + c;
-    // frames of the softmax window of chunk t (Eq. 12)
-    int f_lo = t * a.chunk - a.overlap;
-    if (f_lo < 0) f_lo = 0;
-    int f_hi = (t + 1) * a.chunk;
-    if (f_hi > a.T) f_hi = a.T;
-    f32x4 w = {0.f, 0.f, 0.f, 0.f};
-    for (int f = f_lo; f < f_hi; ++f)
-      for (int sp = 0; sp < a.nsplit; ++sp)
-        w += *reinterpret_cast<const f32x4*>(part + (int64_t)((f - a.frame0) * a.nsplit + sp) * a.elems);
-    const f32x4 acc = total - w;
+  float* const keep = a.total + (int64_t)bh * a.elems + idx;
+  const bool is_s = (int)blockIdx.x * 1024 < a.s_elems;   // the S part is a whole number of blocks
+  auto store = [&](int c, f32x4 x) {
     if (is_s) {
       u32x2 pk;
-      pk[0] = pack_bf16(acc[0], acc[1]);
-      pk[1] = pack_bf16(acc[2], acc[3]);
+      pk[0] = pack_bf16(x[0], x[1]);
+      pk[1] = pack_bf16(x[2], x[3]);
       *reinterpret_cast<u32x2*>(a.state_s + ((int64_t)bh * a.state_slots + c) * a.s_elems + idx) = pk;
     } else {
-      *reinterpret_cast<f32x4*>(a.state_z + ((int64_t)bh * a.state_slots + c) * (a.elems - a.s_elems) +
-                                (idx - a.s_elems)) = acc;
+      *reinterpret_cast<f32x4*>(a.state_z + ((int64_t)bh * a.state_slots + c) * (a.elems - a.s_elems) + (idx - a.s_elems)) = x;
     }
+  };
+  auto piece = [&](int m) { return *reinterpret_cast<const f32x4*>(part + (int64_t)m * a.elems); };
+  f32x4 total = {0.f, 0.f, 0.f, 0.f};
+  if (a.sum_total) {
+    scan_pieces(a.T * a.nsplit, piece, [&](f32x4 x) { total += x; });
+    *reinterpret_cast<f32x4*>(keep) = total;
+  } else {
+    total = *reinterpret_cast<const f32x4*>(keep);
   }
+  auto lo = [&](int c) {   // first piece of chunk c's window (Eq. 12), and the one behind its last
+    const int f = (a.chunk0 + c) * a.chunk - a.overlap;
+    return ((f < 0 ? 0 : f) - a.frame0) * a.nsplit;
+  };
+  auto hi = [&](int c) {
+    const int f = (a.chunk0 + c + 1) * a.chunk;
+    return ((f > a.T ? a.T : f) - a.frame0) * a.nsplit;
+  };
+  int n = 0;
+  for (int c = 0; c < a.n_chunks; ++c) n += hi(c) - lo(c);
+  int lc = 0, lm = lo(0) - 1, next = 0;   // the piece to load, number `next` of the n
+  int c = 0, left = hi(0) - lo(0);        // the chunk to finish, pieces of it to come
+  f32x4 w = {0.f, 0.f, 0.f, 0.f};
+  scan_pieces(n,
+              [&](int m) {
+                const int adv = m == next;   // (in arithmetic: no branch between loads)
+                next += adv;
+                lm += adv;
+                const int cross = lm == hi(lc);
+                lc += cross;
+                lm += cross * (lo(lc) - lm);
+                return piece(lm);
+              },
+              [&](f32x4 x) {
+                w += x;
+                if (--left == 0) {
+                  store(c, total - w);
+                  w = f32x4{0.f, 0.f, 0.f, 0.f};
+                  ++c;
+                  left = hi(c) - lo(c);
+                }
+              });
 }
 
 __global__ void __launch_bounds__(256)
@@ -105,6 +165,9 @@ state_out_kernel(StateOutArgs a) {
 // One tile of 64 features x 16 head-dimension columns of S per block, transposed through LDS
 // both ways: the pieces -- the bulk of the bytes -- and the state slot are moved in 16-byte
 // accesses along the workspace's [d][dprime] rows, the caller's [dprime][d] rows in 64-byte runs.
+// Bound by its launch and one round trip to memory: the first pieces of S and of z are requested with the
+// state.  With those of S behind the transpose and those of z one after the other at the end 5.6 us (12 heads of 128, 8
+// pieces), now 4.9.
 __global__ void __launch_bounds__(256)
 step_state_kernel(StepStateArgs a) {
   __shared__ float tile[64][17];
@@ -113,17 +176,32 @@ step_state_kernel(StepStateArgs a) {
   const int tid = threadIdx.x;
   const int n = a.d * a.dprime, elems = n + a.dprime;
   float* S = a.S + (int64_t)bh * n;
+  const float* part = a.partial + (int64_t)bh * a.partial_slots * elems;
+  const int f4 = tid & 15, el = tid >> 4;   // features 4 f4 .. 4 f4 + 3 of row e0 + el of S^T
+  const int64_t o = (int64_t)(e0 + el) * a.dprime + f0 + 4 * f4;
+  const int zf = f0 + (tid & 63);           // z of this block's 64 features, by the first wave of the first row of blocks
+  f32x4 x[kScanDepth];
+  float zx[kScanDepth], zv = 0.f;
+  auto piece = [&](int u) { return part + (int64_t)(u < a.nsplit ? u : a.nsplit - 1) * elems; };
+  if (blockIdx.y == 0) {
+    zv = a.z[(int64_t)bh * a.dprime + zf];
+    if (a.nsplit > 0) {
+#pragma unroll
+      for (int u = 0; u < kScanDepth; ++u) zx[u] = piece(u)[n + zf];
+    }
+  }
+  if (a.nsplit > 0) {
+#pragma unroll
+    for (int u = 0; u < kScanDepth; ++u) x[u] = *reinterpret_cast<const f32x4*>(piece(u) + o);
+  }
 #pragma unroll
   for (int m = 0; m < 4; ++m) {
     const int idx = tid + 256 * m, row = idx >> 4, col = idx & 15;
     tile[row][col] = S[(int64_t)(f0 + row) * a.d + e0 + col];
   }
   __syncthreads();
-  const float* part = a.partial + (int64_t)bh * a.partial_slots * elems;
   bf16_t* slot = a.state_s + (int64_t)bh * a.state_slots * n;
   {
-    const int f4 = tid & 15, el = tid >> 4;   // features 4 f4 .. 4 f4 + 3 of row e0 + el of S^T
-    const int64_t o = (int64_t)(e0 + el) * a.dprime + f0 + 4 * f4;
     f32x4 v = {tile[4 * f4][el], tile[4 * f4 + 1][el], tile[4 * f4 + 2][el], tile[4 * f4 + 3][el]};
     if (a.write_slot) {
       u32x2 pk;
@@ -131,8 +209,11 @@ step_state_kernel(StepStateArgs a) {
       pk[1] = pack_bf16(v[2], v[3]);
       *reinterpret_cast<u32x2*>(slot + o) = pk;
     }
+#pragma unroll
+    for (int u = 0; u < kScanDepth; ++u)
+      if (u < a.nsplit) v += x[u];
 #pragma unroll 8
-    for (int sp = 0; sp < a.nsplit; ++sp) v += *reinterpret_cast<const f32x4*>(part + (int64_t)sp * elems + o);
+    for (int sp = kScanDepth; sp < a.nsplit; ++sp) v += *reinterpret_cast<const f32x4*>(part + (int64_t)sp * elems + o);
 #pragma unroll
     for (int i = 0; i < 4; ++i) tile[4 * f4 + i][el] = v[i];
   }
@@ -144,12 +225,13 @@ step_state_kernel(StepStateArgs a) {
       S[(int64_t)(f0 + row) * a.d + e0 + col] = tile[row][col];
     }
   }
-  if (blockIdx.y == 0 && tid < 64) {   // z of this block's 64 features
-    const int f = f0 + tid;
-    float v = a.z[(int64_t)bh * a.dprime + f];
-    if (a.write_slot) a.state_z[(int64_t)bh * a.state_slots * a.dprime + f] = v;
-    for (int sp = 0; sp < a.nsplit; ++sp) v += part[(int64_t)sp * elems + n + f];
-    if (a.nsplit > 0) a.z[(int64_t)bh * a.dprime + f] = v;
+  if (blockIdx.y == 0 && tid < 64) {
+    if (a.write_slot) a.state_z[(int64_t)bh * a.state_slots * a.dprime + zf] = zv;
+#pragma unroll
+    for (int u = 0; u < kScanDepth; ++u)
+      if (u < a.nsplit) zv += zx[u];
+    for (int sp = kScanDepth; sp < a.nsplit; ++sp) zv += part[(int64_t)sp * elems + n + zf];
+    if (a.nsplit > 0) a.z[(int64_t)bh * a.dprime + zf] = zv;
   }
 }
 
