@@ -266,6 +266,29 @@ __device__ __forceinline__ u32x4 rsrc_if(u32x4 rsrc, bool on) {
   return rsrc;
 }
 
+// Resident operands by way of LDS.  A wave whose operand rows are 32 rows of memory (weights of its units) would read
+// 32 bytes of each row per instruction, and the address unit takes such an instruction in some 43 cycles: 24 of them in
+// each of eight waves hold a workgroup up for 3.5 - 5 us.  Whole rows through direct loads take 16 cycles per KB.
+// stage_rows moves 32 rows of ROWBYTES bytes, `stride` apart in memory, into a block of LDS that only this wave uses
+// (wait for its loads, no barrier), and staged_fragment reads k-step ks of the lane's row there.
+template <int ROWBYTES>
+__device__ __forceinline__ void stage_rows(u32x4 rsrc, int stride, int soff, uint32_t lds, int lane) {
+  constexpr int CPR = ROWBYTES / 16, RPB = 1024 / ROWBYTES;
+#pragma unroll
+  for (int n = 0; n < 32 / RPB; ++n) {
+    const int j = lane / CPR;
+    direct_load_16(rsrc, j * stride + (((lane % CPR) ^ swz<ROWBYTES>(n * RPB + j)) << 4), soff + n * RPB * stride,
+                   lds + n * 1024);
+  }
+}
+template <int ROWBYTES>
+__device__ __forceinline__ bf16x8 staged_fragment(const char* block, int lane, int ks) {
+  return *reinterpret_cast<const bf16x8*>(block + (tile_off<ROWBYTES>(lane & 31, 8 * (lane >> 5)) ^ (32 * ks)));
+}
+// This wave's loads, and reads of LDS, are done.
+__device__ __forceinline__ void wave_loads_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void wave_reads_done() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
+
 // Makes the compiler wait here for the loads that filled these operands.  Without it the wait
 // goes to their first use inside the tile loop and stays there for every tile, as a count of
 // outstanding loads in which the direct loads issued as inline asm are not known: it then

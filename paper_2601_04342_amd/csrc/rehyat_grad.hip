@@ -233,7 +233,7 @@ act_grad_kernel(ActGradArgs a) {
   // ---- resident operands ----------------------------------------------------
   // first-layer bias in LDS: accumulator register 4i+j is hidden unit 32w + 8i + 4g + j, so a
   // lane reads its four rows of block i with one 16-byte read
-  if (tid < HID) B1s[tid] = a.b1[(int64_t)h * HID + tid];
+  const float b1v = tid < HID ? a.b1[(int64_t)h * HID + tid] : 0.f;
   const float* const b1rows = B1s + wave * 32 + 4 * g;
   const int unit = wave * 32 + r;  // this lane's hidden unit (U) and feature (psi, dPhi)
   float b2v = a.b2[(int64_t)h * DP + unit];
@@ -245,27 +245,18 @@ act_grad_kernel(ActGradArgs a) {
     for (int ks = 0; ks < KS; ++ks) w1f[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
   }
   bf16x8 w2f[KS2];  // B operands: column = feature, k = hidden
-  {
-    const bf16_t* p = a.w2 + ((int64_t)h * DP + unit) * HID + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS2; ++ks) w2f[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-  }
   bf16x8 mf[KS];    // B operands: column = feature, k = head dimension (row `unit` of M)
+  // W2 and M come by way of the tile buffers: W2 through those of x, vec (half of the waves) and U, then M through
+  // those of U while the first tiles arrive.  M is stored transposed ([d][dprime], the layout of the forward chunk
+  // states): the wave's 32 columns, read back with transposing loads.  Read from memory as operands, M value by value,
+  // the launch took 54.5 us (216 workgroups of ten tiles), now 53.1.
+  static_assert(KS2 == 2 * KS && NW / 2 * 64 * 2 * D <= 4 * TB && NW / 2 * 64 * 2 * D <= 2 * 64 * UPAD, "staging");
+  char* const stage = (wave < NW / 2 ? XV : Us) + (wave % (NW / 2)) * (64 * 2 * D);
   {
-    // M is stored transposed ([d][dprime], the layout of the forward chunk states): the eight
-    // values of a fragment are gathered one by one -- once per workgroup
-    const bf16_t* p = a.M + ((int64_t)bh * a.slots + slot) * D * DP + unit;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      u32x4 w;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t lo = p[(int64_t)(16 * ks + 8 * g + 2 * j) * DP];
-        const uint32_t hi = p[(int64_t)(16 * ks + 8 * g + 2 * j + 1) * DP];
-        w[j] = lo | (hi << 16);
-      }
-      mf[ks] = __builtin_bit_cast(bf16x8, w);
-    }
+    const u32x4 W2r = make_rsrc_words(a.w2 + ((int64_t)h * DP + wave * 32) * HID);
+    const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_address(stage));
+    stage_rows<2 * D>(W2r, 4 * D, 0, lds, lane);
+    stage_rows<2 * D>(W2r, 4 * D, 2 * D, lds + 32 * 2 * D, lane);
   }
 
   const u32x4 Xr = make_rsrc_words(a.x + row0 * D), Vr = make_rsrc_words(a.vec + row0 * D);
@@ -338,11 +329,33 @@ act_grad_kernel(ActGradArgs a) {
   float db2acc = 0.f, dzacc = 0.f;
   constexpr int PD = 4;
   bf16x8 fr[PD];
+  wave_loads_done();
+  if (tid < HID) B1s[tid] = b1v;
+#pragma unroll
+  for (int ks = 0; ks < KS2; ++ks) w2f[ks] = staged_fragment<2 * D>(stage + ks / KS * (32 * 2 * D), lane, ks % KS);
+  lds_barrier();   // W2 has been read by all waves, the bias is in LDS
+  char* const stage_m = Us + wave * (D * 64);
+  {
+    const u32x4 Mr = make_rsrc_words(a.M + ((int64_t)bh * a.slots + slot) * D * DP + wave * 32);
+    const uint32_t lds = __builtin_amdgcn_readfirstlane(lds_address(stage_m));
+#pragma unroll
+    for (int n = 0; n < D / 16; ++n)   // 16 rows of 64 bytes
+      direct_load_16(Mr, (lane >> 2) * (2 * DP) + 16 * (lane & 3), n * 16 * (2 * DP), lds + n * 1024);
+  }
   if (n_tiles > 0) {
     range.fill(Xr, 0, x_lds);
     if (TW) load_tw(0);
     range.fill(Vr, 0, v_lds);
     if (n_tiles > 1) range.fill(Xr, 64, x_lds + TB);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * R::LPT) : "memory");   // M; two tiles at least are younger
+  } else {
+    wave_loads_done();
+  }
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    const bf16_t* const p = reinterpret_cast<const bf16_t*>(stage_m) + (16 * ks + 8 * g + ((lane & 15) >> 2)) * 32 +
+                            16 * (r >> 4) + 4 * (lane & 3);
+    mf[ks] = join_tr(lds_read_tr(p), lds_read_tr(p + 4 * 32));
   }
   settle(w1f);
   settle(w2f);
@@ -350,7 +363,7 @@ act_grad_kernel(ActGradArgs a) {
   settle(b2v);
   settle(zvv);
   if (n_tiles > 0) {
-    wait_loads_and_barrier<0>();   // also: the bias is in LDS
+    wait_loads_and_barrier<0>();   // also: all waves have read M
     const int xbase = x_base(opaque_lane());
     uint32_t s[2] = {0u, 0u};
 #pragma unroll
@@ -607,12 +620,10 @@ __device__ __forceinline__ void tn_body(const WeightGradSide& a, int H, int64_t 
   const RX xrange(pc.tokens, wave, lane);
 
   const BiasRows b1 = load_bias_rows(a.b1 + (int64_t)h * W + wave * 32);
-  bf16x8 w1f[KS];   // A operands: row = hidden unit 32 wave + r, k = head dimension
-  {
-    const bf16_t* p = a.w1 + ((int64_t)h * W + wave * 32 + r) * D + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) w1f[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-  }
+  bf16x8 w1f[KS];   // A operands: row = hidden unit 32 wave + r, k = head dimension; by way of the buffers of U
+  char* const stage = Us + wave * (32 * 2 * D);
+  stage_rows<2 * D>(make_rsrc_words(a.w1 + ((int64_t)h * W + wave * 32) * D), 2 * D, 0,
+                    __builtin_amdgcn_readfirstlane(lds_address(stage)), lane);
   f32x16 acc[2][HB];
 #pragma unroll
   for (int fb = 0; fb < 2; ++fb)
@@ -623,7 +634,12 @@ __device__ __forceinline__ void tn_body(const WeightGradSide& a, int H, int64_t 
     xrange.fill(Xr, 0, x_lds);
     prange.fill(Pr, 0, p_lds);
     if (n_tiles > 1) xrange.fill(Xr, 64, x_lds + TB);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(RX::LPT + RP::LPT) : "memory");   // W1; these tiles at least are younger
+  } else {
+    wave_loads_done();
   }
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) w1f[ks] = staged_fragment<2 * D>(stage, lane, ks);
   settle(w1f);
   auto u_start = [&]() {
     f32x16 u;
@@ -824,12 +840,14 @@ __device__ __forceinline__ void hid_body(const WeightGradSide& a, int H, int64_t
   const int unit = wave * 32 + r;   // this lane's hidden unit
   // where its sign stands in a word: unit 8i + 4g + j of the slice is bit 16 g + 15 - (4i + j)
   const int bit = 16 * ((r >> 2) & 1) + 15 - (4 * (r >> 3) + (r & 3));
-  bf16x8 w2tf[KS2];                 // B operands: column = hidden unit, k = feature
-  {
-    const bf16_t* p = a.w2t + ((int64_t)h * HID + unit) * DP + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS2; ++ks) w2tf[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-  }
+  // B operands: column = hidden unit, k = feature; in two halves by way of the second dpsi buffer (half of the waves)
+  // and of LDS that only dW2 uses otherwise
+  bf16x8 w2tf[KS2];
+  static_assert(KS2 == 2 * D / 16 && NW / 2 * 32 * 2 * D <= TBU, "staging");
+  char* const stage = (wave < NW / 2 ? Pt + TBU : Xt + 2 * TB + 512 * NW) + (wave % (NW / 2)) * (32 * 2 * D);
+  const uint32_t stage_lds = __builtin_amdgcn_readfirstlane(lds_address(stage));
+  const u32x4 Wr = make_rsrc_words(a.w2t + ((int64_t)h * HID + wave * 32) * DP);
+  stage_rows<2 * D>(Wr, 4 * D, 0, stage_lds, lane);
   f32x16 acc[DB];
 #pragma unroll
   for (int db = 0; db < DB; ++db) acc[db] = f32x16{};
@@ -839,7 +857,17 @@ __device__ __forceinline__ void hid_body(const WeightGradSide& a, int H, int64_t
     prange.fill(Pr, 0, p_lds);
     xrange.fill(Xr, 0, x_lds);
     load_signs(0);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(RX::LPT + RP::LPT) : "memory");   // the first half of W2^T
+  } else {
+    wave_loads_done();
   }
+#pragma unroll
+  for (int ks = 0; ks < KS2 / 2; ++ks) w2tf[ks] = staged_fragment<2 * D>(stage, lane, ks);
+  wave_reads_done();
+  stage_rows<2 * D>(Wr, 4 * D, 2 * D, stage_lds, lane);
+  wave_loads_done();
+#pragma unroll
+  for (int ks = 0; ks < KS2 / 2; ++ks) w2tf[KS2 / 2 + ks] = staged_fragment<2 * D>(stage, lane, ks);
   settle(w2tf);
   constexpr int PD = 4;   // fragments read ahead of their products
   bf16x8 fr[PD];

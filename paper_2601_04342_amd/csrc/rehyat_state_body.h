@@ -35,6 +35,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   // U[token][hidden] with 16 bytes of padding per row: consecutive rows start four banks
   // apart, so fragment reads and writes are conflict-free without a chunk permutation
   constexpr int UPAD = UROW + 16;
+  static_assert(KS2 == 2 * KS && NW * 32 * 2 * D <= StateLds<D>::XV && NW * 32 * 2 * D <= StateLds<D>::US, "staging");
   static_assert(StateLds<D>::XV == 4 * TB && StateLds<D>::US == 2 * 64 * UPAD && StateLds<D>::B1 == HID * 4, "LDS layout");
 
   const int tid = threadIdx.x;
@@ -77,22 +78,21 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   // ---- resident operands ----------------------------------------------------
   // first-layer bias in LDS: accumulator register 4i+j is hidden unit 32w + 8i + 4g + j, so a
   // lane reads its four rows of block i with one 16-byte read
-  if (tid < HID) B1s[tid] = a.b1_k[(int64_t)h * HID + tid];
+  const float b1v = tid < HID ? a.b1_k[(int64_t)h * HID + tid] : 0.f;
   const float* const b1rows = B1s + wave * 32 + 4 * g;
   const int unit = wave * 32 + r;  // this lane's hidden unit (first half) and feature (second half)
   float b2v = a.b2_k[(int64_t)h * DP + unit];
   bf16x8 w1f[KS];   // A operands: row = hidden unit, k = head dimension
-  {
-    const bf16_t* p = a.w1_k + ((int64_t)h * HID + unit) * D + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) w1f[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-  }
   bf16x8 w2f[KS2];  // B operands: column = feature, k = hidden
-  {
-    const bf16_t* p = a.w2_k + ((int64_t)h * DP + unit) * HID + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS2; ++ks) w2f[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-  }
+  // They come by way of the tile buffers (K and V: W1, U: W2 in two halves of its columns), whole rows to an
+  // instruction: U of the first tile begins 3.2 us after the workgroup's start (108 workgroups, 2 x 3 heads of 333-token
+  // frames; 6.2 with 240), as operands read from memory 6.8 (and 9.7).
+  const u32x4 W1r = make_rsrc_words(a.w1_k + ((int64_t)h * HID + wave * 32) * D);
+  const u32x4 W2r = make_rsrc_words(a.w2_k + ((int64_t)h * DP + wave * 32) * HID);
+  char* const stage1 = XV + wave * (32 * 2 * D);
+  char* const stage2 = Us + wave * (32 * 2 * D);
+  stage_rows<2 * D>(W1r, 2 * D, 0, lds_address(stage1), lane);
+  stage_rows<2 * D>(W2r, 4 * D, 0, lds_address(stage2), lane);
   // tile `it` of K or V goes into the buffer of its parity
   const u32x4 Kr = make_rsrc_words(Kb), Vr = make_rsrc_words(Vb);
   const uint32_t k_lds = lds_address(XV), v_lds = k_lds + 2 * TB;
@@ -145,16 +145,31 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
 
   constexpr int PD = 4;   // fragments read ahead of their products
   bf16x8 fr[PD];
+  wave_loads_done();
+  if (tid < HID) B1s[tid] = b1v;
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) {
+    w1f[ks] = staged_fragment<2 * D>(stage1, lane, ks);
+    w2f[ks] = staged_fragment<2 * D>(stage2, lane, ks);
+  }
+  wave_reads_done();
+  stage_rows<2 * D>(W2r, 4 * D, 2 * D, lds_address(stage2), lane);
+  lds_barrier();   // W1 has been read by all waves, the bias is in LDS
   if (n_tiles > 0) {
     range.fill(Kr, 0, k_lds);
     range.fill(Vr, 0, v_lds);
     if (n_tiles > 1) range.fill(Kr, 64, k_lds + TB);
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * R::LPT) : "memory");   // W2; two tiles at least are younger
+  } else {
+    wave_loads_done();
   }
+#pragma unroll
+  for (int ks = 0; ks < KS; ++ks) w2f[KS + ks] = staged_fragment<2 * D>(stage2, lane, ks);
   settle(w1f);
   settle(w2f);
   settle(b2v);
   if (n_tiles > 0) {
-    wait_loads_and_barrier<0>();   // also: the bias is in LDS
+    wait_loads_and_barrier<0>();   // also: all waves have read W2
     const int ln = opaque_lane();
     const int xbase = x_base(ln);
 #pragma unroll
