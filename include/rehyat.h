@@ -234,8 +234,8 @@ int rehyat_forward_noalloc(const void *q, const void *k, const void *v,
  *             rehyat_phi_backward_workspace_bytes(...) bytes.  Unlike the
  *             forward workspace it grows with N: the gradients of the second
  *             layer's pre-activations are kept token by token, for queries and
- *             keys, the latter over y_hat and dL/dy_hat / den, which they
- *             outlive (about 1.1 KB per token and head at d = 128), beside the
+ *             keys, over y_hat and partial sums, which they outlive (about
+ *             1.1 KB per token and head at d = 128), beside the
  *             chunk states, over which the per-workgroup partial sums of the
  *             weight gradients lie (at most 0.2 GB at d = 128 whenever B*H does
  *             not exceed 256).  Used only

@@ -286,10 +286,9 @@ int choose_frame_pieces(int BH, int T, int HW, int d, int chunk, int overlap, in
   return best;
 }
 
-int launch_state_window(const Ctx& c, const void* k, const void* v, const rehyat_phi_params* phi,
-                        int B, int H, int T, int HW, int d, int chunk, int overlap, int chunk0,
-                        int n_seg, int nsplit) {
-  StateArgs s;
+StateArgs state_args(const Ctx& c, const void* k, const void* v, const rehyat_phi_params* phi, int B, int H, int T, int HW,
+                     int d, int chunk, int overlap, int chunk0, int n_seg, int nsplit) {
+  StateArgs s{};
   s.k = (const bf16_t*)k;
   s.v = (const bf16_t*)v;
   s.w1_k = (const bf16_t*)phi->w1_k;
@@ -309,16 +308,20 @@ int launch_state_window(const Ctx& c, const void* k, const void* v, const rehyat
   s.n_items = B * H * n_seg * nsplit;
   s.items_per_xcd = (s.n_items + 7) / 8;
   s.kv_bh_stride = (int64_t)T * HW * d;
-  s.step_n = 0;
-  s.query_segments = 0;
+  return s;
+}
+
+int launch_state_window(const Ctx& c, const void* k, const void* v, const rehyat_phi_params* phi,
+                        int B, int H, int T, int HW, int d, int chunk, int overlap, int chunk0,
+                        int n_seg, int nsplit) {
+  const StateArgs s = state_args(c, k, v, phi, B, H, T, HW, d, chunk, overlap, chunk0, n_seg, nsplit);
   ProfScope prof(c.prof, 0, c.st);
   hipError_t e = launch_state(s, d, s.items_per_xcd * 8, c.st);
   if (e != hipSuccess) return hip_fail(e, "state kernel launch");
   return REHYAT_OK;
 }
 
-int launch_prefix_window(const Ctx& c, int B, int H, int d, int dp, int n_chunks, int n_seg,
-                         int nsplit, bool first) {
+PrefixArgs prefix_args(const Ctx& c, int B, int H, int d, int dp, int n_chunks, int n_seg, int nsplit, bool first) {
   PrefixArgs p;
   p.partial = (const float*)(c.ws + c.L.partial);
   p.carry = (float*)(c.ws + c.L.carry);
@@ -333,6 +336,12 @@ int launch_prefix_window(const Ctx& c, int B, int H, int d, int dp, int n_chunks
   p.first_window = first ? 1 : 0;
   p.elems = d * dp + dp;
   p.s_elems = d * dp;
+  return p;
+}
+
+int launch_prefix_window(const Ctx& c, int B, int H, int d, int dp, int n_chunks, int n_seg,
+                         int nsplit, bool first) {
+  const PrefixArgs p = prefix_args(c, B, H, d, dp, n_chunks, n_seg, nsplit, first);
   ProfScope prof(c.prof, 1, c.st);
   hipError_t e = launch_prefix(p, c.st);
   if (e != hipSuccess) return hip_fail(e, "prefix kernel launch");
@@ -540,8 +549,8 @@ struct BwdPlan {
   int nc, n_seg;     // chunks; segments (= chunks that read a state)
   int nsplit;        // pieces per segment (state and activation-gradient kernels)
   int n2, n1;        // pieces per side and (b, h) of the weight gradients: dW2, dW1
-  size_t yhat, nS, nL, u, tokw, Rt, rz, w2t, total;
-  size_t dpsi[2], signs[2], p_w2[2], p_w1[2], p_b2[2], p_dz;   // queries, keys
+  size_t yhat, nS, nL, q_part, inv, tokw, Rt, rz, w2t, total;
+  size_t dpsi[2], signs[2], p_w2[2], p_w1[2], p_b2[2];   // queries, keys
 };
 
 BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
@@ -555,8 +564,9 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   P.F = ws_layout(B, H, d, dp, P.sl);
   weight_pieces((int)BH, (int64_t)((N + 63) / 64), d, &P.n2, &P.n1);
   // Areas that are not needed at the same time lie over each other (all launches are on one stream): the partial
-  // sums of the weight gradients over the states and R, which the key side's activation gradients read last,
-  // and what those write over what the query side has read.  480p at 12 heads of 128: 752 -> 498 MB.
+  // sums of the weight gradients over the states and R, which the activation gradients read last, and the
+  // activation gradients over y_hat, n^S, n^L and the partial sums of dL/dS_t.  480p at 12 heads of 128: 501 MB, with
+  // areas of their own 683.
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t o = off;
@@ -574,18 +584,21 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   if (off < sums) off = sums;
   P.yhat = P.dpsi[1] = off;
   take(BH * N * d * sizeof(bf16_t));
-  P.u = take(BH * N * d * sizeof(bf16_t));
+  P.q_part = off;
+  off = P.dpsi[1] + align256(BH * N * dp * sizeof(bf16_t));
+  P.dpsi[0] = take(BH * N * dp * sizeof(bf16_t));
+  const size_t q_end = P.q_part + align256(BH * P.sl.partial * ((size_t)d * dp + dp) * sizeof(float));
+  if (off < q_end) off = q_end;
   P.nS = P.signs[1] = off;
   take(BH * N * sizeof(float));
   P.nL = take(BH * N * sizeof(float));
-  P.tokw = take(BH * N * sizeof(float));
   const size_t signs = BH * N * (hid / 32) * sizeof(uint32_t);
   if (off < P.signs[1] + align256(signs)) off = P.signs[1] + align256(signs);
-  P.dpsi[0] = take(BH * N * dp * sizeof(bf16_t));
+  P.inv = take(BH * N * sizeof(float));
+  P.tokw = take(BH * N * sizeof(float));
   P.signs[0] = take(signs);
   P.w2t = take(2 * (size_t)H * hid * dp * sizeof(bf16_t));
   for (int side = 0; side < 2; ++side) P.p_b2[side] = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
-  P.p_dz = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
   P.total = off;
   return P;
 }
@@ -598,38 +611,35 @@ struct SideParams {
   int64_t lo, hi;
 };
 
-// Activation gradients of one side.  `vec` is u or v, `M`/`zv` the per-segment matrices of dPhi = M vec +
+// Activation gradients of one side.  `vec` is G or v, `M`/`zv` the per-segment matrices of dPhi = inv M vec +
 // tokw zv.
-int activation_gradients(char* ws, const BwdPlan& P, hipStream_t st, int side, const SideParams& sp, const void* vec,
-                         const float* tokw, const bf16_t* M, const float* zv, float* dz_part, int BH, int H, int T, int HW,
-                         int d, int chunk, int overlap) {
+ActGradArgs act_grad_args(char* ws, const BwdPlan& P, int side, const SideParams& sp, const void* vec, size_t M, size_t zv,
+                          int BH, int H, int T, int HW, int chunk, int overlap) {
   ActGradArgs g;
   g.x = (const bf16_t*)sp.x;
   g.vec = (const bf16_t*)vec;
-  g.tokw = tokw;
+  g.inv = (const float*)(ws + P.inv);
+  g.tokw = (const float*)(ws + P.tokw);
   g.w1 = (const bf16_t*)sp.w1;
   g.b1 = (const float*)sp.b1;
   g.w2 = (const bf16_t*)sp.w2;
   g.b2 = (const float*)sp.b2;
-  g.M = M;
-  g.zv = zv;
+  g.M = (const bf16_t*)(ws + M);
+  g.zv = (const float*)(ws + zv);
   g.dpsi = (bf16_t*)(ws + P.dpsi[side]);
   g.signs = (uint32_t*)(ws + P.signs[side]);
   g.db2_part = (float*)(ws + P.p_b2[side]);
-  g.dz_part = dz_part;
   g.H = H;
   g.T = T;
   g.HW = HW;
   g.chunk = chunk;
   g.overlap = overlap;
-  g.query_side = side == 0 ? 1 : 0;
   g.n_seg = P.n_seg;
   g.nsplit = P.nsplit;
   g.slots = P.nc;
   g.n_items = BH * P.n_seg * P.nsplit;
   g.items_per_xcd = (g.n_items + 7) / 8;
-  hipError_t e = launch_act_grad(g, d, g.items_per_xcd * 8, st);
-  return e == hipSuccess ? REHYAT_OK : hip_fail(e, "activation-gradient kernel launch");
+  return g;
 }
 
 // The weight gradients of both sides from their activation gradients, and the sums over batch and
@@ -922,14 +932,18 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
     return REHYAT_OK;
   }
 
-  // ---- forward pass, every chunk state kept (one window) ----------------------------
-  rc = launch_state_window(c, k, v, phi, B, H, T, HW, d, chunk, overlap, 0, P.n_seg, P.nsplit);
-  if (rc != REHYAT_OK) return rc;
-  rc = launch_prefix_window(c, B, H, d, dp, nc, P.n_seg, P.nsplit, true);
-  if (rc != REHYAT_OK) return rc;
+  // ---- forward pass, every chunk state kept (one window); with a saved one the chunk states wait for the sums of the
+  // query side, with which they share their launches
+  const StateArgs ks = state_args(c, k, v, phi, B, H, T, HW, d, chunk, overlap, 0, P.n_seg, P.nsplit);
+  const PrefixArgs pk = prefix_args(c, B, H, d, dp, nc, P.n_seg, P.nsplit, true);
   const float* nS = saved ? saved->nS : (const float*)(ws + P.nS);
   const float* nL = saved ? saved->nL : (const float*)(ws + P.nL);
+  hipError_t e;
   if (!saved) {
+    e = launch_state(ks, d, ks.items_per_xcd * 8, st);
+    if (e != hipSuccess) return hip_fail(e, "state kernel launch");
+    e = launch_prefix(pk, st);
+    if (e != hipSuccess) return hip_fail(e, "prefix kernel launch");
     rehyat_debug_out dbg;
     dbg.m = dbg.aS = dbg.aL = nullptr;
     dbg.nS = (float*)(ws + P.nS);
@@ -939,14 +953,13 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
     if (rc != REHYAT_OK) return rc;
   }
 
-  hipError_t e;
-  // ---- u, w per token; W2 [dp][hidden] -> [hidden][dp] of both maps ---------------------------------------------------------------
+  // ---- 1 / den, w per token; W2 [dp][hidden] -> [hidden][dp] of both maps ----------------
   PrepArgs pa;
   pa.g = (const bf16_t*)grad_out;
   pa.y = (const bf16_t*)y;
   pa.nS = nS;
   pa.nL = nL;
-  pa.u = (bf16_t*)(ws + P.u);
+  pa.inv = (float*)(ws + P.inv);
   pa.tokw = (float*)(ws + P.tokw);
   pa.w2_q = (const bf16_t*)phi->w2_q;
   pa.w2_k = (const bf16_t*)phi->w2_k;
@@ -957,33 +970,36 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
   e = launch_prep(pa, st);
   if (e != hipSuccess) return hip_fail(e, "gradient preparation kernel launch");
 
-  // ---- dL/dS_t partial sums: the chunk-state kernel on (q, u) with phi_q, query segments ---
-  {
-    StateArgs s;
-    s.k = (const bf16_t*)q;
-    s.v = (const bf16_t*)(ws + P.u);
-    s.w1_k = (const bf16_t*)phi->w1_q;
-    s.b1_k = (const float*)phi->b1_q;
-    s.w2_k = (const bf16_t*)phi->w2_q;
-    s.b2_k = (const float*)phi->b2_q;
-    s.partial = (float*)(ws + P.F.partial);
-    s.H = H;
-    s.T = T;
-    s.HW = HW;
-    s.chunk = chunk;
-    s.overlap = overlap;
-    s.chunk0 = 1;
-    s.n_seg = P.n_seg;
-    s.nsplit = P.nsplit;
-    s.partial_slots = P.sl.partial;
-    s.n_items = BH * P.n_seg * P.nsplit;
-    s.items_per_xcd = (s.n_items + 7) / 8;
-    s.kv_bh_stride = N * d;
-    s.step_n = 0;
-    s.query_segments = 1;
-    e = launch_state(s, d, s.items_per_xcd * 8, st);
-    if (e != hipSuccess) return hip_fail(e, "state-gradient kernel launch");
-  }
+  // ---- dL/dS_t, dL/dz_t partial sums: the chunk-state kernel on (q, G) with phi_q, query segments ---
+  StateArgs qs = ks;
+  qs.k = (const bf16_t*)q;
+  qs.v = (const bf16_t*)grad_out;
+  qs.w1_k = (const bf16_t*)phi->w1_q;
+  qs.b1_k = (const float*)phi->b1_q;
+  qs.w2_k = (const bf16_t*)phi->w2_q;
+  qs.b2_k = (const float*)phi->b2_q;
+  qs.partial = (float*)(ws + P.q_part);
+  qs.chunk0 = 1;
+  qs.tok_scale = (const float*)(ws + P.inv);
+  qs.tok_weight = (const float*)(ws + P.tokw);
+  e = launch_state_gradient(qs, saved ? &ks : nullptr, d, st);
+  if (e != hipSuccess) return hip_fail(e, "state-gradient kernel launch");
+
+  // ---- R_tau, r_tau ------------------------------------------------------------------
+  SuffixArgs sa;
+  sa.part = (const float*)(ws + P.q_part);
+  sa.Rt = (bf16_t*)(ws + P.Rt);
+  sa.r = (float*)(ws + P.rz);
+  sa.BH = BH;
+  sa.n_seg = P.n_seg;
+  sa.nsplit = P.nsplit;
+  sa.part_slots = P.sl.partial;
+  sa.slots = nc;
+  sa.elems = d * dp + dp;
+  sa.s_elems = d * dp;
+  sa.dp = dp;
+  e = launch_suffix(sa, saved ? &pk : nullptr, st);
+  if (e != hipSuccess) return hip_fail(e, "suffix kernel launch");
 
   const ChunkRange c1 = chunk_range(T, HW, chunk, overlap, 1), cl = chunk_range(T, HW, chunk, overlap, nc - 1);
   const SideParams sides[2] = {
@@ -991,32 +1007,9 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
        (float*)grads->b2_q, c1.q_lo, N},
       {k, phi->w1_k, phi->b1_k, phi->w2_k, phi->b2_k, (float*)grads->w1_k, (float*)grads->b1_k, (float*)grads->w2_k,
        (float*)grads->b2_k, 0, cl.s_lo}};
-  rc = activation_gradients(ws, P, st, 0, sides[0], ws + P.u, (const float*)(ws + P.tokw),
-                            (const bf16_t*)(ws + P.F.state_s), (const float*)(ws + P.F.state_z), (float*)(ws + P.p_dz), BH, H,
-                            T, HW, d, chunk, overlap);
-  if (rc != REHYAT_OK) return rc;
-
-  // ---- R_tau, r_tau ------------------------------------------------------------------
-  SuffixArgs sa;
-  sa.s_part = (const float*)(ws + P.F.partial);
-  sa.z_part = (const float*)(ws + P.p_dz);
-  sa.Rt = (bf16_t*)(ws + P.Rt);
-  sa.r = (float*)(ws + P.rz);
-  sa.BH = BH;
-  sa.n_seg = P.n_seg;
-  sa.s_nsplit = P.nsplit;
-  sa.s_slots = P.sl.partial;
-  sa.z_nsplit = P.nsplit;
-  sa.slots = nc;
-  sa.elems = d * dp + dp;
-  sa.s_elems = d * dp;
-  sa.dp = dp;
-  e = launch_suffix(sa, st);
-  if (e != hipSuccess) return hip_fail(e, "suffix kernel launch");
-
-  rc = activation_gradients(ws, P, st, 1, sides[1], v, nullptr, (const bf16_t*)(ws + P.Rt), (const float*)(ws + P.rz),
-                            nullptr, BH, H, T, HW, d, chunk, overlap);
-  if (rc != REHYAT_OK) return rc;
+  e = launch_act_grad(act_grad_args(ws, P, 0, sides[0], grad_out, P.F.state_s, P.F.state_z, BH, H, T, HW, chunk, overlap),
+                      act_grad_args(ws, P, 1, sides[1], v, P.Rt, P.rz, BH, H, T, HW, chunk, overlap), d, st);
+  if (e != hipSuccess) return hip_fail(e, "activation-gradient kernel launch");
   return weight_gradients(ws, P, st, sides, B, H, T, HW, d);
 }
 

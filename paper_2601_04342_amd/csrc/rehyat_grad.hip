@@ -11,11 +11,11 @@
 // and then through phi = [psi_1, psi_2^2], psi = relu(W2 U + b2), U = relu(W1 x + b1).
 //
 // Kernels, in launch order (queries, then keys, where there are two):
-//   prep_kernel        u, w per token (HBM-bound)
-//   state_kernel       (rehyat_state.hip, query segments) dL/dS_t partial sums
+//   prep_kernel        1 / den, w per token (HBM-bound)
+//   state_gradient_kernel   (rehyat_state.hip) dL/dS_t, dL/dz_t partial sums
 //   act_grad_kernel    recomputes U and psi, forms dPhi and dpsi per token; writes dpsi token-major, the
-//                      signs of U, and the partial sums of db2 and dL/dz_t
-//   suffix_kernel      R_tau, r_tau from the partial sums (between the two activation gradients)
+//                      signs of U, and the partial sums of db2; both sides in one launch
+//   suffix_kernel      (rehyat_prefix.hip, before it) R_tau, r_tau from the partial sums
 //   weight_grad_kernel of both sides: dW2 = dpsi^T U over tokens (U recomputed from x);
 //                      dU = (dpsi W2) [U > 0], dW1 = dU^T x, db1 = sum dU
 //   reduce_kernel      sums the per-workgroup partials over batch and pieces
@@ -32,7 +32,8 @@
 namespace rehyat {
 
 // ------------------------------------------------------------------------------------
-// u_i = G_i / den_i (bf16), w_i = -(G_i . y_i) / den_i.  Eight elements per thread, D/8
+// 1 / den_i, w_i = -(G_i . y_i) / den_i; u = G / den itself is not written (48.4 us at 480p with it, 34.6 without; the
+// sums over it gain as well: 12 % less error of the gradients, G being exact in bf16).  Eight elements per thread, D/8
 // consecutive lanes per token.  The last blocks of the launch transpose the second-layer weights of both
 // maps (32 x 32 per block, through a padded LDS tile): 5 us as a launch of their own, nothing beside
 // this one, which is bound by memory.
@@ -71,19 +72,17 @@ prep_kernel(PrepArgs a, int token_blocks) {
   const u32x4 yr = *reinterpret_cast<const u32x4*>(a.y + off);
   const float inv = 1.0f / (a.nS[tok] + a.nL[tok]);
   float dot = 0.f;
-  u32x4 ur;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const float g0 = __builtin_bit_cast(float, gr[i] << 16), g1 = __builtin_bit_cast(float, gr[i] & 0xffff0000u);
     const float y0 = __builtin_bit_cast(float, yr[i] << 16), y1 = __builtin_bit_cast(float, yr[i] & 0xffff0000u);
     dot += g0 * y0 + g1 * y1;
-    ur[i] = pack_bf16(g0 * inv, g1 * inv);
   }
 #pragma unroll
   for (int m = 1; m < LPT; m <<= 1) dot += __shfl_xor(dot, m);
-  if (live) {
-    *reinterpret_cast<u32x4*>(a.u + off) = ur;
-    if (part == 0) a.tokw[tok] = -dot * inv;
+  if (live && part == 0) {
+    a.inv[tok] = inv;
+    a.tokw[tok] = -dot * inv;
   }
 }
 
@@ -93,63 +92,6 @@ hipError_t launch_prep(const PrepArgs& a, hipStream_t stream) {
   const unsigned tokens = (unsigned)((threads + 255) / 256), grid = tokens + 2 * a.H * nb * nb;
   if (a.d == 128) hipLaunchKernelGGL(prep_kernel<128>, dim3(grid), dim3(256), 0, stream, a, (int)tokens);
   else hipLaunchKernelGGL(prep_kernel<64>, dim3(grid), dim3(256), 0, stream, a, (int)tokens);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------
-// R_tau = sum over segments s >= tau of the chunk-state gradient partials (segment s holds
-// dL/dS of chunk s+1, so this is the sum over chunks t > tau), r_tau likewise.  Each thread
-// owns four consecutive elements and walks the segments from the last to the first (fixed
-// order: bit-reproducible).
-// ------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256)
-suffix_kernel(SuffixArgs a) {
-  const int bh = blockIdx.y;
-  const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;
-  if (idx >= a.elems) return;
-  const bool is_s = idx < a.s_elems;
-  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-  // pieces of segment c, then its sum goes out; kScanDepth pieces are loaded ahead of their sums
-  const int ns = is_s ? a.s_nsplit : a.z_nsplit;
-  const float* const base = is_s ? a.s_part + (int64_t)bh * a.s_slots * a.elems + idx
-                                 : a.z_part + (int64_t)bh * a.n_seg * a.z_nsplit * a.dp + (idx - a.s_elems);
-  const int64_t stride = is_s ? a.elems : a.dp;
-  int lc = a.n_seg - 1, lsp = 0;   // next piece to load
-  int c = a.n_seg - 1, sp = 0;     // next piece to add
-  while (c >= 0) {
-    f32x4 x[kScanDepth];
-#pragma unroll
-    for (int u = 0; u < kScanDepth; ++u) {
-      if (lc >= 0) {
-        x[u] = *reinterpret_cast<const f32x4*>(base + ((int64_t)lc * ns + lsp) * stride);
-        if (++lsp == ns) {
-          lsp = 0;
-          --lc;
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < kScanDepth; ++u) {
-      if (c < 0) break;
-      acc += x[u];
-      if (++sp < ns) continue;
-      if (is_s) {
-        u32x2 pk;
-        pk[0] = pack_bf16(acc[0], acc[1]);
-        pk[1] = pack_bf16(acc[2], acc[3]);
-        *reinterpret_cast<u32x2*>(a.Rt + ((int64_t)bh * a.slots + c) * a.s_elems + idx) = pk;
-      } else {
-        *reinterpret_cast<f32x4*>(a.r + ((int64_t)bh * a.slots + c) * a.dp + idx - a.s_elems) = acc;
-      }
-      sp = 0;
-      --c;
-    }
-  }
-}
-
-hipError_t launch_suffix(const SuffixArgs& a, hipStream_t stream) {
-  dim3 grid((a.elems / 4 + 255) / 256, a.BH);
-  hipLaunchKernelGGL(suffix_kernel, grid, dim3(256), 0, stream, a);
   return hipGetLastError();
 }
 
@@ -168,14 +110,23 @@ hipError_t launch_suffix(const SuffixArgs& a, hipStream_t stream) {
 // they have landed: vector memory operations of a wave complete in the order issued, stores included,
 // and the step's stores (four of dpsi, one of signs) are younger than its loads.
 // ------------------------------------------------------------------------------------
-// Bound by memory: 1.06 KB per token read and written, 3.8 TB/s at the 480p shape (108 us for the queries,
-// 103 for the keys) against 4.75 of a plain copy; the order of the products made no difference to that,
-// the sign words cost 2 - 5 us and save the first-layer gradient a quarter of its products.
+// Bound by memory: 1.06 KB per token read and written, 3.4 - 3.8 TB/s at the 480p shape against 4.75 of a plain copy; the
+// order of the products made no difference to that, the sign words cost 2 - 5 us and save the first-layer gradient a
+// quarter of its products.  Both sides in one launch, the queries' dL/dz_t left to the chunk-state kernel and G
+// scaled here instead of u read: 320x480 106 -> 101.5 us, 480p 240 -> 238.6.
 // Two waves per SIMD, also where a workgroup has four waves: with the whole register file to use the
 // compiler keeps accumulators in AGPRs and copies each one out before vector work.
+template <int D, int NW>
+struct ActGradLds {
+  char XV[4 * 64 * 2 * D];               // x tiles 0/1, then vec tiles 0/1
+  char Us[2 * 64 * (2 * D * 2 + 16)];    // U of the current and of the next tile
+  char Stg[NW * 32 * 80];                // dpsi on its way out
+  float Tok[4 * 64];                     // scale and weight of the tokens of two tiles
+  float B1s[2 * D];
+};
+// TW: the query side, with a scale and a weight per token
 template <int D, int NW, bool TW>
-__global__ void __launch_bounds__(64 * NW, 2)
-act_grad_kernel(ActGradArgs a) {
+__device__ __forceinline__ void act_grad_body(const ActGradArgs& a, int block, ActGradLds<D, NW>& lds) {
   constexpr int HID = 2 * D, DP = 2 * D;
   constexpr int KS = D / 16;
   constexpr int KS2 = HID / 16;
@@ -188,11 +139,13 @@ act_grad_kernel(ActGradArgs a) {
   constexpr int UPAD = UROW + 16;
   static_assert(DP / NW == 32, "each wave owns 32 features");
 
-  __shared__ __attribute__((aligned(1024))) char XV[4 * TB];   // x tiles 0/1, then vec tiles 0/1
-  __shared__ __attribute__((aligned(1024))) char Us[2 * 64 * UPAD];
-  __shared__ __attribute__((aligned(1024))) char Stg[NW * 32 * SROW];
-  __shared__ __attribute__((aligned(256))) float Tws[2 * 64];
-  __shared__ __attribute__((aligned(256))) float B1s[HID];
+  static_assert(sizeof(lds.Us) == 2 * 64 * UPAD && sizeof(lds.Stg) == NW * 32 * SROW && sizeof(lds.XV) % 1024 == 0 &&
+                (sizeof(lds.XV) + sizeof(lds.Us)) % 1024 == 0 && sizeof(lds.Stg) % 256 == 0, "LDS layout");
+  char* const XV = lds.XV;
+  char* const Us = lds.Us;
+  char* const Stg = lds.Stg;
+  float* const Tok = lds.Tok;
+  float* const B1s = lds.B1s;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -200,7 +153,7 @@ act_grad_kernel(ActGradArgs a) {
   const int g = lane >> 5;
   const int r = lane & 31;
 
-  const int item = xcd_swizzle(blockIdx.x, a.items_per_xcd);
+  const int item = xcd_swizzle(block, a.items_per_xcd);
   if (item >= a.n_items) return;
   const int sp = item % a.nsplit;
   const int rest = item / a.nsplit;
@@ -210,7 +163,7 @@ act_grad_kernel(ActGradArgs a) {
 
   int64_t seg_lo, seg_hi;
   int slot;
-  if (a.query_side) {
+  if (TW) {
     const ChunkRange cr = chunk_range(a.T, a.HW, a.chunk, a.overlap, seg + 1);
     seg_lo = cr.q_lo;
     seg_hi = cr.q_hi;
@@ -260,16 +213,18 @@ act_grad_kernel(ActGradArgs a) {
   }
 
   const u32x4 Xr = make_rsrc_words(a.x + row0 * D), Vr = make_rsrc_words(a.vec + row0 * D);
-  const u32x4 Twr = make_rsrc_words(TW ? (const void*)(a.tokw + row0) : (const void*)a.x);
-  const uint32_t x_lds = lds_address(XV), v_lds = x_lds + 2 * TB, tw_lds = lds_address(Tws);
+  // scales by even waves, weights by odd ones
+  const u32x4 Tr = make_rsrc_words(TW ? (const void*)((wave & 1 ? a.tokw : a.inv) + row0) : (const void*)a.x);
+  const uint32_t x_lds = lds_address(XV), v_lds = x_lds + 2 * TB;
+  const uint32_t tok_lds = __builtin_amdgcn_readfirstlane(lds_address(Tok) + 256 * (wave & 1));
   using R = RangeTiles<2 * D, NW>;
   const R range(n_tokens, wave, lane);
-  auto load_tw = [&](int it) {   // the tile's 64 token weights, moved by every wave alike
+  auto load_tok = [&](int it) {   // of the tile's 64 tokens
     const int row = n_tokens < 64 ? 0 : 64 * it < n_tokens - 64 ? 64 * it : n_tokens - 64;
     int ln = lane;
     asm volatile("" : "+v"(ln));
-    direct_load_4(Twr, 4 * (ln < n_tokens ? ln : n_tokens - 1), __builtin_amdgcn_readfirstlane(4 * row),
-                  tw_lds + (it & 1) * 256);
+    direct_load_4(Tr, 4 * (ln < n_tokens ? ln : n_tokens - 1), __builtin_amdgcn_readfirstlane(4 * row),
+                  tok_lds + (it & 1) * 512);
   };
   const int uwbase = r * UPAD + wave * 64 + 8 * g;   // write: token r, units 32w + 8i + 4g .. +3 at + 16 i
   const int urbase = r * UPAD + 16 * g;              // read: A fragment of token r, k-step ks at + 32 ks
@@ -326,7 +281,7 @@ act_grad_kernel(ActGradArgs a) {
   // fragment of token row r, k-step ks inside an x or vec tile: ^ 32 ks
   auto x_base = [&](int ln) { return tile_off<2 * D>(ln & 31, 8 * (ln >> 5)); };
 
-  float db2acc = 0.f, dzacc = 0.f;
+  float db2acc = 0.f;
   constexpr int PD = 4;
   bf16x8 fr[PD];
   wave_loads_done();
@@ -344,7 +299,7 @@ act_grad_kernel(ActGradArgs a) {
   }
   if (n_tiles > 0) {
     range.fill(Xr, 0, x_lds);
-    if (TW) load_tw(0);
+    if (TW) load_tok(0);
     range.fill(Vr, 0, v_lds);
     if (n_tiles > 1) range.fill(Xr, 64, x_lds + TB);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * R::LPT) : "memory");   // M; two tiles at least are younger
@@ -386,7 +341,6 @@ act_grad_kernel(ActGradArgs a) {
     const char* const Vs = XV + (2 + (it & 1)) * TB;
     const char* const Xs = XV + ((it + 1) & 1) * TB;
     const char* const Uc = Us + (it & 1) * (64 * UPAD);
-    const float* const tws = Tws + (it & 1) * 64;
     const int ln = opaque_lane();
     const int xbase = x_base(ln);
     const int first = range.first(64 * it), count = range.count(64 * it), row = tile_row(it);
@@ -397,7 +351,13 @@ act_grad_kernel(ActGradArgs a) {
     static_assert(NM % PD == 0, "the fragment ring closes over a step");
     f32x16 ps[2], dphi[2], u[2];
     uint32_t sgn[2] = {0u, 0u};
-    float pdb[2] = {0.f, 0.f}, pdz[2] = {0.f, 0.f};   // a half's own sums: short chains of additions in fp32
+    float pdb[2] = {0.f, 0.f};   // a half's own sums: short chains of additions in fp32
+    f32x4 scale, weight;         // of four tokens
+    auto read_tok = [&](int tb, int q) {
+      const float* const p = Tok + (it & 1) * 128 + 32 * tb + 8 * q + 4 * g;
+      scale = *reinterpret_cast<const f32x4*>(p);
+      weight = *reinterpret_cast<const f32x4*>(p + 64);
+    };
     auto fetch = [&](auto MC) {
       constexpr int m = decltype(MC)::value;
       if constexpr (m >= NM) {
@@ -414,21 +374,16 @@ act_grad_kernel(ActGradArgs a) {
     auto elements = [&](auto TBC, auto IC) {   // tokens 8 i + 4 g .. + 3 of the half, in two pairs
       constexpr int tb = decltype(TBC)::value, q = decltype(IC)::value, i = q / 2;
       float dp[2];
-      f32x2 tw = {1.f, 1.f};   // weights of zv
-      if (TW) tw = *reinterpret_cast<const f32x2*>(tws + 32 * tb + 8 * i + 4 * g + 2 * (q & 1));
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int e = 2 * q + j;
         const bool live = MORE || (unsigned)(32 * tb + 8 * i + 4 * g + (e & 3) - first) < (unsigned)count;
         const float psi = fmaxf(ps[tb][e] + b2v, 0.f);
-        const float base = TW ? dphi[tb][e] + tw[j] * zvv : dphi[tb][e] + zvv;   // dL/dPhi
+        const float base = TW ? dphi[tb][e] * scale[e & 3] + weight[e & 3] * zvv : dphi[tb][e] + zvv;   // dL/dPhi
         dp[j] = squared ? (psi + psi) * base : (psi > 0.f ? base : 0.f);
         pdb[tb] += live ? dp[j] : 0.f;
-        // dL/dz_t is a sum over queries only
-        if (TW) pdz[tb] += live ? tw[j] * (squared ? psi * psi : psi) : 0.f;
       }
       pin(pdb[tb]);
-      if (TW) pin(pdz[tb]);
       const uint32_t pk = pack_bf16(dp[0], dp[1]);
       char* const w = Sg + (8 * i + 4 * g + 2 * (q & 1)) * SROW + 2 * r;
       *reinterpret_cast<bf16_t*>(w) = (bf16_t)pk;
@@ -462,12 +417,13 @@ act_grad_kernel(ActGradArgs a) {
         if constexpr (i < R::LPT) range.template load<i>(Xd, xs, xd);
         else range.template load<i - R::LPT>(Vr, vs, vd);
       }
-      if constexpr (MORE && TW && m == 4 * R::LPT + 1) load_tw(it + 1);
+      if constexpr (MORE && TW && m == 4 * R::LPT + 1) load_tok(it + 1);
       static_for<2>([&](auto TBC) {
         constexpr int tb = decltype(TBC)::value, p = m - (tb + 1) * LH - 2;
         if constexpr (p >= 0 && p * kQ < 8) {
           static_for<kQ>([&](auto JC) { elements(TBC, std::integral_constant<int, p * kQ + decltype(JC)::value>{}); });
         }
+        if constexpr (TW && p >= -1 && (p + 1) * kQ < 8) read_tok(tb, (p + 1) * kQ / 2);   // a slot ahead
         if constexpr (p == 8 / kQ) leave(tb);
       });
       if constexpr (MORE) {
@@ -487,15 +443,14 @@ act_grad_kernel(ActGradArgs a) {
                                                                   32 * decltype(MC)::value);
       });
     } else {
-      static_for<8>([&](auto IC) { elements(std::integral_constant<int, 1>{}, IC); });
+      static_for<8>([&](auto IC) {
+        if constexpr (TW && decltype(IC)::value % 2 == 0) read_tok(1, decltype(IC)::value / 2);
+        elements(std::integral_constant<int, 1>{}, IC);
+      });
       leave(1);
     }
     db2acc += pdb[0];
     db2acc += pdb[1];
-    if (TW) {
-      dzacc += pdz[0];
-      dzacc += pdz[1];
-    }
   };
   auto all_tiles = [&](auto SQC) {   // the waves of both instances meet at the same barriers
     // (fragments read before the branch would be kept, spilled, for the instance behind the other)
@@ -511,21 +466,24 @@ act_grad_kernel(ActGradArgs a) {
   else all_tiles(std::false_type{});
 
   const float db2 = half_swap_sum(db2acc);
-  const float dz = half_swap_sum(dzacc);
-  if (g == 0) {
-    a.db2_part[(int64_t)item * DP + unit] = db2;
-    if (a.dz_part) a.dz_part[(int64_t)item * DP + unit] = dz;
-  }
+  if (g == 0) a.db2_part[(int64_t)item * DP + unit] = db2;
 }
 
-hipError_t launch_act_grad(const ActGradArgs& a, int d, int grid, hipStream_t stream) {
-  if (d == 128) {
-    if (a.tokw) hipLaunchKernelGGL((act_grad_kernel<128, 8, true>), dim3(grid), dim3(512), 0, stream, a);
-    else hipLaunchKernelGGL((act_grad_kernel<128, 8, false>), dim3(grid), dim3(512), 0, stream, a);
-  } else {
-    if (a.tokw) hipLaunchKernelGGL((act_grad_kernel<64, 4, true>), dim3(grid), dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((act_grad_kernel<64, 4, false>), dim3(grid), dim3(256), 0, stream, a);
-  }
+// Both sides in one launch, the queries in the first q_blocks workgroups.
+template <int D, int NW>
+__global__ void __launch_bounds__(64 * NW, 2)
+act_grad_kernel(ActGradArgs queries, ActGradArgs keys, int q_blocks) {
+  __shared__ __attribute__((aligned(1024))) ActGradLds<D, NW> lds;
+  if ((int)blockIdx.x < q_blocks) act_grad_body<D, NW, true>(queries, blockIdx.x, lds);
+  else act_grad_body<D, NW, false>(keys, blockIdx.x - q_blocks, lds);
+}
+
+hipError_t launch_act_grad(const ActGradArgs& queries, const ActGradArgs& keys, int d, hipStream_t stream) {
+  const int q_blocks = queries.items_per_xcd * 8, grid = q_blocks + keys.items_per_xcd * 8;
+  if (d == 128)
+    hipLaunchKernelGGL((act_grad_kernel<128, 8>), dim3(grid), dim3(512), 0, stream, queries, keys, q_blocks);
+  else
+    hipLaunchKernelGGL((act_grad_kernel<64, 4>), dim3(grid), dim3(256), 0, stream, queries, keys, q_blocks);
   return hipGetLastError();
 }
 

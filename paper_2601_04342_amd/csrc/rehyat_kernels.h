@@ -30,8 +30,10 @@ struct StateArgs {
   int64_t kv_bh_stride; // elements between the k (and v) rows of consecutive (b, h)
   int step_n;           // > 0: one segment, rows [0, step_n) of k / v (streaming step); the
                         // frame geometry above is then unused
-  int query_segments;   // 1: segment s is the query range [q_lo, q_hi) of chunk chunk0 + s
-                        // (the sums of phi_q(q) u^T behind the gradient of the chunk state)
+  // Gradient of the chunk state (k = q, v = G): segment s is the query range [q_lo, q_hi) of chunk chunk0 + s, and the
+  // sums are those of (tok_scale phi_q(q)) G^T and tok_weight phi_q(q).
+  const float* tok_scale;    // [BH, N] 1 / den
+  const float* tok_weight;   // [BH, N] w
 };
 
 // pieces in flight per thread of the prefix and suffix passes
@@ -136,18 +138,19 @@ struct StepStateArgs {
 // With G = dL/dy_hat, den_i = n^S_i + n^L_i, u_i = G_i / den_i, w_i = -(G_i . y_i) / den_i:
 //   dL/dPhi_q,i = S_t u_i + w_i z_t                 (queries of chunk t)
 //   dL/dS_t = sum_i Phi_q,i u_i^T ,  dL/dz_t = sum_i w_i Phi_q,i
+// (u is never written: the kernels read G, and scale Phi and S_t G by 1 / den)
 //   dL/dPhi_k,j = R_tau v_j + r_tau ,  R_tau = sum_{t > tau} dL/dS_t ,  r_tau likewise,
 // for keys j of segment tau = [s_lo(tau), s_lo(tau+1)) (Eq. 13: they belong to the linear
 // set of every later chunk), followed by the backward pass of the two-layer map.
 // =================================================================================
 
-// u = bf16(G / den), w = -(G . y) / den per token
+// 1 / den and w = -(G . y) / den per token
 struct PrepArgs {
   const bf16_t* g;    // [tokens, d] upstream gradient
   const bf16_t* y;    // [tokens, d] forward output
   const float* nS;    // [tokens]
   const float* nL;    // [tokens]
-  bf16_t* u;          // [tokens, d]
+  float* inv;         // [tokens]
   float* tokw;        // [tokens]
   const bf16_t* w2_q; // [H, 2d, 2d]
   const bf16_t* w2_k;
@@ -158,21 +161,21 @@ struct PrepArgs {
 
 // R_tau, r_tau: sums over the later chunks of the chunk-state gradients
 struct SuffixArgs {
-  const float* s_part;  // [BH, s_slots, elems]: segment s, piece p at slot s*s_nsplit + p; S^T part used
-  const float* z_part;  // [(bh*n_seg + s)*z_nsplit + p][dp]
+  const float* part;    // [BH, part_slots, elems]: segment s, piece p at slot s*nsplit + p
   bf16_t* Rt;           // [BH, slots, d, dp]  (transposed, as the forward chunk states)
   float* r;             // [BH, slots, dp]
-  int BH, n_seg, s_nsplit, s_slots, z_nsplit, slots;
+  int BH, n_seg, nsplit, part_slots, slots;
   int elems, s_elems, dp;
 };
 
 // Activation gradients of one side (queries or keys): recomputes U = relu(W1 x + b1) and
-// psi = relu(W2 U + b2), forms dPhi = M vec + tokw * zv for the token's segment, and writes
+// psi = relu(W2 U + b2), forms dPhi = inv * M vec + tokw * zv for the token's segment, and writes
 // dpsi = dPhi * dphi/dpsi token-major for the weight-gradient kernels.
 struct ActGradArgs {
   const bf16_t* x;      // [BH, N, d]  q or k
-  const bf16_t* vec;    // [BH, N, d]  u (query side) or v (key side)
-  const float* tokw;    // [BH, N] per-token weight of zv (query side); unused on the key side (1)
+  const bf16_t* vec;    // [BH, N, d]  G (query side) or v (key side)
+  const float* tokw;    // [BH, N] per-token weight of zv and scale of M vec (query side); unused on the key side (1)
+  const float* inv;
   const bf16_t* w1;
   const float* b1;
   const bf16_t* w2;
@@ -182,9 +185,8 @@ struct ActGradArgs {
   bf16_t* dpsi;         // [BH, N, dp]
   uint32_t* signs;      // [BH, 2d/32, N]  which hidden units of a token are positive, 32 to a word
   float* db2_part;      // [n_items, dp]  sum over the item's tokens of dpsi
-  float* dz_part;       // [n_items, dp]  sum of tokw * phi (query side), or null
   int H, T, HW, chunk, overlap;
-  int query_side;       // 1: segment s = queries of chunk s+1, slot s+1; 0: key segment s, slot s
+                        // query side: segment s = queries of chunk s+1, slot s+1; else key segment s, slot s
   int n_seg, nsplit, slots, n_items, items_per_xcd;
 };
 
@@ -228,8 +230,9 @@ struct ReduceJobs {
 };
 
 hipError_t launch_prep(const PrepArgs& a, hipStream_t stream);
-hipError_t launch_suffix(const SuffixArgs& a, hipStream_t stream);
-hipError_t launch_act_grad(const ActGradArgs& a, int d, int grid, hipStream_t stream);
+// with `prefix`: that pass in the same launch
+hipError_t launch_suffix(const SuffixArgs& a, const PrefixArgs* prefix, hipStream_t stream);
+hipError_t launch_act_grad(const ActGradArgs& queries, const ActGradArgs& keys, int d, hipStream_t stream);
 hipError_t launch_weight_grad(const WeightGradArgs& a, int d, int grid, hipStream_t stream);
 // pieces of the tokens (`tiles` of 64) of each side and (b, h) in that launch: n2 for dW2, n1 for dW1
 void weight_pieces(int BH, int64_t tiles, int d, int* n2, int* n1);
@@ -237,6 +240,8 @@ hipError_t launch_reduce(const ReduceJobs& jobs, hipStream_t stream);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t stream);
 
 hipError_t launch_state(const StateArgs& a, int d, int grid, hipStream_t stream);
+// the sums behind the gradient of the chunk states (tok_scale, tok_weight set); with `keys`: those sums in the same launch
+hipError_t launch_state_gradient(const StateArgs& queries, const StateArgs* keys, int d, hipStream_t stream);
 hipError_t launch_prefix(const PrefixArgs& a, hipStream_t stream);
 // `split`: attn_split_kernel, otherwise attn_kernel.  `absorb` (streaming step with split only):
 // chunk-state pieces run by further workgroups of the launch.

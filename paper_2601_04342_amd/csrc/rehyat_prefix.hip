@@ -14,9 +14,7 @@ namespace rehyat {
 // Pieces a thread loads before it sums them (in rehyat_kernels.h: also the suffix pass).  One
 // piece at a time, each load behind the store of the state before it, the 20 segments of the 480p shape
 // took 12.0 us at 47 MB, with eight loads ahead it takes 10.3 (suffix pass 18.1 and 12.5).
-__global__ void __launch_bounds__(256)
-prefix_kernel(PrefixArgs a) {
-  const int bh = blockIdx.y;
+__device__ __forceinline__ void prefix_body(const PrefixArgs& a, int bh) {
   const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (idx >= a.elems) return;
   const float* part = a.partial + (int64_t)bh * a.partial_slots * a.elems + idx;
@@ -55,6 +53,60 @@ prefix_kernel(PrefixArgs a) {
     }
   }
   *reinterpret_cast<f32x4*>(carry) = acc;
+}
+
+// ------------------------------------------------------------------------------------
+// R_tau = sum over segments s >= tau of the chunk-state gradient partials (segment s holds
+// dL/dS of chunk s+1, so this is the sum over chunks t > tau), r_tau likewise.  Each thread
+// owns four consecutive elements and walks the segments from the last to the first (fixed
+// order: bit-reproducible).
+// ------------------------------------------------------------------------------------
+__device__ __forceinline__ void suffix_body(const SuffixArgs& a, int bh) {
+  const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;
+  if (idx >= a.elems) return;
+  const bool is_s = idx < a.s_elems;
+  f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+  // pieces of segment c, then its sum goes out; kScanDepth pieces are loaded ahead of their sums
+  const int ns = a.nsplit;
+  const float* const base = a.part + (int64_t)bh * a.part_slots * a.elems + idx;
+  int lc = a.n_seg - 1, lsp = 0;   // next piece to load
+  int c = a.n_seg - 1, sp = 0;     // next piece to add
+  while (c >= 0) {
+    f32x4 x[kScanDepth];
+#pragma unroll
+    for (int u = 0; u < kScanDepth; ++u) {
+      if (lc >= 0) {
+        x[u] = *reinterpret_cast<const f32x4*>(base + ((int64_t)lc * ns + lsp) * a.elems);
+        if (++lsp == ns) {
+          lsp = 0;
+          --lc;
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < kScanDepth; ++u) {
+      if (c < 0) break;
+      acc += x[u];
+      if (++sp < ns) continue;
+      if (is_s) {
+        u32x2 pk;
+        pk[0] = pack_bf16(acc[0], acc[1]);
+        pk[1] = pack_bf16(acc[2], acc[3]);
+        *reinterpret_cast<u32x2*>(a.Rt + ((int64_t)bh * a.slots + c) * a.s_elems + idx) = pk;
+      } else {
+        *reinterpret_cast<f32x4*>(a.r + ((int64_t)bh * a.slots + c) * a.dp + idx - a.s_elems) = acc;
+      }
+      sp = 0;
+      --c;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256) prefix_kernel(PrefixArgs a) { prefix_body(a, blockIdx.y); }
+// The suffix pass of n (batch, head)s, and behind them a prefix pass.
+__global__ void __launch_bounds__(256) suffix_kernel(SuffixArgs a, PrefixArgs prefix, int n) {
+  if ((int)blockIdx.y < n) suffix_body(a, blockIdx.y);
+  else prefix_body(prefix, blockIdx.y - n);
 }
 
 // Walks `total` pieces in order: add(load(0)), add(load(1)), ...  kScanDepth loads are in flight all the time; load(m) is
@@ -253,6 +305,14 @@ hipError_t launch_zero_state(float* S, float* z, int BH, int d, int dprime, hipS
 hipError_t launch_prefix(const PrefixArgs& a, hipStream_t stream) {
   dim3 grid((a.elems / 4 + 255) / 256, a.BH);
   hipLaunchKernelGGL(prefix_kernel, grid, dim3(256), 0, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_suffix(const SuffixArgs& a, const PrefixArgs* prefix, hipStream_t stream) {
+  PrefixArgs p{};
+  if (prefix) p = *prefix;
+  dim3 grid((a.elems / 4 + 255) / 256, prefix ? 2 * a.BH : a.BH);
+  hipLaunchKernelGGL(suffix_kernel, grid, dim3(256), 0, stream, a, p, a.BH);
   return hipGetLastError();
 }
 

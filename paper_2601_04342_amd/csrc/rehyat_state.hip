@@ -37,11 +37,35 @@ state_kernel(StateArgs a) {
   state_body<D, NW>(a, blockIdx.x, XV, Us, B1s);
 }
 
+// The sums behind the gradient of the chunk states (phi_q of the queries, G), and of the keys in the same launch where
+// both are wanted at once: the first k_blocks workgroups.
+template <int D, int NW>
+__global__ void __launch_bounds__(64 * NW, 2)
+state_gradient_kernel(StateArgs queries, StateArgs keys, int k_blocks) {
+  __shared__ __attribute__((aligned(1024))) char XV[StateLds<D>::XV];
+  __shared__ __attribute__((aligned(1024))) char Us[StateLds<D>::US];
+  __shared__ __attribute__((aligned(256))) float B1s[StateLds<D>::B1 / 4];
+  __shared__ __attribute__((aligned(256))) float Tok[4 * 64];
+  if ((int)blockIdx.x < k_blocks) state_body<D, NW>(keys, blockIdx.x, XV, Us, B1s);
+  else state_body<D, NW, true>(queries, blockIdx.x - k_blocks, XV, Us, B1s, Tok);
+}
+
 hipError_t launch_state(const StateArgs& a, int d, int grid, hipStream_t stream) {
   if (d == 128) {
     hipLaunchKernelGGL((state_kernel<128, 8>), dim3(grid), dim3(512), 0, stream, a);
   } else {
     hipLaunchKernelGGL((state_kernel<64, 4>), dim3(grid), dim3(256), 0, stream, a);
+  }
+  return hipGetLastError();
+}
+
+hipError_t launch_state_gradient(const StateArgs& queries, const StateArgs* keys, int d, hipStream_t stream) {
+  const int k_blocks = keys ? keys->items_per_xcd * 8 : 0, grid = k_blocks + queries.items_per_xcd * 8;
+  const StateArgs& k = keys ? *keys : queries;
+  if (d == 128) {
+    hipLaunchKernelGGL((state_gradient_kernel<128, 8>), dim3(grid), dim3(512), 0, stream, queries, k, k_blocks);
+  } else {
+    hipLaunchKernelGGL((state_gradient_kernel<64, 4>), dim3(grid), dim3(256), 0, stream, queries, k, k_blocks);
   }
   return hipGetLastError();
 }

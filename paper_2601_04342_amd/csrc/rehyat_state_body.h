@@ -17,9 +17,11 @@ struct StateLds {
 };
 
 // The work of workgroup `block`; XV, Us and B1s as in StateLds, 1024-, 1024- and 256-byte aligned.
-// Waves beyond NW must not enter.
-template <int D, int NW>
-__device__ __forceinline__ void state_body(const StateArgs& a, int block, char* XV, char* Us, float* B1s) {
+// Waves beyond NW must not enter.  QUERIES: query segments with a scale and a weight per token (StateArgs), which
+// arrive with the tiles: Tok holds 64 of both for two tiles.
+template <int D, int NW, bool QUERIES = false>
+__device__ __forceinline__ void state_body(const StateArgs& a, int block, char* XV, char* Us, float* B1s,
+                                           float* Tok = nullptr) {
   constexpr int HID = 2 * D, DP = 2 * D;
   constexpr int KS = D / 16;      // k-steps across the head dimension
   constexpr int KS2 = HID / 16;   // k-steps across the hidden layer
@@ -58,7 +60,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
     const int tt = a.chunk0 + seg;
     const int nchunks = num_chunks(a.T, a.chunk);
     const ChunkRange cr = chunk_range(a.T, a.HW, a.chunk, a.overlap, tt);
-    if (a.query_segments) {   // the queries of chunk tt (gradient of the chunk state)
+    if (QUERIES) {   // the queries of chunk tt
       seg_lo = cr.q_lo;
       seg_hi = cr.q_hi;
     } else {
@@ -98,6 +100,17 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
   const uint32_t k_lds = lds_address(XV), v_lds = k_lds + 2 * TB;
   using R = RangeTiles<2 * D, NW>;
   const R range(n_tokens, wave, lane);
+  // scales by even waves, weights by odd ones
+  const int64_t tok0 = QUERIES ? (int64_t)bh * a.T * a.HW + lo : 0;
+  const u32x4 Tr = make_rsrc_words(QUERIES ? (const void*)((wave & 1 ? a.tok_weight : a.tok_scale) + tok0) : (const void*)Kb);
+  const uint32_t tok_lds = QUERIES ? __builtin_amdgcn_readfirstlane(lds_address(Tok) + 256 * (wave & 1)) : 0u;
+  auto load_tok = [&](int it) {
+    const int row = n_tokens < 64 ? 0 : 64 * it < n_tokens - 64 ? 64 * it : n_tokens - 64;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    direct_load_4(Tr, 4 * (ln < n_tokens ? ln : n_tokens - 1), __builtin_amdgcn_readfirstlane(4 * row),
+                  tok_lds + (it & 1) * 512);
+  };
   const int uwbase = r * UPAD + wave * 64 + 8 * g;   // write: token r, units 32w + 8i + 4g .. +3 at + 16 i
   const int urbase = r * UPAD + 16 * g;              // read: A fragment of token r, k-step ks at + 32 ks
 
@@ -159,6 +172,7 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
     range.fill(Kr, 0, k_lds);
     range.fill(Vr, 0, v_lds);
     if (n_tiles > 1) range.fill(Kr, 64, k_lds + TB);
+    if (QUERIES) load_tok(0);
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * R::LPT) : "memory");   // W2; two tiles at least are younger
   } else {
     wave_loads_done();
@@ -211,6 +225,16 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
     static_assert(S0 + 3 < NM - PD, "U is stored before the barrier that publishes it");
     f32x16 u[2], ps[2];
     uint32_t fb[2][8];   // phi as operands
+    constexpr int kPairs = 8 / LS;       // element pairs per slot
+    f32x2 scale[kPairs], weight[kPairs]; // of a slot's tokens, read one slot ahead
+    auto read_tok = [&](int tb, int i) {
+#pragma unroll
+      for (int n = 0; n < kPairs; ++n) {
+        const float* const p = Tok + (it & 1) * 128 + 32 * tb + 8 * ((i + n) >> 1) + 4 * g + 2 * ((i + n) & 1);
+        scale[n] = *reinterpret_cast<const f32x2*>(p);
+        weight[n] = *reinterpret_cast<const f32x2*>(p + 64);
+      }
+    };
     float part[2] = {0.f, 0.f};
     auto fetch = [&](auto MC) {   // the LDS operand of product m
       constexpr int m = decltype(MC)::value;
@@ -252,16 +276,19 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
         x[j] = fmaxf(ps[tb][e] + b2v, 0.f);
         if (squared) x[j] = x[j] * x[j];
         if (!MORE && (unsigned)(32 * tb + 8 * (e >> 2) + 4 * g + (e & 3) - first) >= (unsigned)count) x[j] *= kAgain;
+        if (QUERIES) {
+          part[tb] += weight[i % kPairs][j] * x[j];
+          x[j] *= scale[i % kPairs][j];
+        }
       }
       fb[tb][i] = pack_bf16(x[0], x[1]);
       // The normaliser sums the features as rounded for the product: with unrounded ones S and z
       // weigh a token differently, and for keys that resemble each other the differences add up
       // (equal keys: error of y against fp64 up to 30 % larger, of gradients 40 %).
-      part[tb] = sum_pair<kDotSum>(fb[tb][i], part[tb]);
+      if (!QUERIES) part[tb] = sum_pair<kDotSum>(fb[tb][i], part[tb]);
       pin(part[tb]);
       pin(fb[tb][i]);
     };
-    constexpr int kPairs = 8 / LS;   // element pairs per slot
     static_for<NM>([&](auto MC) {
       constexpr int m = decltype(MC)::value;
       if constexpr (MORE && m == NM - PD) wait_loads_and_barrier<0>();
@@ -272,11 +299,13 @@ __device__ __forceinline__ void state_body(const StateArgs& a, int block, char* 
         if constexpr (i < R::LPT) range.template load<i>(Kd, ks, kd);
         else range.template load<i - R::LPT>(Vr, vs, vd);
       }
+      if constexpr (QUERIES && MORE && m == 4 * R::LPT + 1) load_tok(it + 1);
       static_for<2>([&](auto TBC) {
         constexpr int tb = decltype(TBC)::value;
         constexpr int p = m - (tb ? F1 : F0) - 2;   // two products behind the group's last one
         if constexpr (p >= 0 && kPairs * p < 8)
           static_for<kPairs>([&](auto JC) { phi(TBC, std::integral_constant<int, kPairs * p + decltype(JC)::value>{}); });
+        if constexpr (QUERIES && p >= -1 && kPairs * (p + 1) < 8) read_tok(tb, kPairs * (p + 1));
         constexpr int q = m - (tb ? S0 : P1) - 2;   // two quads of units per slot: done before the barrier
         if constexpr (MORE && q >= 0 && q < 2) {
           u_store(u[tb], 2 * q, Ud, tb);

@@ -196,6 +196,31 @@ def test_p320_chunk3_overlap1_gradients():
     full_size_case("p320_t21_c3", 1, 4)
 
 
+@pytest.mark.parametrize("case", [
+    # the sums of both sides share their launches here, tokens carry a scale and a weight; pieces of fewer than 64
+    # tokens, of 64, one more, ragged; an empty key segment (the window of chunk 1 still holds everything)
+    (1, 2, 4, 37, 128, 1, 0), (1, 1, 3, 64, 128, 1, 0), (2, 1, 5, 65, 64, 1, 1), (1, 3, 4, 129, 128, 1, 1),
+    (1, 1, 9, 200, 64, 2, 0),
+])
+def test_saved_forward_pass_at_the_edges_of_tiles(case):
+    B, H, T, HW, d, chunk, overlap = case
+    q, k, v = synth.make_qkv(B, H, T * HW, d, seed=sum(case))
+    phi = synth.make_phi(H, d, seed=sum(case) + 1, gain=4.0)
+    G = synth.make_grad_out(B, H, T * HW, d, seed=sum(case) + 2)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    dG = G.to("cuda", torch.bfloat16).contiguous()
+    out, comps = binding.forward(dq, dk, dv, dphi, T, HW, chunk, overlap=overlap, debug=True)
+    need = binding.phi_backward_workspace_bytes(B, H, T, HW, d, chunk)
+    ws = torch.full((need + 4096,), 255, device="cuda", dtype=torch.uint8)   # NaN wherever nothing was written
+    grads, _ = binding.phi_backward(dq, dk, dv, dphi, dG, T, HW, chunk, overlap=overlap, workspace=ws[:need],
+                                    saved=(out, comps["nS"], comps["nL"]))
+    torch.cuda.synchronize()
+    assert (ws[need:] == 255).all()
+    ref, _ = ograd.phi_backward(*parity.oracle_inputs(q, k, v, phi), G.double().numpy(), T, HW, chunk, overlap,
+                                hidden_round="bf16")
+    check_grads(grads, ref, str(case))
+
+
 def test_saved_forward_pass_gives_the_same_gradients():
     """The distillation step has already run the forward pass: handing its output and the
     components n^S, n^L to the gradient call skips the attention kernel there."""
