@@ -756,16 +756,22 @@ attn_kernel(AttnArgs a) {
   }
 
   // =========================== merge (Eq. 5) ================================
-  if (row >= cr.q_hi) return;
+  // The rows leave by way of LDS, whole lines to an instruction: two buffers that the last step does not read hold a
+  // block for each wave.  In the accumulator's pieces (8 bytes a lane, 16 of each of 32 rows per instruction) one layer
+  // at 480p took 531.1 us, now 521.6; 720p 1,981 and 1,965, 24 heads of 64 at 480p 497.5 and 491.6; with the split
+  // kernel 2 x 3 heads of 333-token frames 42.5 and 41.5, 21 streaming steps at 480p 1,197 and 1,176.
+  if (!wave_live) return;
+  const bool valid = row < cr.q_hi;
   const int64_t o = (int64_t)bh * N + row;
-  if (g == 0 && a.dbg_nL) a.dbg_nL[o] = nL * dscale;
+  if (valid && g == 0 && a.dbg_nL) a.dbg_nL[o] = nL * dscale;
   const float inv = 1.0f / (nS + nL);
+  char* const rows_out = tiles + (D == 128 ? 0 : 2) * TB + wave * (32 * 2 * D);
 #pragma unroll
   for (int db = 0; db < DB; ++db) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int col = 32 * db + 8 * i + 4 * g;
-      if (a.dbg_aL) {
+      if (valid && a.dbg_aL) {
         f32x4 as = {0.f, 0.f, 0.f, 0.f};
         if (a.dbg_aS) as = *reinterpret_cast<const f32x4*>(a.dbg_aS + o * D + col);
         f32x4 x;
@@ -782,8 +788,15 @@ attn_kernel(AttnArgs a) {
       u32x2 pk;
       pk[0] = pack_bf16(rows.O[db][4 * i] * inv, rows.O[db][4 * i + 1] * inv);
       pk[1] = pack_bf16(rows.O[db][4 * i + 2] * inv, rows.O[db][4 * i + 3] * inv);
-      *reinterpret_cast<u32x2*>(Og + row * D + col) = pk;
+      *reinterpret_cast<u32x2*>(rows_out + tile_off<2 * D>(r, col)) = pk;
     }
+  }
+#pragma unroll
+  for (int n = 0; n < D / 16; ++n) {
+    constexpr int CPR = D / 8;   // chunks of 16 bytes per row
+    const int rw = n * (64 / CPR) + lane / CPR, c = lane % CPR;
+    const u32x4 x = *reinterpret_cast<const u32x4*>(rows_out + tile_off<2 * D>(rw, 8 * c));
+    if (qw0 + rw < cr.q_hi) *reinterpret_cast<u32x4*>(Og + (qw0 + rw) * D + 8 * c) = x;
   }
 }
 
@@ -1183,33 +1196,47 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
     for (int n = 0; n < 2 * DB; ++n)
       *slot(qg, (2 * DB) * other + n) = quad((DB / 2) * other + (n >> 2), n & 3);
     lds_barrier();
-    if (row >= cr.q_hi) return;
+    if (!wave_live) return;
+    const bool valid = row < cr.q_hi;
     const float nLt = xlin[0][32 * qg + r] + xlin[1][32 * qg + r];
     const int64_t o = (int64_t)bh * N + row;
-    if (own == 0 && g == 0 && a.dbg_nL) a.dbg_nL[o] = nLt * dscale;
+    if (valid && own == 0 && g == 0 && a.dbg_nL) a.dbg_nL[o] = nLt * dscale;
     const float inv = 1.0f / (nS + nLt);
+    // the rows leave by way of the slots that this wave has read, as in attn_kernel
+    f32x4 y[2 * DB];
+#pragma unroll
+    for (int n = 0; n < 2 * DB; ++n) y[n] = quad((DB / 2) * own + (n >> 2), n & 3) + *slot(qg, (2 * DB) * own + n);
+    char* const rows_out = tiles + (qg * (4 * DB) + (2 * DB) * own) * 1024;
+    constexpr int CPR = D / 16;                               // chunks of 16 bytes per half row
+    auto place = [](int rw, int c) { return rw * D + ((c ^ ((D == 128 ? rw : rw >> 1) % CPR)) << 4); };
 #pragma unroll
     for (int n = 0; n < 2 * DB; ++n) {
       const int db = (DB / 2) * own + (n >> 2), i = n & 3;
       const int col = 32 * db + 8 * i + 4 * g;
-      const f32x4 y = quad(db, i) + *slot(qg, (2 * DB) * own + n);
-      if (a.dbg_aL) {
+      if (valid && a.dbg_aL) {
         f32x4 as = {0.f, 0.f, 0.f, 0.f};
         if (a.dbg_aS) as = *reinterpret_cast<const f32x4*>(a.dbg_aS + o * D + col);
         f32x4 x;
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
           // rounded as when a^S was stored, so that an empty linear set reports exactly zero
-          float t = y[jj] * dscale;
+          float t = y[n][jj] * dscale;
           asm volatile("" : "+v"(t));
           x[jj] = t - as[jj];
         }
         *reinterpret_cast<f32x4*>(a.dbg_aL + o * D + col) = x;
       }
       u32x2 pk;
-      pk[0] = pack_bf16(y[0] * inv, y[1] * inv);
-      pk[1] = pack_bf16(y[2] * inv, y[3] * inv);
-      *reinterpret_cast<u32x2*>(Og + row * D + col) = pk;
+      pk[0] = pack_bf16(y[n][0] * inv, y[n][1] * inv);
+      pk[1] = pack_bf16(y[n][2] * inv, y[n][3] * inv);
+      *reinterpret_cast<u32x2*>(rows_out + place(r, n) + 8 * g) = pk;   // chunk n of the half row
+    }
+    const int64_t q_w = q0 + 32 * qg;
+#pragma unroll
+    for (int n = 0; n < CPR / 2; ++n) {
+      const int rw = n * (64 / CPR) + lane / CPR, c = lane % CPR;
+      const u32x4 x = *reinterpret_cast<const u32x4*>(rows_out + place(rw, c));
+      if (q_w + rw < cr.q_hi) *reinterpret_cast<u32x4*>(Og + (q_w + rw) * D + (D / 2) * own + 8 * c) = x;
     }
   };
   if (kg == 0) finish(std::integral_constant<int, 0>{});
