@@ -796,7 +796,7 @@ attn_kernel(AttnArgs a) {
     constexpr int CPR = D / 8;   // chunks of 16 bytes per row
     const int rw = n * (64 / CPR) + lane / CPR, c = lane % CPR;
     const u32x4 x = *reinterpret_cast<const u32x4*>(rows_out + tile_off<2 * D>(rw, 8 * c));
-    if (qw0 + rw < cr.q_hi) *reinterpret_cast<u32x4*>(Og + (qw0 + rw) * D + 8 * c) = x;
+    if (qw0 + rw < cr.q_hi) store_through(Og + q0 * D, (32 * wave + rw) * (2 * D) + 16 * c, x);
   }
 }
 
@@ -1236,7 +1236,7 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
     for (int n = 0; n < CPR / 2; ++n) {
       const int rw = n * (64 / CPR) + lane / CPR, c = lane % CPR;
       const u32x4 x = *reinterpret_cast<const u32x4*>(rows_out + place(rw, c));
-      if (q_w + rw < cr.q_hi) *reinterpret_cast<u32x4*>(Og + (q_w + rw) * D + (D / 2) * own + 8 * c) = x;
+      if (q_w + rw < cr.q_hi) store_through(Og + q0 * D, (32 * qg + rw) * (2 * D) + D * own + 16 * c, x);
     }
   };
   if (kg == 0) finish(std::integral_constant<int, 0>{});
