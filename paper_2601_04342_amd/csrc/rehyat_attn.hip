@@ -615,13 +615,18 @@ template <int D>
 __global__ void __launch_bounds__(64 * kAttnNW, D == 64 ? 3 : 2)
 attn_kernel(AttnArgs a) {
   using C = AttnShape<D>;
-  constexpr int HID = C::HID, DP = C::DP, KS = C::KS, DB = C::DB, NT = 64 * kAttnNW;
+  constexpr int HID = C::HID, DP = C::DP, KS = C::KS, DB = C::DB;
   constexpr int TB = C::TILE_BYTES;
   // four tile buffers; phase S: K tiles in 0/1, V tiles in 2/3
   __shared__ __attribute__((aligned(1024))) char tiles[4 * TB];
-  __shared__ __attribute__((aligned(16))) float sb1[HID];
-  __shared__ __attribute__((aligned(16))) float sb2[DP];
-  __shared__ __attribute__((aligned(16))) float sz[DP];
+  // the queries on their way into registers (d = 128: half of them, the others in the V buffer of tile 1, so that two
+  // workgroups have 80 KB each); then the per-head vectors of phase L
+  constexpr int QB = 32 * 2 * D;   // a wave's queries
+  __shared__ __attribute__((aligned(1024))) char spare[kAttnNW * QB - (D == 128 ? TB : 0)];
+  static_assert(sizeof(spare) >= (HID + 2 * DP) * sizeof(float), "the vectors fit");
+  float* const sb1 = reinterpret_cast<float*>(spare);
+  float* const sb2 = sb1 + HID;
+  float* const sz = sb2 + DP;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -653,12 +658,13 @@ attn_kernel(AttnArgs a) {
   // a wave whose 32 queries all lie beyond the chunk (last query tile) still moves its
   // share of every tile and meets every barrier, but computes nothing
   const bool wave_live = qw0 < cr.q_hi;
+  // They come by way of a block of LDS of the wave's own, whole rows to an instruction.  As operands, 32 bytes of each of 32
+  // rows to one, one layer at 480p took 505.8 us, now 503.7; 720p 1,949 and 1,939.5, 24 heads of 64 at 480p 476.7 and 474.2.
   bf16x8 Qr[KS];
-  {
-    const bf16_t* p = Qg + (row < cr.q_hi ? row : cr.q_hi - 1) * D + 8 * g;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) Qr[ks] = *reinterpret_cast<const bf16x8*>(p + 16 * ks);
-  }
+  char* const q_block = D == 64 ? spare + wave * QB : wave < 2 ? tiles + 3 * TB + wave * QB : spare + (wave - 2) * QB;
+  if (wave_live)
+    tile_load_asm<2 * D, QB, 1>(make_rsrc_words(Qg + qw0 * D), 0, __builtin_amdgcn_readfirstlane(lds_address(q_block)), 0, lane,
+                                (int)(cr.q_hi - qw0 < 32 ? cr.q_hi - qw0 : 32));
   SoftmaxRows<D> rows;
 #pragma unroll
   for (int db = 0; db < DB; ++db) rows.O[db] = f32x16{};
@@ -672,18 +678,21 @@ attn_kernel(AttnArgs a) {
     const SoftmaxTiles<D> st{make_rsrc_words(Kg + cr.s_lo * D), make_rsrc_words(Vg + cr.s_lo * D), lds_address(tiles),
                              tiles, RangeTiles<2 * D, 4>(n_keys, wave, lane), 0, 1, (n_keys + 63) / 64, lane};
     st.request();
-    // per-head vectors of phase L (their loads complete long before phase L, whose
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * SoftmaxTiles<D>::LPT) : "memory");   // the queries; K and V are younger
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) Qr[ks] = staged_fragment<2 * D>(q_block, lane, ks);
+    wait_loads_and_barrier<0>();
+    // per-head vectors of phase L, 64 values to an instruction (the tile loop waits for them, long before phase L, whose
     // counted waits must see tile loads only)
     if (has_linear) {
-      const float* zt = a.state_z + ((int64_t)bh * a.state_slots + tc) * DP;
-      for (int i = tid; i < HID; i += NT) sb1[i] = a.b1_q[(int64_t)h * HID + i];
-      for (int i = tid; i < DP; i += NT) {
-        sb2[i] = a.b2_q[(int64_t)h * DP + i];
-        sz[i] = zt[i];
+      const float* const zt = a.state_z + ((int64_t)bh * a.state_slots + tc) * DP;
+      for (int i = wave; i < 3 * (DP / 64); i += kAttnNW) {
+        const int which = i / (DP / 64), part = i % (DP / 64);
+        const float* const src = which == 0 ? a.b1_q + (int64_t)h * HID : which == 1 ? a.b2_q + (int64_t)h * DP : zt;
+        direct_load_4(make_rsrc_words(src), 4 * lane, 256 * part,
+                      __builtin_amdgcn_readfirstlane(lds_address(spare) + 256 * i));
       }
     }
-    settle(Qr);
-    wait_loads_and_barrier<0>();   // also publishes the bias vectors
     auto none = [](auto) {};
     if (wave_live) st.template run<true, false, 0>(Qr, rows, a.scale_log2e, false, none);
     else st.template run<false, false, 0>(Qr, rows, a.scale_log2e, false, none);
