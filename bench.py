@@ -31,7 +31,7 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, published
 # Anything else reports null.
 ATTN_TRAFFIC = {
     # 2.0 x 174,820 KiB + 1.0 x 98,280 KiB (profiles/wan480p_hbm_traffic_pmc.md)
-    ("wan480p", "forward", 307): 458_700_000,
+    ("wan480p", "forward", 308): 446_500_000,
 }
 
 

@@ -725,7 +725,7 @@ Slots slots_that_fit(int B, int H, int d, int dp, size_t bytes) {
 
 extern "C" {
 
-int rehyat_version(void) { return 307; }
+int rehyat_version(void) { return 308; }
 
 const char* rehyat_status_string(int code) {
   switch (code) {

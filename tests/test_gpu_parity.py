@@ -340,3 +340,14 @@ def test_last_chunk_in_a_window_of_its_own():
     finally:
         binding.profile_enable(False)
     assert launches["state"] == 1 and launches["attn"] == 2, launches
+
+
+@pytest.mark.parametrize("case", [
+    # one launch forms the total and the states: more pieces than loads in flight, fewer, one; the second of two windows
+    # of chunks finds the total that the first left; frames in several pieces; windows clipped at both ends
+    (1, 2, 40, 24, 64, 1, 0), (1, 1, 33, 20, 128, 1, 2), (1, 1, 2, 70, 64, 1, 0), (1, 2, 9, 300, 128, 2, 1),
+    (2, 1, 17, 40, 128, 3, 0),
+])
+def test_bidirectional_totals_and_windows(case):
+    B, H, T, HW, d, chunk, overlap = case
+    parity.run_case(B, H, T, HW, d, chunk, overlap, 0, 3.0, seed=sum(case), causal=False)
