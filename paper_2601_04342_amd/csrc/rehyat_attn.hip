@@ -364,54 +364,45 @@ struct LinStep {
   int younger;        // tiles that may still be in flight when the step starts
   int n_issue;        // tiles issued after the step's barrier
   int kind[2], idx[2], buf[2];
-  int buf_w, buf_s;   // buffers read by the step (W1 or W2 tile; S tile)
+  int buf_w;          // buffer read by the step
 };
 enum { kW1 = 0, kW2 = 1, kS = 2 };
 
+// Steps of the hidden layer (a W1 tile each); then W2 of feature block p lies in w_buf(p), S of pair p of blocks in
+// s_buf(p).
 template <int D>
 struct LinSched;
 template <>
-struct LinSched<128> {   // 4 W1 steps, then 8 feature-block steps
+struct LinSched<128> {
   static constexpr int NPRO = 4;
-  static constexpr LinStep pro(int i) { return LinStep{0, 1, {kW1, 0}, {i, 0}, {i, 0}, 0, 0}; }
+  static constexpr LinStep pro(int i) { return LinStep{0, 1, {kW1, 0}, {i, 0}, {i, 0}, 0}; }
   static constexpr LinStep step(int st) {
     switch (st) {
-      case 0: return LinStep{3, 0, {0, 0}, {0, 0}, {0, 0}, 0, 0};
-      case 1: return LinStep{2, 1, {kS, 0}, {0, 0}, {0, 0}, 1, 0};
-      case 2: return LinStep{2, 1, {kW2, 0}, {0, 0}, {1, 0}, 2, 0};
-      case 3: return LinStep{2, 1, {kW2, 0}, {1, 0}, {2, 0}, 3, 0};
-      case 4: return LinStep{1, 1, {kS, 0}, {1, 0}, {3, 0}, 1, 0};
-      case 5: return LinStep{1, 1, {kW2, 0}, {2, 0}, {1, 0}, 2, 0};
-      case 6: return LinStep{0, 2, {kW2, kS}, {3, 2}, {2, 0}, 1, 3};
-      case 7: return LinStep{1, 1, {kW2, 0}, {4, 0}, {1, 0}, 2, 3};
-      case 8: return LinStep{0, 2, {kW2, kS}, {5, 3}, {2, 3}, 1, 0};
-      case 9: return LinStep{1, 1, {kW2, 0}, {6, 0}, {1, 0}, 2, 0};
-      case 10: return LinStep{0, 1, {kW2, 0}, {7, 0}, {2, 0}, 1, 3};
-      default: return LinStep{0, 0, {0, 0}, {0, 0}, {0, 0}, 2, 3};
+      case 0: return LinStep{3, 0, {0, 0}, {0, 0}, {0, 0}, 0};
+      case 1: return LinStep{2, 1, {kS, 0}, {0, 0}, {0, 0}, 1};
+      case 2: return LinStep{2, 1, {kW2, 0}, {0, 0}, {1, 0}, 2};
+      default: return LinStep{2, 1, {kW2, 0}, {1, 0}, {2, 0}, 3};
     }
   }
+  static constexpr int w_buf(int p) { return 1 + (p & 1); }
+  static constexpr int s_buf(int p) { return p & 1 ? 3 : 0; }
 };
 template <>
-struct LinSched<64> {    // 2 W1 steps, then 4 feature-block steps
+struct LinSched<64> {
   static constexpr int NPRO = 4;
   static constexpr LinStep pro(int i) {
     switch (i) {
-      case 0: return LinStep{0, 1, {kW1, 0}, {0, 0}, {0, 0}, 0, 0};
-      case 1: return LinStep{0, 1, {kW1, 0}, {1, 0}, {1, 0}, 0, 0};
-      case 2: return LinStep{0, 1, {kS, 0}, {0, 0}, {2, 0}, 0, 0};
-      default: return LinStep{0, 1, {kW2, 0}, {0, 0}, {3, 0}, 0, 0};
+      case 0: return LinStep{0, 1, {kW1, 0}, {0, 0}, {0, 0}, 0};
+      case 1: return LinStep{0, 1, {kW1, 0}, {1, 0}, {1, 0}, 0};
+      case 2: return LinStep{0, 1, {kS, 0}, {0, 0}, {2, 0}, 0};
+      default: return LinStep{0, 1, {kW2, 0}, {0, 0}, {3, 0}, 0};
     }
   }
   static constexpr LinStep step(int st) {
-    switch (st) {
-      case 0: return LinStep{3, 0, {0, 0}, {0, 0}, {0, 0}, 0, 0};
-      case 1: return LinStep{2, 1, {kW2, 0}, {1, 0}, {0, 0}, 1, 0};
-      case 2: return LinStep{1, 1, {kS, 0}, {1, 0}, {1, 0}, 3, 2};
-      case 3: return LinStep{1, 1, {kW2, 0}, {2, 0}, {3, 0}, 0, 2};
-      case 4: return LinStep{0, 1, {kW2, 0}, {3, 0}, {0, 0}, 3, 1};
-      default: return LinStep{0, 0, {0, 0}, {0, 0}, {0, 0}, 0, 1};
-    }
+    return st == 0 ? LinStep{3, 0, {0, 0}, {0, 0}, {0, 0}, 0} : LinStep{2, 1, {kW2, 0}, {1, 0}, {0, 0}, 1};
   }
+  static constexpr int w_buf(int p) { return p & 1 ? 0 : 3; }
+  static constexpr int s_buf(int p) { return p & 1 ? 1 : 2; }
 };
 
 // Requests of phase L tiles by NW waves (kinds as above), one per-lane offset for all blocks a wave
@@ -504,54 +495,106 @@ __device__ __forceinline__ void lin_hidden(const char* Ws, int wbase, const floa
   finish(NB - 1, 1);
 }
 
-// One block of 32 features: psi^T = relu(W2 U^T + b2), phi (SQ: squared), its share of n^L, and
-// O += S^T phi with the block's 32 columns of the S tile (the upper half of its 64 if `upper`).
-template <int D, bool SQ>
-__device__ __forceinline__ float lin_features(const char* Ws, const char* Ss, int wbase, int sbase, bool upper,
-                                              const float* bias, const float* z, int g, float lin_scale,
-                                              const bf16x8 (&Ub)[D / 8], f32x16 (&O)[D / 32]) {
-  constexpr int KS = D / 16, DB = D / 32, NW = 2 * KS, NM = NW + 2 * DB;
-  f32x16 acc, zv;
-  bf16x8 fr[kAhead], fb[2];
-  float part = 0.f;
-  asm volatile("" : "+v"(wbase), "+v"(sbase));
-  if (upper) sbase ^= 64;
+// NB feature blocks of a wave as one stream of products: psi of block 0, then psi of p + 1 and O += S^T phi of p in turn.
+// phi of a block lies under the psi of the next one (of the last: under the read-out of the one before it), and operands
+// are read kAhead products ahead, across the blocks.
+template <int D, int NB>
+struct LinStream {
+  static constexpr int KS = D / 16, DB = D / 32, NW = 2 * KS, NS = 2 * DB, BL = NW + NS, NM = NB * BL;
+  bool psi;
+  int p, n;   // product n of block p
+  static constexpr LinStream at(int m) {
+    if (m < NW) return LinStream{true, 0, m};
+    const int q = (m - NW) / BL, n = (m - NW) % BL;
+    return q == NB - 1 ? LinStream{false, q, n} : n < NW ? LinStream{true, q + 1, n} : LinStream{false, q, n - NW};
+  }
+  static constexpr int psi_at(int p) { return p == 0 ? 0 : NW + (p - 1) * BL; }
+  static constexpr int s_at(int p) { return NW + p * BL + (p == NB - 1 ? 0 : NW); }
+  static constexpr int phi_at(int p, int i) {   // the slot of pair i of phi of block p
+    return p < NB - 1 ? psi_at(p + 1) + 2 + i * (NW - 4) / 8 : s_at(NB - 2) + 1 + i * (NS - 1) / 8;
+  }
+};
+// Block p: W2 tile at tiles + w_off(p), S tile at s_off(p) (its upper 32 features if s_half(p)), bias and z at
+// + VSTRIDE p.  `before(m)` stands in front of product m (barriers), `behind(m)` behind it (requests); with LIVE false they
+// are all that is left.  Returns the wave's share of n^L, added to nL block by block.
+template <int D, int NB, int VSTRIDE, bool LIVE, typename WOff, typename SOff, typename SHalf, typename Before, typename Behind>
+__device__ __forceinline__ float lin_stream(const char* tiles, int wk, int sk, const float* bias, const float* z, int g,
+                                            float lin_scale, const bf16x8 (&Ub)[D / 8], f32x16 (&O)[D / 32], float nL,
+                                            WOff w_off, SOff s_off, SHalf s_half, Before before, Behind behind) {
+  using L = LinStream<D, NB>;
+  constexpr int KS = L::KS, DB = L::DB;
+  f32x16 ps[2];
+  // z of four features and of the next four; at d = 64 pairs of three quads stand in one slot
+  constexpr int ZR = D == 128 ? 2 : 4;
+  f32x4 zq[ZR];
+  uint32_t fb[2][8];
+  float part[2];
+  bf16x8 fr[kAhead];
   auto fetch = [&](auto MC) {
     constexpr int m = decltype(MC)::value;
-    if constexpr (m < NW)
-      fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(Ws + (wbase ^ (32 * (m % KS))) + (m / KS) * (32 * 2 * D));
-    else if constexpr (m < NM)
-      fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(Ss + (sbase ^ (32 * ((m - NW) / DB))) + (m - NW) % DB * (32 * 128));
-  };
-  lin_vector(bias, g, acc);
-  static_for<kAhead>([&](auto MC) { fetch(MC); });
-  static_for<NM>([&](auto MC) {
-    constexpr int m = decltype(MC)::value;
-    if constexpr (m < NW) {
-      acc = mfma(fr[m % kAhead], Ub[m], acc);
-    } else {
-      if constexpr (m == NW) {
-        // the read-out rounds phi to bf16 (MFMA operand); the normaliser takes it unrounded: the
-        // 256 rounding errors of a row have random signs and relative size 2^-9, far below the
-        // bar on n^L, and the rounding costs two instructions per feature
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          float x = fmaxf(acc[e], 0.f);
-          if (SQ) x = x * x;
-          x = x * lin_scale;
-          acc[e] = x;
-          part += x * zv[e];
-        }
-        fb[0] = acc_to_operand(acc, 0);
-        fb[1] = acc_to_operand(acc, 1);
-      }
-      O[(m - NW) % DB] = mfma(fr[m % kAhead], fb[(m - NW) / DB], O[(m - NW) % DB]);
+    if constexpr (m < L::NM) {
+      constexpr L t = L::at(m);
+      if constexpr (t.psi)
+        fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(tiles + w_off(t.p) + (wk ^ (32 * (t.n % KS))) + t.n / KS * (32 * 2 * D));
+      else
+        fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(tiles + s_off(t.p) + (sk ^ (64 * s_half(t.p)) ^ (32 * (t.n / DB))) +
+                                                          t.n % DB * (32 * 128));
     }
-    if constexpr (m == NW - 6) lin_vector(z, g, zv);
-    fetch(std::integral_constant<int, m + kAhead>{});
+  };
+  auto phi = [&](auto PC, auto IC) {   // elements 2i, 2i+1
+    constexpr int p = decltype(PC)::value, i = decltype(IC)::value;
+    if constexpr (i == 0) part[p & 1] = 0.f;
+    float x[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      // the read-out rounds phi to bf16 (MFMA operand); the normaliser takes it unrounded: the
+      // 256 rounding errors of a row have random signs and relative size 2^-9, far below the
+      // bar on n^L, and the rounding costs two instructions per feature
+      x[j] = fmaxf(ps[p & 1][2 * i + j], 0.f);
+      if (p >= NB / 2) x[j] = x[j] * x[j];
+      x[j] = x[j] * lin_scale;
+      part[p & 1] += x[j] * zq[(i >> 1) % ZR][2 * (i & 1) + j];
+    }
+    fb[p & 1][i] = pack_bf16(x[0], x[1]);
+    if constexpr (i == 7) nL += part[p & 1];
+  };
+  if constexpr (LIVE) {
+    lin_vector(bias, g, ps[0]);
+    static_for<kAhead>([&](auto MC) { fetch(MC); });
+  }
+  static_for<L::NM>([&](auto MC) {
+    constexpr int m = decltype(MC)::value;
+    constexpr L t = L::at(m);
+    if constexpr (t.n == 0) asm volatile("" : "+v"(wk), "+v"(sk));   // offsets of a block are not kept for the next
+    before(MC);
+    if constexpr (LIVE) {
+      if constexpr (t.psi) {
+        ps[t.p & 1] = mfma(fr[m % kAhead], Ub[t.n], ps[t.p & 1]);
+      } else {
+        constexpr int ks = t.n / DB, db = t.n % DB, b = t.p & 1;
+        const u32x4 w = {fb[b][4 * ks], fb[b][4 * ks + 1], fb[b][4 * ks + 2], fb[b][4 * ks + 3]};
+        O[db] = mfma(fr[m % kAhead], __builtin_bit_cast(bf16x8, w), O[db]);
+      }
+      fetch(std::integral_constant<int, m + kAhead>{});
+    }
+    behind(MC);
+    if constexpr (LIVE) {
+      static_for<NB>([&](auto PC) {
+        constexpr int p = decltype(PC)::value;
+        if constexpr (p >= 1 && m + 2 == L::psi_at(p)) lin_vector(bias + VSTRIDE * p, g, ps[p & 1]);
+        static_for<4>([&](auto QC) {   // four features of accumulator registers 4q .. 4q + 3, a slot ahead
+          constexpr int q = decltype(QC)::value;
+          if constexpr (m + 1 == L::phi_at(p, 2 * q))
+            zq[q % ZR] = *reinterpret_cast<const f32x4*>(z + VSTRIDE * p + 16 * (q >> 1) + 8 * g + 4 * (q & 1));
+        });
+        static_for<8>([&](auto IC) {
+          if constexpr (L::phi_at(p, decltype(IC)::value) == m) phi(PC, IC);
+        });
+      });
+    }
     __builtin_amdgcn_sched_barrier(0);
   });
-  return part;
+  return nL;
 }
 
 template <int D, int ST>
@@ -747,20 +790,47 @@ attn_kernel(AttnArgs a) {
     const float lin_scale = __builtin_amdgcn_exp2f((a.stab_mode == 1 ? 0.f : rows.max) - rows.ref);
     const int wbase = lin_row_base<D>(lane), sbase = tile_off<128>(r, 8 * g);
     bf16x8 Ub[HID / 16];  // U^T = relu(W1 Q^T + b1) as B operands, natural k order
-    static_for<NW1 + NPB>([&](auto ST) {
+    static_for<NW1>([&](auto ST) {
       constexpr int st = decltype(ST)::value;
       constexpr LinStep sd = LinStepC<D, st>::value;
       wait_loads_and_barrier<sd.younger * LinTiles<D, kAttnNW>::LPT>();
       issue_all(LinStepC<D, st>{});
       if (!wave_live) return;  // this step of this wave only (the lambda is one step)
-      if constexpr (st < NW1) {
-        lin_hidden<D, 2, 0, 0>(tiles + sd.buf_w * TB, wbase, sb1 + 64 * st, g, Qr, Ub + 4 * st, [](auto) {});
-      } else {
-        constexpr int pb = st - NW1;
-        nL += lin_features<D, (32 * pb >= DP / 2)>(tiles + sd.buf_w * TB, tiles + sd.buf_s * TB, wbase, sbase, pb & 1,
-                                                   sb2 + 32 * pb, sz + 32 * pb, g, lin_scale, Ub, rows.O);
-      }
+      lin_hidden<D, 2, 0, 0>(tiles + sd.buf_w * TB, wbase, sb1 + 64 * st, g, Qr, Ub + 4 * st, [](auto) {});
     });
+    // The feature blocks, W2 of even and odd blocks and S of even and odd pairs of blocks in two buffers each.  A barrier stands
+    // kAhead products before the end of psi 0 and of the read-outs: W2 of the block after the next has landed there, its
+    // predecessor's buffer is free for W2 of the one behind that, and after an odd block that of its S.
+    // As one stream because phi and the first fragments of a block stood between its products and the next block's: block by
+    // block one layer at 480p took 498.1 us, now 489.8; 720p 1,857 and 1,838, 101 frames of 600 tokens 1,193 and 1,179, two
+    // 480p layers with three-frame chunks 1,968 and 1,955, 24 heads of 64 at 480p 472.7 and 471.1; the same results bit for bit.
+    using L = LinStream<D, NPB>;
+    using T = LinTiles<D, kAttnNW>;
+    auto stream = [&](auto LIVEC) {
+      auto before = [&](auto MC) {
+        constexpr int m = decltype(MC)::value;
+        static_for<NPB - 1>([&](auto PC) {   // at the end of block p - 1's read-out (p = 0: of psi 0)
+          constexpr int p = decltype(PC)::value;
+          if constexpr (m + kAhead == L::psi_at(p + 1)) wait_loads_and_barrier<0>();
+        });
+      };
+      auto behind = [&](auto MC) {
+        constexpr int m = decltype(MC)::value;
+        if constexpr (m % 2 == 1 && m / 2 < T::LPT) lt.load(kS, 1, SCH::s_buf(1), m / 2);
+        static_for<NPB - 2>([&](auto PC) {   // behind the barrier at the end of block p - 1: W2 of block p + 2, S of a pair
+          constexpr int p = decltype(PC)::value, i = m - (L::psi_at(p + 1) - kAhead) - 1;
+          if constexpr (i >= 0 && i % 2 == 0 && i / 2 < T::LPT) lt.load(kW2, p + 2, SCH::w_buf(p + 2), i / 2);
+          if constexpr (p >= 2 && p % 2 == 0 && p / 2 + 1 < NPB / 2 && i >= 0 && i % 2 == 1 && i / 2 < T::LPT)
+            lt.load(kS, p / 2 + 1, SCH::s_buf(p / 2 + 1), i / 2);
+        });
+      };
+      nL = lin_stream<D, NPB, 32, decltype(LIVEC)::value>(
+          tiles, wbase, sbase, sb2, sz, g, lin_scale, Ub, rows.O, nL, [](int p) { return SCH::w_buf(p) * TB; },
+          [](int p) { return SCH::s_buf(p / 2) * TB; }, [](int p) { return p & 1; }, before, behind);
+    };
+    wait_loads_and_barrier<0>();   // W2 of blocks 0 and 1 and the first S; W1 is dead
+    if (wave_live) stream(std::true_type{});
+    else stream(std::false_type{});
     nL = half_swap_sum(nL);
   }
 
@@ -1085,110 +1155,33 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
     place_s(0);
     wait_loads_and_barrier<0>();   // sets 0 and 1; W1 is dead
     request_s(1);
-    // The wave's feature blocks 2p + kg, p = 0 .. NP-1, as one stream of products: psi of block 0, then psi of p + 1 and
-    // O += S^T phi of p in turn.  phi of a block lies under the psi of the next one (of the last: under the read-out of the
-    // one before it).  Both waves of a SIMD are in the same phase here, so that neither fills the other's gaps:
-    // block by block, each fragment read and each phi in the way of the products, it took 5.0 us (streaming step
-    // 5.7), now 3.3 (4.2).
+    // The wave's feature blocks are 2p + kg, p = 0 .. NP-1.  Both waves of a SIMD are in the same phase here, so that
+    // neither fills the other's gaps: block by block, each fragment read and each phi in the way of the products, it took
+    // 5.0 us (streaming step 5.7), as one stream 3.3 (4.2).
     // Barriers stand where tiles have to have landed, kAhead products before their own.
     auto stream = [&](auto LIVEC) {
-      constexpr bool LIVE = decltype(LIVEC)::value;
-      constexpr int NW = 2 * KS, NS = 2 * DB, BL = NW + NS, NM = NP * BL;
-      struct Slot {
-        bool psi;
-        int p, n;   // product n of block p
-      };
-      auto slot = [](int m) {
-        if (m < NW) return Slot{true, 0, m};
-        const int q = (m - NW) / BL, n = (m - NW) % BL;
-        return q == NP - 1 ? Slot{false, q, n} : n < NW ? Slot{true, q + 1, n} : Slot{false, q, n - NW};
-      };
-      auto psi_at = [](int p) { return p == 0 ? 0 : NW + (p - 1) * BL; };
-      auto s_at = [](int p) { return NW + p * BL + (p == NP - 1 ? 0 : NW); };
-      // the slot of pair i of phi of block p
-      auto phi_at = [=](int p, int i) {
-        return p < NP - 1 ? psi_at(p + 1) + 2 + i * (NW - 4) / 8 : s_at(NP - 2) + 1 + i * (NS - 1) / 8;
-      };
-      int wk = wbase + kg * TB, sk = sbase ^ (kg * 64);
-      f32x16 ps[2];
-      // z of four features and of the next four; at d = 64 pairs of three quads stand in one slot
-      constexpr int ZR = D == 128 ? 2 : 4;
-      f32x4 zq[ZR];
-      uint32_t fb[2][8];
-      float part[2];
-      bf16x8 fr[kAhead];
-      auto fetch = [&](auto MC) {
+      using L = LinStream<D, NP>;
+      auto before = [&](auto MC) {
         constexpr int m = decltype(MC)::value;
-        if constexpr (m < NM) {
-          constexpr Slot t = slot(m);
-          if constexpr (t.psi)
-            fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(tiles + w2_buf(t.p) * TB + (wk ^ (32 * (t.n % KS))) +
-                                                              t.n / KS * (32 * 2 * D));
-          else
-            fr[m % kAhead] = *reinterpret_cast<const bf16x8*>(tiles + s_buf(t.p) * TB + (sk ^ (32 * (t.n / DB))) +
-                                                              t.n % DB * (32 * 128));
-        }
-      };
-      auto phi = [&](auto PC, auto IC) {   // elements 2i, 2i+1; n^L takes them unrounded, as in lin_features
-        constexpr int p = decltype(PC)::value, i = decltype(IC)::value;
-        if constexpr (i == 0) part[p & 1] = 0.f;
-        float x[2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          x[j] = fmaxf(ps[p & 1][2 * i + j], 0.f);
-          if (64 * p >= DP / 2) x[j] = x[j] * x[j];
-          x[j] = x[j] * lin_scale;
-          part[p & 1] += x[j] * zq[(i >> 1) % ZR][2 * (i & 1) + j];
-        }
-        fb[p & 1][i] = pack_bf16(x[0], x[1]);
-        if constexpr (i == 7) nL += part[p & 1];
-      };
-      if constexpr (LIVE) {
-        lin_vector(sb2 + 32 * kg, g, ps[0]);
-        static_for<kAhead>([&](auto MC) { fetch(MC); });
-      }
-      static_for<NM>([&](auto MC) {
-        constexpr int m = decltype(MC)::value;
-        constexpr Slot t = slot(m);
-        if constexpr (t.n == 0) asm volatile("" : "+v"(wk), "+v"(sk));   // offsets of a block are not kept for the next
         // before the psi of blocks 2 and 3, and before the last read-out, where everything but its S is dead
         static_for<NP>([&](auto PC) {
           constexpr int p = decltype(PC)::value;
-          if constexpr (p >= 1 && m + kAhead == (p + 1 < NP ? psi_at(p + 1) : s_at(p))) {
+          if constexpr (p >= 1 && m + kAhead == (p + 1 < NP ? L::psi_at(p + 1) : L::s_at(p))) {
             place_s(p);
             wait_loads_and_barrier<0>();
             if constexpr (p + 1 < NP) request_s(p + 1);
           }
         });
-        if constexpr (LIVE) {
-          if constexpr (t.psi) {
-            ps[t.p & 1] = mfma(fr[m % kAhead], Ub[t.n], ps[t.p & 1]);
-          } else {
-            constexpr int ks = t.n / DB, db = t.n % DB, b = t.p & 1;
-            const u32x4 w = {fb[b][4 * ks], fb[b][4 * ks + 1], fb[b][4 * ks + 2], fb[b][4 * ks + 3]};
-            rows.O[db] = mfma(fr[m % kAhead], __builtin_bit_cast(bf16x8, w), rows.O[db]);
-          }
-          fetch(std::integral_constant<int, m + kAhead>{});
-        }
+      };
+      auto behind = [&](auto MC) {
+        constexpr int m = decltype(MC)::value;
         if constexpr (m % 2 == 1 && m / 2 < N3) load_second(std::integral_constant<int, m / 2>{});
-        constexpr int b1 = NP > 2 ? psi_at(2) - kAhead : 0, i4 = (m - b1 - 1) / 2;
+        constexpr int b1 = NP > 2 ? L::psi_at(2) - kAhead : 0, i4 = (m - b1 - 1) / 2;
         if constexpr (NP > 2 && m > b1 && (m - b1) % 2 == 1 && i4 < N4) load_third(std::integral_constant<int, i4>{});
-        if constexpr (LIVE) {
-          static_for<NP>([&](auto PC) {
-            constexpr int p = decltype(PC)::value;
-            if constexpr (p >= 1 && m + 2 == psi_at(p)) lin_vector(sb2 + 32 * (2 * p + kg), g, ps[p & 1]);
-            static_for<4>([&](auto QC) {   // four features of accumulator registers 4q .. 4q + 3, a slot ahead
-              constexpr int q = decltype(QC)::value;
-              if constexpr (m + 1 == phi_at(p, 2 * q))
-                zq[q % ZR] = *reinterpret_cast<const f32x4*>(sz + 32 * (2 * p + kg) + 16 * (q >> 1) + 8 * g + 4 * (q & 1));
-            });
-            static_for<8>([&](auto IC) {
-              if constexpr (phi_at(p, decltype(IC)::value) == m) phi(PC, IC);
-            });
-          });
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      });
+      };
+      nL = lin_stream<D, NP, 64, decltype(LIVEC)::value>(
+          tiles, wbase + kg * TB, sbase ^ (kg * 64), sb2 + 32 * kg, sz + 32 * kg, g, lin_scale, Ub, rows.O, nL,
+          [=](int p) { return w2_buf(p) * TB; }, [=](int p) { return s_buf(p) * TB; }, [](int) { return 0; }, before, behind);
     };
     if (wave_live) stream(std::true_type{});
     else stream(std::false_type{});
