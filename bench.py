@@ -30,8 +30,8 @@ PEAK_BF16_TFLOPS = 2500.0   # MI355X dense bf16 MFMA, published
 # and valid for the library version they were measured on (profiles/*_hbm_traffic_pmc.md).
 # Anything else reports null.
 ATTN_TRAFFIC = {
-    # 2.0 x 174,820 KiB + 1.0 x 98,280 KiB (profiles/wan480p_hbm_traffic_pmc.md)
-    ("wan480p", "forward", 308): 446_500_000,
+    # 2.0 x 169,119 KiB + 1.0 x 98,280 KiB (profiles/wan480p_hbm_traffic_pmc.md)
+    ("wan480p", "forward", 308): 447_000_000,
 }
 
 
