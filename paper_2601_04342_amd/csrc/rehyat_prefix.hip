@@ -14,7 +14,8 @@ namespace rehyat {
 // Pieces a thread loads before it sums them (in rehyat_kernels.h: also the suffix pass).  One
 // piece at a time, each load behind the store of the state before it, the 20 segments of the 480p shape
 // took 12.0 us at 47 MB, with eight loads ahead it takes 10.3 (suffix pass 18.1 and 12.5).
-__device__ __forceinline__ void prefix_body(const PrefixArgs& a, int bh) {
+__device__ __forceinline__ void prefix_body(const PrefixArgs& a) {
+  const int bh = blockIdx.y;
   const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (idx >= a.elems) return;
   const float* part = a.partial + (int64_t)bh * a.partial_slots * a.elems + idx;
@@ -61,7 +62,8 @@ __device__ __forceinline__ void prefix_body(const PrefixArgs& a, int bh) {
 // owns four consecutive elements and walks the segments from the last to the first (fixed
 // order: bit-reproducible).
 // ------------------------------------------------------------------------------------
-__device__ __forceinline__ void suffix_body(const SuffixArgs& a, int bh) {
+__device__ __forceinline__ void suffix_body(const SuffixArgs& a) {
+  const int bh = blockIdx.y;
   const int idx = (blockIdx.x * 256 + threadIdx.x) * 4;
   if (idx >= a.elems) return;
   const bool is_s = idx < a.s_elems;
@@ -102,11 +104,12 @@ __device__ __forceinline__ void suffix_body(const SuffixArgs& a, int bh) {
   }
 }
 
-__global__ void __launch_bounds__(256) prefix_kernel(PrefixArgs a) { prefix_body(a, blockIdx.y); }
-// The suffix pass of n (batch, head)s, and behind them a prefix pass.
-__global__ void __launch_bounds__(256) suffix_kernel(SuffixArgs a, PrefixArgs prefix, int n) {
-  if ((int)blockIdx.y < n) suffix_body(a, blockIdx.y);
-  else prefix_body(prefix, blockIdx.y - n);
+__global__ void __launch_bounds__(256) prefix_kernel(PrefixArgs a) { prefix_body(a); }
+// The suffix pass, and with a second layer of blocks a prefix pass.  (Layers, not rows behind the rows of the first: a
+// grid holds 65,535 rows, and a call may have as many (batch, head)s.)
+__global__ void __launch_bounds__(256) suffix_kernel(SuffixArgs a, PrefixArgs prefix) {
+  if (blockIdx.z == 0) suffix_body(a);
+  else prefix_body(prefix);
 }
 
 // Walks `total` pieces in order: add(load(0)), add(load(1)), ...  kScanDepth loads are in flight all the time; load(m) is
@@ -311,8 +314,8 @@ hipError_t launch_prefix(const PrefixArgs& a, hipStream_t stream) {
 hipError_t launch_suffix(const SuffixArgs& a, const PrefixArgs* prefix, hipStream_t stream) {
   PrefixArgs p{};
   if (prefix) p = *prefix;
-  dim3 grid((a.elems / 4 + 255) / 256, prefix ? 2 * a.BH : a.BH);
-  hipLaunchKernelGGL(suffix_kernel, grid, dim3(256), 0, stream, a, p, a.BH);
+  dim3 grid((a.elems / 4 + 255) / 256, a.BH, prefix ? 2 : 1);
+  hipLaunchKernelGGL(suffix_kernel, grid, dim3(256), 0, stream, a, p);
   return hipGetLastError();
 }
 

@@ -269,3 +269,27 @@ def test_bias_gradient_sums_stay_short(d, H, HW):
     worst = (err / want.abs().clamp_min(1e-300)).max().item()
     print(f"   worst relative error {worst:.2e}, bound {bound:.2e}", flush=True)
     assert (err <= bound * want.abs()).all(), worst
+
+
+def test_saved_forward_pass_of_more_batch_heads_than_half_a_grid():
+    """32,800 (batch, head)s: the two passes that share a launch would need more rows of blocks than the 65,535 of a
+    grid if one lay behind the other.  Three batch elements carry the same G, the others none, so every entry is three
+    times that of a call with one, up to the two additions (each rounds to 2^-24)."""
+    B, H, T, HW, d = 16400, 2, 2, 1, 64
+    N = T * HW
+    q, k, v = synth.make_qkv(1, H, N, d, seed=31)
+    phi = synth.make_phi(H, d, seed=32, gain=4.0)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    dG = synth.make_grad_out(1, H, N, d, seed=33).to("cuda", torch.bfloat16)
+    out, comps = binding.forward(dq, dk, dv, dphi, T, HW, 1, debug=True)
+    one, _ = binding.phi_backward(dq, dk, dv, dphi, dG, T, HW, 1, saved=(out, comps["nS"], comps["nL"]))
+    many = lambda t: t.expand(B, *t.shape[1:]).contiguous()
+    G = torch.zeros_like(many(dG))
+    G[[0, B // 2, B - 1]] = dG[0]
+    got, _ = binding.phi_backward(many(dq), many(dk), many(dv), dphi, G, T, HW, 1,
+                                  saved=(many(out), many(comps["nS"]), many(comps["nL"])))
+    torch.cuda.synchronize()
+    for n in synth.PHI_NAMES:
+        want = 3.0 * one[n].double()
+        assert (want != 0).any(), n
+        assert ((got[n].double() - want).abs() <= 2.0 ** -22 * want.abs()).all(), n
