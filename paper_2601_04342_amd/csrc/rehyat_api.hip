@@ -549,10 +549,21 @@ struct BwdPlan {
   int nc, n_seg;     // chunks; segments (= chunks that read a state)
   int nsplit;        // pieces per segment (state and activation-gradient kernels)
   int n2, n1;        // pieces per side and (b, h) of the weight gradients: dW2, dW1
+  bool both_sums;    // the partial sums of queries and keys have an area each
+  bool both_acts;    // 1 / den and w outlive the activation gradients of the queries
   size_t yhat, nS, nL, q_part, inv, tokw, Rt, rz, w2t, total;
   size_t dpsi[2], signs[2], p_w2[2], p_w1[2], p_b2[2];   // queries, keys
 };
 
+// Areas that are not needed at the same time lie over each other (all launches are on one stream): the partial sums of
+// the weight gradients over the states and R, which the activation gradients read last, and those over y_hat, n^S, n^L.
+// One after the other, queries before keys, the sides share what is left: one area of chunk-state sums, and 1 / den and w
+// where the signs of the keys will be.  Launches that the sides share need more at once, and are taken where the total
+// is no larger than that and an area for the sums of dL/dz (what buffers were sized for when nothing was shared): the sums
+// of one side or of both lie over the activation gradients then, which come later.
+// 480p at 12 heads of 128: 479 MB, one after the other 498.  Where segments are a few dozen tokens the sums are larger
+// than the activation gradients, and there is one area of them (22 heads, 93 frames of 16 tokens 553 MB, one after the other
+// 590; with two 831).
 BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   BwdPlan P;
   const int dp = 2 * d, hid = 2 * d;
@@ -561,45 +572,66 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   P.n_seg = P.nc > 1 ? P.nc - 1 : 1;
   P.nsplit = choose_cut((int)BH, P.n_seg, P.n_seg, (int64_t)chunk * HW, 0, d, kMaxSplit * P.nc, P.n_seg).nsplit;
   P.sl = Slots{P.n_seg * P.nsplit, P.nc};
-  P.F = ws_layout(B, H, d, dp, P.sl);
   weight_pieces((int)BH, (int64_t)((N + 63) / 64), d, &P.n2, &P.n1);
-  // Areas that are not needed at the same time lie over each other (all launches are on one stream): the partial
-  // sums of the weight gradients over the states and R, which the activation gradients read last, and the
-  // activation gradients over y_hat, n^S, n^L and the partial sums of dL/dS_t.  480p at 12 heads of 128: 501 MB, with
-  // areas of their own 683.
-  size_t off = 0;
-  auto take = [&](size_t bytes) {
-    const size_t o = off;
-    off += align256(bytes);
-    return o;
+  const size_t elems = (size_t)d * dp + dp, token_floats = BH * N * sizeof(float);
+  const size_t sums = align256(BH * P.sl.partial * elems * sizeof(float));
+  // sums_early: the first area of sums, too, lies over the activation gradients
+  auto lay_out = [&](bool both_sums, bool sums_early, bool both_acts) {
+    size_t off = 0;
+    auto take = [&](size_t bytes) {
+      const size_t o = off;
+      off += align256(bytes);
+      return o;
+    };
+    P.both_sums = both_sums;
+    P.both_acts = both_acts;
+    for (int side = 0; side < 2; ++side) {
+      P.p_w2[side] = take(BH * P.n2 * (size_t)dp * hid * sizeof(float));
+      P.p_w1[side] = take(BH * P.n1 * ((size_t)d * hid + hid) * sizeof(float));
+    }
+    const size_t weight_sums = off;
+    off = 0;
+    if (!sums_early) P.F.partial = take(sums);
+    P.F.state_s = take(BH * P.nc * (size_t)d * dp * sizeof(bf16_t));
+    P.F.state_z = take(BH * P.nc * (size_t)dp * sizeof(float));
+    P.F.carry = take(BH * elems * sizeof(float));
+    P.Rt = take(BH * P.nc * (size_t)dp * d * sizeof(bf16_t));
+    P.rz = take(BH * P.nc * (size_t)dp * sizeof(float));
+    if (both_acts) {
+      P.inv = take(token_floats);
+      P.tokw = take(token_floats);
+    }
+    if (off < weight_sums) off = weight_sums;
+    size_t early = off;   // end of what lies over the activation gradients
+    auto take_early = [&](size_t bytes) {
+      const size_t o = early;
+      early += bytes;
+      return o;
+    };
+    P.yhat = P.dpsi[1] = take(BH * N * dp * sizeof(bf16_t));
+    P.dpsi[0] = take(BH * N * dp * sizeof(bf16_t));
+    const size_t signs = BH * N * (hid / 32) * sizeof(uint32_t);   // 16 bytes per token at least
+    P.nS = P.signs[1] = take(signs);
+    P.nL = P.nS + token_floats;
+    if (!both_acts) {
+      P.inv = P.nL + token_floats;
+      P.tokw = P.inv + token_floats;
+    }
+    P.signs[0] = take(signs);
+    if (sums_early) P.F.partial = take_early(sums);
+    P.q_part = both_sums ? take_early(sums) : P.F.partial;
+    if (off < early) off = early;
+    P.w2t = take(2 * (size_t)H * hid * dp * sizeof(bf16_t));
+    for (int side = 0; side < 2; ++side) P.p_b2[side] = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
+    P.F.total = P.total = off;
   };
-  for (int side = 0; side < 2; ++side) {
-    P.p_w2[side] = take(BH * P.n2 * (size_t)dp * hid * sizeof(float));
-    P.p_w1[side] = take(BH * P.n1 * ((size_t)d * hid + hid) * sizeof(float));
+  lay_out(false, false, false);
+  const size_t most = P.total + align256(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
+  for (int form = 0; form < 4; ++form) {
+    lay_out(form < 2, form % 2 == 0, true);
+    if (P.total <= most) return P;
   }
-  const size_t sums = off;
-  off = P.F.total;
-  P.Rt = take(BH * P.nc * (size_t)dp * d * sizeof(bf16_t));
-  P.rz = take(BH * P.nc * (size_t)dp * sizeof(float));
-  if (off < sums) off = sums;
-  P.yhat = P.dpsi[1] = off;
-  take(BH * N * d * sizeof(bf16_t));
-  P.q_part = off;
-  off = P.dpsi[1] + align256(BH * N * dp * sizeof(bf16_t));
-  P.dpsi[0] = take(BH * N * dp * sizeof(bf16_t));
-  const size_t q_end = P.q_part + align256(BH * P.sl.partial * ((size_t)d * dp + dp) * sizeof(float));
-  if (off < q_end) off = q_end;
-  P.nS = P.signs[1] = off;
-  take(BH * N * sizeof(float));
-  P.nL = take(BH * N * sizeof(float));
-  const size_t signs = BH * N * (hid / 32) * sizeof(uint32_t);
-  if (off < P.signs[1] + align256(signs)) off = P.signs[1] + align256(signs);
-  P.inv = take(BH * N * sizeof(float));
-  P.tokw = take(BH * N * sizeof(float));
-  P.signs[0] = take(signs);
-  P.w2t = take(2 * (size_t)H * hid * dp * sizeof(bf16_t));
-  for (int side = 0; side < 2; ++side) P.p_b2[side] = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
-  P.total = off;
+  lay_out(false, false, false);
   return P;
 }
 
@@ -932,18 +964,21 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
     return REHYAT_OK;
   }
 
-  // ---- forward pass, every chunk state kept (one window); with a saved one the chunk states wait for the sums of the
-  // query side, with which they share their launches
+  // ---- forward pass, every chunk state kept (one window); with a saved one the chunk states wait, where both sides'
+  // sums have room, for those of the query side, with which they share their launches
   const StateArgs ks = state_args(c, k, v, phi, B, H, T, HW, d, chunk, overlap, 0, P.n_seg, P.nsplit);
   const PrefixArgs pk = prefix_args(c, B, H, d, dp, nc, P.n_seg, P.nsplit, true);
   const float* nS = saved ? saved->nS : (const float*)(ws + P.nS);
   const float* nL = saved ? saved->nL : (const float*)(ws + P.nL);
+  const bool shared_sums = saved && P.both_sums;
   hipError_t e;
-  if (!saved) {
+  if (!shared_sums) {
     e = launch_state(ks, d, ks.items_per_xcd * 8, st);
     if (e != hipSuccess) return hip_fail(e, "state kernel launch");
     e = launch_prefix(pk, st);
     if (e != hipSuccess) return hip_fail(e, "prefix kernel launch");
+  }
+  if (!saved) {
     rehyat_debug_out dbg;
     dbg.m = dbg.aS = dbg.aL = nullptr;
     dbg.nS = (float*)(ws + P.nS);
@@ -982,7 +1017,7 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
   qs.chunk0 = 1;
   qs.tok_scale = (const float*)(ws + P.inv);
   qs.tok_weight = (const float*)(ws + P.tokw);
-  e = launch_state_gradient(qs, saved ? &ks : nullptr, d, st);
+  e = launch_state_gradient(qs, shared_sums ? &ks : nullptr, d, st);
   if (e != hipSuccess) return hip_fail(e, "state-gradient kernel launch");
 
   // ---- R_tau, r_tau ------------------------------------------------------------------
@@ -998,7 +1033,7 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
   sa.elems = d * dp + dp;
   sa.s_elems = d * dp;
   sa.dp = dp;
-  e = launch_suffix(sa, saved ? &pk : nullptr, st);
+  e = launch_suffix(sa, shared_sums ? &pk : nullptr, st);
   if (e != hipSuccess) return hip_fail(e, "suffix kernel launch");
 
   const ChunkRange c1 = chunk_range(T, HW, chunk, overlap, 1), cl = chunk_range(T, HW, chunk, overlap, nc - 1);
@@ -1007,8 +1042,10 @@ int rehyat_phi_backward(const void* q, const void* k, const void* v, const rehya
        (float*)grads->b2_q, c1.q_lo, N},
       {k, phi->w1_k, phi->b1_k, phi->w2_k, phi->b2_k, (float*)grads->w1_k, (float*)grads->b1_k, (float*)grads->w2_k,
        (float*)grads->b2_k, 0, cl.s_lo}};
-  e = launch_act_grad(act_grad_args(ws, P, 0, sides[0], grad_out, P.F.state_s, P.F.state_z, BH, H, T, HW, chunk, overlap),
-                      act_grad_args(ws, P, 1, sides[1], v, P.Rt, P.rz, BH, H, T, HW, chunk, overlap), d, st);
+  const ActGradArgs gq = act_grad_args(ws, P, 0, sides[0], grad_out, P.F.state_s, P.F.state_z, BH, H, T, HW, chunk, overlap);
+  const ActGradArgs gk = act_grad_args(ws, P, 1, sides[1], v, P.Rt, P.rz, BH, H, T, HW, chunk, overlap);
+  e = launch_act_grad(&gq, P.both_acts ? &gk : nullptr, d, st);
+  if (e == hipSuccess && !P.both_acts) e = launch_act_grad(nullptr, &gk, d, st);
   if (e != hipSuccess) return hip_fail(e, "activation-gradient kernel launch");
   return weight_gradients(ws, P, st, sides, B, H, T, HW, d);
 }

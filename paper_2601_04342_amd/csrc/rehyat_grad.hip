@@ -14,7 +14,8 @@
 //   prep_kernel        1 / den, w per token (HBM-bound)
 //   state_gradient_kernel   (rehyat_state.hip) dL/dS_t, dL/dz_t partial sums
 //   act_grad_kernel    recomputes U and psi, forms dPhi and dpsi per token; writes dpsi token-major, the
-//                      signs of U, and the partial sums of db2; both sides in one launch
+//                      signs of U, and the partial sums of db2; both sides in one launch where the workspace
+//                      has room (rehyat_api.hip)
 //   suffix_kernel      (rehyat_prefix.hip, before it) R_tau, r_tau from the partial sums
 //   weight_grad_kernel of both sides: dW2 = dpsi^T U over tokens (U recomputed from x);
 //                      dU = (dpsi W2) [U > 0], dW1 = dU^T x, db1 = sum dU
@@ -469,7 +470,7 @@ __device__ __forceinline__ void act_grad_body(const ActGradArgs& a, int block, A
   if (g == 0) a.db2_part[(int64_t)item * DP + unit] = db2;
 }
 
-// Both sides in one launch, the queries in the first q_blocks workgroups.
+// One side or both in one launch, the queries in the first q_blocks workgroups.
 template <int D, int NW>
 __global__ void __launch_bounds__(64 * NW, 2)
 act_grad_kernel(ActGradArgs queries, ActGradArgs keys, int q_blocks) {
@@ -478,12 +479,13 @@ act_grad_kernel(ActGradArgs queries, ActGradArgs keys, int q_blocks) {
   else act_grad_body<D, NW, false>(keys, blockIdx.x - q_blocks, lds);
 }
 
-hipError_t launch_act_grad(const ActGradArgs& queries, const ActGradArgs& keys, int d, hipStream_t stream) {
-  const int q_blocks = queries.items_per_xcd * 8, grid = q_blocks + keys.items_per_xcd * 8;
+hipError_t launch_act_grad(const ActGradArgs* queries, const ActGradArgs* keys, int d, hipStream_t stream) {
+  const int q_blocks = queries ? queries->items_per_xcd * 8 : 0, grid = q_blocks + (keys ? keys->items_per_xcd * 8 : 0);
+  const ActGradArgs &q = queries ? *queries : *keys, &k = keys ? *keys : *queries;
   if (d == 128)
-    hipLaunchKernelGGL((act_grad_kernel<128, 8>), dim3(grid), dim3(512), 0, stream, queries, keys, q_blocks);
+    hipLaunchKernelGGL((act_grad_kernel<128, 8>), dim3(grid), dim3(512), 0, stream, q, k, q_blocks);
   else
-    hipLaunchKernelGGL((act_grad_kernel<64, 4>), dim3(grid), dim3(256), 0, stream, queries, keys, q_blocks);
+    hipLaunchKernelGGL((act_grad_kernel<64, 4>), dim3(grid), dim3(256), 0, stream, q, k, q_blocks);
   return hipGetLastError();
 }
 

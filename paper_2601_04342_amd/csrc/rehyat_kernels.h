@@ -232,7 +232,8 @@ struct ReduceJobs {
 hipError_t launch_prep(const PrepArgs& a, hipStream_t stream);
 // with `prefix`: that pass in the same launch
 hipError_t launch_suffix(const SuffixArgs& a, const PrefixArgs* prefix, hipStream_t stream);
-hipError_t launch_act_grad(const ActGradArgs& queries, const ActGradArgs& keys, int d, hipStream_t stream);
+// of one side (the other null) or of both
+hipError_t launch_act_grad(const ActGradArgs* queries, const ActGradArgs* keys, int d, hipStream_t stream);
 hipError_t launch_weight_grad(const WeightGradArgs& a, int d, int grid, hipStream_t stream);
 // pieces of the tokens (`tiles` of 64) of each side and (b, h) in that launch: n2 for dW2, n1 for dW1
 void weight_pieces(int BH, int64_t tiles, int d, int* n2, int* n1);

@@ -293,3 +293,40 @@ def test_saved_forward_pass_of_more_batch_heads_than_half_a_grid():
         want = 3.0 * one[n].double()
         assert (want != 0).any(), n
         assert ((got[n].double() - want).abs() <= 2.0 ** -22 * want.abs()).all(), n
+
+
+@pytest.mark.parametrize("saved", [False, True])
+@pytest.mark.parametrize("case,copies", [
+    ((1, 1, 8, 550, 128, 2, 0), 1),     # sums of both sides over the activation gradients
+    ((1, 3, 28, 42, 64, 7, 1), 1),      # those of the queries only
+    ((2, 3, 50, 20, 64, 1, 0), 1),      # one area of sums, over the activation gradients
+    ((1, 2, 40, 29, 128, 7, 2), 1),     # beside them
+    ((1, 2, 4, 4105, 64, 1, 0), 64),    # activation gradients of one side after the other
+])
+def test_every_layout_of_the_workspace(case, copies, saved):
+    """What lies over what differs with the sizes: gradients against the oracle, in a workspace of exactly the stated size
+    that holds NaN wherever the call has not written.  Of `copies` equal batch elements two carry a G."""
+    B, H, T, HW, d, chunk, overlap = case
+    q, k, v = synth.make_qkv(B, H, T * HW, d, seed=sum(case))
+    phi = synth.make_phi(H, d, seed=sum(case) + 1, gain=4.0)
+    G = synth.make_grad_out(B, H, T * HW, d, seed=sum(case) + 2)
+    dq, dk, dv, dphi = parity.to_device(q, k, v, phi)
+    dG = G.to("cuda", torch.bfloat16).contiguous()
+    many = lambda t: t.expand(copies, *t.shape[1:]).contiguous() if copies > 1 else t
+    fwd = None
+    if saved:
+        out, comps = binding.forward(dq, dk, dv, dphi, T, HW, chunk, overlap=overlap, debug=True)
+        fwd = many(out), many(comps["nS"]), many(comps["nL"])
+    if copies > 1:
+        G = 2.0 * G
+        one, dG = dG, torch.zeros_like(many(dG))
+        dG[[0, copies - 1]] = one[0]
+    need = binding.phi_backward_workspace_bytes(B * copies, H, T, HW, d, chunk)
+    ws = torch.full((need + 4096,), 255, device="cuda", dtype=torch.uint8)
+    grads, _ = binding.phi_backward(many(dq), many(dk), many(dv), dphi, dG, T, HW, chunk, overlap=overlap,
+                                    workspace=ws[:need], saved=fwd)
+    torch.cuda.synchronize()
+    assert (ws[need:] == 255).all()
+    ref, _ = ograd.phi_backward(*parity.oracle_inputs(q, k, v, phi), G.double().numpy(), T, HW, chunk, overlap,
+                                hidden_round="bf16")
+    check_grads(grads, ref, f"{case} x {copies}, saved {saved}")
