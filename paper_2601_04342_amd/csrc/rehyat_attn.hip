@@ -513,6 +513,38 @@ struct LinStream {
   static constexpr int phi_at(int p, int i) {   // the slot of pair i of phi of block p
     return p < NB - 1 ? psi_at(p + 1) + 2 + i * (NW - 4) / 8 : s_at(NB - 2) + 1 + i * (NS - 1) / 8;
   }
+  // The other way round, what stands in slot m.  As functions: with an `if constexpr` per slot, block and pair this file took
+  // 131 s to compile, now 34, to the same instructions.
+  struct Part {
+    int p, first, n;   // elements first .. first + n - 1 of block p
+  };
+  static constexpr Part phi_in(int m) {   // pairs of phi
+    Part x{0, 0, 0};
+    for (int p = 0; p < NB; ++p)
+      for (int i = 7; i >= 0; --i)
+        if (phi_at(p, i) == m) x = Part{p, i, x.n + 1};
+    return x;
+  }
+  static constexpr Part quads_in(int m) {   // the four features that pairs 2q and 2q + 1 need, a slot ahead of them
+    Part x{0, 0, 0};
+    for (int p = 0; p < NB; ++p)
+      for (int q = 3; q >= 0; --q)
+        if (phi_at(p, 2 * q) == m + 1) x = Part{p, q, x.n + 1};
+    return x;
+  }
+  static constexpr int bias_in(int m) {   // the block whose bias is read, 0: none
+    int x = 0;
+    for (int p = 1; p < NB; ++p)
+      if (psi_at(p) == m + 2) x = p;
+    return x;
+  }
+  // kAhead products before the psi of block p: slot m lies n slots behind that of the last such p (p = 0: of none)
+  static constexpr Part since_psi(int m) {
+    Part x{0, 0, 0};
+    for (int p = 1; p < NB; ++p)
+      if (m + kAhead >= psi_at(p)) x = Part{p, 0, m + kAhead - psi_at(p)};
+    return x;
+  }
 };
 // Block p: W2 tile at tiles + w_off(p), S tile at s_off(p) (its upper 32 features if s_half(p)), bias and z at
 // + VSTRIDE p.  `before(m)` stands in front of product m (barriers), `behind(m)` behind it (requests); with LIVE false they
@@ -579,17 +611,15 @@ __device__ __forceinline__ float lin_stream(const char* tiles, int wk, int sk, c
     }
     behind(MC);
     if constexpr (LIVE) {
-      static_for<NB>([&](auto PC) {
-        constexpr int p = decltype(PC)::value;
-        if constexpr (p >= 1 && m + 2 == L::psi_at(p)) lin_vector(bias + VSTRIDE * p, g, ps[p & 1]);
-        static_for<4>([&](auto QC) {   // four features of accumulator registers 4q .. 4q + 3, a slot ahead
-          constexpr int q = decltype(QC)::value;
-          if constexpr (m + 1 == L::phi_at(p, 2 * q))
-            zq[q % ZR] = *reinterpret_cast<const f32x4*>(z + VSTRIDE * p + 16 * (q >> 1) + 8 * g + 4 * (q & 1));
-        });
-        static_for<8>([&](auto IC) {
-          if constexpr (L::phi_at(p, decltype(IC)::value) == m) phi(PC, IC);
-        });
+      constexpr int bias_p = L::bias_in(m);
+      if constexpr (bias_p > 0) lin_vector(bias + VSTRIDE * bias_p, g, ps[bias_p & 1]);
+      constexpr typename L::Part quads = L::quads_in(m), pairs = L::phi_in(m);
+      static_for<quads.n>([&](auto QC) {   // features of accumulator registers 4q .. 4q + 3
+        constexpr int q = quads.first + decltype(QC)::value;
+        zq[q % ZR] = *reinterpret_cast<const f32x4*>(z + VSTRIDE * quads.p + 16 * (q >> 1) + 8 * g + 4 * (q & 1));
+      });
+      static_for<pairs.n>([&](auto IC) {
+        phi(std::integral_constant<int, pairs.p>{}, std::integral_constant<int, pairs.first + decltype(IC)::value>{});
       });
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -808,21 +838,19 @@ attn_kernel(AttnArgs a) {
     using T = LinTiles<D, kAttnNW>;
     auto stream = [&](auto LIVEC) {
       auto before = [&](auto MC) {
-        constexpr int m = decltype(MC)::value;
-        static_for<NPB - 1>([&](auto PC) {   // at the end of block p - 1's read-out (p = 0: of psi 0)
-          constexpr int p = decltype(PC)::value;
-          if constexpr (m + kAhead == L::psi_at(p + 1)) wait_loads_and_barrier<0>();
-        });
+        constexpr typename L::Part at = L::since_psi(decltype(MC)::value);
+        if constexpr (at.p > 0 && at.n == 0) wait_loads_and_barrier<0>();
       };
       auto behind = [&](auto MC) {
         constexpr int m = decltype(MC)::value;
         if constexpr (m % 2 == 1 && m / 2 < T::LPT) lt.load(kS, 1, SCH::s_buf(1), m / 2);
-        static_for<NPB - 2>([&](auto PC) {   // behind the barrier at the end of block p - 1: W2 of block p + 2, S of a pair
-          constexpr int p = decltype(PC)::value, i = m - (L::psi_at(p + 1) - kAhead) - 1;
-          if constexpr (i >= 0 && i % 2 == 0 && i / 2 < T::LPT) lt.load(kW2, p + 2, SCH::w_buf(p + 2), i / 2);
-          if constexpr (p >= 2 && p % 2 == 0 && p / 2 + 1 < NPB / 2 && i >= 0 && i % 2 == 1 && i / 2 < T::LPT)
-            lt.load(kS, p / 2 + 1, SCH::s_buf(p / 2 + 1), i / 2);
-        });
+        // behind the barrier before psi p: W2 of block p + 1, and with an odd p S of its pair
+        constexpr typename L::Part at = L::since_psi(m);
+        constexpr int p = at.p, i = at.n - 1;
+        if constexpr (p > 0 && p + 1 < NPB && i >= 0 && i / 2 < T::LPT) {
+          if constexpr (i % 2 == 0) lt.load(kW2, p + 1, SCH::w_buf(p + 1), i / 2);
+          else if constexpr (p > 2 && p % 2 == 1) lt.load(kS, (p + 1) / 2, SCH::s_buf((p + 1) / 2), i / 2);
+        }
       };
       nL = lin_stream<D, NPB, 32, decltype(LIVEC)::value>(
           tiles, wbase, sbase, sb2, sz, g, lin_scale, Ub, rows.O, nL, [](int p) { return SCH::w_buf(p) * TB; },
@@ -1163,15 +1191,14 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
       using L = LinStream<D, NP>;
       auto before = [&](auto MC) {
         constexpr int m = decltype(MC)::value;
+        constexpr typename L::Part at = L::since_psi(m);
         // before the psi of blocks 2 and 3, and before the last read-out, where everything but its S is dead
-        static_for<NP>([&](auto PC) {
-          constexpr int p = decltype(PC)::value;
-          if constexpr (p >= 1 && m + kAhead == (p + 1 < NP ? L::psi_at(p + 1) : L::s_at(p))) {
-            place_s(p);
-            wait_loads_and_barrier<0>();
-            if constexpr (p + 1 < NP) request_s(p + 1);
-          }
-        });
+        constexpr int p = m + kAhead == L::s_at(NP - 1) ? NP - 1 : at.n == 0 ? at.p - 1 : 0;
+        if constexpr (p >= 1) {
+          place_s(p);
+          wait_loads_and_barrier<0>();
+          if constexpr (p + 1 < NP) request_s(p + 1);
+        }
       };
       auto behind = [&](auto MC) {
         constexpr int m = decltype(MC)::value;
