@@ -238,11 +238,18 @@ def _phi_struct(phi, d):
                      w2k.data_ptr(), b2k.data_ptr(), hidden, dprime, 2, 0), H
 
 
+# torch's own shortcuts past the stream object; where a torch does not have them, that object serves
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream_handle(stream):
     """The caller's stream, or the current one of the current device, as the library takes it."""
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    return stream.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None or _current_device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_current_device())
 
 
 def _check_qkv(q, k, v):

@@ -3,9 +3,11 @@ every symbol the header declares, reproduces the hand-written chunk tables
 bit-exactly and turns bad arguments into error codes before any GPU work."""
 import ctypes
 import heapq
+import importlib.util
 import os
 import re
 import subprocess
+import types
 
 import pytest
 import torch
@@ -140,6 +142,18 @@ def test_binding_rejects_wrong_tensor_types():
     q = torch.zeros(1, 2, 8, 64)
     with pytest.raises(TypeError):
         binding.forward(q, q, q, {}, 2, 4, 1)
+
+
+@pytest.mark.parametrize("missing", ["_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_without_torch_internals(missing, monkeypatch):
+    """A torch without the private shortcuts: the stream object's handle."""
+    monkeypatch.delattr(torch._C, missing, raising=False)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x1234))
+    spec = importlib.util.spec_from_file_location("binding_again", binding.__file__)
+    again = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(again)
+    assert again._stream_handle(None) == 0x1234
+    assert again._stream_handle(types.SimpleNamespace(cuda_stream=0x5678)) == 0x5678
 
 
 def test_chunk_longer_than_the_video_is_one_chunk():
