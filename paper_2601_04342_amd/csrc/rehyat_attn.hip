@@ -356,32 +356,31 @@ struct SoftmaxTiles {
 //   W2 tile pb: W2 rows [32pb, 32pb+32); tile rows 0..31 hold their first k-half
 //               (2D bytes), tile rows 32..63 the second
 //   S tile pp : S_t^T columns [64pp, 64pp+64) of all D rows, rows of 128 bytes
-// A step needs its tiles landed (at most `younger` tiles issued after them may
-// still be in flight) and, after its barrier, issues up to two further tiles
-// into buffers whose last readers have passed that barrier.
+// A step of the hidden layer needs its W1 tile landed (at most `younger` tiles issued after it may
+// still be in flight) and, after its barrier, issues at most one further tile into a buffer whose last
+// readers have passed that barrier.
 // ---------------------------------------------------------------------------
+enum { kNone = -1, kW1 = 0, kW2 = 1, kS = 2 };
 struct LinStep {
-  int younger;        // tiles that may still be in flight when the step starts
-  int n_issue;        // tiles issued after the step's barrier
-  int kind[2], idx[2], buf[2];
-  int buf_w;          // buffer read by the step
+  int younger;          // tiles that may still be in flight when the step starts
+  int buf_w;            // buffer read by the step
+  int kind, idx, buf;   // tile issued after the step's barrier
 };
-enum { kW1 = 0, kW2 = 1, kS = 2 };
 
-// Steps of the hidden layer (a W1 tile each); then W2 of feature block p lies in w_buf(p), S of pair p of blocks in
-// s_buf(p).
+// The first requests (pro) and the steps of the hidden layer, a W1 tile each; then W2 of feature block p lies in w_buf(p),
+// S of pair p of blocks in s_buf(p).
 template <int D>
 struct LinSched;
 template <>
 struct LinSched<128> {
   static constexpr int NPRO = 4;
-  static constexpr LinStep pro(int i) { return LinStep{0, 1, {kW1, 0}, {i, 0}, {i, 0}, 0}; }
+  static constexpr LinStep pro(int i) { return LinStep{0, 0, kW1, i, i}; }
   static constexpr LinStep step(int st) {
     switch (st) {
-      case 0: return LinStep{3, 0, {0, 0}, {0, 0}, {0, 0}, 0};
-      case 1: return LinStep{2, 1, {kS, 0}, {0, 0}, {0, 0}, 1};
-      case 2: return LinStep{2, 1, {kW2, 0}, {0, 0}, {1, 0}, 2};
-      default: return LinStep{2, 1, {kW2, 0}, {1, 0}, {2, 0}, 3};
+      case 0: return LinStep{3, 0, kNone, 0, 0};
+      case 1: return LinStep{2, 1, kS, 0, 0};
+      case 2: return LinStep{2, 2, kW2, 0, 1};
+      default: return LinStep{2, 3, kW2, 1, 2};
     }
   }
   static constexpr int w_buf(int p) { return 1 + (p & 1); }
@@ -392,15 +391,13 @@ struct LinSched<64> {
   static constexpr int NPRO = 4;
   static constexpr LinStep pro(int i) {
     switch (i) {
-      case 0: return LinStep{0, 1, {kW1, 0}, {0, 0}, {0, 0}, 0};
-      case 1: return LinStep{0, 1, {kW1, 0}, {1, 0}, {1, 0}, 0};
-      case 2: return LinStep{0, 1, {kS, 0}, {0, 0}, {2, 0}, 0};
-      default: return LinStep{0, 1, {kW2, 0}, {0, 0}, {3, 0}, 0};
+      case 0: return LinStep{0, 0, kW1, 0, 0};
+      case 1: return LinStep{0, 0, kW1, 1, 1};
+      case 2: return LinStep{0, 0, kS, 0, 2};
+      default: return LinStep{0, 0, kW2, 0, 3};
     }
   }
-  static constexpr LinStep step(int st) {
-    return st == 0 ? LinStep{3, 0, {0, 0}, {0, 0}, {0, 0}, 0} : LinStep{2, 1, {kW2, 0}, {1, 0}, {0, 0}, 1};
-  }
+  static constexpr LinStep step(int st) { return st == 0 ? LinStep{3, 0, kNone, 0, 0} : LinStep{2, 1, kW2, 1, 0}; }
   static constexpr int w_buf(int p) { return p & 1 ? 0 : 3; }
   static constexpr int s_buf(int p) { return p & 1 ? 1 : 2; }
 };
@@ -777,10 +774,9 @@ attn_kernel(AttnArgs a) {
   const LinTiles<D, kAttnNW> lt{make_rsrc_words(a.w1_q + (int64_t)h * HID * D), make_rsrc_words(a.w2_q + (int64_t)h * DP * HID),
                                 make_rsrc_words(a.state_s + ((int64_t)bh * a.state_slots + tc) * (int64_t)D * DP),
                                 lds_address(tiles), wave, lane};
-  auto issue_all = [&](auto SD) {   // the tiles a step (or the prologue) issues
+  auto issue = [&](auto SD) {   // the tile that a step (or the prologue) issues
     constexpr LinStep sd = decltype(SD)::value;
-    if constexpr (sd.n_issue > 0) lt.issue(sd.kind[0], sd.idx[0], sd.buf[0]);
-    if constexpr (sd.n_issue > 1) lt.issue(sd.kind[1], sd.idx[1], sd.buf[1]);
+    if constexpr (sd.kind != kNone) lt.issue(sd.kind, sd.idx, sd.buf);
   };
   // complete the softmax normaliser across the two lane halves
   // All sums are relative to 2^-ref; the components are reported relative to the
@@ -813,7 +809,7 @@ attn_kernel(AttnArgs a) {
   // =========================== phase L =====================================
   float nL = 0.f;
   if (has_linear) {
-    static_for<SCH::NPRO>([&](auto I) { issue_all(LinProC<D, decltype(I)::value>{}); });
+    static_for<SCH::NPRO>([&](auto I) { issue(LinProC<D, decltype(I)::value>{}); });
     constexpr int NW1 = HID / 64, NPB = DP / 32;
     // The softmax sums are relative to 2^-ref: with c_i = row maximum (Eq. 6, 8) the
     // linear terms weigh 2^(max - ref) beside them, with c = 0 they weigh 2^-ref.
@@ -824,7 +820,7 @@ attn_kernel(AttnArgs a) {
       constexpr int st = decltype(ST)::value;
       constexpr LinStep sd = LinStepC<D, st>::value;
       wait_loads_and_barrier<sd.younger * LinTiles<D, kAttnNW>::LPT>();
-      issue_all(LinStepC<D, st>{});
+      issue(LinStepC<D, st>{});
       if (!wave_live) return;  // this step of this wave only (the lambda is one step)
       lin_hidden<D, 2, 0, 0>(tiles + sd.buf_w * TB, wbase, sb1 + 64 * st, g, Qr, Ub + 4 * st, [](auto) {});
     });
