@@ -1261,7 +1261,12 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
     for (int n = 0; n < CPR / 2; ++n) {
       const int rw = n * (64 / CPR) + lane / CPR, c = lane % CPR;
       const u32x4 x = *reinterpret_cast<const u32x4*>(rows_out + place(rw, c));
-      if (q_w + rw < cr.q_hi) store_through(Og + q0 * D, (32 * qg + rw) * (2 * D) + D * own + 16 * c, x);
+      const int off = (32 * qg + rw) * (2 * D) + D * own + 16 * c;
+      if (q_w + rw >= cr.q_hi) continue;
+      // half a row is a whole line at d = 128 only.  Stored through at d = 64, 21 steps of 12 heads at 480p took 765 us instead
+      // of 756, of 16 heads of 1,000-token frames 409.5 instead of 403; calls over a whole sequence even
+      if constexpr (D == 128) store_through(Og + q0 * D, off, x);
+      else *reinterpret_cast<u32x4*>(reinterpret_cast<char*>(Og + q0 * D) + off) = x;
     }
   };
   if (kg == 0) finish(std::integral_constant<int, 0>{});

@@ -358,7 +358,7 @@ __device__ __forceinline__ float half_swap_sum(float x) {
 
 // 16 bytes a lane at base + off through the XCD's L2 to memory at once (agent scope), for whole lines that a launch writes
 // last: what it leaves dirty there is written back when it ends, before the next one begins (21 streaming steps at 480p
-// 1,170 -> 1,165 us, one layer 509.9 -> 509.1).  `base` is wave-uniform, `off` below 2 GiB.
+// 1,170 -> 1,165 us, one layer 509.9 -> 509.1).  Half lines need the L2 to become whole ones.  `base` is wave-uniform, `off` below 2 GiB.
 __device__ __forceinline__ void store_through(void* base, int off, u32x4 x) {
   constexpr int kAgent = 16;   // sc1
   __builtin_amdgcn_raw_buffer_store_b128(x, __builtin_amdgcn_make_buffer_rsrc(base, 0, 0x7fffffff, 0x00020000), off, 0, kAgent);
