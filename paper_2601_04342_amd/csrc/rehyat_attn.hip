@@ -1285,7 +1285,8 @@ attn_split_kernel(AttnArgs a, StateArgs sa, int attn_blocks) {
 // where its smaller error began to cost little, 2.266e-3 instead of 2.297e-3 relative to fp64 at 4 heads of 333-token
 // frames, T_o = 1: each group rounds its weights relative to a maximum of its own, whose weight of 1 is exact).  Time
 // alone would put them at about 200, 600, 560 and 1,000 keys now, for 2 - 4 % of the calls between (at d = 64 without
-// a read-out 10 %); they stay, so that a row of fewer keys has the same bits in a launch of any number of items.
+// a read-out 10 %).  What the present ones keep: a row of fewer keys has the same bits in a launch of any number of items.
+// From a line on its last bits depend on whether the launch has more than 256.
 bool attn_splits(int64_t n_items, int64_t n_keys, int d, bool read_out) {
   return n_items <= 256 && n_keys >= (d == 128 ? (read_out ? 448 : 960) : read_out ? 960 : 1664);
 }

@@ -34,7 +34,7 @@ namespace rehyat {
 
 // ------------------------------------------------------------------------------------
 // 1 / den_i, w_i = -(G_i . y_i) / den_i; u = G / den itself is not written (48.4 us at 480p with it, 34.6 without; the
-// sums over it gain as well: 12 % less error of the gradients, G being exact in bf16).  Eight elements per thread, D/8
+// sums over it gain as well: 11 % less error of the gradients, G being exact in bf16).  Eight elements per thread, D/8
 // consecutive lanes per token.  The last blocks of the launch transpose the second-layer weights of both
 // maps (32 x 32 per block, through a padded LDS tile): 5 us as a launch of their own, nothing beside
 // this one, which is bound by memory.

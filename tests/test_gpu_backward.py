@@ -12,7 +12,7 @@ pytestmark = pytest.mark.gpu
 
 # Bars on each of the eight gradient tensors, relative to the tensor's own scale.  Every entry
 # is a sum over tokens of signed products whose factors pass through bf16 on the GPU (MFMA
-# operands): u = G/den, Phi_q, the states S_t and R_tau, dpsi, dU, and y_hat inside w -- up to
+# operands): Phi_q/den, Phi_q, the states S_t and R_tau, dpsi, dU, and y_hat inside w -- up to
 # six roundings of relative size <= 2^-8 (rms 2^-9 / sqrt 3 = 1.1e-3) along one path, fp32
 # accumulation.  The terms of a sum have random signs, so the relative error of the sum stays at
 # the level of one term's: about sqrt(6) * 1.1e-3 = 2.8e-3 in the Frobenius norm (4e-3 to 5e-3 when
