@@ -6,6 +6,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <algorithm>
 #include <atomic>
 #include <mutex>
 
@@ -555,15 +556,15 @@ struct BwdPlan {
   size_t dpsi[2], signs[2], p_w2[2], p_w1[2], p_b2[2];   // queries, keys
 };
 
-// Areas that are not needed at the same time lie over each other (all launches are on one stream): the partial sums of
-// the weight gradients over the states and R, which the activation gradients read last, and those over y_hat, n^S, n^L.
-// One after the other, queries before keys, the sides share what is left: one area of chunk-state sums, and 1 / den and w
-// where the signs of the keys will be.  Launches that the sides share need more at once, and are taken where the total
-// is no larger than that and an area for the sums of dL/dz (what buffers were sized for when nothing was shared): the sums
-// of one side or of both lie over the activation gradients then, which come later.
-// 480p at 12 heads of 128: 479 MB, one after the other 498.  Where segments are a few dozen tokens the sums are larger
-// than the activation gradients, and there is one area of them (22 heads, 93 frames of 16 tokens 553 MB, one after the other
-// 590; with two 831).
+// Areas that are not needed at the same time lie over each other (all launches are on one stream).  The partial sums of the
+// weight gradients, the last to come, lie over the states and R, which the activation gradients read last; the activation
+// gradients over y_hat, n^S, n^L; and the partial sums of the chunk states, which come before both, over both.
+// Launches that the sides share need more at once than one side after the other, queries before keys: an area of chunk-state
+// sums each (with a saved forward pass), and 1 / den and w beside the signs of the keys instead of where those will be.  They
+// are taken where that needs no more bytes than the sides used to need one after the other, with every sum in an area of its
+// own: buffers that were large enough stay so.  480p at 12 heads of 128: 479 MB, formerly 498.  There is no room for
+// both sides' sums where the segments of many heads are a few dozen tokens (22 heads, 93 frames of 16 tokens 553 MB, formerly
+// 590; with two areas 831), and none for 1 / den and w in some calls with d = 64 and pieces of more than 4,100 tokens.
 BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   BwdPlan P;
   const int dp = 2 * d, hid = 2 * d;
@@ -573,44 +574,50 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
   P.nsplit = choose_cut((int)BH, P.n_seg, P.n_seg, (int64_t)chunk * HW, 0, d, kMaxSplit * P.nc, P.n_seg).nsplit;
   P.sl = Slots{P.n_seg * P.nsplit, P.nc};
   weight_pieces((int)BH, (int64_t)((N + 63) / 64), d, &P.n2, &P.n1);
+
   const size_t elems = (size_t)d * dp + dp, token_floats = BH * N * sizeof(float);
-  const size_t sums = align256(BH * P.sl.partial * elems * sizeof(float));
-  // sums_early: the first area of sums, too, lies over the activation gradients
-  auto lay_out = [&](bool both_sums, bool sums_early, bool both_acts) {
+  const size_t sums = align256(BH * P.sl.partial * elems * sizeof(float)), carry = align256(BH * elems * sizeof(float));
+  const size_t mat = align256(BH * P.nc * (size_t)d * dp * sizeof(bf16_t)), vec = align256(BH * P.nc * (size_t)dp * sizeof(float));
+  const size_t sums_w2 = align256(BH * P.n2 * (size_t)dp * hid * sizeof(float));
+  const size_t sums_w1 = align256(BH * P.n1 * ((size_t)d * hid + hid) * sizeof(float));
+  const size_t sums_b2 = align256(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
+  const size_t dpsi = align256(BH * N * dp * sizeof(bf16_t));
+  const size_t signs = align256(BH * N * (hid / 32) * sizeof(uint32_t));   // 16 bytes per token at least
+  const size_t w2t = align256(2 * (size_t)H * hid * dp * sizeof(bf16_t));
+  const size_t most = std::max(sums + 2 * (mat + vec) + carry, 2 * (sums_w2 + sums_w1)) + 2 * (dpsi + signs) + w2t + 3 * sums_b2;
+
+  auto lay_out = [&](bool both_sums, bool both_acts) {
     size_t off = 0;
-    auto take = [&](size_t bytes) {
+    auto take = [&](size_t bytes) {   // a multiple of 256
       const size_t o = off;
-      off += align256(bytes);
+      off += bytes;
       return o;
     };
     P.both_sums = both_sums;
     P.both_acts = both_acts;
     for (int side = 0; side < 2; ++side) {
-      P.p_w2[side] = take(BH * P.n2 * (size_t)dp * hid * sizeof(float));
-      P.p_w1[side] = take(BH * P.n1 * ((size_t)d * hid + hid) * sizeof(float));
+      P.p_w2[side] = take(sums_w2);
+      P.p_w1[side] = take(sums_w1);
     }
-    const size_t weight_sums = off;
+    const size_t weights_end = off;
     off = 0;
-    if (!sums_early) P.F.partial = take(sums);
-    P.F.state_s = take(BH * P.nc * (size_t)d * dp * sizeof(bf16_t));
-    P.F.state_z = take(BH * P.nc * (size_t)dp * sizeof(float));
-    P.F.carry = take(BH * elems * sizeof(float));
-    P.Rt = take(BH * P.nc * (size_t)dp * d * sizeof(bf16_t));
-    P.rz = take(BH * P.nc * (size_t)dp * sizeof(float));
+    P.F.state_s = take(mat);
+    P.F.state_z = take(vec);
+    P.F.carry = take(carry);
+    P.Rt = take(mat);
+    P.rz = take(vec);
     if (both_acts) {
-      P.inv = take(token_floats);
-      P.tokw = take(token_floats);
+      P.inv = take(align256(token_floats));
+      P.tokw = take(align256(token_floats));
     }
-    if (off < weight_sums) off = weight_sums;
-    size_t early = off;   // end of what lies over the activation gradients
-    auto take_early = [&](size_t bytes) {
-      const size_t o = early;
-      early += bytes;
-      return o;
-    };
-    P.yhat = P.dpsi[1] = take(BH * N * dp * sizeof(bf16_t));
-    P.dpsi[0] = take(BH * N * dp * sizeof(bf16_t));
-    const size_t signs = BH * N * (hid / 32) * sizeof(uint32_t);   // 16 bytes per token at least
+    const size_t states_end = off;
+    P.F.partial = take(sums);
+    P.q_part = both_sums ? take(sums) : P.F.partial;
+    const size_t sums_end = off;
+    off = std::max(states_end, weights_end);
+    P.yhat = P.dpsi[1] = take(dpsi);
+    P.dpsi[0] = take(dpsi);
+    if (!both_acts) off = std::max(off, sums_end);   // 1 / den and w come before the second use of the sums
     P.nS = P.signs[1] = take(signs);
     P.nL = P.nS + token_floats;
     if (!both_acts) {
@@ -618,20 +625,14 @@ BwdPlan bwd_plan(int B, int H, int T, int HW, int d, int chunk) {
       P.tokw = P.inv + token_floats;
     }
     P.signs[0] = take(signs);
-    if (sums_early) P.F.partial = take_early(sums);
-    P.q_part = both_sums ? take_early(sums) : P.F.partial;
-    if (off < early) off = early;
-    P.w2t = take(2 * (size_t)H * hid * dp * sizeof(bf16_t));
-    for (int side = 0; side < 2; ++side) P.p_b2[side] = take(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
+    off = std::max(off, sums_end);
+    P.w2t = take(w2t);
+    for (int side = 0; side < 2; ++side) P.p_b2[side] = take(sums_b2);
     P.F.total = P.total = off;
   };
-  lay_out(false, false, false);
-  const size_t most = P.total + align256(BH * P.n_seg * P.nsplit * (size_t)dp * sizeof(float));
-  for (int form = 0; form < 4; ++form) {
-    lay_out(form < 2, form % 2 == 0, true);
-    if (P.total <= most) return P;
-  }
-  lay_out(false, false, false);
+  lay_out(true, true);
+  if (P.total > most) lay_out(false, true);
+  if (P.total > most) lay_out(false, false);
   return P;
 }
 

@@ -297,10 +297,10 @@ def test_saved_forward_pass_of_more_batch_heads_than_half_a_grid():
 
 @pytest.mark.parametrize("saved", [False, True])
 @pytest.mark.parametrize("case,copies", [
-    ((1, 1, 8, 550, 128, 2, 0), 1),     # sums of both sides over the activation gradients
-    ((1, 3, 28, 42, 64, 7, 1), 1),      # those of the queries only
-    ((2, 3, 50, 20, 64, 1, 0), 1),      # one area of sums, over the activation gradients
-    ((1, 2, 40, 29, 128, 7, 2), 1),     # beside them
+    ((1, 1, 8, 550, 128, 2, 0), 1),     # sums of both sides, within what the weight gradients' sums take later
+    ((1, 3, 28, 42, 64, 7, 1), 1),      # and the activation gradients
+    ((1, 2, 40, 29, 128, 7, 2), 1),     # short pieces, empty key segments
+    ((2, 3, 50, 20, 64, 1, 0), 1),      # one area of sums, larger than the activation gradients
     ((1, 2, 4, 4105, 64, 1, 0), 64),    # activation gradients of one side after the other
 ])
 def test_every_layout_of_the_workspace(case, copies, saved):
